@@ -52,18 +52,19 @@ bc_status graph_create(int32_t n, int64_t m, const int32_t* row_ptr, const int32
     }
     std::unique_ptr<bc_graph> g(new bc_graph());
     g->stream = stream;
-    g->ordered = ordered;
+    // small graphs keep their numbering: their node records stay in the
+    // caches anyway, and the second build would dominate their upload
+    const bool relabel = !(flags & (BC_DIRECTED | BC_KEEP_IDS)) && n >= kRelabelMinNodes;
+    g->ordered = ordered || relabel;  // the first build of a renumbered graph lasts as long as this call
     (void)hipGetDevice(&g->device);
     bc_status s = graph_build(g.get(), n, m, row_ptr, col, flags & ~(uint32_t)BC_KEEP_IDS);
     if (s != BC_OK) {
         (void)hipStreamSynchronize(g->stream);
         return s;
     }
-    // small graphs keep their numbering: their node records stay in the
-    // caches anyway, and the second build would dominate their upload
-    if (!(flags & (BC_DIRECTED | BC_KEEP_IDS)) && n >= kRelabelMinNodes) {
+    if (relabel) {
         bc_graph* h = nullptr;
-        s = graph_relabel(g.get(), flags & ~(uint32_t)(BC_DEVICE_PTRS | BC_KEEP_IDS | BC_VALIDATE), ordered, &h);
+        s = graph_relabel(g.get(), ordered, &h);
         (void)hipStreamSynchronize(g->stream);
         if (s != BC_OK) return s;
         g.reset(h);

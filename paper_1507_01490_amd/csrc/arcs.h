@@ -14,6 +14,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <utility>
+
+#include "bc_internal.h"
+
 namespace bc {
 
 constexpr int kArcBlk = 256;       // threads per workgroup of the arc kernels
@@ -142,11 +146,34 @@ __device__ inline unsigned long long wave_max64(unsigned long long x) {
 }
 __device__ inline unsigned long long wave_min64(unsigned long long x) { return ~wave_max64(~x); }
 
+// *out = max(*out, x over the workgroup): one atomic per workgroup.  Atomics
+// on one address take about 12 ns each here, so the kernels that end in one
+// also keep to kReduceGrid workgroups (k_loc_far over 300,000 nodes: 57 us
+// with one atomic per wave of a full grid, 6 us).
+constexpr int64_t kReduceGrid = 256;
+template <bool kMin = false>
+__device__ inline void block_extreme64(unsigned long long x, unsigned long long* out) {
+    __shared__ unsigned long long part[kArcBlk / 64];
+    x = kMin ? wave_min64(x) : wave_max64(x);
+    __syncthreads();  // part may still be read by an earlier call
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = x;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int k = 1; k < kArcBlk / 64; ++k) x = kMin ? min(x, part[k]) : max(x, part[k]);
+    if (kMin) {
+        if (x != ~0ull) atomicMin(out, x);
+    } else if (x) {
+        atomicMax(out, x);
+    }
+}
+
 // ---- breadth-first level over a frontier list
 
 constexpr int kListBuf = 1024;      // reached nodes staged in LDS before one global append
 constexpr uint32_t kListHeavy = 8192;  // entries with more arcs are spread over many workgroups
-constexpr uint32_t kListGrid = 1024;   // workgroups a long list is spread over
+constexpr uint32_t kListGrid = 1024;   // workgroups a list is spread over
+constexpr int kListAhead = 8;          // levels launched before the host looks at their lengths
+constexpr size_t kListCtrWords = 2 * (kListAhead + 1);
 
 struct ListLds {
     int32_t beg[kArcBlk];
@@ -174,13 +201,17 @@ __device__ inline void stage_flush(ListLds& L, int32_t* N, uint32_t* ncount) {
     __syncthreads();
 }
 
-// Every out-arc of the frontier entries F[0, flen), `per` (at most kArcBlk)
-// entries a workgroup: op(target, entry index) says whether the target joins
-// the list N.  Entries above kListHeavy arcs go to the heavy list instead.
+// Every out-arc of the frontier entries F[0, *flen_p): op(target, entry index)
+// says whether the target joins the list N.  A workgroup takes `per` (at most
+// kArcBlk) entries at a time, so that a short list of long rows fills the chip
+// too.  Entries above kListHeavy arcs go to the heavy list instead.
 template <class Op>
 __global__ __launch_bounds__(kArcBlk) void k_list_arcs(const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
-                                                       const int32_t* F, uint32_t flen, uint32_t per, Op op,
-                                                       int32_t* N, uint32_t* ncount, uint32_t* heavy, uint32_t* hcount) {
+                                                       const int32_t* F, const uint32_t* flen_p, Op op, int32_t* N,
+                                                       uint32_t* ncount, uint32_t* heavy, uint32_t* hcount) {
+    const uint32_t flen = *flen_p;
+    if (flen == 0) return;
+    const uint32_t per = min((flen + gridDim.x - 1) / gridDim.x, (uint32_t)kArcBlk);
     __shared__ ListLds L;
     const uint32_t tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -272,20 +303,39 @@ __global__ __launch_bounds__(kArcBlk) void k_list_heavy(const int32_t* __restric
 // Entries of one list with more than kListHeavy arcs (rows are distinct).
 inline size_t heavy_words(int64_t m) { return (size_t)(m / kListHeavy) + 1; }
 
-// One breadth-first level: ctr[0] (list length) and ctr[1] (heavy entries)
-// are zero on entry; heavy holds heavy_words(m) words.  `per` spreads the list over
-// kListGrid workgroups, so that a short list of long rows fills the chip too.
+// One breadth-first level over F[0, *flen): the reached nodes go to N, their
+// count to ctr[0] (ctr[0] and ctr[1] are zero on entry; heavy holds
+// heavy_words(m) words).
 template <class Op>
-inline void list_arcs(const int32_t* rp, const int32_t* col, const int32_t* F, uint32_t flen, Op op, int32_t* N,
+inline void list_arcs(const int32_t* rp, const int32_t* col, const int32_t* F, const uint32_t* flen, Op op, int32_t* N,
                       uint32_t* ctr, uint32_t* heavy, hipStream_t s) {
-    uint32_t per = (flen + kListGrid - 1) / kListGrid;
-    if (per > (uint32_t)kArcBlk) per = kArcBlk;
-    if (per < 1) per = 1;
-    uint32_t blocks = (flen + per - 1) / per;
-    if (blocks > 8192) blocks = 8192;
-    if (blocks < 1) blocks = 1;
-    k_list_arcs<Op><<<blocks, kArcBlk, 0, s>>>(rp, col, F, flen, per, op, N, ctr, heavy, ctr + 1);
+    k_list_arcs<Op><<<kListGrid, kArcBlk, 0, s>>>(rp, col, F, flen, op, N, ctr, heavy, ctr + 1);
     k_list_heavy<Op><<<dim3(64, 16), kArcBlk, 0, s>>>(rp, col, F, op, N, ctr, heavy, ctr + 1);
+}
+
+// Breadth-first search from q0[0], all levels: make_op(d) visits the arcs out
+// of level d.  kListAhead levels are launched at a time, each reading its
+// length on the device; a level past the end costs two empty launches, a
+// round trip to the host per level cost more than most levels.  ctr holds
+// kListCtrWords words; *reached counts the nodes, the source among them.
+template <class MakeOp>
+inline bc_status list_bfs(const int32_t* rp, const int32_t* col, int32_t* q0, int32_t* q1, MakeOp make_op,
+                          uint32_t* ctr, uint32_t* heavy, uint64_t* reached, hipStream_t s) {
+    uint32_t len[kListCtrWords] = {1};
+    BC_HIP(hipMemcpyAsync(ctr, len, sizeof(uint32_t), hipMemcpyHostToDevice, s));
+    *reached = 1;
+    for (int32_t d = 0;;) {
+        BC_HIP(hipMemsetAsync(ctr + 2, 0, sizeof(uint32_t) * (kListCtrWords - 2), s));
+        for (int l = 0; l < kListAhead; ++l, ++d) {
+            list_arcs(rp, col, q0, ctr + 2 * l, make_op(d), q1, ctr + 2 * (l + 1), heavy, s);
+            std::swap(q0, q1);
+        }
+        BC_HIP(hipMemcpyAsync(len, ctr, sizeof(len), hipMemcpyDeviceToHost, s));
+        BC_HIP(hipStreamSynchronize(s));
+        for (int l = 1; l <= kListAhead; ++l) *reached += len[2 * l];
+        if (len[2 * kListAhead] == 0) return BC_OK;
+        BC_HIP(hipMemcpyAsync(ctr, ctr + 2 * kListAhead, sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
+    }
 }
 
 }  // namespace bc

@@ -71,6 +71,20 @@ __global__ __launch_bounds__(kArcBlk) void k_validate_arcs(int32_t n, int64_t m,
     if (bits) atomicOr(err, bits);
 }
 
+// *any = 1 when a sorted row holds a self-loop or a repeat
+__global__ __launch_bounds__(kArcBlk) void k_any_drop(int32_t n, int64_t m, const int32_t* __restrict__ rp,
+                                                      const int32_t* __restrict__ col, uint32_t* any) {
+    __shared__ ArcRowLds L;
+    const int32_t e0 = (int32_t)(blockIdx.x * (int64_t)kArcTile), e1 = (int32_t)min((int64_t)e0 + kArcTile, m);
+    block_arc_rows(rp, n, e0, e1, L);
+    bool drop = false;
+    for (int32_t e = e0 + threadIdx.x; e < e1; e += kArcBlk) {
+        const int32_t u = L.row[e - e0], w = col[e];
+        drop = drop || w == u || (e > rp[u] && w == col[e - 1]);
+    }
+    if (drop) *any = 1u;
+}
+
 // keep[i] = 1 for the first copy of each non-loop arc of a sorted row
 __global__ void k_mark_keep(int32_t n, const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
                             int32_t* __restrict__ cnt) {
@@ -139,37 +153,113 @@ __device__ int32_t uf_find(int32_t* P, int32_t v) {
     }
 }
 
-__global__ void k_uf_init(int32_t n, int32_t* P) {
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += stride) P[u] = (int32_t)u;
+__device__ inline void uf_unite(int32_t* P, int32_t a, int32_t b) {
+    for (;;) {
+        a = uf_find(P, a);
+        b = uf_find(P, b);
+        if (a == b) return;
+        if (a < b) { int32_t t = a; a = b; b = t; }
+        if (atomicCAS(&P[a], a, b) == a) return;
+    }
 }
 
-__global__ void k_uf_union(int32_t n, const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
-                           int32_t* P) {
+// Components in steps, since nearly all arcs of a real graph join nodes that
+// already share one:
+//   k_uf_init   every node points to its smallest neighbour if that is
+//               smaller than itself (a forest without any atomic: pointers
+//               only fall), then to its root (k_uf_flatten)
+//   k_uf_hook   the first arcs of every row, three rounds without a retry loop
+//   k_uf_giant  the most frequent root among a sample of the nodes
+//   k_uf_rest   the other arcs of the nodes outside that root's tree only (an
+//               edge that leaves the tree is in the row of its outer end too)
+// One thread per row over all arcs took 953 us on a collaboration graph of
+// 300,000 actors (5.7M arcs), these 203 us together; on a Barabasi-Albert
+// graph of 10^6 nodes 13.1 ms, in the hub rows, now 292 us.
+__global__ void k_uf_init(int32_t n, const int32_t* __restrict__ rp, const int32_t* __restrict__ col, int32_t* P) {
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += stride) {
-        for (int32_t i = rp[u]; i < rp[u + 1]; ++i) {
-            int32_t w = col[i];
-            if (w < (int32_t)u) continue;  // each undirected edge once
-            int32_t a = (int32_t)u, b = w;
-            for (;;) {
-                a = uf_find(P, a);
-                b = uf_find(P, b);
-                if (a == b) break;
-                if (a < b) { int32_t t = a; a = b; b = t; }
-                if (atomicCAS(&P[a], a, b) == a) break;
-            }
+        const int32_t b = rp[u];
+        P[u] = b < rp[u + 1] ? min((int32_t)u, col[b]) : (int32_t)u;  // rows are sorted
+    }
+}
+
+__global__ void k_uf_flatten(int32_t n, int32_t* P) {
+    int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += stride)
+        st_relaxed(&P[u], uf_find(P, (int32_t)u));
+}
+
+// Flattened forest: the roots of both ends of the first kUfHook arcs of every
+// row are joined, the larger under the smaller.  A root that meets several
+// smaller ones keeps one; the next round and k_uf_rest join the others.
+constexpr int kUfHook = 4;
+constexpr int kUfRounds = 3;
+
+__global__ void k_uf_hook(int32_t n, const int32_t* __restrict__ rp, const int32_t* __restrict__ col, int32_t* P) {
+    int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += stride) {
+        const int32_t b = rp[u], e = min(rp[u + 1], b + kUfHook);
+        if (b >= e) continue;
+        const int32_t r = ld_relaxed(&P[u]);
+        for (int32_t i = b; i < e; ++i) {
+            const int32_t q = ld_relaxed(&P[col[i]]);
+            const int32_t hi = max(q, r), lo = min(q, r);
+            if (hi != lo && ld_relaxed(&P[hi]) > lo) atomicMin(&P[hi], lo);
         }
     }
 }
 
-__global__ void k_uf_count(int32_t n, int32_t* P, uint32_t* __restrict__ size, int32_t* __restrict__ label) {
+// *giant = the root most of kBlk evenly spaced nodes share (one workgroup)
+__global__ __launch_bounds__(kBlk) void k_uf_giant(int32_t n, int32_t* P, int32_t* giant) {
+    __shared__ int32_t root[kBlk];
+    __shared__ unsigned long long best;
+    const int tid = threadIdx.x;
+    if (tid == 0) best = 0;
+    root[tid] = uf_find(P, (int32_t)((int64_t)n * tid / kBlk));
+    __syncthreads();
+    uint32_t c = 0;
+    for (int i = 0; i < kBlk; ++i) c += root[i] == root[tid];
+    atomicMax(&best, ((unsigned long long)c << 32) | (uint32_t)root[tid]);
+    __syncthreads();
+    if (tid == 0) *giant = (int32_t)(uint32_t)best;
+}
+
+__global__ void k_uf_rest(int32_t n, const int32_t* __restrict__ rp, const int32_t* __restrict__ col, int32_t* P,
+                          const int32_t* __restrict__ giant) {
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const int32_t g = *giant;
     for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += stride) {
-        int32_t r = uf_find(P, (int32_t)u);
-        label[u] = r;
-        atomicAdd(&size[r], 1u);
+        const int32_t b = rp[u], e = rp[u + 1];
+        if (b >= e || uf_find(P, (int32_t)u) == uf_find(P, g)) continue;
+        for (int32_t i = b; i < e; ++i) uf_unite(P, (int32_t)u, col[i]);
     }
+}
+
+// Component sizes.  The giant one is counted per workgroup and the others per
+// wave: with an atomic per node, all nodes of the giant component met at one
+// counter (300,000 nodes: 1370 -> 24 us).
+__global__ __launch_bounds__(kBlk) void k_uf_count(int32_t n, int32_t* P, const int32_t* __restrict__ giant,
+                                                   uint32_t* __restrict__ size, int32_t* __restrict__ label) {
+    __shared__ uint32_t s_giant;
+    if (threadIdx.x == 0) s_giant = 0;
+    __syncthreads();
+    const int32_t g = uf_find(P, *giant);
+    uint32_t mine = 0;
+    int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < n; base += stride) {
+        const int64_t u = base + threadIdx.x;
+        const bool on = u < n;
+        int32_t r = 0;
+        if (on) {
+            r = uf_find(P, (int32_t)u);
+            label[u] = r;
+            mine += r == g;
+        }
+        wave_count_key(on && r != g, r, size);
+    }
+    if (mine) atomicAdd(&s_giant, mine);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_giant) atomicAdd(&size[g], s_giant);
 }
 
 __global__ void k_uf_reach(int32_t n, const int32_t* __restrict__ label, const uint32_t* __restrict__ size,
@@ -277,23 +367,26 @@ __global__ void k_loc_init(int32_t n, int32_t* __restrict__ dist, uint32_t* __re
     }
 }
 
-// One level: the out-arcs of F[0, flen) (at distance d, order positions
-// base + i) discover level d + 1 into N; with ppos, every parent offers its
-// position and the smallest is kept.
-__global__ void k_loc_expand(const int32_t* __restrict__ rp, const int32_t* __restrict__ col, const int32_t* F,
-                             uint32_t flen, int32_t d, uint32_t base, int32_t* dist, uint32_t* ppos, int32_t* N,
-                             uint32_t* ncount) {
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < flen; i += stride) {
-        const int32_t u = F[i];
-        for (int32_t e = rp[u]; e < rp[u + 1]; ++e) {
-            const int32_t w = col[e];
-            const int32_t old = atomicCAS(&dist[w], -1, d + 1);
-            if (old == -1) N[atomicAdd(ncount, 1u)] = w;
-            if (ppos && (old == -1 || old == d + 1)) atomicMin(&ppos[w], base + (uint32_t)i);
+// One level: the out-arcs of a list at distance d (order positions base + i)
+// discover level d + 1; with ppos, every parent offers its position and the
+// smallest is kept.  Plain reads first: dist leaves -1 once and ppos only
+// falls, so an old copy costs an atomic and never a result.
+struct LocOp {
+    int32_t* dist;
+    uint32_t* ppos;
+    int32_t d;
+    uint32_t base;
+    __device__ bool operator()(int32_t w, uint32_t i) const {
+        int32_t old = dist[w];
+        bool first = false;
+        if (old == -1) {
+            old = atomicCAS(&dist[w], -1, d + 1);
+            first = old == -1;
         }
+        if (ppos && (first || old == d + 1) && ppos[w] > base + i) atomicMin(&ppos[w], base + i);
+        return first;
     }
-}
+};
 
 // keys of a discovered level: (earliest parent position, id)
 __global__ void k_loc_keys(uint32_t cnt, const int32_t* __restrict__ N, const uint32_t* __restrict__ ppos,
@@ -306,20 +399,24 @@ __global__ void k_loc_keys(uint32_t cnt, const int32_t* __restrict__ N, const ui
 // farthest reached node: max (dist, -id) packed; and on-path test for the centre
 __global__ void k_loc_far(int32_t n, const int32_t* __restrict__ dist, unsigned long long* best) {
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    unsigned long long mx = 0;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride)
         if (dist[v] >= 0)
-            atomicMax(best, ((unsigned long long)(uint32_t)dist[v] << 32) | (0xFFFFFFFFu - (uint32_t)v));
+            mx = max(mx, ((unsigned long long)(uint32_t)dist[v] << 32) | (0xFFFFFFFFu - (uint32_t)v));
+    block_extreme64(mx, best);
 }
 
 // centre: on a shortest a-b path (da + db = D), nearest to the middle, smallest id
 __global__ void k_loc_centre(int32_t n, const int32_t* __restrict__ da, const int32_t* __restrict__ db, int32_t D,
                              unsigned long long* best) {
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    unsigned long long mn = ~0ull;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
         if (da[v] < 0 || db[v] < 0 || da[v] + db[v] != D) continue;
         const uint32_t off = (uint32_t)abs(2 * da[v] - D);
-        atomicMin(best, ((unsigned long long)off << 32) | (uint32_t)v);
+        mn = min(mn, ((unsigned long long)off << 32) | (uint32_t)v);
     }
+    block_extreme64<true>(mn, best);
 }
 
 __global__ void k_loc_unreached(int32_t n, const int32_t* __restrict__ order_deg, const int32_t* __restrict__ dist,
@@ -521,13 +618,6 @@ __global__ void k_inverse(int32_t n, const int32_t* __restrict__ orig, int32_t* 
     for (int32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < n; u += gridDim.x * blockDim.x) inv[orig[u]] = u;
 }
 
-// row lengths of the renumbered graph: len[u] = outdeg(orig[u])
-__global__ void k_relabel_len(int32_t n, const int32_t* __restrict__ orig, const uint32_t* __restrict__ deg,
-                              int32_t* __restrict__ len) {
-    for (int32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < n; u += gridDim.x * blockDim.x)
-        len[u] = (int32_t)deg[orig[u]];
-}
-
 // rows of the renumbered graph: row u is row orig[u] with every target
 // renamed by inv (one wave per row)
 __global__ void k_relabel_rows(int32_t n, const int32_t* __restrict__ orig, const int32_t* __restrict__ inv,
@@ -554,6 +644,17 @@ __global__ void k_gather_rows(int32_t n, int width, const int32_t* __restrict__ 
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
         const int64_t v = i / width, w = i % width;
         dst[i] = src[(int64_t)inv[v] * width + w];
+    }
+}
+
+// degree and component size of node u of the renumbered graph
+__global__ void k_relabel_nodes(int32_t n, const int32_t* __restrict__ orig, const uint32_t* __restrict__ deg,
+                                const uint32_t* __restrict__ x, uint32_t* __restrict__ ndeg, uint32_t* __restrict__ x0,
+                                uint32_t* __restrict__ x1) {
+    for (int32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < n; u += gridDim.x * blockDim.x) {
+        const int32_t v = orig[u];
+        ndeg[u] = deg[v];
+        x0[u] = x1[u] = x[v];
     }
 }
 
@@ -585,10 +686,12 @@ bc_status graph_build(bc_graph* g, int32_t n, int64_t m, const int32_t* rp_in, c
         set_error("m = %lld arcs does not fit int32 offsets", (long long)m);
         return BC_EGRAPH;
     }
-    DevBuf rp0, col0, errb, tmp;
-    BC_TRY(rp0.alloc_on(sizeof(int32_t) * ((size_t)n + 1), s));
-    BC_TRY(col0.alloc_on(sizeof(int32_t) * (size_t)(m > 0 ? m : 1), s));
-    BC_TRY(errb.alloc_on(sizeof(uint32_t), s));
+    DevBuf raw, rp0, col0, errb, tmp;
+    Carve cr;
+    cr.add(rp0, sizeof(int32_t) * ((size_t)n + 1));
+    cr.add(col0, sizeof(int32_t) * (size_t)m);
+    cr.add(errb, sizeof(uint32_t));
+    BC_TRY(cr.place_on(raw, s));
     hipMemcpyKind kind = dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
     BC_HIP(hipMemcpyAsync(rp0.p, rp_in, sizeof(int32_t) * ((size_t)n + 1), kind, s));
     if (m > 0) BC_HIP(hipMemcpyAsync(col0.p, col_in, sizeof(int32_t) * (size_t)m, kind, s));
@@ -604,43 +707,62 @@ bc_status graph_build(bc_graph* g, int32_t n, int64_t m, const int32_t* rp_in, c
     if (err & 2u) { set_error("col entry outside [0, n)"); return BC_EGRAPH; }
 
     int64_t mc = m;
+    // the graph's arrays, in one allocation once the arc count is known
+    auto place = [&]() -> bc_status {
+        Carve c;
+        c.add(g->rp, sizeof(int32_t) * ((size_t)n + 1));
+        c.add(g->col, sizeof(int32_t) * (size_t)mc);
+        c.add(g->deg, sizeof(uint32_t) * (size_t)n);
+        c.add(g->adj, sizeof(int2) * (size_t)mc);
+        c.add(g->x0, sizeof(uint32_t) * (size_t)n);
+        c.add(g->x1, sizeof(uint32_t) * (size_t)n);
+        return gplace(g, c, g->base, s);
+    };
     if (err & 4u) {
         // canonical form: sort every row, then drop self-loops and repeats
-        DevBuf sorted, cnt, nrp;
-        BC_TRY(sorted.alloc_on(sizeof(int32_t) * (size_t)(m > 0 ? m : 1), s));
-        BC_TRY(cnt.alloc_on(sizeof(int32_t) * (size_t)(n > 0 ? n : 1), s));
-        BC_TRY(nrp.alloc_on(sizeof(int32_t) * ((size_t)n + 1), s));
+        DevBuf sorted;
+        BC_TRY(sorted.alloc_on(sizeof(int32_t) * (size_t)m, s));
         const int32_t* rpp = rp0.as<int32_t>();
         BC_TRY(cub_call([&](void* t, size_t& b) {
             return hipcub::DeviceSegmentedRadixSort::SortKeys(t, b, col0.as<int32_t>(), sorted.as<int32_t>(),
                                                               (int)m, n, rpp, rpp + 1, 0, 32, s);
         }, s, tmp));
-        k_mark_keep<<<grid_for(n), kBlk, 0, s>>>(n, rpp, sorted.as<int32_t>(), cnt.as<int32_t>());
-        BC_TRY(cub_call([&](void* t, size_t& b) {
-            return hipcub::DeviceScan::ExclusiveSum(t, b, cnt.as<int32_t>(), nrp.as<int32_t>(), n, s);
-        }, s, tmp));
-        k_set_last<<<1, 1, 0, s>>>(nrp.as<int32_t>(), n, cnt.as<int32_t>());
-        int32_t newm = 0;
-        BC_HIP(hipMemcpyAsync(&newm, nrp.as<int32_t>() + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        // nothing to drop (rows that were only unsorted): the sorted rows are
+        // the canonical ones
+        BC_HIP(hipMemsetAsync(errb.p, 0, sizeof(uint32_t), s));
+        k_any_drop<<<arc_tiles(m), kArcBlk, 0, s>>>(n, m, rpp, sorted.as<int32_t>(), errb.as<uint32_t>());
+        uint32_t drop = 0;
+        BC_HIP(hipMemcpyAsync(&drop, errb.p, sizeof(drop), hipMemcpyDeviceToHost, s));
         BC_HIP(hipStreamSynchronize(s));
-        mc = newm;
-        BC_TRY(galloc(g, g->rp, sizeof(int32_t) * ((size_t)n + 1), s));
-        BC_TRY(galloc(g, g->col, sizeof(int32_t) * (size_t)(mc > 0 ? mc : 1), s));
-        BC_HIP(hipMemcpyAsync(g->rp.p, nrp.p, sizeof(int32_t) * ((size_t)n + 1), hipMemcpyDeviceToDevice, s));
-        k_compact_rows<<<grid_for(n), kBlk, 0, s>>>(n, rpp, sorted.as<int32_t>(), g->rp.as<int32_t>(),
-                                                    g->col.as<int32_t>());
+        if (drop) {
+            DevBuf all, cnt, nrp;
+            Carve c;
+            c.add(cnt, sizeof(int32_t) * (size_t)n);
+            c.add(nrp, sizeof(int32_t) * ((size_t)n + 1));
+            BC_TRY(c.place_on(all, s));
+            k_mark_keep<<<grid_for(n), kBlk, 0, s>>>(n, rpp, sorted.as<int32_t>(), cnt.as<int32_t>());
+            BC_TRY(cub_call([&](void* t, size_t& b) {
+                return hipcub::DeviceScan::ExclusiveSum(t, b, cnt.as<int32_t>(), nrp.as<int32_t>(), n, s);
+            }, s, tmp));
+            k_set_last<<<1, 1, 0, s>>>(nrp.as<int32_t>(), n, cnt.as<int32_t>());
+            int32_t newm = 0;
+            BC_HIP(hipMemcpyAsync(&newm, nrp.as<int32_t>() + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+            BC_HIP(hipStreamSynchronize(s));
+            mc = newm;
+            BC_TRY(place());
+            BC_HIP(hipMemcpyAsync(g->rp.p, nrp.p, sizeof(int32_t) * ((size_t)n + 1), hipMemcpyDeviceToDevice, s));
+            k_compact_rows<<<grid_for(n), kBlk, 0, s>>>(n, rpp, sorted.as<int32_t>(), g->rp.as<int32_t>(),
+                                                        g->col.as<int32_t>());
+        } else {
+            BC_TRY(place());
+            BC_HIP(hipMemcpyAsync(g->rp.p, rpp, sizeof(int32_t) * ((size_t)n + 1), hipMemcpyDeviceToDevice, s));
+            BC_HIP(hipMemcpyAsync(g->col.p, sorted.p, sizeof(int32_t) * (size_t)m, hipMemcpyDeviceToDevice, s));
+        }
         BC_HIP(hipStreamSynchronize(s));
     } else {
-        if (g->ordered) {
-            g->rp.swap(rp0);
-            g->col.swap(col0);
-        } else {
-            BC_TRY(g->rp.alloc(sizeof(int32_t) * ((size_t)n + 1)));
-            BC_TRY(g->col.alloc(sizeof(int32_t) * (size_t)(m > 0 ? m : 1)));
-            BC_HIP(hipMemcpyAsync(g->rp.p, rp0.p, sizeof(int32_t) * ((size_t)n + 1), hipMemcpyDeviceToDevice, s));
-            if (m > 0)
-                BC_HIP(hipMemcpyAsync(g->col.p, col0.p, sizeof(int32_t) * (size_t)m, hipMemcpyDeviceToDevice, s));
-        }
+        BC_TRY(place());
+        BC_HIP(hipMemcpyAsync(g->rp.p, rp0.p, sizeof(int32_t) * ((size_t)n + 1), hipMemcpyDeviceToDevice, s));
+        if (m > 0) BC_HIP(hipMemcpyAsync(g->col.p, col0.p, sizeof(int32_t) * (size_t)m, hipMemcpyDeviceToDevice, s));
     }
 
     g->dg.n = n;
@@ -648,14 +770,10 @@ bc_status graph_build(bc_graph* g, int32_t n, int64_t m, const int32_t* rp_in, c
     g->dg.directed = directed ? 1 : 0;
     g->dg.rp = g->rp.as<int32_t>();
     g->dg.col = g->col.as<int32_t>();
-    BC_TRY(galloc(g, g->deg, sizeof(uint32_t) * (size_t)(n > 0 ? n : 1), s));
     k_degree<<<grid_for(n), kBlk, 0, s>>>(n, g->dg.rp, g->deg.as<uint32_t>());
     g->dg.deg = g->deg.as<uint32_t>();
-    BC_TRY(galloc(g, g->adj, sizeof(int2) * (size_t)(mc > 0 ? mc : 1), s));
     if (mc > 0) k_pack_adj<<<grid_for(mc), kBlk, 0, s>>>(mc, g->dg.col, g->dg.deg, g->adj.as<int2>());
     g->dg.adj = g->adj.as<int2>();
-    BC_TRY(galloc(g, g->x0, sizeof(uint32_t) * (size_t)(n > 0 ? n : 1), s));
-    BC_TRY(galloc(g, g->x1, sizeof(uint32_t) * (size_t)(n > 0 ? n : 1), s));
     g->dg.x0 = g->x0.as<uint32_t>();
     g->dg.x1 = g->x1.as<uint32_t>();
 
@@ -669,15 +787,25 @@ bc_status graph_build(bc_graph* g, int32_t n, int64_t m, const int32_t* rp_in, c
         }
         g->dg.irp = g->dg.rp;
         g->dg.icol = g->dg.col;
-        DevBuf P, size, label;
-        BC_TRY(P.alloc_on(sizeof(int32_t) * (size_t)(n > 0 ? n : 1), s));
-        BC_TRY(size.alloc_on(sizeof(uint32_t) * (size_t)(n > 0 ? n : 1), s));
-        BC_TRY(label.alloc_on(sizeof(int32_t) * (size_t)(n > 0 ? n : 1), s));
+        DevBuf all, P, size, label, giant;
+        Carve c;
+        c.add(P, sizeof(int32_t) * (size_t)n);
+        c.add(size, sizeof(uint32_t) * (size_t)(n > 0 ? n : 1));
+        c.add(label, sizeof(int32_t) * (size_t)n);
+        c.add(giant, sizeof(int32_t));
+        BC_TRY(c.place_on(all, s));
         BC_HIP(hipMemsetAsync(size.p, 0, sizeof(uint32_t) * (size_t)(n > 0 ? n : 1), s));
         if (n > 0) {
-            k_uf_init<<<grid_for(n), kBlk, 0, s>>>(n, P.as<int32_t>());
-            k_uf_union<<<grid_for(n), kBlk, 0, s>>>(n, g->dg.rp, g->dg.col, P.as<int32_t>());
-            k_uf_count<<<grid_for(n), kBlk, 0, s>>>(n, P.as<int32_t>(), size.as<uint32_t>(), label.as<int32_t>());
+            k_uf_init<<<grid_for(n), kBlk, 0, s>>>(n, g->dg.rp, g->dg.col, P.as<int32_t>());
+            k_uf_flatten<<<grid_for(n), kBlk, 0, s>>>(n, P.as<int32_t>());
+            for (int round = 0; round < kUfRounds; ++round) {
+                k_uf_hook<<<grid_for(n), kBlk, 0, s>>>(n, g->dg.rp, g->dg.col, P.as<int32_t>());
+                k_uf_flatten<<<grid_for(n), kBlk, 0, s>>>(n, P.as<int32_t>());
+            }
+            k_uf_giant<<<1, kBlk, 0, s>>>(n, P.as<int32_t>(), giant.as<int32_t>());
+            k_uf_rest<<<grid_for(n), kBlk, 0, s>>>(n, g->dg.rp, g->dg.col, P.as<int32_t>(), giant.as<int32_t>());
+            k_uf_count<<<grid_for(n, 4 * kReduceGrid), kBlk, 0, s>>>(n, P.as<int32_t>(), giant.as<int32_t>(),
+                                                                     size.as<uint32_t>(), label.as<int32_t>());
             k_uf_reach<<<grid_for(n), kBlk, 0, s>>>(n, label.as<int32_t>(), size.as<uint32_t>(),
                                                     g->x0.as<uint32_t>(), g->x1.as<uint32_t>());
         }
@@ -697,9 +825,11 @@ bc_status order_by_degree(bc_graph* g, int32_t* d_order, hipStream_t s) {
     if (n == 0) return BC_OK;
     std::unique_lock<std::mutex> lk(g->cache_mu);
     if (!g->have_order_deg) {
-        DevBuf k0, k1, tmp;
-        BC_TRY(k0.alloc_on(sizeof(uint64_t) * (size_t)n, s));
-        BC_TRY(k1.alloc_on(sizeof(uint64_t) * (size_t)n, s));
+        DevBuf all, k0, k1, tmp;
+        Carve c;
+        c.add(k0, sizeof(uint64_t) * (size_t)n);
+        c.add(k1, sizeof(uint64_t) * (size_t)n);
+        BC_TRY(c.place_on(all, s));
         BC_TRY(galloc(g, g->order_deg, sizeof(int32_t) * (size_t)n, s));
         k_degree_keys<<<grid_for(n), kBlk, 0, s>>>(n, g->dg.deg, g->dg.orig, k0.as<uint64_t>());
         BC_TRY(cub_call([&](void* t, size_t& b) {
@@ -900,33 +1030,64 @@ bc_status order_head_grouped(bc_graph* g, const int32_t* d_by_score, int32_t hea
     return BC_OK;
 }
 
-// Level-synchronous BFS from src over the out-arcs; dist[] (-1 = not
-// reached).  With order != nullptr the discovery order (levels sorted by
-// earliest parent position, then id) is written to order[0, *reached).
-static bc_status loc_bfs(bc_graph* g, int32_t src, int32_t* dist, uint32_t* ppos, int32_t* order, int32_t* reached,
-                         DevBuf& la, DevBuf& lb, DevBuf& k0, DevBuf& k1, DevBuf& cnt, DevBuf& tmp, hipStream_t s) {
+// Scratch of the searches below: two lists, heavy entries, level counters,
+// sort keys.
+struct LocScratch {
+    DevBuf la, lb, heavy, ctr, k0, k1, tmp;
+    void add_to(Carve& c, int32_t n, int64_t m) {
+        c.add(la, sizeof(int32_t) * (size_t)n);
+        c.add(lb, sizeof(int32_t) * (size_t)n);
+        c.add(heavy, sizeof(uint32_t) * heavy_words(m));
+        c.add(ctr, sizeof(uint32_t) * kListCtrWords);
+        c.add(k0, sizeof(uint64_t) * (size_t)n);
+        c.add(k1, sizeof(uint64_t) * (size_t)n);
+    }
+};
+
+// Level-synchronous BFS from src over the out-arcs; dist[] (-1 = not reached).
+static bc_status loc_dist(bc_graph* g, int32_t src, int32_t* dist, LocScratch& X, hipStream_t s) {
+    const int32_t n = g->dg.n;
+    k_loc_init<<<grid_for(n), kBlk, 0, s>>>(n, dist, nullptr);
+    const int32_t zero = 0;
+    BC_HIP(hipMemcpyAsync(dist + src, &zero, sizeof(int32_t), hipMemcpyHostToDevice, s));
+    BC_HIP(hipMemcpyAsync(X.la.p, &src, sizeof(int32_t), hipMemcpyHostToDevice, s));
+    uint64_t reached = 0;
+    return list_bfs(g->dg.rp, g->dg.col, X.la.as<int32_t>(), X.lb.as<int32_t>(),
+                    [&](int32_t d) { return LocOp{dist, nullptr, d, 0}; }, X.ctr.as<uint32_t>(),
+                    X.heavy.as<uint32_t>(), &reached, s);
+}
+
+// The same search with its discovery order (levels sorted by earliest parent
+// position, then id) written to order[0, *reached).  A level's positions need
+// the sorted level before it, and the sort its length on the host.
+static bc_status loc_order(bc_graph* g, int32_t src, int32_t* dist, uint32_t* ppos, int32_t* order, int32_t* reached,
+                           LocScratch& X, hipStream_t s) {
     const int32_t n = g->dg.n;
     k_loc_init<<<grid_for(n), kBlk, 0, s>>>(n, dist, ppos);
     const int32_t zero = 0;
+    const uint32_t one = 1;
+    uint32_t* ctr = X.ctr.as<uint32_t>();  // this level's and the next one's (length, heavy) pairs, in turn
     BC_HIP(hipMemcpyAsync(dist + src, &zero, sizeof(int32_t), hipMemcpyHostToDevice, s));
-    BC_HIP(hipMemcpyAsync(la.p, &src, sizeof(int32_t), hipMemcpyHostToDevice, s));
-    if (order) BC_HIP(hipMemcpyAsync(order, &src, sizeof(int32_t), hipMemcpyHostToDevice, s));
+    BC_HIP(hipMemcpyAsync(X.la.p, &src, sizeof(int32_t), hipMemcpyHostToDevice, s));
+    BC_HIP(hipMemcpyAsync(order, &src, sizeof(int32_t), hipMemcpyHostToDevice, s));
+    BC_HIP(hipMemcpyAsync(ctr, &one, sizeof(uint32_t), hipMemcpyHostToDevice, s));
     uint32_t flen = 1, base = 0;
-    int32_t* F = la.as<int32_t>();
-    int32_t* N = lb.as<int32_t>();
+    int32_t* F = X.la.as<int32_t>();
+    int32_t* N = X.lb.as<int32_t>();
     for (int32_t d = 0; flen > 0; ++d) {
-        BC_HIP(hipMemsetAsync(cnt.p, 0, sizeof(uint32_t), s));
-        k_loc_expand<<<grid_for(flen), kBlk, 0, s>>>(g->dg.rp, g->dg.col, F, flen, d, base, dist, ppos, N,
-                                                      cnt.as<uint32_t>());
+        uint32_t *cur = ctr + 2 * (d & 1), *nxt = ctr + 2 * ((d + 1) & 1);
+        BC_HIP(hipMemsetAsync(nxt, 0, 2 * sizeof(uint32_t), s));
+        list_arcs(g->dg.rp, g->dg.col, F, cur, LocOp{dist, ppos, d, base}, N, nxt, X.heavy.as<uint32_t>(), s);
         uint32_t nc = 0;
-        BC_HIP(hipMemcpyAsync(&nc, cnt.p, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+        BC_HIP(hipMemcpyAsync(&nc, nxt, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
         BC_HIP(hipStreamSynchronize(s));
-        if (order && nc > 0) {
-            k_loc_keys<<<grid_for(nc), kBlk, 0, s>>>(nc, N, ppos, k0.as<uint64_t>());
+        if (nc > 0) {
+            k_loc_keys<<<grid_for(nc), kBlk, 0, s>>>(nc, N, ppos, X.k0.as<uint64_t>());
             BC_TRY(cub_call([&](void* t, size_t& b) {
-                return hipcub::DeviceRadixSort::SortKeys(t, b, k0.as<uint64_t>(), k1.as<uint64_t>(), (int)nc, 0, 64, s);
-            }, s, tmp));
-            k_low32<<<grid_for(nc), kBlk, 0, s>>>((int32_t)nc, k1.as<uint64_t>(), N);
+                return hipcub::DeviceRadixSort::SortKeys(t, b, X.k0.as<uint64_t>(), X.k1.as<uint64_t>(), (int)nc, 0, 64,
+                                                         s);
+            }, s, X.tmp));
+            k_low32<<<grid_for(nc), kBlk, 0, s>>>((int32_t)nc, X.k1.as<uint64_t>(), N);
             BC_HIP(hipMemcpyAsync(order + base + flen, N, sizeof(int32_t) * nc, hipMemcpyDeviceToDevice, s));
         }
         base += flen;
@@ -953,18 +1114,17 @@ static bc_status locality_seed(bc_graph* g, hipStream_t s) {
             BC_TRY(order_by_degree(g, deg_order.as<int32_t>(), s));
             lk.lock();
             if (!g->have_order_loc_seed) {
-                DevBuf da, db, ppos, la, lb, k0, k1, cnt, best, flag, nsel, tmp;
-                BC_TRY(da.alloc_on(sizeof(int32_t) * (size_t)n, s));
-                BC_TRY(db.alloc_on(sizeof(int32_t) * (size_t)n, s));
-                BC_TRY(ppos.alloc_on(sizeof(uint32_t) * (size_t)n, s));
-                BC_TRY(la.alloc_on(sizeof(int32_t) * (size_t)n, s));
-                BC_TRY(lb.alloc_on(sizeof(int32_t) * (size_t)n, s));
-                BC_TRY(k0.alloc_on(sizeof(uint64_t) * (size_t)n, s));
-                BC_TRY(k1.alloc_on(sizeof(uint64_t) * (size_t)n, s));
-                BC_TRY(cnt.alloc_on(sizeof(uint32_t), s));
-                BC_TRY(best.alloc_on(sizeof(unsigned long long), s));
-                BC_TRY(flag.alloc_on((size_t)n, s));
-                BC_TRY(nsel.alloc_on(sizeof(int32_t), s));
+                DevBuf all, da, db, ppos, best, flag, nsel;
+                LocScratch X;
+                Carve cv;
+                cv.add(da, sizeof(int32_t) * (size_t)n);
+                cv.add(db, sizeof(int32_t) * (size_t)n);
+                cv.add(ppos, sizeof(uint32_t) * (size_t)n);
+                cv.add(best, sizeof(unsigned long long));
+                cv.add(flag, (size_t)n);
+                cv.add(nsel, sizeof(int32_t));
+                X.add_to(cv, n, g->dg.m);
+                BC_TRY(cv.place_on(all, s));
                 BC_TRY(galloc(g, g->order_loc_seed, sizeof(int32_t) * (size_t)n, s));
                 int32_t* ord = g->order_loc_seed.as<int32_t>();
                 int32_t u0 = 0, reached = 0;
@@ -973,7 +1133,7 @@ static bc_status locality_seed(bc_graph* g, hipStream_t s) {
                 auto farthest = [&](int32_t* dist, int32_t* out) -> bc_status {
                     const unsigned long long z = 0;
                     BC_HIP(hipMemcpyAsync(best.p, &z, sizeof(z), hipMemcpyHostToDevice, s));
-                    k_loc_far<<<grid_for(n), kBlk, 0, s>>>(n, dist, best.as<unsigned long long>());
+                    k_loc_far<<<grid_for(n, kReduceGrid), kBlk, 0, s>>>(n, dist, best.as<unsigned long long>());
                     unsigned long long b = 0;
                     BC_HIP(hipMemcpyAsync(&b, best.p, sizeof(b), hipMemcpyDeviceToHost, s));
                     BC_HIP(hipStreamSynchronize(s));
@@ -982,30 +1142,29 @@ static bc_status locality_seed(bc_graph* g, hipStream_t s) {
                 };
                 // double sweep: u0 -> a (farthest), a -> b (farthest); centre on a-b
                 int32_t a = 0, b = 0;
-                BC_TRY(loc_bfs(g, u0, da.as<int32_t>(), nullptr, nullptr, &reached, la, lb, k0, k1, cnt, tmp, s));
+                BC_TRY(loc_dist(g, u0, da.as<int32_t>(), X, s));
                 BC_TRY(farthest(da.as<int32_t>(), &a));
-                BC_TRY(loc_bfs(g, a, da.as<int32_t>(), nullptr, nullptr, &reached, la, lb, k0, k1, cnt, tmp, s));
+                BC_TRY(loc_dist(g, a, da.as<int32_t>(), X, s));
                 BC_TRY(farthest(da.as<int32_t>(), &b));
                 int32_t D = 0;
                 BC_HIP(hipMemcpyAsync(&D, da.as<int32_t>() + b, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-                BC_TRY(loc_bfs(g, b, db.as<int32_t>(), nullptr, nullptr, &reached, la, lb, k0, k1, cnt, tmp, s));
+                BC_TRY(loc_dist(g, b, db.as<int32_t>(), X, s));
                 const unsigned long long mx = ~0ull;
                 BC_HIP(hipMemcpyAsync(best.p, &mx, sizeof(mx), hipMemcpyHostToDevice, s));
-                k_loc_centre<<<grid_for(n), kBlk, 0, s>>>(n, da.as<int32_t>(), db.as<int32_t>(), D,
+                k_loc_centre<<<grid_for(n, kReduceGrid), kBlk, 0, s>>>(n, da.as<int32_t>(), db.as<int32_t>(), D,
                                                           best.as<unsigned long long>());
                 unsigned long long cb = 0;
                 BC_HIP(hipMemcpyAsync(&cb, best.p, sizeof(cb), hipMemcpyDeviceToHost, s));
                 BC_HIP(hipStreamSynchronize(s));
                 const int32_t c = cb == ~0ull ? u0 : (int32_t)(uint32_t)(cb & 0xFFFFFFFFu);
                 // ordered BFS from the centre, then the other components in degree order
-                BC_TRY(loc_bfs(g, c, da.as<int32_t>(), ppos.as<uint32_t>(), ord, &reached, la, lb, k0, k1, cnt, tmp,
-                               s));
+                BC_TRY(loc_order(g, c, da.as<int32_t>(), ppos.as<uint32_t>(), ord, &reached, X, s));
                 k_loc_unreached<<<grid_for(n), kBlk, 0, s>>>(n, deg_order.as<int32_t>(), da.as<int32_t>(),
                                                              flag.as<uint8_t>());
                 BC_TRY(cub_call([&](void* t, size_t& bb) {
                     return hipcub::DeviceSelect::Flagged(t, bb, deg_order.as<int32_t>(), flag.as<uint8_t>(),
                                                          ord + reached, nsel.as<int32_t>(), n, s);
-                }, s, tmp));
+                }, s, X.tmp));
                 int32_t rest = 0;
                 BC_HIP(hipMemcpyAsync(&rest, nsel.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
                 BC_HIP(hipStreamSynchronize(s));
@@ -1141,11 +1300,12 @@ bc_status rows_to_caller(bc_graph* g, const void* d_src, void* d_dst, int width,
 // The renumbered graph: nodes in the locality seed order (breadth-first from
 // an approximate centre, then the other components by degree), so that a
 // node's neighbours, which a batch reaches together, have nearby ids and
-// their node records share cache lines and memory pages.  Built by a second
-// pass of graph_build over the renamed rows (which sorts them); the result
-// is the same graph up to the names of its nodes.
-bc_status graph_relabel(bc_graph* g, uint32_t flags, bool ordered, bc_graph** out) {
+// their node records share cache lines and memory pages.  Its rows are the
+// canonical rows renamed and sorted again, and its degrees and component
+// sizes are the first build's, so nothing is checked or searched twice.
+bc_status graph_relabel(bc_graph* g, bool ordered, bc_graph** out) {
     *out = nullptr;
+    auto t0 = std::chrono::steady_clock::now();
     const int32_t n = g->dg.n;
     const int64_t m = g->dg.m;
     hipStream_t s = g->stream;
@@ -1154,28 +1314,54 @@ bc_status graph_relabel(bc_graph* g, uint32_t flags, bool ordered, bc_graph** ou
     h->stream = s;
     h->ordered = ordered;
     h->device = g->device;
-    BC_TRY(galloc(h.get(), h->orig, sizeof(int32_t) * (size_t)n, s));
-    BC_TRY(galloc(h.get(), h->inv, sizeof(int32_t) * (size_t)n, s));
+    Carve c;
+    c.add(h->rp, sizeof(int32_t) * ((size_t)n + 1));
+    c.add(h->col, sizeof(int32_t) * (size_t)m);
+    c.add(h->deg, sizeof(uint32_t) * (size_t)n);
+    c.add(h->adj, sizeof(int2) * (size_t)m);
+    c.add(h->x0, sizeof(uint32_t) * (size_t)n);
+    c.add(h->x1, sizeof(uint32_t) * (size_t)n);
+    c.add(h->orig, sizeof(int32_t) * (size_t)n);
+    c.add(h->inv, sizeof(int32_t) * (size_t)n);
+    BC_TRY(gplace(h.get(), c, h->base, s));
+    int32_t *rp = h->rp.as<int32_t>(), *col = h->col.as<int32_t>();
+    uint32_t* deg = h->deg.as<uint32_t>();
     BC_HIP(hipMemcpyAsync(h->orig.p, g->order_loc_seed.p, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToDevice, s));
     k_inverse<<<grid_for(n), kBlk, 0, s>>>(n, h->orig.as<int32_t>(), h->inv.as<int32_t>());
-    DevBuf len, nrp, ncol, tmp;
-    BC_TRY(len.alloc_on(sizeof(int32_t) * (size_t)n, s));
-    BC_TRY(nrp.alloc_on(sizeof(int32_t) * ((size_t)n + 1), s));
-    BC_TRY(ncol.alloc_on(sizeof(int32_t) * (size_t)(m > 0 ? m : 1), s));
-    k_relabel_len<<<grid_for(n), kBlk, 0, s>>>(n, h->orig.as<int32_t>(), g->dg.deg, len.as<int32_t>());
+    k_relabel_nodes<<<grid_for(n), kBlk, 0, s>>>(n, h->orig.as<int32_t>(), g->dg.deg, g->dg.x0, deg,
+                                                 h->x0.as<uint32_t>(), h->x1.as<uint32_t>());
+    DevBuf ncol, tmp;
     BC_TRY(cub_call([&](void* t, size_t& b) {
-        return hipcub::DeviceScan::ExclusiveSum(t, b, len.as<int32_t>(), nrp.as<int32_t>(), n, s);
+        return hipcub::DeviceScan::ExclusiveSum(t, b, reinterpret_cast<const int32_t*>(deg), rp, n, s);
     }, s, tmp));
     const int32_t mm = (int32_t)m;
-    BC_HIP(hipMemcpyAsync(nrp.as<int32_t>() + n, &mm, sizeof(int32_t), hipMemcpyHostToDevice, s));
-    k_relabel_rows<<<grid_for((int64_t)n * 64), kBlk, 0, s>>>(n, h->orig.as<int32_t>(), h->inv.as<int32_t>(),
-                                                                g->dg.rp, g->dg.col, nrp.as<int32_t>(),
-                                                                ncol.as<int32_t>());
+    BC_HIP(hipMemcpyAsync(rp + n, &mm, sizeof(int32_t), hipMemcpyHostToDevice, s));
+    if (m > 0) {
+        BC_TRY(ncol.alloc_on(sizeof(int32_t) * (size_t)m, s));
+        k_relabel_rows<<<grid_for((int64_t)n * 64), kBlk, 0, s>>>(n, h->orig.as<int32_t>(), h->inv.as<int32_t>(),
+                                                                    g->dg.rp, g->dg.col, rp, ncol.as<int32_t>());
+        BC_TRY(cub_call([&](void* t, size_t& b) {
+            return hipcub::DeviceSegmentedRadixSort::SortKeys(t, b, ncol.as<int32_t>(), col, (int)m, n, rp, rp + 1, 0,
+                                                              32, s);
+        }, s, tmp));
+        k_pack_adj<<<grid_for(m), kBlk, 0, s>>>(m, col, deg, h->adj.as<int2>());
+    }
+    BC_HIP(hipGetLastError());
     BC_HIP(hipStreamSynchronize(s));
-    BC_TRY(graph_build(h.get(), n, m, nrp.as<int32_t>(), ncol.as<int32_t>(), flags | BC_DEVICE_PTRS));
-    h->dg.orig = h->orig.as<int32_t>();
+    DevGraph& d = h->dg;
+    d.n = n;
+    d.m = m;
+    d.directed = 0;
+    d.rp = d.irp = rp;
+    d.col = d.icol = col;
+    d.deg = deg;
+    d.adj = h->adj.as<int2>();
+    d.x0 = h->x0.as<uint32_t>();
+    d.x1 = h->x1.as<uint32_t>();
+    d.orig = h->orig.as<int32_t>();
     h->relabeled = true;
-    h->preprocess_ms += g->preprocess_ms;
+    h->preprocess_ms =
+        g->preprocess_ms + std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     *out = h.release();
     return BC_OK;
 }

@@ -113,8 +113,7 @@ __global__ void k_pivot(int32_t n, const int32_t* __restrict__ rp, const int32_t
         if (sc > 0x7FFFFFFFull) sc = 0x7FFFFFFFull;
         mx = max(mx, (unsigned long long)((sc << 32) | (uint32_t)v));
     }
-    mx = wave_max64(mx);
-    if (__lane_id() == 0 && mx) atomicMax(best, mx);
+    block_extreme64(mx, best);
 }
 
 // A level of a breadth-first search restricted to active nodes: mark bit
@@ -197,8 +196,16 @@ __global__ void k_is_root(int32_t n, const int32_t* __restrict__ comp, int32_t* 
     GSTRIDE_LOOP(v, n) flag[v] = comp[v] == (int32_t)v ? 1 : 0;
 }
 
-__global__ void k_cid(int32_t n, const int32_t* __restrict__ comp, const int32_t* __restrict__ rootpos,
-                      int32_t* __restrict__ cid, uint32_t* __restrict__ wsize) {
+// The component of `common` (the pivot's, mostly the giant one; -1: none) is
+// counted per workgroup, the others per wave.
+__global__ __launch_bounds__(kBlk) void k_cid(int32_t n, const int32_t* __restrict__ comp,
+                                              const int32_t* __restrict__ rootpos, int32_t common,
+                                              int32_t* __restrict__ cid, uint32_t* __restrict__ wsize) {
+    __shared__ uint32_t s_common;
+    if (threadIdx.x == 0) s_common = 0;
+    __syncthreads();
+    const int32_t cc = common >= 0 ? rootpos[common] : -1;
+    uint32_t mine = 0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < n; base += stride) {
         const int64_t v = base + threadIdx.x;
@@ -207,9 +214,13 @@ __global__ void k_cid(int32_t n, const int32_t* __restrict__ comp, const int32_t
         if (on) {
             c = rootpos[comp[v]];
             cid[v] = c;
+            mine += c == cc;
         }
-        wave_count_key(on, c, wsize);
+        wave_count_key(on && c != cc, c, wsize);
     }
+    if (mine) atomicAdd(&s_common, mine);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_common) atomicAdd(&wsize[cc], s_common);
 }
 
 // Arcs between components, one arc per thread, one append per wave.
@@ -451,8 +462,7 @@ __global__ void k_dag_heavy_close(const int32_t* __restrict__ heavy, const uint3
 }
 
 // The largest component: max over nodes of (w(cid[v]) << 32 | (2^31 - 1 - v)),
-// i.e. the largest size, then the smallest node id.  Wave-reduced, one
-// atomic per wave.
+// i.e. the largest size, then the smallest node id.
 __global__ void k_big_pick(int32_t n, const int32_t* __restrict__ cid, const uint32_t* __restrict__ wsize,
                            unsigned long long* best) {
     unsigned long long mx = 0;
@@ -460,11 +470,7 @@ __global__ void k_big_pick(int32_t n, const int32_t* __restrict__ cid, const uin
         unsigned long long key = ((unsigned long long)wsize[cid[v]] << 32) | (uint32_t)(0x7FFFFFFF - (int32_t)v);
         if (key > mx) mx = key;
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        unsigned long long o = __shfl_xor(mx, off);
-        if (o > mx) mx = o;
-    }
-    if (__lane_id() == 0 && mx) atomicMax(best, mx);
+    block_extreme64(mx, best);
 }
 
 // a level of an unrestricted breadth-first search; mark[] = 1 once reached
@@ -541,8 +547,9 @@ bc_status directed_reach(bc_graph* g) {
     const int32_t *rp = g->dg.rp, *col = g->dg.col, *irp = g->dg.irp, *icol = g->dg.icol;
 
     // ---- SCCs
-    DevBuf comp, comp_next, color, mark, q0, q1, best, hv;
+    DevBuf comp, comp_next, color, mark, q0, q1, best, hv, lctr;
     BC_TRY(hv.alloc_on(sizeof(uint32_t) * heavy_words(m), s));
+    BC_TRY(lctr.alloc_on(sizeof(uint32_t) * kListCtrWords, s));
     BC_TRY(comp.alloc_on(sizeof(int32_t) * N, s));
     BC_TRY(comp_next.alloc_on(sizeof(int32_t) * N, s));
     BC_TRY(color.alloc_on(sizeof(int32_t) * N, s));
@@ -564,14 +571,16 @@ bc_status directed_reach(bc_graph* g) {
     };
     BC_TRY(trim(4));
     // forward-backward from the pivot of largest in-degree x out-degree
+    int32_t common = -1;  // the pivot, which is its component's root
     {
         BC_HIP(hipMemsetAsync(best.p, 0, sizeof(unsigned long long), s));
-        k_pivot<<<grid_for(n), kBlk, 0, s>>>(n, rp, irp, cp, best.as<unsigned long long>());
+        k_pivot<<<grid_for(n, kReduceGrid), kBlk, 0, s>>>(n, rp, irp, cp, best.as<unsigned long long>());
         unsigned long long bk = 0;
         BC_HIP(hipMemcpyAsync(&bk, best.p, sizeof(bk), hipMemcpyDeviceToHost, s));
         BC_HIP(hipStreamSynchronize(s));
         if ((bk >> 32) > 0) {
             int32_t pivot = (int32_t)(bk & 0xFFFFFFFFu);
+            common = pivot;
             BC_HIP(hipMemsetAsync(mark.p, 0, sizeof(uint32_t) * N, s));
             for (int dir = 0; dir < 2; ++dir) {
                 const int32_t* R = dir == 0 ? rp : irp;
@@ -584,16 +593,10 @@ bc_status directed_reach(bc_graph* g) {
                 pbits |= bit;
                 BC_HIP(hipMemcpyAsync(mark.as<uint32_t>() + pivot, &pbits, sizeof(uint32_t), hipMemcpyHostToDevice, s));
                 BC_HIP(hipMemcpyAsync(q0.p, &pivot, sizeof(int32_t), hipMemcpyHostToDevice, s));
-                int32_t fn = 1;
-                int32_t *fq = q0.as<int32_t>(), *nq = q1.as<int32_t>();
-                uint32_t* lc = reinterpret_cast<uint32_t*>(fl + 4);  // list length, heavy entries
-                while (fn > 0) {
-                    BC_HIP(hipMemsetAsync(lc, 0, 2 * sizeof(uint32_t), s));
-                    list_arcs(R, C, fq, (uint32_t)fn, ReachOp{cp, mark.as<uint32_t>(), bit}, nq, lc,
-                              hv.as<uint32_t>(), s);
-                    BC_TRY(read_i32(fl + 4, &fn, s));
-                    std::swap(fq, nq);
-                }
+                uint64_t reached = 0;
+                BC_TRY(list_bfs(R, C, q0.as<int32_t>(), q1.as<int32_t>(),
+                                [&](int32_t) { return ReachOp{cp, mark.as<uint32_t>(), bit}; }, lctr.as<uint32_t>(),
+                                hv.as<uint32_t>(), &reached, s));
             }
             k_fwbw_assign<<<grid_for(n), kBlk, 0, s>>>(n, mark.as<uint32_t>(), cp, pivot);
         }
@@ -646,7 +649,7 @@ bc_status directed_reach(bc_graph* g) {
     const size_t NC = (size_t)(nc > 0 ? nc : 1);
     BC_TRY(wsize.alloc_on(sizeof(uint32_t) * NC, s));
     BC_HIP(hipMemsetAsync(wsize.p, 0, sizeof(uint32_t) * NC, s));
-    k_cid<<<grid_for(n), kBlk, 0, s>>>(n, cp, rootpos.as<int32_t>(), cid.as<int32_t>(), wsize.as<uint32_t>());
+    k_cid<<<grid_for(n, 4 * kReduceGrid), kBlk, 0, s>>>(n, cp, rootpos.as<int32_t>(), common, cid.as<int32_t>(), wsize.as<uint32_t>());
     BC_TRY(keys.alloc_on(sizeof(uint64_t) * (size_t)(m > 0 ? m : 1), s));
     BC_TRY(keys2.alloc_on(sizeof(uint64_t) * (size_t)(m > 0 ? m : 1), s));
     BC_HIP(hipMemsetAsync(fl + 3, 0, sizeof(int32_t), s));
@@ -682,7 +685,7 @@ bc_status directed_reach(bc_graph* g) {
     DevBuf inRT, omega2, toT;
     if (g->big_scc && nc > 0) {
         BC_HIP(hipMemsetAsync(best.p, 0, sizeof(unsigned long long), s));
-        k_big_pick<<<grid_for(n), kBlk, 0, s>>>(n, cid.as<int32_t>(), wsize.as<uint32_t>(),
+        k_big_pick<<<grid_for(n, kReduceGrid), kBlk, 0, s>>>(n, cid.as<int32_t>(), wsize.as<uint32_t>(),
                                                 best.as<unsigned long long>());
         unsigned long long bk = 0;
         BC_HIP(hipMemcpyAsync(&bk, best.p, sizeof(bk), hipMemcpyDeviceToHost, s));
@@ -697,17 +700,9 @@ bc_status directed_reach(bc_graph* g) {
         const uint32_t one = 1;
         BC_HIP(hipMemcpyAsync(mk + root, &one, sizeof(uint32_t), hipMemcpyHostToDevice, s));
         BC_HIP(hipMemcpyAsync(q0.p, &root, sizeof(int32_t), hipMemcpyHostToDevice, s));
-        uint64_t reached = 1;
-        int32_t fn = 1;
-        int32_t *fq = q0.as<int32_t>(), *nq = q1.as<int32_t>();
-        uint32_t* lc = reinterpret_cast<uint32_t*>(fl + 4);
-        while (fn > 0) {
-            BC_HIP(hipMemsetAsync(lc, 0, 2 * sizeof(uint32_t), s));
-            list_arcs(rp, col, fq, (uint32_t)fn, BfsOp{mk}, nq, lc, hv.as<uint32_t>(), s);
-            BC_TRY(read_i32(fl + 4, &fn, s));
-            reached += (uint64_t)fn;
-            std::swap(fq, nq);
-        }
+        uint64_t reached = 0;
+        BC_TRY(list_bfs(rp, col, q0.as<int32_t>(), q1.as<int32_t>(), [&](int32_t) { return BfsOp{mk}; },
+                        lctr.as<uint32_t>(), hv.as<uint32_t>(), &reached, s));
         int32_t c_big = 0;
         BC_TRY(read_i32(cid.as<int32_t>() + root, &c_big, s));
         BC_TRY(inRT.alloc_on(sizeof(int32_t) * NC, s));
