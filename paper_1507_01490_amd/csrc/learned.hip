@@ -250,10 +250,6 @@ __global__ void k_minmax_init(unsigned long long* mm) {
 
 // ------------------------------------------------------------ perceptron
 
-__device__ inline void load_params(const float* __restrict__ p, float* s) {
-    for (int i = threadIdx.x; i < kNP; i += blockDim.x) s[i] = p[i];
-}
-
 // h1 = relu(W1 x + b1) for one sample
 __device__ inline void layer1(const float* P, float x0, float x1, float x2, float h1[kH]) {
 #pragma unroll
@@ -289,34 +285,55 @@ __global__ __launch_bounds__(kBlk) void k_mlp_forward(const float* __restrict__ 
     }
 }
 
-// Loss gradient over one tile of kTile samples per workgroup, with the
-// unnormalised output gradient dy = 2 w (y - t); the reduction kernel sums
-// the tiles in a fixed order and divides by sum w.  Per tile row (sample):
-// X (3), DY, H1/H2 (forward activations), G2 = dL/d(pre-activation of layer
-// 2), G1 = dL/d(pre-activation of layer 1).  Partial row per tile:
-// the kNP gradient entries, then sum w r^2 and sum w.
+// Loss gradient over one tile of kTile samples per workgroup (four waves of 32
+// samples), with the unnormalised output gradient dy = 2 w (y - t); the
+// reduction kernel sums the tiles in a fixed order and divides by sum w.
+// Partial row per tile: the kNP gradient entries, then sum w r^2 and sum w.
+//
+// The three 64-wide products (layer 2 forward, its input gradient G1 = G2 W2,
+// its weight gradient G2' H1) run on the matrix cores in fp32, 32x32x2 tiles:
+// lane l holds A[l % 32][l / 32] and B[l / 32][l % 32], and register r of the
+// result is row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32.  Layer 1 is
+// computed straight in the A layout; only H1 and G2 pass through LDS (rows of
+// kH + 2 words: the 64 lanes of an A read then fall on 64 banks).  32,768
+// samples are 256 tiles, one per compute unit: bound by the products, 192
+// matrix instructions a wave (5 us).  Measured 22 us; one thread per sample
+// with the activations in rows of 64 words (all lanes on one bank) took 91.
+using v16f = __attribute__((ext_vector_type(16))) float;
+constexpr int kRow = kH + 2;
+
 struct GradLds {
-    float P[kNP];
+    float W2[kH * kRow];
+    float W1[3 * kH], B1[kH], B2[kH], W3[kH];
     float X[kTile][3];
-    float DY[kTile];
-    float H1[kTile][kH];
-    float H2[kTile][kH];
-    float G2[kTile][kH];
-    float G1[kTile][kH];
-    float WR2[kTile], WS[kTile];
+    float T[kTile], WS[kTile], DY[kTile], WR2[kTile];
+    float H1[kTile * kRow], G2[kTile * kRow];
+    float red[kBlk / 64][6][kH];  // per wave: db1, dW1 (3), db2, dw3
 };
+
+__device__ inline v16f mfma32(float a, float b, v16f c) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
 
 __global__ __launch_bounds__(kBlk) void k_mlp_grad(const float* __restrict__ params, const float* __restrict__ x,
                                                    const float* __restrict__ t, const float* __restrict__ w,
                                                    int64_t rows, const int32_t* __restrict__ idx, int64_t count,
                                                    float* __restrict__ part, uint32_t* __restrict__ bad) {
     __shared__ GradLds L;
-    load_params(params, L.P);
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int sl = lane & 31, h = lane >> 5;
+    const int s0 = wave * 32;  // this wave's samples
     const int64_t base = (int64_t)blockIdx.x * kTile;
-    __syncthreads();
+    for (int i = tid; i < kH * kH; i += kBlk) L.W2[(i / kH) * kRow + i % kH] = params[kOffW2 + i];
+    if (tid < 3 * kH) L.W1[tid] = params[kOffW1 + tid];
+    if (tid < kH) {
+        L.B1[tid] = params[kOffB1 + tid];
+        L.B2[tid] = params[kOffB2 + tid];
+        L.W3[tid] = params[kOffW3 + tid];
+    }
+    const float b3 = params[kOffB3];
     if (tid < kTile) {
-        int64_t s = base + tid;
+        const int64_t s = base + tid;
         float x0 = 0.f, x1 = 0.f, x2 = 0.f, ws = 0.f, tv = 0.f;
         int64_t v = s < count ? (idx ? (int64_t)idx[s] : s) : -1;
         if (s < count && (v < 0 || v >= rows)) {
@@ -333,102 +350,151 @@ __global__ __launch_bounds__(kBlk) void k_mlp_grad(const float* __restrict__ par
         L.X[tid][0] = x0;
         L.X[tid][1] = x1;
         L.X[tid][2] = x2;
-        float h1[kH];
-        layer1(L.P, x0, x1, x2, h1);
-        float out = L.P[kOffB3];
-        for (int j = 0; j < kH; ++j) {
-            float h2 = unit2(L.P, h1, j);
-            L.H2[tid][j] = h2;
-            out = fmaf(L.P[kOffW3 + j], h2, out);
-        }
-        float r = out - tv;
-        float dy = 2.f * ws * r;  // ws = 0 outside the sample range
-        L.DY[tid] = dy;
-        L.WR2[tid] = ws * r * r;
-        L.WS[tid] = ws;
-        float g1[kH];
-#pragma unroll
-        for (int i = 0; i < kH; ++i) g1[i] = 0.f;
-        for (int j = 0; j < kH; ++j) {
-            float g2 = L.H2[tid][j] > 0.f ? dy * L.P[kOffW3 + j] : 0.f;
-            L.G2[tid][j] = g2;
-#pragma unroll
-            for (int i = 0; i < kH; ++i) g1[i] = fmaf(L.P[kOffW2 + j * kH + i], g2, g1[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < kH; ++i) {
-            L.H1[tid][i] = h1[i];
-            L.G1[tid][i] = h1[i] > 0.f ? g1[i] : 0.f;
-        }
+        L.T[tid] = tv;
+        L.WS[tid] = ws;  // 0 outside the sample range
     }
     __syncthreads();
-    float* out = part + (size_t)blockIdx.x * (kNP + 2);
-    // dW2[j][i0 .. i0+15] = sum over the tile of G2[s][j] H1[s][i]
+    // layer 1: lane (sl, h) takes the units of parity h of its sample
+    float h1[kH / 2];
     {
-        const int j = tid >> 2, i0 = (tid & 3) * 16;
-        float a[16];
+        const float x0 = L.X[s0 + sl][0], x1 = L.X[s0 + sl][1], x2 = L.X[s0 + sl][2];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) a[q] = 0.f;
-        for (int s = 0; s < kTile; ++s) {
-            float g = L.G2[s][j];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) a[q] = fmaf(g, L.H1[s][i0 + q], a[q]);
+        for (int k = 0; k < kH / 2; ++k) {
+            const int i = 2 * k + h;
+            float a = L.B1[i];
+            a = fmaf(L.W1[i * 3 + 0], x0, a);
+            a = fmaf(L.W1[i * 3 + 1], x1, a);
+            a = fmaf(L.W1[i * 3 + 2], x2, a);
+            h1[k] = fmaxf(a, 0.f);
+            L.H1[(s0 + sl) * kRow + i] = h1[k];
         }
-#pragma unroll
-        for (int q = 0; q < 16; ++q) out[kOffW2 + j * kH + i0 + q] = a[q];
     }
-    // the small entries: W1 (192), b1 (64), b2 (64), w3 (64), b3, loss sums
-    for (int e = tid; e < 192 + 64 + 64 + 64 + 1 + 2; e += kBlk) {
-        float a = 0.f;
-        int dst;
-        if (e < 192) {
-            int i = e / 3, c = e % 3;
-            for (int s = 0; s < kTile; ++s) a = fmaf(L.G1[s][i], L.X[s][c], a);
-            dst = kOffW1 + e;
-        } else if (e < 256) {
-            int i = e - 192;
-            for (int s = 0; s < kTile; ++s) a += L.G1[s][i];
-            dst = kOffB1 + i;
-        } else if (e < 320) {
-            int j = e - 256;
-            for (int s = 0; s < kTile; ++s) a += L.G2[s][j];
-            dst = kOffB2 + j;
-        } else if (e < 384) {
-            int j = e - 320;
-            for (int s = 0; s < kTile; ++s) a = fmaf(L.DY[s], L.H2[s][j], a);
-            dst = kOffW3 + j;
-        } else if (e == 384) {
-            for (int s = 0; s < kTile; ++s) a += L.DY[s];
-            dst = kOffB3;
-        } else if (e == 385) {
-            for (int s = 0; s < kTile; ++s) a += L.WR2[s];
-            dst = kNP;
-        } else {
-            for (int s = 0; s < kTile; ++s) a += L.WS[s];
-            dst = kNP + 1;
+    // layer 2 pre-activations Z[s][j], j = sl and sl + 32
+    v16f z0, z1;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        z0[r] = L.B2[sl];
+        z1[r] = L.B2[32 + sl];
+    }
+#pragma unroll
+    for (int k = 0; k < kH / 2; ++k) {
+        z0 = mfma32(h1[k], L.W2[sl * kRow + 2 * k + h], z0);
+        z1 = mfma32(h1[k], L.W2[(32 + sl) * kRow + 2 * k + h], z1);
+    }
+    // output, residual and G2 = dL/dZ; this lane's column sums of G2 and dy H2
+    const float w30 = L.W3[sl], w31 = L.W3[32 + sl];
+    float b20 = 0.f, b21 = 0.f, g30 = 0.f, g31 = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int s = s0 + 8 * (r >> 2) + 4 * h + (r & 3);
+        const float a0 = fmaxf(z0[r], 0.f), a1 = fmaxf(z1[r], 0.f);
+        float out = fmaf(a1, w31, a0 * w30);
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) out += __shfl_xor(out, o);
+        const float res = out + b3 - L.T[s];
+        const float dy = 2.f * L.WS[s] * res;
+        if (sl == 0) {
+            L.DY[s] = dy;
+            L.WR2[s] = L.WS[s] * res * res;
         }
+        const float g0 = a0 > 0.f ? dy * w30 : 0.f, g1 = a1 > 0.f ? dy * w31 : 0.f;
+        L.G2[s * kRow + sl] = g0;
+        L.G2[s * kRow + 32 + sl] = g1;
+        b20 += g0;
+        b21 += g1;
+        g30 = fmaf(dy, a0, g30);
+        g31 = fmaf(dy, a1, g31);
+    }
+    __syncthreads();
+    // G1 = (G2 W2) where layer 1 was active; column sums of G1 and G1 x
+    v16f y0 = {}, y1 = {};
+#pragma unroll
+    for (int k = 0; k < kH / 2; ++k) {
+        const float a = L.G2[(s0 + sl) * kRow + 2 * k + h];
+        y0 = mfma32(a, L.W2[(2 * k + h) * kRow + sl], y0);
+        y1 = mfma32(a, L.W2[(2 * k + h) * kRow + 32 + sl], y1);
+    }
+    float c0[4] = {0.f, 0.f, 0.f, 0.f}, c1[4] = {0.f, 0.f, 0.f, 0.f};  // db1, dW1 of units sl and sl + 32
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int s = s0 + 8 * (r >> 2) + 4 * h + (r & 3);
+        const float g0 = L.H1[s * kRow + sl] > 0.f ? y0[r] : 0.f;
+        const float g1 = L.H1[s * kRow + 32 + sl] > 0.f ? y1[r] : 0.f;
+        c0[0] += g0;
+        c1[0] += g1;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            c0[1 + c] = fmaf(g0, L.X[s][c], c0[1 + c]);
+            c1[1 + c] = fmaf(g1, L.X[s][c], c1[1 + c]);
+        }
+    }
+    const float col0[6] = {c0[0], c0[1], c0[2], c0[3], b20, g30};
+    const float col1[6] = {c1[0], c1[1], c1[2], c1[3], b21, g31};
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+        const float u = col0[q] + __shfl_xor(col0[q], 32), v = col1[q] + __shfl_xor(col1[q], 32);
+        L.red[wave][q][lane] = h ? v : u;  // lanes 0..31: units 0..31, lanes 32..63: units 32..63
+    }
+    // dW2[j][i] = sum over the tile of G2[s][j] H1[s][i], one quadrant per wave
+    const int j0 = 32 * (wave >> 1), i0 = 32 * (wave & 1);
+    v16f d = {};
+#pragma unroll 16
+    for (int k = 0; k < kTile / 2; ++k)
+        d = mfma32(L.G2[(2 * k + h) * kRow + j0 + sl], L.H1[(2 * k + h) * kRow + i0 + sl], d);
+    float* out = part + (size_t)blockIdx.x * (kNP + 2);
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        out[kOffW2 + (j0 + 8 * (r >> 2) + 4 * h + (r & 3)) * kH + i0 + sl] = d[r];
+    __syncthreads();
+    // the small entries: waves in order
+    for (int e = tid; e < 6 * kH; e += kBlk) {
+        const int q = e / kH, i = e % kH;
+        float a = 0.f;
+        for (int k = 0; k < kBlk / 64; ++k) a += L.red[k][q][i];
+        const int dst = q == 0 ? kOffB1 + i : (q < 4 ? kOffW1 + 3 * i + q - 1 : (q == 4 ? kOffB2 + i : kOffW3 + i));
         out[dst] = a;
     }
+    if (wave < 3) {
+        const float* v = wave == 0 ? L.DY : (wave == 1 ? L.WR2 : L.WS);
+        float a = v[lane] + v[lane + 64];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
+        if (lane == 0) out[wave == 0 ? kOffB3 : kNP + wave - 1] = a;
+    }
 }
+static_assert(kTile == 128 && kBlk == 256, "four waves of 32 samples, two sums of 64");
 
-// grad[p] = (sum over tiles, in tile order, in double) / sum w; loss likewise.
-__global__ void k_mlp_grad_reduce(int ntiles, const float* __restrict__ part, float* __restrict__ grad,
-                                  double* __restrict__ loss) {
-    __shared__ double s_sw;
-    if (threadIdx.x == 0) {
-        double sw = 0.0;
-        for (int b = 0; b < ntiles; ++b) sw += part[(size_t)b * (kNP + 2) + kNP + 1];
-        s_sw = sw;
-    }
+// grad[p] = (sum over tiles, in double, in an order set by ntiles alone) / sum
+// w; loss likewise.  64 entries per workgroup, the tiles dealt over its 16
+// waves: one thread per entry and a serial sum of w took 117 us on 256 tiles,
+// this 8 us.
+constexpr int kRedBlk = 1024;
+__global__ __launch_bounds__(kRedBlk) void k_mlp_grad_reduce(int ntiles, const float* __restrict__ part,
+                                                             float* __restrict__ grad, double* __restrict__ loss) {
+    __shared__ double s_w[kRedBlk / 64];
+    __shared__ double s_p[kRedBlk / 64][64];
+    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+    constexpr int kG = kRedBlk / 64;
+    double sw = 0.0;
+    for (int b = threadIdx.x; b < ntiles; b += kRedBlk) sw += part[(size_t)b * (kNP + 2) + kNP + 1];
+    for (int o = 32; o > 0; o >>= 1) sw += __shfl_xor(sw, o);
+    if (lane == 0) s_w[g] = sw;
+    const int p = blockIdx.x * 64 + lane;
+    double a = 0.0;
+    if (p < kNP + 1)
+        for (int b = g; b < ntiles; b += kG) a += part[(size_t)b * (kNP + 2) + p];
+    s_p[g][lane] = a;
     __syncthreads();
-    const double sw = s_sw;
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < kNP + 1; p += gridDim.x * blockDim.x) {
-        double a = 0.0;
-        for (int b = 0; b < ntiles; ++b) a += part[(size_t)b * (kNP + 2) + p];
-        double v = sw > 0.0 ? a / sw : 0.0;
-        if (p < kNP) grad[p] = (float)v;
-        else *loss = v;
+    if (g != 0 || p >= kNP + 1) return;
+    sw = 0.0;
+    a = 0.0;
+    for (int k = 0; k < kG; ++k) {
+        sw += s_w[k];
+        a += s_p[k][lane];
     }
+    const double v = sw > 0.0 ? a / sw : 0.0;
+    if (p < kNP) grad[p] = (float)v;
+    else *loss = v;
 }
 
 __global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
@@ -523,14 +589,15 @@ bc_status mlp_loss_grad(const float* params, const float* x, const float* t, con
         set_error("too many samples in one gradient call (%lld)", (long long)count);
         return BC_EINVAL;
     }
-    DevBuf part, dres;
-    BC_TRY(part.alloc_on(sizeof(float) * (kNP + 2) * (size_t)ntiles, s));
-    BC_TRY(dres.alloc_on(sizeof(double) * 2, s));
+    DevBuf all, part, dres;
+    Carve c;
+    c.add(part, sizeof(float) * (kNP + 2) * (size_t)ntiles);
+    c.add(dres, sizeof(double) * 2);
+    BC_TRY(c.place_on(all, s));
     BC_HIP(hipMemsetAsync(dres.p, 0, sizeof(double) * 2, s));
     uint32_t* d_bad = reinterpret_cast<uint32_t*>(dres.as<double>() + 1);
     k_mlp_grad<<<(unsigned)ntiles, kBlk, 0, s>>>(params, x, t, w, rows, idx, count, part.as<float>(), d_bad);
-    k_mlp_grad_reduce<<<(kNP + 1 + kBlk - 1) / kBlk, kBlk, 0, s>>>((int)ntiles, part.as<float>(), grad,
-                                                                     dres.as<double>());
+    k_mlp_grad_reduce<<<(kNP + 1 + 63) / 64, kRedBlk, 0, s>>>((int)ntiles, part.as<float>(), grad, dres.as<double>());
     BC_HIP(hipGetLastError());
     double res[2] = {0.0, 0.0};
     BC_HIP(hipMemcpyAsync(res, dres.p, sizeof(res), hipMemcpyDeviceToHost, s));

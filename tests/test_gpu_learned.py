@@ -241,3 +241,26 @@ def test_learned_locality_order(width):
         res = G.topk(k, mode="batched", width=width, order="learned_locality")
     ref = oracle.topk(g, k)
     assert res.ids.tolist() == ref["ids"].tolist() and res.farness.tolist() == ref["f"].tolist()
+
+
+@pytest.mark.parametrize("count", [1, 31, 32, 33, 127, 128, 129, 128 * 17 + 5])
+def test_loss_grad_at_tile_edges(count):
+    """Tiles of 128 samples in four waves of 32: one short, exact, one over,
+    and more tiles than the reduction has waves.  Parameters, inputs, labels
+    and weights are small integers, so that every product and sum of a tile is
+    an integer below 2^24 and exact in fp32: the gradient has to equal the
+    oracle's to the last bit."""
+    rng = np.random.default_rng(count)
+    p = (rng.integers(-1, 2, bc.MLP_PARAMS) * (rng.random(bc.MLP_PARAMS) < 0.3)).astype(np.float32)
+    x = rng.integers(-2, 3, (count, 3)).astype(np.float32)
+    t = rng.integers(-9, 10, count).astype(np.float32)
+    w = rng.integers(1, 3, count).astype(np.float32)
+    args = [a.astype(np.float64) for a in (p, x, t, w)]
+    lref, gref, mag = omlp.loss_grad(*args)
+    sw = args[3].sum()
+    assert float(np.max(mag)) * sw / count * 128 < 2.0 ** 22  # a tile's sums stay exact
+    grad, loss = bc.mlp_loss_grad(cuda(p), cuda(x), cuda(t), cuda(w))
+    want = (np.rint(gref * sw) / sw).astype(np.float32)
+    assert np.max(np.abs(gref * sw - np.rint(gref * sw))) < 1e-6
+    assert grad.cpu().numpy().tolist() == want.tolist()
+    assert loss == np.rint(lref * sw) / sw
