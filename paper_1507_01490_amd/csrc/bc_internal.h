@@ -7,6 +7,7 @@
 //   adj[m]   (int2)        (col[e], deg[col[e]]): each arc with its target's
 //                          out-degree, so a level step that counts ~gamma reads
 //                          the degree in the same coalesced stream as the target
+//   heavy[*nheavy]         nodes of more than kPullWave in-arcs
 //   x0[n], x1[n] (u32)     reach data: undirected x0 = x1 = r(v) (component size);
 //                          directed x0 = alpha(v), x1 = omega(v)
 //   orig[n]                the caller's id of each node, or null when the graph
@@ -62,7 +63,12 @@ struct DevGraph {
     const uint32_t* x0;
     const uint32_t* x1;
     const int32_t* orig;
+    const int32_t* heavy;     // nodes with more than kPullWave in-arcs, and how many (device word)
+    const uint32_t* nheavy;
 };
+
+constexpr int32_t kPullWave = 64;  // in-arcs above which a bottom-up step gives a node a wave of its own
+inline size_t heavy_nodes(int64_t m) { return (size_t)(m / (kPullWave + 1)) + 1; }
 
 // Raise the release threshold of the device's default memory pool once per
 // device, so that stream-ordered frees keep their memory in the pool.
@@ -168,14 +174,16 @@ namespace bc {
 // query leaves seen/nxt/cur all zero (each batch resets the nodes it
 // reached), so a cached workspace is reused without clearing.
 struct Workspace {
-    int ww = 0;        // mask words per node the buffers were sized for
-    int slots = 0;     // batched slots allocated
-    DevBuf seen, qa, qb, clr;     // level-synchronous slot: node records and lists
+    int ww = 0;        // mask words per node the persistent slots were sized for
+    int slots = 0;     // persistent slots allocated
+    struct Lv {        // level-synchronous slots of one width (split layout), in one allocation
+        int slots = 0;
+        DevBuf mem, ctl, next, ns, cur, stamp, srcs, qa, qb, clr;
+    } lv[3];           // W = 64, 128, 256
     DevBuf bseen, bqa, bqb, bclr;  // persistent slots
-    DevBuf srcs, ctl, nextb, slot_stamp, defer;
-    bool plain_ready = false;
+    DevBuf nextb, slot_stamp, defer;
     hipStream_t stream = nullptr;  // stream its buffers are ordered on
-    uint32_t* hctl = nullptr;      // pinned copy of the level-synchronous control block
+    uint32_t* hctl = nullptr;      // pinned: the level-synchronous slots' reports
     hipStream_t cap = nullptr;     // private stream that captures level-step graphs
     Workspace() = default;
     explicit Workspace(hipStream_t s) : stream(s) {}
@@ -192,7 +200,7 @@ struct Workspace {
 struct bc_graph {
     bc::DevGraph dg{};
     bc::DevBuf base, fbase;  // memory of the arrays below / of the features (Carve)
-    bc::DevBuf rp, col, irp, icol, deg, adj, x0, x1;
+    bc::DevBuf rp, col, irp, icol, deg, adj, x0, x1, heavy, nheavy;
     bc::DevBuf order_deg;  // cached degree order (int32 n), built on first use
     bool have_order_deg = false;
     bc::DevBuf order_grp;  // cached grouped degree order

@@ -664,6 +664,28 @@ __global__ void k_gather_f32(int32_t n, const int32_t* __restrict__ orig, const 
     for (int32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < n; u += gridDim.x * blockDim.x) dst[u] = src[orig[u]];
 }
 
+// nodes of more than kPullWave in-arcs
+__global__ void k_heavy_nodes(int32_t n, const int32_t* __restrict__ irp, int32_t* __restrict__ heavy,
+                              uint32_t* nheavy) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < n; base += stride) {
+        const int64_t v = base + threadIdx.x;
+        const bool on = v < n && irp[v + 1] - irp[v] > kPullWave;
+        const uint32_t p = wave_claim(on, nheavy);
+        if (on) heavy[p] = (int32_t)v;
+    }
+}
+
+bc_status heavy_list(bc_graph* g, hipStream_t s) {
+    BC_HIP(hipMemsetAsync(g->nheavy.p, 0, sizeof(uint32_t), s));
+    if (g->dg.n > 0)
+        k_heavy_nodes<<<grid_for(g->dg.n), kBlk, 0, s>>>(g->dg.n, g->dg.irp, g->heavy.as<int32_t>(),
+                                                        g->nheavy.as<uint32_t>());
+    g->dg.heavy = g->heavy.as<int32_t>();
+    g->dg.nheavy = g->nheavy.as<uint32_t>();
+    return BC_OK;
+}
+
 template <class F>
 bc_status cub_call(F&& f, hipStream_t s, DevBuf& tmp) {
     size_t bytes = 0;
@@ -716,6 +738,8 @@ bc_status graph_build(bc_graph* g, int32_t n, int64_t m, const int32_t* rp_in, c
         c.add(g->adj, sizeof(int2) * (size_t)mc);
         c.add(g->x0, sizeof(uint32_t) * (size_t)n);
         c.add(g->x1, sizeof(uint32_t) * (size_t)n);
+        c.add(g->heavy, sizeof(int32_t) * heavy_nodes(mc));
+        c.add(g->nheavy, sizeof(uint32_t));
         return gplace(g, c, g->base, s);
     };
     if (err & 4u) {
@@ -814,7 +838,9 @@ bc_status graph_build(bc_graph* g, int32_t n, int64_t m, const int32_t* rp_in, c
         g->big_scc = (flags & BC_BIG_SCC) != 0;
         BC_TRY(directed_reach(g));
     }
+    BC_TRY(heavy_list(g, s));
     BC_HIP(hipGetLastError());
+    BC_HIP(hipStreamSynchronize(s));
     auto t1 = std::chrono::steady_clock::now();
     g->preprocess_ms = std::chrono::duration<double, std::milli>(t1 - t0).count();
     return BC_OK;
@@ -1323,6 +1349,8 @@ bc_status graph_relabel(bc_graph* g, bool ordered, bc_graph** out) {
     c.add(h->x1, sizeof(uint32_t) * (size_t)n);
     c.add(h->orig, sizeof(int32_t) * (size_t)n);
     c.add(h->inv, sizeof(int32_t) * (size_t)n);
+    c.add(h->heavy, sizeof(int32_t) * heavy_nodes(m));
+    c.add(h->nheavy, sizeof(uint32_t));
     BC_TRY(gplace(h.get(), c, h->base, s));
     int32_t *rp = h->rp.as<int32_t>(), *col = h->col.as<int32_t>();
     uint32_t* deg = h->deg.as<uint32_t>();
@@ -1347,7 +1375,6 @@ bc_status graph_relabel(bc_graph* g, bool ordered, bc_graph** out) {
         k_pack_adj<<<grid_for(m), kBlk, 0, s>>>(m, col, deg, h->adj.as<int2>());
     }
     BC_HIP(hipGetLastError());
-    BC_HIP(hipStreamSynchronize(s));
     DevGraph& d = h->dg;
     d.n = n;
     d.m = m;
@@ -1359,6 +1386,8 @@ bc_status graph_relabel(bc_graph* g, bool ordered, bc_graph** out) {
     d.x0 = h->x0.as<uint32_t>();
     d.x1 = h->x1.as<uint32_t>();
     d.orig = h->orig.as<int32_t>();
+    BC_TRY(heavy_list(h.get(), s));
+    BC_HIP(hipStreamSynchronize(s));
     h->relabeled = true;
     h->preprocess_ms =
         g->preprocess_ms + std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();

@@ -47,9 +47,16 @@ namespace bc {
 namespace {
 
 constexpr int kBlk = 256;  // threads per workgroup in every level kernel (and the most sources per batch)
-constexpr int kBatchBlk = 1024;  // threads per workgroup of the persistent batched kernel
+constexpr int kBatchBlk = 1024;  // threads per workgroup of the persistent batched and the narrow level kernels
 
-// words per node record: seen, nxt, cur (WW each) + meta, padded to 32/64/128 B
+// Node state of a slot, in one of two layouts:
+//   record (D = false, the persistent kernels): seen, nxt, cur (WW words each)
+//     and meta (out-degree << 32 | first-touch stamp) in one record padded to
+//     32/64/128 B, so that a node costs one line however much of it is touched
+//   split (D = true, the level-synchronous kernels): seen and nxt side by side
+//     (2 WW words), cur in a dense array of its own and the stamps in another
+//     (WW > 1); out-degrees come from the graph.  A bottom-up step gathers cur
+//     words alone: at W = 256 four nodes share a line instead of one
 template <int WW>
 struct Layout {
     static constexpr int SW = WW == 1 ? 4 : (WW == 2 ? 8 : 16);
@@ -113,6 +120,7 @@ struct Ctl {
     uint32_t d, flen, nlen, clen;  // level, frontier length, reached-list and reset-list counters
     uint32_t live, pull, chunk, done_blocks;
     uint32_t stamp, ran;           // ran: a level kernel ran in this step (captured level steps)
+    uint32_t state, pad_;          // LV_*: what the slot's batch waits for (host loop)
     unsigned long long front_arcs, acc_arcs;
     unsigned long long active[4];
     uint32_t cnt_g[256];
@@ -121,16 +129,64 @@ struct Ctl {
 };
 
 struct SlotPtrs {
-    uint64_t* ns;   // n * SW node records
-    int32_t* qa;    // n, frontier list F
-    int32_t* qb;    // n, reached list N
-    int32_t* clr;   // n, reset list
+    uint64_t* ns;     // n node records (SW words), or n pairs seen, nxt (2 WW words, split layout)
+    int32_t* qa;      // n, frontier list F
+    int32_t* qb;      // n, reached list N
+    int32_t* clr;     // n, reset list
+    uint64_t* cur;    // split layout: n * WW cur words
+    uint32_t* stamp;  // split layout, WW > 1: n first-touch stamps
 };
+template <int WW, bool D>
+__device__ inline uint64_t* node_rec(const SlotPtrs& P, int32_t w) {
+    return &P.ns[(size_t)w * (D ? 2 * WW : Layout<WW>::SW)];
+}
+template <int WW, bool D>
+__device__ inline uint64_t* node_cur(const SlotPtrs& P, int32_t w) {
+    if constexpr (D) return &P.cur[(size_t)w * WW];
+    else return node_rec<WW, false>(P, w) + Layout<WW>::CUR;
+}
+template <int WW, bool D>
+__device__ inline uint32_t* node_stamp(const SlotPtrs& P, int32_t w) {
+    if constexpr (D) return &P.stamp[w];
+    else return reinterpret_cast<uint32_t*>(node_rec<WW, false>(P, w) + Layout<WW>::META);
+}
 
 struct LevelParams {
     float pull_alpha, pull_beta;
     int32_t can_pull;
 };
+
+// What the batch of a level-synchronous slot waits for when the narrow kernel
+// hands it back to the host.
+enum : uint32_t { LV_IDLE = 0, LV_PUSH = 1, LV_PULL = 2, LV_CLEAR = 3, LV_DONE = 4 };
+struct LvReport {  // one per slot, in pinned host memory
+    uint32_t state, flen, clen, d;
+    unsigned long long front_arcs, pad_;
+};
+static_assert(sizeof(LvReport) == 32, "one report per 32 bytes");
+
+constexpr size_t kLvBytes = (size_t)1 << 30;  // of their slots, unless one alone needs more
+constexpr int kMaxSlots = 32;  // batches the level-synchronous kernels run side by side
+// The slots a level-synchronous launch works on: gridDim.y of them, blockIdx.y
+// picks one.
+struct LvSlots {
+    SlotPtrs base;
+    size_t n;       // nodes per slot
+    Ctl* C;
+    SrcState* S;    // kBlk sources per slot
+    uint8_t id[kMaxSlots];
+};
+template <int WW>
+__device__ inline SlotPtrs slot_ptrs(const LvSlots& L, size_t i) {
+    SlotPtrs P;
+    P.ns = L.base.ns + i * L.n * (2 * WW);
+    P.qa = L.base.qa + i * L.n;
+    P.qb = L.base.qb + i * L.n;
+    P.clr = L.base.clr + i * L.n;
+    P.cur = L.base.cur + i * L.n * WW;
+    P.stamp = L.base.stamp ? L.base.stamp + i * L.n : nullptr;
+    return P;
+}
 
 // ------------------------------------------------------------ helpers
 
@@ -279,42 +335,64 @@ __device__ inline void append_if(bool app, int32_t w, int32_t* list, uint32_t* c
     if (app) list[base + __popcll(bal & ((1ull << lane) - 1ull))] = w;
 }
 
-// Workgroup-aggregated append of w[u] where app[u] holds, u < N: one atomic
-// on the global counter per workgroup and call instead of one per wave (the
-// level-synchronous kernels' counters are single words that every wave of
-// the grid would otherwise hit).  sh: B / 64 + 1 words of LDS.  Call with
-// the whole workgroup.
-template <int B, int N>
-__device__ inline void block_append(const bool* app, const int32_t* w, int32_t* list, uint32_t* ctr, uint32_t* sh) {
-    const int lane = (int)lane_id();
-    const int wave = threadIdx.x >> 6;
-    unsigned long long bal[N];
-    uint32_t wc = 0;
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-        bal[u] = __ballot(app[u]);
-        wc += (uint32_t)__popcll(bal[u]);
+// LDS written by some lanes of a wave is read by others of the same wave.
+__device__ inline void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A wave's stage for a global list: nodes gather in LDS and go out behind one
+// global atomic per kStage nodes.  Every atomic on a list's length takes about
+// 12 ns, one after the other, whichever wave issues it: a level that reaches
+// 10^6 nodes spent 190 us on them with one per wave and 64 nodes.  Converged
+// wave.
+constexpr uint32_t kStage = 512;
+struct WaveStage {
+    int32_t* buf;   // kStage words of LDS, this wave's own
+    uint32_t cnt;   // the same in every lane
+    __device__ void flush(int32_t* list, uint32_t* ctr) {
+        if (cnt == 0) return;
+        wave_lds_sync();
+        uint32_t base = 0;
+        if (__lane_id() == 0) base = atomicAdd(ctr, cnt);
+        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+        for (uint32_t i = __lane_id(); i < cnt; i += 64) list[base + i] = buf[i];
+        wave_lds_sync();
+        cnt = 0;
     }
-    if (lane == 0) sh[wave] = wc;
+    __device__ void push(bool on, int32_t w, int32_t* list, uint32_t* ctr) {
+        const unsigned long long bal = __ballot(on);
+        if (bal == 0) return;
+        const uint32_t k = (uint32_t)__popcll(bal);
+        if (cnt + k > kStage) flush(list, ctr);
+        if (on) buf[cnt + __popcll(bal & ((1ull << __lane_id()) - 1ull))] = w;
+        cnt += k;
+    }
+};
+
+// What the workgroup's stages hold at the end of a list kernel, behind one
+// atomic (4,096 waves with one each took 50 us).  sh: B / 64 + 1 words of LDS.
+// Whole workgroup.
+template <int B>
+__device__ inline void block_flush(WaveStage& s, int32_t* list, uint32_t* ctr, uint32_t* sh) {
+    const int wave = threadIdx.x >> 6;
+    if (__lane_id() == 0) sh[wave] = s.cnt;
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t t = 0;
         for (int i = 0; i < B / 64; ++i) {
-            const uint32_t x = sh[i];
+            const uint32_t c = sh[i];
             sh[i] = t;
-            t += x;
+            t += c;
         }
         sh[B / 64] = t ? atomicAdd(ctr, t) : 0u;
     }
     __syncthreads();
-    uint32_t pos = sh[B / 64] + sh[wave];
-    const unsigned long long lt = (1ull << lane) - 1ull;
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-        if (app[u]) list[pos + (uint32_t)__popcll(bal[u] & lt)] = w[u];
-        pos += (uint32_t)__popcll(bal[u]);
-    }
-    __syncthreads();  // sh is reused by the next call
+    const uint32_t base = sh[B / 64] + sh[wave];
+    for (uint32_t i = __lane_id(); i < s.cnt; i += 64) list[base + i] = s.buf[i];
+    s.cnt = 0;
+    __syncthreads();
 }
 
 // gamma(b) += 1 and tgamma(b) += deg for every bit b of `bits` (word j)
@@ -388,7 +466,7 @@ __device__ inline void wave_count_nodes(const uint64_t* nb, uint32_t deg, uint32
 // L2 (they were written by atomics this level).  The out-degree comes from
 // the record's meta word, or from degs[] when the records are shared by the
 // batches of several graphs (their meta words then hold no degree).
-template <int WW, int B>
+template <int WW, int B, bool D = false>
 __device__ void count_level(const SlotPtrs& P, const int32_t* N, uint32_t len, uint32_t* cg, unsigned long long* ct,
                             const uint32_t* degs = nullptr) {
     using Lo = Layout<WW>;
@@ -401,11 +479,12 @@ __device__ void count_level(const SlotPtrs& P, const int32_t* N, uint32_t len, u
 #pragma unroll
         for (int j = 0; j < WW; ++j) nb[j] = 0;
         if (i < len) {
-            uint64_t* rec = &P.ns[(size_t)N[i] * Lo::SW];
+            uint64_t* rec = node_rec<WW, D>(P, N[i]);
 #pragma unroll
             for (int j = 0; j < WW; ++j)
                 nb[j] = __hip_atomic_load(&rec[Lo::NXT + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            deg = degs ? degs[N[i]] : (uint32_t)(rec[Lo::META] >> 32);
+            if constexpr (D) deg = degs[N[i]];
+            else deg = degs ? degs[N[i]] : (uint32_t)(rec[Lo::META] >> 32);
         }
         wave_count_nodes<WW>(nb, deg, cg, ct);
     }
@@ -414,9 +493,10 @@ __device__ void count_level(const SlotPtrs& P, const int32_t* N, uint32_t len, u
 // Arc u->w for the live source bits m of u: OR the unseen ones into nxt[w]
 // (the per-source counters are taken later, once per reached node).  Returns
 // whether w is new this level.
-template <int WW>
-__device__ inline bool visit(uint64_t* rec, const uint64_t* m, uint32_t stamp) {
+template <int WW, bool D>
+__device__ inline bool visit(const SlotPtrs& P, int32_t w, const uint64_t* m, uint32_t stamp) {
     using Lo = Layout<WW>;
+    uint64_t* rec = node_rec<WW, D>(P, w);
     uint64_t nb[WW];
     uint64_t any = 0;
     if constexpr (WW == 1) {
@@ -440,7 +520,7 @@ __device__ inline bool visit(uint64_t* rec, const uint64_t* m, uint32_t stamp) {
 #pragma unroll
         for (int j = 0; j < WW; ++j)
             if (nb[j]) atomicOr((unsigned long long*)&rec[Lo::NXT + j], (unsigned long long)nb[j]);
-        return atomicMax(reinterpret_cast<uint32_t*>(&rec[Lo::META]), stamp) < stamp;
+        return atomicMax(node_stamp<WW, D>(P, w), stamp) < stamp;
     }
 }
 
@@ -482,18 +562,20 @@ struct LdsExpand {
     uint32_t chunk;
 };
 
-// Expand entries [e0, e1) (at most kBlk) of the frontier list F: every arc of
+// Expand entries [e0, e1) (at most B) of the frontier list F: every arc of
 // every entry with a live bit, balanced over the workgroup by a scan of the
 // degrees.  Nodes reached for the first time this level go to N once.  Each
 // thread takes kArcs arcs per round (a, a + B, ...) and issues all their
 // target loads before it visits any target's record: two in the
 // level-synchronous kernel, one in the persistent kernels, where the second
-// arc's registers cost more than its overlap gains.
-template <int WW, int B = kBlk, int kArcs = 2, bool kBlockAppend = false>
+// arc's registers cost more than its overlap gains.  In the split layout an
+// entry's cur words are zeroed once read (nothing else reads them in a push
+// step).  With stg, the nodes go through the waves' stages to a global list;
+// without, nctr is a counter in LDS.
+template <int WW, int B = kBlk, int kArcs = 2, bool D = false>
 __device__ void expand_entries(const DevGraph& G, const SlotPtrs& P, const int32_t* F, uint32_t e0, uint32_t e1,
                                const uint64_t* act, int32_t* N, uint32_t* nctr, uint32_t stamp, LdsExpand<WW, B>& L,
-                               unsigned long long* arcs, unsigned long long* entries, uint32_t* bsh = nullptr) {
-    using Lo = Layout<WW>;
+                               unsigned long long* arcs, unsigned long long* entries, WaveStage* stg = nullptr) {
     const int tid = threadIdx.x;
     const uint32_t e = e0 + tid;
     uint32_t deg = 0;
@@ -503,11 +585,12 @@ __device__ void expand_entries(const DevGraph& G, const SlotPtrs& P, const int32
     for (int j = 0; j < WW; ++j) m[j] = 0;
     if (e < e1) {
         const int32_t u = F[e];
-        const uint64_t* rec = &P.ns[(size_t)u * Lo::SW];
+        uint64_t* cur = node_cur<WW, D>(P, u);
         uint64_t any = 0;
 #pragma unroll
         for (int j = 0; j < WW; ++j) {
-            m[j] = rec[Lo::CUR + j] & act[j];
+            m[j] = cur[j] & act[j];
+            if constexpr (D) cur[j] = 0;
             any |= m[j];
         }
         if (any) {
@@ -524,11 +607,16 @@ __device__ void expand_entries(const DevGraph& G, const SlotPtrs& P, const int32
     const uint32_t off = block_exscan<B>(deg, L.scan, &total);
     L.off[tid] = off;
     __syncthreads();
-    if constexpr (kArcs == 1) {
-        for (uint32_t a0 = 0; a0 < total; a0 += B) {
-            const uint32_t a = a0 + tid;
-            bool app = false;
-            int32_t w = 0;
+    for (uint32_t a0 = 0; a0 < total; a0 += kArcs * B) {
+        bool app[kArcs];
+        int32_t w[kArcs];
+        uint32_t own[kArcs];
+#pragma unroll
+        for (int u = 0; u < kArcs; ++u) {
+            app[u] = false;
+            w[u] = 0;
+            own[u] = 0;
+            const uint32_t a = a0 + (uint32_t)u * B + tid;
             if (a < total) {
                 // owner entry: the last i with off[i] <= a (off[0] = 0 <= a)
                 uint32_t lo = 0, hi = B;
@@ -536,45 +624,18 @@ __device__ void expand_entries(const DevGraph& G, const SlotPtrs& P, const int32
                     const uint32_t mid = (lo + hi) >> 1;
                     if (L.off[mid] <= a) lo = mid + 1; else hi = mid;
                 }
-                const uint32_t i = lo - 1;
-                w = G.col[L.beg[i] + (int32_t)(a - L.off[i])];
-                app = visit<WW>(&P.ns[(size_t)w * Lo::SW], &L.m[i * WW], stamp);
+                own[u] = lo - 1;
+                w[u] = G.col[L.beg[own[u]] + (int32_t)(a - L.off[own[u]])];
+                app[u] = true;
             }
-            if constexpr (kBlockAppend) block_append<B, 1>(&app, &w, N, nctr, bsh);
-            else append_if(app, w, N, nctr);
         }
-    } else {
-        for (uint32_t a0 = 0; a0 < total; a0 += kArcs * B) {
-            bool app[kArcs];
-            int32_t w[kArcs];
-            uint32_t own[kArcs];
 #pragma unroll
-            for (int u = 0; u < kArcs; ++u) {
-                app[u] = false;
-                w[u] = 0;
-                own[u] = 0;
-                const uint32_t a = a0 + (uint32_t)u * B + tid;
-                if (a < total) {
-                    // owner entry: the last i with off[i] <= a (off[0] = 0 <= a)
-                    uint32_t lo = 0, hi = B;
-                    while (lo < hi) {
-                        const uint32_t mid = (lo + hi) >> 1;
-                        if (L.off[mid] <= a) lo = mid + 1; else hi = mid;
-                    }
-                    own[u] = lo - 1;
-                    w[u] = G.col[L.beg[own[u]] + (int32_t)(a - L.off[own[u]])];
-                    app[u] = true;
-                }
-            }
+        for (int u = 0; u < kArcs; ++u)
+            if (app[u]) app[u] = visit<WW, D>(P, w[u], &L.m[own[u] * WW], stamp);
 #pragma unroll
-            for (int u = 0; u < kArcs; ++u)
-                if (app[u]) app[u] = visit<WW>(&P.ns[(size_t)w[u] * Lo::SW], &L.m[own[u] * WW], stamp);
-            if constexpr (kBlockAppend) {
-                block_append<B, kArcs>(app, w, N, nctr, bsh);
-            } else {
-#pragma unroll
-                for (int u = 0; u < kArcs; ++u) append_if(app[u], w[u], N, nctr);
-            }
+        for (int u = 0; u < kArcs; ++u) {
+            if (stg) stg->push(app[u], w[u], N, nctr);
+            else append_if(app[u], w[u], N, nctr);
         }
     }
     if (tid == 0) *arcs += total;
@@ -582,29 +643,31 @@ __device__ void expand_entries(const DevGraph& G, const SlotPtrs& P, const int32
 }
 
 // Zero the cur masks of the list entries [first, len) (stride).
-template <int WW>
+template <int WW, bool D = false>
 __device__ inline void clear_cur(const SlotPtrs& P, const int32_t* F, uint32_t len, uint32_t first, uint32_t stride) {
-    using Lo = Layout<WW>;
     for (uint32_t i = first + threadIdx.x; i < len; i += stride) {
-        uint64_t* rec = &P.ns[(size_t)F[i] * Lo::SW];
+        uint64_t* cur = node_cur<WW, D>(P, F[i]);
 #pragma unroll
-        for (int j = 0; j < WW; ++j) rec[Lo::CUR + j] = 0;
+        for (int j = 0; j < WW; ++j) cur[j] = 0;
     }
 }
 
 // Build the new frontier from the reached list N[0, len) once the cut step
 // has run: nxt is reset everywhere; the live bits go to seen and cur, nodes
 // with a live bit go to the frontier list F, first-seen nodes to the reset
-// list.  With no live bit at all only nxt is reset.  Block-uniform loop.
+// list.  With no live bit at all only nxt is reset.  Converged waves.
 // kFresh: the caller's compute unit holds no copy of the records that
 // predates the level's atomic updates (a kernel of its own, or after a grid
 // barrier's acquire), so nxt is read with a plain load; otherwise (the
-// persistent kernels, whose own plain loads may have cached a record before
-// the atomics changed it) it is taken with an exchange.
-template <int WW, bool kFresh = false>
+// persistent and narrow kernels, whose own plain loads may have cached a
+// record before the atomics changed it) it is taken with an exchange.
+// sf, sc: the waves' stages when F and the reset list have global counters
+// (the caller flushes them).
+template <int WW, bool D = false, bool kFresh = false>
 __device__ void build_level(const SlotPtrs& P, const int32_t* N, uint32_t len, uint32_t first, uint32_t stride,
                             const uint64_t* act, bool any_live, int32_t* F, uint32_t* fctr, uint32_t* clen,
-                            unsigned long long* arcs, uint32_t* seen_filter = nullptr, uint32_t* bsh = nullptr) {
+                            unsigned long long* arcs, uint32_t* seen_filter = nullptr, const uint32_t* degs = nullptr,
+                            WaveStage* sf = nullptr, WaveStage* sc = nullptr) {
     using Lo = Layout<WW>;
     const int tid = threadIdx.x;
     unsigned long long my_arcs = 0;
@@ -614,7 +677,7 @@ __device__ void build_level(const SlotPtrs& P, const int32_t* N, uint32_t len, u
         int32_t w = 0;
         if (i < len) {
             w = N[i];
-            uint64_t* rec = &P.ns[(size_t)w * Lo::SW];
+            uint64_t* rec = node_rec<WW, D>(P, w);
             if (!any_live) {
 #pragma unroll
                 for (int j = 0; j < WW; ++j) rec[Lo::NXT + j] = 0;
@@ -638,27 +701,27 @@ __device__ void build_level(const SlotPtrs& P, const int32_t* N, uint32_t len, u
                     }
                 }
                 if (any) {
+                    uint64_t* cur = node_cur<WW, D>(P, w);
                     uint64_t old_any = 0;
 #pragma unroll
                     for (int j = 0; j < WW; ++j) {
                         const uint64_t old = rec[j];
                         old_any |= old;
                         rec[j] = old | nb[j];
-                        rec[Lo::CUR + j] = nb[j];
+                        cur[j] = nb[j];
                     }
                     keep = true;
                     fresh = old_any == 0ull;
-                    my_arcs += (uint32_t)(rec[Lo::META] >> 32);
+                    if constexpr (D) my_arcs += degs[w];
+                    else my_arcs += (uint32_t)(rec[Lo::META] >> 32);
                     if (seen_filter) filter_set(seen_filter, w);
                 }
             }
         }
         if (any_live) {
-            if constexpr (kFresh) {
-                // a kernel of its own over the whole grid: one global atomic
-                // per workgroup and list (kBlk threads)
-                block_append<kBlk, 1>(&keep, &w, F, fctr, bsh);
-                block_append<kBlk, 1>(&fresh, &w, P.clr, clen, bsh);
+            if (sf) {
+                sf->push(keep, w, F, fctr);
+                sc->push(fresh, w, P.clr, clen);
             } else {
                 append_if(keep, w, F, fctr);
                 append_if(fresh, w, P.clr, clen);
@@ -690,9 +753,10 @@ __device__ uint32_t cut_step(const TopKDev& T, SrcState* S, int W, uint32_t d, b
     // edge per node back to Gamma_{d-1} (still scanned, so still in m_vis)
     uint64_t back = 0;
     if (tid < W) {
-        SrcState s = S[tid];
+        SrcState& s = S[tid];  // changed field by field: a copied struct ended up in scratch
+        const int32_t status = s.status;
         uint32_t fl = 0;
-        if (s.status == S_LIVE && apply) {
+        if (status == S_LIVE && apply) {
             uint32_t g;
             unsigned long long t;
             if (global_counts) {
@@ -711,10 +775,9 @@ __device__ uint32_t cut_step(const TopKDev& T, SrcState* S, int W, uint32_t d, b
                 back = T.footnote ? ((uint64_t)g < t ? (uint64_t)g : t) : 0;
                 s.tg = t - back;
             }
-        } else if (s.status == S_TRIVIAL && !apply) {
+        } else if (status == S_TRIVIAL && !apply) {
             fl = 1;
         }
-        S[tid] = s;
         s_flags[tid] = fl;
     }
     if (tid == 0) *s_live = 0;
@@ -789,23 +852,23 @@ __device__ uint32_t cut_step(const TopKDev& T, SrcState* S, int W, uint32_t d, b
     const bool have_th = CL.have_th != 0;
     bool live = false;
     if (tid < W) {
-        SrcState s = S[tid];
+        SrcState& s = S[tid];
         if (s.status == S_LIVE) {
+            const uint64_t mvis = s.mvis, next = s.tg + back;  // next: arcs out of Gamma_d
             if (have_th && cut_rule(s, d, CL.th)) {
                 s.status = S_CUT;
                 atomicAdd(&st->n_cut, 1ull);
-                if (s.mvis) atomicAdd(&st->m_vis, (unsigned long long)s.mvis);
-            } else if (D && D->budget && s.tg + back > D->budget) {
+                if (mvis) atomicAdd(&st->m_vis, (unsigned long long)mvis);
+            } else if (D && D->budget && next > D->budget) {
                 // too deep for one workgroup: restart it on the whole GPU later
                 s.status = S_DEFER;
                 D->ids[atomicAdd(D->cnt, 1u)] = s.id;
                 atomicAdd(&st->n_deferred, 1ull);
-                if (s.mvis) atomicAdd(&st->m_vis, (unsigned long long)s.mvis);
+                if (mvis) atomicAdd(&st->m_vis, (unsigned long long)mvis);
             } else {
-                s.mvis += s.tg + back;  // this source scans the out-arcs of Gamma_d
+                s.mvis = mvis + next;  // this source scans the out-arcs of Gamma_d
                 live = true;
             }
-            S[tid] = s;
         }
     }
     const unsigned long long bal = __ballot(live);
@@ -876,10 +939,9 @@ __device__ uint32_t trial_cut(const TopKDev& T, SrcState* S, int W, uint32_t d, 
 
 // Initialise the W sources of batch b: the frontier list F and the reset
 // list hold the sources themselves, each with its one-hot mask.
-template <int WW>
+template <int WW, bool D = false>
 __device__ void init_batch(const DevGraph& G, const int32_t* order, int32_t n, uint32_t b, int W, const SlotPtrs& P,
                            SrcState* S, uint32_t* flen_lds, unsigned long long* arcs_lds) {
-    using Lo = Layout<WW>;
     const int tid = threadIdx.x;
     if (tid == 0) {
         *flen_lds = 0;
@@ -902,12 +964,12 @@ __device__ void init_batch(const DevGraph& G, const int32_t* order, int32_t n, u
             s.status = s.x0 <= 1 ? S_TRIVIAL : S_LIVE;
             if (s.status == S_LIVE) {
                 const uint64_t bit = 1ull << (tid & 63);
-                uint64_t* rec = &P.ns[(size_t)v * Lo::SW];
+                uint64_t *rec = node_rec<WW, D>(P, v), *cur = node_cur<WW, D>(P, v);
 #pragma unroll
                 for (int j = 0; j < WW; ++j) {
                     const uint64_t x = (j == (tid >> 6)) ? bit : 0ull;
                     rec[j] = x;
-                    rec[Lo::CUR + j] = x;
+                    cur[j] = x;
                 }
                 const uint32_t pos = atomicAdd(flen_lds, 1u);
                 P.qa[pos] = v;
@@ -936,17 +998,36 @@ __global__ void k_slot_init(const uint32_t* __restrict__ deg, int32_t n, uint64_
         ns[i * Lo::SW + Lo::META] = (uint64_t)deg[i % (size_t)n] << 32;
 }
 
-// ------------------------------------------------------- plain kernels
+// ----------------------------------------------- level-synchronous kernels
 //
-// One batch at a time; per level the host launches
-//   expand (or pull; its last workgroup runs the cut step) -> clearcur -> build
-// and reads the control block to see whether any source is still live.
+// A batch on a slot of its own (split layout).  The narrow kernel runs every
+// level that one workgroup finishes sooner than a round trip to the host,
+// batch after batch; a wider level goes through
+//   push:  expand -> count (its last workgroup runs the cut step) -> build
+//   pull:  pull (likewise) -> clearcur -> build
+// over the whole GPU.  Several slots run side by side (gridDim.y), so that one
+// launch carries a level of each of their batches.  The other drivers
+// (captured level steps, one cooperative launch) use slot 0 and no narrow
+// kernel.
+
+constexpr int kLvBlk = 1024;  // threads per workgroup: few, large workgroups, since each ends in up to
+                              // 512 device-wide atomics (the level's counters; see WaveStage for their cost)
+
+// Direction of the next level from the frontier's arcs and nodes.
+__device__ inline uint32_t next_pull(uint32_t pull, unsigned long long fa, uint32_t flen, const DevGraph& G,
+                                     const LevelParams& lp) {
+    if (lp.can_pull) {
+        if (!pull && lp.pull_alpha > 0.f && (double)fa > (double)G.m / lp.pull_alpha) return 1;
+        if (pull && (double)flen < (double)G.n / lp.pull_beta) return 0;
+    }
+    return pull;
+}
 
 template <int WW>
 __device__ void plain_init_body(const DevGraph& G, const int32_t* order, int32_t count, uint32_t b, int W,
                                 const SlotPtrs& P, SrcState* S, Ctl* C, const TopKDev& T, QStats* st, CutLds& CL,
                                 uint32_t& s_flen, unsigned long long& s_arcs, uint64_t* s_act) {
-    init_batch<WW>(G, order, count, b, W, P, S, &s_flen, &s_arcs);
+    init_batch<WW, true>(G, order, count, b, W, P, S, &s_flen, &s_arcs);
     const uint32_t live = cut_step<WW>(T, S, W, 0, false, nullptr, nullptr, false, false, st, s_act, CL);
     if (threadIdx.x == 0) {
         C->stamp = C->stamp + 1;
@@ -967,18 +1048,18 @@ __device__ void plain_init_body(const DevGraph& G, const int32_t* order, int32_t
 
 template <int WW>
 __global__ __launch_bounds__(kBlk) void k_plain_init(DevGraph G, const int32_t* order, int32_t count, uint32_t b,
-                                                    int W, SlotPtrs P, SrcState* S, Ctl* C, TopKDev T, QStats* st) {
+                                                    int W, LvSlots L, TopKDev T, QStats* st) {
     __shared__ CutLds CL;
     __shared__ uint32_t s_flen;
     __shared__ unsigned long long s_arcs;
     __shared__ uint64_t s_act[4];
-    plain_init_body<WW>(G, order, count, b, W, P, S, C, T, st, CL, s_flen, s_arcs, s_act);
+    plain_init_body<WW>(G, order, count, b, W, slot_ptrs<WW>(L, 0), L.S, L.C, T, st, CL, s_flen, s_arcs, s_act);
 }
 
-// Shared epilogue of the plain expand/pull kernels: flush the workgroup's bit
-// counters; the last workgroup to finish runs the cut step for the level.
+// Shared epilogue of the count and pull kernels: flush the workgroup's bit
+// counters; the last workgroup of the slot runs the cut step for the level.
 template <int WW>
-__device__ void plain_level_epilogue(Ctl* C, SrcState* S, TopKDev T, QStats* st, int W, const uint32_t* cg,
+__device__ void plain_level_epilogue(Ctl* C, SrcState* S, const TopKDev& T, QStats* st, int W, const uint32_t* cg,
                                      const unsigned long long* ct, CutLds& CL, uint64_t* s_act, uint32_t* s_last) {
     const int tid = threadIdx.x;
     if (tid < W && cg[tid]) {
@@ -992,7 +1073,7 @@ __device__ void plain_level_epilogue(Ctl* C, SrcState* S, TopKDev T, QStats* st,
     if (!*s_last) return;
     __threadfence();
     const uint32_t d = C->d;
-    const uint32_t live = cut_step<WW>(T, S, W, d + 1, true, C->cnt_g, C->cnt_t, true, false, st, s_act, CL);
+    const uint32_t live = cut_step<WW>(T, S, W, d + 1, true, C->cnt_g, C->cnt_t, true, true, st, s_act, CL);
     if (tid < W) {
         C->cnt_g[tid] = 0;
         C->cnt_t[tid] = 0;
@@ -1015,68 +1096,89 @@ __device__ void plain_level_epilogue(Ctl* C, SrcState* S, TopKDev T, QStats* st,
 // source is live and the step's direction is push (the pull kernel of the
 // same step takes the other case).  Every thread reads the same control
 // words, written by kernels that finished before this one started.
+//
 // Frontier entries per chunk a workgroup claims in a push step: about
 // kChunkArcs arcs (the level's arcs spread evenly over its entries), at most
-// kBlk.  A level of a few heavy entries, such as the hub sources of level 0
-// in degree order, then spreads over many workgroups instead of one.
+// kLvBlk, and fewer arcs where the level would otherwise give less than
+// kChunkMin chunks: a level of a few heavy entries, such as the hub sources of
+// level 0 in degree order, then spreads over many workgroups instead of one.
 constexpr unsigned long long kChunkArcs = 4096;
+constexpr unsigned long long kChunkMin = 256;
 __host__ __device__ inline uint32_t expand_chunk(uint32_t flen, unsigned long long arcs) {
-    if (arcs == 0) return kBlk;
-    const unsigned long long per = (unsigned long long)flen * kChunkArcs / arcs;
-    return per < 1 ? 1u : (per > (unsigned long long)kBlk ? (uint32_t)kBlk : (uint32_t)per);
+    if (arcs == 0) return kLvBlk;
+    unsigned long long want = arcs / kChunkMin;
+    want = want < kLvBlk ? (unsigned long long)kLvBlk : (want > kChunkArcs ? kChunkArcs : want);
+    const unsigned long long per = (unsigned long long)flen * want / arcs;
+    return per < 1 ? 1u : (per > (unsigned long long)kLvBlk ? (uint32_t)kLvBlk : (uint32_t)per);
 }
 
 template <int WW>
-__device__ void plain_expand_body(const DevGraph& G, const SlotPtrs& P, Ctl* C, QStats* st, LdsExpand<WW>& L,
-                                  uint64_t* s_act, unsigned long long& s_arcs, unsigned long long& s_ent,
-                                  uint32_t* bsh) {
+struct PushLds {
+    LdsExpand<WW, kLvBlk> L;
+    int32_t stage[kLvBlk / 64][kStage];
+    uint64_t act[4];
+    unsigned long long arcs, ent;
+    uint32_t sh[kLvBlk / 64 + 1];
+};
+
+template <int WW>
+__device__ void plain_expand_body(const DevGraph& G, const SlotPtrs& P, Ctl* C, QStats* st, PushLds<WW>& X) {
     const uint32_t flen = C->flen, stamp = C->stamp;
     const uint32_t per = expand_chunk(flen, C->front_arcs);
     const int tid = threadIdx.x;
-    if (tid < WW) s_act[tid] = C->active[tid];
+    if (tid < WW) X.act[tid] = C->active[tid];
     if (tid == 0) {
-        s_arcs = 0;
-        s_ent = 0;
+        X.arcs = 0;
+        X.ent = 0;
     }
+    WaveStage stg{X.stage[tid >> 6], 0};
     __syncthreads();
     for (;;) {
-        if (tid == 0) L.chunk = atomicAdd(&C->chunk, 1u);
+        if (tid == 0) X.L.chunk = atomicAdd(&C->chunk, 1u);
         __syncthreads();
-        const unsigned long long e0 = (unsigned long long)L.chunk * per;
+        const unsigned long long e0 = (unsigned long long)X.L.chunk * per;
         __syncthreads();
         if (e0 >= flen) break;
-        expand_entries<WW, kBlk, 2, true>(G, P, P.qa, (uint32_t)e0, min(flen, (uint32_t)e0 + per), s_act, P.qb,
-                                          &C->nlen, stamp, L, &s_arcs, &s_ent, bsh);
+        expand_entries<WW, kLvBlk, 2, true>(G, P, P.qa, (uint32_t)e0, min(flen, (uint32_t)e0 + per), X.act, P.qb,
+                                              &C->nlen, stamp, X.L, &X.arcs, &X.ent, &stg);
     }
-    if (tid == 0 && s_arcs) atomicAdd(&st->node_arcs, s_arcs);
-    if (tid == 0 && s_ent) atomicAdd(&st->frontier_entries, s_ent);
+    block_flush<kLvBlk>(stg, P.qb, &C->nlen, X.sh);
+    if (tid == 0 && X.arcs) atomicAdd(&st->node_arcs, X.arcs);
+    if (tid == 0 && X.ent) atomicAdd(&st->frontier_entries, X.ent);
 }
 
 template <int WW>
-__global__ __launch_bounds__(kBlk) void k_plain_expand(DevGraph G, SlotPtrs P, Ctl* C, QStats* st, int gated) {
+__global__ __launch_bounds__(kLvBlk) void k_plain_expand(DevGraph G, LvSlots L, QStats* st, int gated) {
+    __shared__ PushLds<WW> X;
+    const size_t i = L.id[blockIdx.y];
+    Ctl* C = L.C + i;
     if (gated && (C->live == 0 || C->pull != 0)) return;
-    __shared__ LdsExpand<WW> L;
-    __shared__ uint64_t s_act[4];
-    __shared__ unsigned long long s_arcs, s_ent;
-    __shared__ uint32_t bsh[kBlk / 64 + 1];
-    plain_expand_body<WW>(G, P, C, st, L, s_act, s_arcs, s_ent, bsh);
+    plain_expand_body<WW>(G, slot_ptrs<WW>(L, i), C, st, X);
 }
 
 // After a push step: the per-source counters of the level from its list of
 // newly reached nodes (once per node), then the cut step in the last
 // workgroup.  Same gate as the push step.
+struct CountLds {
+    uint32_t cg[kBlk];
+    unsigned long long ct[kBlk];
+    CutLds CL;
+    uint32_t last;
+    uint64_t act[4];
+};
+
 template <int WW>
-__device__ void plain_count_body(const SlotPtrs& P, SrcState* S, Ctl* C, const TopKDev& T, QStats* st, int W,
-                                 uint32_t* cg, unsigned long long* ct, CutLds& CL, uint32_t& s_last,
-                                 uint64_t* s_act) {
-    using Lo = Layout<WW>;
+__device__ void plain_count_body(const DevGraph& G, const SlotPtrs& P, SrcState* S, Ctl* C, const TopKDev& T,
+                                 QStats* st, int W, CountLds& X) {
     const uint32_t tid = threadIdx.x;
-    cg[tid] = 0;
-    ct[tid] = 0;
+    if (tid < kBlk) {
+        X.cg[tid] = 0;
+        X.ct[tid] = 0;
+    }
     __syncthreads();
     const uint32_t len = C->nlen;
-    const uint32_t stride = gridDim.x * kBlk;
-    for (uint32_t base = blockIdx.x * kBlk; base < len; base += stride) {
+    const uint32_t stride = gridDim.x * kLvBlk;
+    for (uint32_t base = blockIdx.x * kLvBlk; base < len; base += stride) {
         if (base + (tid & ~63u) >= len) break;  // wave-uniform: nothing left for this wave
         const uint32_t i = base + tid;
         uint64_t nb[WW];
@@ -1084,37 +1186,27 @@ __device__ void plain_count_body(const SlotPtrs& P, SrcState* S, Ctl* C, const T
 #pragma unroll
         for (int j = 0; j < WW; ++j) nb[j] = 0;
         if (i < len) {
-            const uint64_t* rec = &P.ns[(size_t)P.qb[i] * Lo::SW];
+            const int32_t w = P.qb[i];
+            const uint64_t* rec = node_rec<WW, true>(P, w);
 #pragma unroll
-            for (int j = 0; j < WW; ++j) nb[j] = rec[Lo::NXT + j];
-            deg = (uint32_t)(rec[Lo::META] >> 32);
+            for (int j = 0; j < WW; ++j) nb[j] = rec[WW + j];
+            deg = G.deg[w];
         }
-        wave_count_nodes<WW>(nb, deg, cg, ct);
+        wave_count_nodes<WW>(nb, deg, X.cg, X.ct);
     }
     __syncthreads();
-    plain_level_epilogue<WW>(C, S, T, st, W, cg, ct, CL, s_act, &s_last);
+    plain_level_epilogue<WW>(C, S, T, st, W, X.cg, X.ct, X.CL, X.act, &X.last);
 }
 
 template <int WW>
-__global__ __launch_bounds__(kBlk) void k_plain_count(SlotPtrs P, SrcState* S, Ctl* C, TopKDev T, QStats* st,
-                                                     int W, int gated) {
+__global__ __launch_bounds__(kLvBlk) void k_plain_count(DevGraph G, LvSlots L, TopKDev T, QStats* st, int W,
+                                                       int gated) {
+    __shared__ CountLds X;
+    const size_t i = L.id[blockIdx.y];
+    Ctl* C = L.C + i;
     if (gated && (C->live == 0 || C->pull != 0)) return;
-    __shared__ uint32_t cg[kBlk];
-    __shared__ unsigned long long ct[kBlk];
-    __shared__ CutLds CL;
-    __shared__ uint32_t s_last;
-    __shared__ uint64_t s_act[4];
-    plain_count_body<WW>(P, S, C, T, st, W, cg, ct, CL, s_last, s_act);
+    plain_count_body<WW>(G, slot_ptrs<WW>(L, i), L.S + i * kBlk, C, T, st, W, X);
 }
-
-// Bottom-up step: every node not yet seen by some live source looks for an
-// in-neighbour in the frontier of that source (early exit once all of its
-// unseen live bits are found).  One thread owns a node, so all bits it finds
-// are new and counted here.  A node with more than kPullWave in-arcs is
-// scanned by its whole wave, 64 arcs a round, the bits found OR-reduced over
-// the wave (on skewed graphs one thread walking a hub's list serially held
-// its wave, and the level, for the whole walk).
-constexpr int32_t kPullWave = 32;
 
 // OR of x over the 64 lanes of the wave, in every lane.
 __device__ inline uint64_t wave_or(uint64_t x) {
@@ -1123,172 +1215,283 @@ __device__ inline uint64_t wave_or(uint64_t x) {
     return x;
 }
 
+// Bottom-up step: every node not yet seen by some live source looks for an
+// in-neighbour in the frontier of that source.  A wave owns 64 nodes, so all
+// bits it finds are new and counted here.  The lists of its nodes with up to
+// kPullWave in-arcs are walked as one flat sequence, 64 arcs at a time (two
+// such rounds in flight), each lane ORing what it finds into its node's word
+// in LDS; a node that has all its unseen bits is passed over.  A longer list
+// is walked by a whole wave, kPullAhead rounds at a time before it looks
+// whether all bits are found; the graph keeps a list of these nodes, dealt one
+// to a wave over the grid, since renumbering puts the hubs side by side and a
+// wave with 64 of them lasted a millisecond.  (One thread per node walked its list with two
+// dependent loads an arc: about 770 us a level on a Barabasi-Albert graph of
+// 10^6 nodes at W = 256, now 200-300.)
+constexpr int kPullAhead = 4;
+constexpr int kPullFlat = 2;
+
+template <int WW>
+struct PullWaveLds {
+    uint64_t acc[64 * WW], unv[64 * WW];
+    uint32_t off[64];
+    int32_t beg[64];
+};
+
+// The 64 nodes w .. of one wave (lane's node w < G.n, else none); appends the
+// nodes that found something to N (through stg to a global counter, or without
+// one to a counter in LDS).  Counts the arcs read.  Converged wave.
+template <int WW>
+__device__ __forceinline__ void pull_nodes(const DevGraph& G, const SlotPtrs& P, const uint64_t* act, int64_t w, PullWaveLds<WW>& L,
+                           uint32_t* cg, unsigned long long* ct, WaveStage* stg, uint32_t* nlen,
+                           unsigned long long& scanned) {
+    const int lane = (int)lane_id();
+    uint64_t unv[WW];
+    uint64_t any = 0;
+    int32_t e0 = 0, e1 = 0;
+    uint64_t* rec = nullptr;
+#pragma unroll
+    for (int j = 0; j < WW; ++j) unv[j] = 0;
+    if (w < G.n) {
+        rec = node_rec<WW, true>(P, (int32_t)w);
+#pragma unroll
+        for (int j = 0; j < WW; ++j) {
+            unv[j] = act[j] & ~rec[j];
+            any |= unv[j];
+        }
+        if (any) {
+            e0 = G.irp[w];
+            e1 = G.irp[w + 1];
+        }
+    }
+    const uint32_t len = e1 - e0 > kPullWave ? 0u : (uint32_t)(e1 - e0);  // longer lists: pull_heavy
+    if (__ballot(len != 0) == 0ull) return;
+    uint32_t x = len;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o);
+        if (lane >= o) x += y;
+    }
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readfirstlane((int)__shfl(x, 63));
+    L.off[lane] = x - len;
+    L.beg[lane] = e0;
+#pragma unroll
+    for (int j = 0; j < WW; ++j) {
+        L.acc[lane * WW + j] = 0;
+        L.unv[lane * WW + j] = unv[j];
+    }
+    wave_lds_sync();
+    for (uint32_t a0 = 0; a0 < total; a0 += 64 * kPullFlat) {
+        int32_t u[kPullFlat];
+        uint32_t own[kPullFlat];
+#pragma unroll
+        for (int q = 0; q < kPullFlat; ++q) {
+            const uint32_t a = a0 + (uint32_t)(q * 64 + lane);
+            u[q] = -1;
+            own[q] = 0;
+            if (a < total) {
+                // owner: the last lane with off <= a (off[0] = 0), which has arcs
+                uint32_t o = 0;
+#pragma unroll
+                for (uint32_t b = 32; b > 0; b >>= 1)
+                    if (L.off[o + b] <= a) o += b;
+                uint64_t open = 0;
+#pragma unroll
+                for (int j = 0; j < WW; ++j) open |= L.unv[o * WW + j] & ~L.acc[o * WW + j];
+                own[q] = o;
+                if (open) u[q] = G.icol[L.beg[o] + (int32_t)(a - L.off[o])];
+            }
+        }
+        uint64_t c[kPullFlat * WW];
+#pragma unroll
+        for (int q = 0; q < kPullFlat; ++q) {
+            const uint64_t* cur = node_cur<WW, true>(P, max(u[q], 0));
+            scanned += u[q] >= 0;
+#pragma unroll
+            for (int j = 0; j < WW; ++j) c[q * WW + j] = u[q] >= 0 ? cur[j] : 0ull;
+        }
+#pragma unroll
+        for (int q = 0; q < kPullFlat; ++q) {
+#pragma unroll
+            for (int j = 0; j < WW; ++j) {
+                const uint64_t bits = c[q * WW + j] & L.unv[own[q] * WW + j];
+                if (bits) atomicOr((unsigned long long*)&L.acc[own[q] * WW + j], (unsigned long long)bits);
+            }
+        }
+        wave_lds_sync();
+    }
+    uint64_t got = 0, acc[WW];
+    uint32_t deg = 0;
+#pragma unroll
+    for (int j = 0; j < WW; ++j) {
+        acc[j] = L.acc[lane * WW + j];
+        got |= acc[j];
+    }
+    if (got) {
+        deg = G.deg[w];
+#pragma unroll
+        for (int j = 0; j < WW; ++j) rec[WW + j] = acc[j];
+    }
+    wave_lds_sync();
+    wave_count_nodes<WW>(acc, deg, cg, ct);
+    if (stg) stg->push(got != 0, (int32_t)w, P.qb, nlen);
+    else append_if(got != 0, (int32_t)w, P.qb, nlen);
+}
+
+// One node with more than kPullWave in-arcs, its list read by the whole wave;
+// returns in lane 0 whether it found something.  Converged wave.
+template <int WW>
+__device__ __forceinline__ bool pull_heavy(const DevGraph& G, const SlotPtrs& P, const uint64_t* act, int32_t w,
+                                           uint32_t* cg, unsigned long long* ct, unsigned long long& scanned) {
+    const int lane = (int)lane_id();
+    uint64_t* rec = node_rec<WW, true>(P, w);
+    uint64_t unv[WW], acc[WW], any = 0;
+#pragma unroll
+    for (int j = 0; j < WW; ++j) {
+        unv[j] = act[j] & ~rec[j];
+        any |= unv[j];
+        acc[j] = 0;
+    }
+    if (any == 0) return false;  // the same record in every lane
+    const int32_t h0 = G.irp[w], h1 = G.irp[w + 1];
+    for (int64_t eb = h0; eb < h1; eb += 64 * kPullAhead) {
+        int32_t u[kPullAhead];
+#pragma unroll
+        for (int q = 0; q < kPullAhead; ++q) {
+            const int64_t e = eb + q * 64 + lane;
+            u[q] = e < h1 ? G.icol[e] : -1;
+        }
+        uint64_t part[WW];
+#pragma unroll
+        for (int j = 0; j < WW; ++j) part[j] = 0;
+#pragma unroll
+        for (int q = 0; q < kPullAhead; ++q) {
+            const uint64_t* cur = node_cur<WW, true>(P, max(u[q], 0));
+            scanned += u[q] >= 0;
+#pragma unroll
+            for (int j = 0; j < WW; ++j) part[j] |= u[q] >= 0 ? cur[j] : 0ull;
+        }
+        bool full = true;
+#pragma unroll
+        for (int j = 0; j < WW; ++j) {
+            acc[j] |= wave_or(part[j] & unv[j]);
+            full = full && (acc[j] == unv[j]);
+        }
+        if (full) break;
+    }
+    uint64_t got = 0;
+#pragma unroll
+    for (int j = 0; j < WW; ++j) got |= acc[j];
+    if (got == 0) return false;
+    const uint32_t deg = G.deg[w];
+    // lane b counts for source j * 64 + b
+#pragma unroll
+    for (int j = 0; j < WW; ++j) {
+        if (lane == 0) rec[WW + j] = acc[j];
+        if ((acc[j] >> lane) & 1ull) {
+            atomicAdd(&cg[j * 64 + lane], 1u);
+            atomicAdd(&ct[j * 64 + lane], (unsigned long long)deg);
+        }
+    }
+    return lane == 0;
+}
+
+template <int WW>
+struct PullLds {
+    PullWaveLds<WW> w[kLvBlk / 64];
+    int32_t stage[kLvBlk / 64][kStage];
+    uint32_t sh[kLvBlk / 64 + 1];
+    unsigned long long scanned;
+    CountLds c;
+};
+
 template <int WW>
 __device__ void plain_pull_body(const DevGraph& G, const SlotPtrs& P, SrcState* S, Ctl* C, const TopKDev& T,
-                                QStats* st, int W, uint32_t* cg, unsigned long long* ct, CutLds& CL,
-                                uint32_t& s_last, uint64_t* s_act, uint32_t* bsh) {
-    using Lo = Layout<WW>;
+                                QStats* st, int W, PullLds<WW>& X) {
     const int tid = threadIdx.x;
-    const int lane = (int)lane_id();
     uint64_t act[WW];
 #pragma unroll
     for (int j = 0; j < WW; ++j) act[j] = C->active[j];
-    cg[tid] = 0;
-    ct[tid] = 0;
+    if (tid < kBlk) {
+        X.c.cg[tid] = 0;
+        X.c.ct[tid] = 0;
+    }
     __syncthreads();
     unsigned long long scanned = 0;
-    const uint32_t stride = gridDim.x * kBlk;
-    for (uint32_t base = blockIdx.x * kBlk; base < (uint32_t)G.n; base += stride) {
-        const int32_t w = (int32_t)(base + tid);
-        bool app = false;
-        uint64_t pbits[WW], unv[WW], acc[WW];
-        uint32_t pdeg = 0;
-        uint64_t any = 0;
-        int32_t e0 = 0, e1 = 0;
-#pragma unroll
-        for (int j = 0; j < WW; ++j) {
-            pbits[j] = 0;
-            unv[j] = 0;
-            acc[j] = 0;
-        }
-        uint64_t* rec = nullptr;
-        if (w < G.n) {
-            rec = &P.ns[(size_t)w * Lo::SW];
-#pragma unroll
-            for (int j = 0; j < WW; ++j) {
-                unv[j] = act[j] & ~rec[j];
-                any |= unv[j];
-            }
-            if (any) {
-                e0 = G.irp[w];
-                e1 = G.irp[w + 1];
-            }
-        }
-        const bool heavy = any && e1 - e0 > kPullWave;
-        if (any && !heavy) {
-            for (int32_t e = e0; e < e1; ++e) {
-                const uint64_t* ur = &P.ns[(size_t)G.icol[e] * Lo::SW];
-                ++scanned;
-                bool full = true;
-#pragma unroll
-                for (int j = 0; j < WW; ++j) {
-                    acc[j] |= ur[Lo::CUR + j] & unv[j];
-                    full = full && (acc[j] == unv[j]);
-                }
-                if (full) break;
-            }
-        }
-        // the wave's heavy nodes, one at a time, each list read by all lanes
-        unsigned long long hm = __ballot(heavy);
-        while (hm) {
-            const int l = __ffsll((long long)hm) - 1;
-            hm &= hm - 1;
-            const int32_t h0 = __shfl(e0, l), h1 = __shfl(e1, l);
-            uint64_t hu[WW], ha[WW];
-#pragma unroll
-            for (int j = 0; j < WW; ++j) {
-                hu[j] = __shfl(unv[j], l);
-                ha[j] = 0;
-            }
-            for (int32_t eb = h0; eb < h1; eb += 64) {
-                const int32_t e = eb + lane;
-                uint64_t part[WW];
-#pragma unroll
-                for (int j = 0; j < WW; ++j) part[j] = 0;
-                if (e < h1) {
-                    const uint64_t* ur = &P.ns[(size_t)G.icol[e] * Lo::SW];
-#pragma unroll
-                    for (int j = 0; j < WW; ++j) part[j] = ur[Lo::CUR + j] & hu[j];
-                }
-                if (lane == 0) scanned += (unsigned long long)min(64, h1 - eb);
-                bool full = true;
-#pragma unroll
-                for (int j = 0; j < WW; ++j) {
-                    ha[j] |= wave_or(part[j]);
-                    full = full && (ha[j] == hu[j]);
-                }
-                if (full) break;
-            }
-            if (lane == l) {
-#pragma unroll
-                for (int j = 0; j < WW; ++j) acc[j] = ha[j];
-            }
-        }
-        if (any) {
-            uint64_t got = 0;
-#pragma unroll
-            for (int j = 0; j < WW; ++j) got |= acc[j];
-            if (got) {
-                pdeg = (uint32_t)(rec[Lo::META] >> 32);
-#pragma unroll
-                for (int j = 0; j < WW; ++j) {
-                    rec[Lo::NXT + j] = acc[j];
-                    pbits[j] = acc[j];
-                }
-                app = true;
-            }
-        }
-        wave_count_nodes<WW>(pbits, pdeg, cg, ct);
-        block_append<kBlk, 1>(&app, &w, P.qb, &C->nlen, bsh);
+    PullWaveLds<WW>& Lw = X.w[tid >> 6];
+    WaveStage stg{X.stage[tid >> 6], 0};
+    const uint32_t nheavy = *G.nheavy, waves = gridDim.x * (kLvBlk / 64);
+    for (uint32_t h = (uint32_t)(tid >> 6) * gridDim.x + blockIdx.x; h < nheavy; h += waves) {
+        const int32_t w = G.heavy[h];
+        stg.push(pull_heavy<WW>(G, P, act, w, X.c.cg, X.c.ct, scanned), w, P.qb, &C->nlen);
     }
-    if (scanned) atomicAdd(&st->node_arcs, scanned);
+    // waves take 64 nodes at a time, neighbouring waves neighbouring nodes
+    const int64_t stride = (int64_t)gridDim.x * kLvBlk;
+    for (int64_t base = (int64_t)blockIdx.x * kLvBlk + (tid & ~63); base < G.n; base += stride)
+        pull_nodes<WW>(G, P, act, base + (tid & 63), Lw, X.c.cg, X.c.ct, &stg, &C->nlen, scanned);
+    if (tid == 0) X.scanned = 0;
+    block_flush<kLvBlk>(stg, P.qb, &C->nlen, X.sh);
+    for (int o = 32; o > 0; o >>= 1) scanned += __shfl_xor(scanned, o);
+    if ((tid & 63) == 0 && scanned) atomicAdd(&X.scanned, scanned);
     __syncthreads();
-    plain_level_epilogue<WW>(C, S, T, st, W, cg, ct, CL, s_act, &s_last);
+    if (tid == 0 && X.scanned) atomicAdd(&st->node_arcs, X.scanned);
+    plain_level_epilogue<WW>(C, S, T, st, W, X.c.cg, X.c.ct, X.c.CL, X.c.act, &X.c.last);
 }
 
 template <int WW>
-__global__ __launch_bounds__(kBlk) void k_plain_pull(DevGraph G, SlotPtrs P, SrcState* S, Ctl* C, TopKDev T,
-                                                    QStats* st, int W, int gated) {
+__global__ __launch_bounds__(kLvBlk) void k_plain_pull(DevGraph G, LvSlots L, TopKDev T, QStats* st, int W,
+                                                      int gated) {
+    __shared__ PullLds<WW> X;
+    const size_t i = L.id[blockIdx.y];
+    Ctl* C = L.C + i;
     if (gated && (C->live == 0 || C->pull == 0)) return;
-    __shared__ uint32_t cg[kBlk];
-    __shared__ unsigned long long ct[kBlk];
-    __shared__ CutLds CL;
-    __shared__ uint32_t s_last;
-    __shared__ uint64_t s_act[4];
-    __shared__ uint32_t bsh[kBlk / 64 + 1];
-    plain_pull_body<WW>(G, P, S, C, T, st, W, cg, ct, CL, s_last, s_act, bsh);
+    plain_pull_body<WW>(G, slot_ptrs<WW>(L, i), L.S + i * kBlk, C, T, st, W, X);
 }
 
+// Zero the cur words of the frontier expanded (a push step has done so itself).
 template <int WW>
-__global__ __launch_bounds__(kBlk) void k_plain_clearcur(SlotPtrs P, Ctl* C, int gated) {
+__global__ __launch_bounds__(kBlk) void k_plain_clearcur(LvSlots L, int gated) {
+    const size_t i = L.id[blockIdx.y];
+    const Ctl* C = L.C + i;
     if (gated && C->ran == 0) return;
-    clear_cur<WW>(P, P.qa, C->flen, blockIdx.x * kBlk, gridDim.x * kBlk);
+    clear_cur<WW, true>(slot_ptrs<WW>(L, i), slot_ptrs<WW>(L, i).qa, C->flen, blockIdx.x * kBlk, gridDim.x * kBlk);
 }
 
 // Materialise the level (or only reset nxt when nothing is live); the last
 // workgroup closes the level: frontier length, next direction.  The chunk
 // counter is idle between levels and counts finished workgroups here; the
 // done_blocks word counts the new frontier entries.
+struct BuildLds {
+    int32_t stage[kLvBlk / 64][2][kStage];
+    uint32_t last, sh[kLvBlk / 64 + 1];
+    unsigned long long arcs;
+};
+
 template <int WW>
-__device__ void plain_build_body(const DevGraph& G, const SlotPtrs& P, Ctl* C, const LevelParams& lp,
-                                 uint32_t& s_last, unsigned long long& s_arcs, uint32_t* bsh) {
+__device__ void plain_build_body(const DevGraph& G, const SlotPtrs& P, Ctl* C, const LevelParams& lp, BuildLds& X) {
     const int tid = threadIdx.x;
     uint64_t act[WW];
 #pragma unroll
     for (int j = 0; j < WW; ++j) act[j] = C->active[j];
     const bool any_live = C->live != 0;
     const uint32_t nlen = C->nlen;
-    if (tid == 0) s_arcs = 0;
+    if (tid == 0) X.arcs = 0;
     __syncthreads();
-    build_level<WW, true>(P, P.qb, nlen, blockIdx.x * kBlk, gridDim.x * kBlk, act, any_live, P.qa, &C->done_blocks,
-                          &C->clen, &s_arcs, nullptr, bsh);
-    __syncthreads();
-    if (tid == 0 && s_arcs) atomicAdd(&C->acc_arcs, s_arcs);
+    WaveStage sf{X.stage[tid >> 6][0], 0}, sc{X.stage[tid >> 6][1], 0};
+    build_level<WW, true, true>(P, P.qb, nlen, blockIdx.x * kLvBlk, gridDim.x * kLvBlk, act, any_live, P.qa,
+                                &C->done_blocks, &C->clen, &X.arcs, nullptr, G.deg, &sf, &sc);
+    block_flush<kLvBlk>(sf, P.qa, &C->done_blocks, X.sh);
+    block_flush<kLvBlk>(sc, P.clr, &C->clen, X.sh);
+    if (tid == 0 && X.arcs) atomicAdd(&C->acc_arcs, X.arcs);
     __threadfence();
     __syncthreads();
-    if (tid == 0) s_last = (atomicAdd(&C->chunk, 1u) == gridDim.x - 1) ? 1u : 0u;
+    if (tid == 0) X.last = (atomicAdd(&C->chunk, 1u) == gridDim.x - 1) ? 1u : 0u;
     __syncthreads();
-    if (!s_last || tid != 0) return;
+    if (!X.last || tid != 0) return;
     __threadfence();
     const uint32_t flen =
         any_live ? __hip_atomic_load(&C->done_blocks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
     const unsigned long long fa = __hip_atomic_load(&C->acc_arcs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    uint32_t pull = C->pull;
-    if (lp.can_pull) {
-        if (!pull && lp.pull_alpha > 0.f && (double)fa > (double)G.m / lp.pull_alpha) pull = 1;
-        else if (pull && (double)flen < (double)G.n / lp.pull_beta) pull = 0;
-    }
-    C->pull = pull;
+    C->pull = next_pull(C->pull, fa, flen, G, lp);
     C->flen = flen;
     C->nlen = 0;
     C->front_arcs = fa;
@@ -1301,34 +1504,195 @@ __device__ void plain_build_body(const DevGraph& G, const SlotPtrs& P, Ctl* C, c
 }
 
 template <int WW>
-__global__ __launch_bounds__(kBlk) void k_plain_build(DevGraph G, SlotPtrs P, Ctl* C, LevelParams lp, int gated) {
+__global__ __launch_bounds__(kLvBlk) void k_plain_build(DevGraph G, LvSlots L, LevelParams lp, int gated) {
+    __shared__ BuildLds X;
+    const size_t i = L.id[blockIdx.y];
+    Ctl* C = L.C + i;
     if (gated && C->ran == 0) return;
-    __shared__ uint32_t s_last;
-    __shared__ unsigned long long s_arcs;
-    __shared__ uint32_t bsh[kBlk / 64 + 1];
-    plain_build_body<WW>(G, P, C, lp, s_last, s_arcs, bsh);
+    plain_build_body<WW>(G, slot_ptrs<WW>(L, i), C, lp, X);
 }
 
 // End of a batch: reset seen and cur of every node the batch reached (nxt
 // is already zero; cur is non-zero only for sources of a batch that ended
 // at level 0).
 template <int WW>
-__device__ void plain_clear_body(const SlotPtrs& P, Ctl* C) {
-    using Lo = Layout<WW>;
-    const uint32_t nc = C->clen;
-    for (uint32_t i = blockIdx.x * kBlk + threadIdx.x; i < nc; i += gridDim.x * kBlk) {
-        uint64_t* rec = &P.ns[(size_t)P.clr[i] * Lo::SW];
+__device__ void plain_clear_body(const SlotPtrs& P, uint32_t nc, uint32_t first, uint32_t stride) {
+    for (uint32_t i = first + threadIdx.x; i < nc; i += stride) {
+        const int32_t w = P.clr[i];
+        uint64_t *rec = node_rec<WW, true>(P, w), *cur = node_cur<WW, true>(P, w);
 #pragma unroll
         for (int j = 0; j < WW; ++j) {
             rec[j] = 0;
-            rec[Lo::CUR + j] = 0;
+            cur[j] = 0;
         }
     }
 }
 
 template <int WW>
-__global__ __launch_bounds__(kBlk) void k_plain_clear(SlotPtrs P, Ctl* C) {
-    plain_clear_body<WW>(P, C);
+__global__ __launch_bounds__(kBlk) void k_plain_clear(LvSlots L) {
+    const size_t i = L.id[blockIdx.y];
+    plain_clear_body<WW>(slot_ptrs<WW>(L, i), L.C[i].clen, blockIdx.x * kBlk, gridDim.x * kBlk);
+}
+
+// Shared memory of the record-based persistent kernels (one slot per
+// workgroup, every level of a batch inside the workgroup) and of the narrow
+// level kernel.
+template <int WW, int B>
+struct RecLds {
+    LdsExpand<WW, B> LE;
+    SrcState S[kBlk];
+    uint32_t cg[kBlk];
+    unsigned long long ct[kBlk];
+    CutLds CL;
+    uint32_t flen, nlen, clen;
+    uint64_t act[4];
+    unsigned long long arcs, narcs, ent;  // narcs, ent: arcs and frontier entries expanded
+};
+
+// Levels that one workgroup runs: up to `narrow` frontier arcs (push), or, on
+// a graph of at most that many nodes and arcs, any level.  A push level of
+// kNarrowArcs arcs takes one workgroup about 40 us, as long as the wide
+// kernels' launches and the round trip to the host; below that it wins (a
+// level of 600 arcs: 12 against 45 us).
+constexpr unsigned long long kNarrowArcs = 8192;
+constexpr uint32_t kNarrowPull = 32768;   // nodes + arcs of a graph whose pull steps stay here too
+constexpr uint32_t kNarrowClear = 65536;  // reset-list entries cleared here
+
+// One workgroup per slot: carries its batch on from where the wide kernels
+// left it, and takes further batches (claimed from *next_batch, nb in all),
+// until a level is wide, the reset list is long, or no batch is left.
+template <int WW>
+__global__ __launch_bounds__(kBatchBlk) void k_plain_run(DevGraph G, const int32_t* order, int32_t count, uint32_t nb,
+                                                        int W, LvSlots L, uint32_t* next_batch, TopKDev T, QStats* st,
+                                                        LevelParams lp, unsigned long long narrow, LvReport* report) {
+    constexpr int B = kBatchBlk;
+    __shared__ RecLds<WW, B> R;
+    __shared__ PullWaveLds<WW> X[B / 64];
+    __shared__ uint32_t s_b;
+    const int tid = threadIdx.x;
+    const size_t slot = L.id[blockIdx.x];
+    Ctl* C = L.C + slot;
+    SrcState* Sg = L.S + slot * kBlk;
+    const SlotPtrs P = slot_ptrs<WW>(L, slot);
+    const bool narrow_pull = narrow != 0 && (unsigned long long)G.n + (unsigned long long)G.m <= kNarrowPull;
+    uint32_t state = C->state, d = C->d, flen = C->flen, clen = C->clen, live = C->live, pull = C->pull,
+             stamp = C->stamp;
+    unsigned long long fa = C->front_arcs;
+    bool in_batch = state == LV_PUSH || state == LV_PULL;
+    if (in_batch && tid < W) R.S[tid] = Sg[tid];
+    if (tid < 4) R.act[tid] = C->active[tid];
+    if (tid == 0) {
+        R.narcs = 0;
+        R.ent = 0;
+    }
+    unsigned long long levels = 0, pulls = 0, disc = 0, batches = 0, scanned = 0;
+    __syncthreads();
+    for (;;) {
+        if (!in_batch) {
+            if (tid == 0) s_b = atomicAdd(next_batch, 1u);
+            __syncthreads();
+            const uint32_t b = uni32(s_b);
+            __syncthreads();
+            if (b >= nb) {
+                state = LV_DONE;
+                break;
+            }
+            ++batches;
+            init_batch<WW, true>(G, order, count, b, W, P, R.S, &R.flen, &R.arcs);
+            live = uni32(cut_step<WW>(T, R.S, W, 0, false, nullptr, nullptr, false, true, st, R.act, R.CL));
+            flen = clen = uni32(R.flen);
+            fa = uni64(R.arcs);
+            d = 0;
+            pull = 0;
+            ++stamp;
+            in_batch = true;
+        }
+        if (!live) {
+            if (clen > kNarrowClear) {
+                state = LV_CLEAR;
+                break;
+            }
+            plain_clear_body<WW>(P, clen, 0, B);
+            __syncthreads();
+            in_batch = false;
+            continue;
+        }
+        if (pull ? !narrow_pull : fa > narrow) {
+            state = pull ? LV_PULL : LV_PUSH;
+            break;
+        }
+        if (tid < kBlk) {
+            R.cg[tid] = 0;
+            R.ct[tid] = 0;
+        }
+        if (tid == 0) {
+            R.nlen = 0;
+            R.clen = clen;
+            R.arcs = 0;
+            R.flen = 0;
+        }
+        __syncthreads();
+        if (pull) {
+            uint64_t act[WW];
+#pragma unroll
+            for (int j = 0; j < WW; ++j) act[j] = uni64(R.act[j]);
+            const uint32_t nheavy = *G.nheavy;
+            for (uint32_t h = (uint32_t)tid >> 6; h < nheavy; h += B / 64) {
+                const int32_t w = G.heavy[h];
+                append_if(pull_heavy<WW>(G, P, act, w, R.cg, R.ct, scanned), w, P.qb, &R.nlen);
+            }
+            for (int64_t base = tid & ~63; base < G.n; base += B)
+                pull_nodes<WW>(G, P, act, base + (tid & 63), X[tid >> 6], R.cg, R.ct, nullptr, &R.nlen, scanned);
+            __threadfence();  // nxt and the list are read by other waves next
+            __syncthreads();
+            clear_cur<WW, true>(P, P.qa, flen, 0, B);
+            ++pulls;
+        } else {
+            for (uint32_t e0 = 0; e0 < flen; e0 += B)
+                expand_entries<WW, B, 1, true>(G, P, P.qa, e0, min(flen, e0 + B), R.act, P.qb, &R.nlen, stamp, R.LE,
+                                               &R.narcs, &R.ent);
+            __syncthreads();
+            count_level<WW, B, true>(P, P.qb, uni32(R.nlen), R.cg, R.ct, G.deg);
+        }
+        __syncthreads();
+        const uint32_t nlen = uni32(R.nlen);
+        disc += nlen;
+        ++levels;
+        ++d;
+        live = uni32(cut_step<WW>(T, R.S, W, d, true, R.cg, R.ct, false, true, st, R.act, R.CL));
+        build_level<WW, true>(P, P.qb, nlen, 0, B, R.act, live != 0, P.qa, &R.flen, &R.clen, &R.arcs, nullptr, G.deg);
+        __syncthreads();
+        flen = live ? uni32(R.flen) : 0;
+        clen = uni32(R.clen);
+        fa = uni64(R.arcs);
+        pull = next_pull(pull, fa, flen, G, lp);
+        ++stamp;
+        __syncthreads();
+    }
+    __syncthreads();
+    if ((state == LV_PUSH || state == LV_PULL) && tid < W) Sg[tid] = R.S[tid];
+    for (int o = 32; o > 0; o >>= 1) scanned += __shfl_xor(scanned, o);
+    if ((tid & 63) == 0 && scanned) atomicAdd(&st->node_arcs, scanned);
+    if (tid == 0) {
+        C->state = state;
+        C->d = d;
+        C->flen = flen;
+        C->nlen = 0;
+        C->clen = clen;
+        C->live = live;
+        C->pull = pull;
+        C->stamp = stamp;
+        C->front_arcs = fa;
+        C->chunk = 0;
+        for (int j = 0; j < 4; ++j) C->active[j] = j < WW ? R.act[j] : 0;
+        if (levels) atomicAdd(&st->levels, levels);
+        if (pulls) atomicAdd(&st->pull_levels, pulls);
+        if (disc) atomicAdd(&st->discovered, disc);
+        if (batches) atomicAdd(&st->batches, batches);
+        if (R.narcs) atomicAdd(&st->node_arcs, R.narcs);
+        if (R.ent) atomicAdd(&st->frontier_entries, R.ent);
+        report[blockIdx.x] = LvReport{state, flen, clen, d, fa, 0};
+    }
 }
 
 // Every level of `nb` consecutive batches in one cooperative launch: the
@@ -1347,18 +1711,26 @@ __device__ inline void grid_barrier(cooperative_groups::grid_group& g) {
 }
 
 template <int WW>
-__global__ __launch_bounds__(kBlk) void k_plain_coop(DevGraph G, const int32_t* order, int32_t count, uint32_t b0,
-                                                    uint32_t nb, int W, SlotPtrs P, SrcState* S, Ctl* C, TopKDev T,
-                                                    QStats* st, LevelParams lp) {
+union CoopLds {
+    PushLds<WW> push;
+    CountLds count;
+    PullLds<WW> pull;
+    BuildLds build;
+};
+
+template <int WW>
+__global__ __launch_bounds__(kLvBlk) void k_plain_coop(DevGraph G, const int32_t* order, int32_t count, uint32_t b0,
+                                                      uint32_t nb, int W, LvSlots L, TopKDev T, QStats* st,
+                                                      LevelParams lp) {
     cooperative_groups::grid_group grid = cooperative_groups::this_grid();
-    __shared__ LdsExpand<WW> L;
-    __shared__ uint32_t cg[kBlk];
-    __shared__ unsigned long long ct[kBlk];
+    __shared__ CoopLds<WW> X;
     __shared__ CutLds CL;
-    __shared__ uint32_t s_last, s_flen;
-    __shared__ unsigned long long s_arcs, s_ent;
+    __shared__ uint32_t s_flen;
+    __shared__ unsigned long long s_arcs;
     __shared__ uint64_t s_act[4];
-    __shared__ uint32_t bsh[kBlk / 64 + 1];
+    const SlotPtrs P = slot_ptrs<WW>(L, 0);
+    SrcState* S = L.S;
+    Ctl* C = L.C;
     const uint32_t n = (uint32_t)G.n;
     for (uint32_t b = b0; b < b0 + nb; ++b) {
         if (blockIdx.x == 0) plain_init_body<WW>(G, order, count, b, W, P, S, C, T, st, CL, s_flen, s_arcs, s_act);
@@ -1372,51 +1744,37 @@ __global__ __launch_bounds__(kBlk) void k_plain_coop(DevGraph G, const int32_t* 
             }
             if (!live) break;
             if (pull) {
-                plain_pull_body<WW>(G, P, S, C, T, st, W, cg, ct, CL, s_last, s_act, bsh);
+                plain_pull_body<WW>(G, P, S, C, T, st, W, X.pull);
                 grid_barrier(grid);
             } else {
-                plain_expand_body<WW>(G, P, C, st, L, s_act, s_arcs, s_ent, bsh);
+                plain_expand_body<WW>(G, P, C, st, X.push);
                 grid_barrier(grid);
                 if (ldu32(&C->nlen) > n) {
                     bad = true;
                     break;
                 }
-                plain_count_body<WW>(P, S, C, T, st, W, cg, ct, CL, s_last, s_act);
+                plain_count_body<WW>(G, P, S, C, T, st, W, X.count);
                 grid_barrier(grid);
             }
             if (ldu32(&C->nlen) > n) {
                 bad = true;
                 break;
             }
-            clear_cur<WW>(P, P.qa, ldu32(&C->flen), blockIdx.x * kBlk, gridDim.x * kBlk);
+            clear_cur<WW, true>(P, P.qa, ldu32(&C->flen), blockIdx.x * kLvBlk, gridDim.x * kLvBlk);
             grid_barrier(grid);
-            plain_build_body<WW>(G, P, C, lp, s_last, s_arcs, bsh);
+            plain_build_body<WW>(G, P, C, lp, X.build);
             grid_barrier(grid);
         }
         if (bad) {
             if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(&C->err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return;  // every workgroup read the same lengths, so all of them end here
         }
-        plain_clear_body<WW>(P, C);
+        plain_clear_body<WW>(P, C->clen, blockIdx.x * kLvBlk, gridDim.x * kLvBlk);
         grid_barrier(grid);
     }
 }
 
 // ------------------------------------------------------ batched kernel
-
-// Shared memory of the record-based persistent kernels (one slot per
-// workgroup, every level of a batch inside the workgroup).
-template <int WW, int B>
-struct RecLds {
-    LdsExpand<WW, B> LE;
-    SrcState S[kBlk];
-    uint32_t cg[kBlk];
-    unsigned long long ct[kBlk];
-    CutLds CL;
-    uint32_t flen, nlen, clen;
-    uint64_t act[4];
-    unsigned long long arcs, narcs, ent;  // narcs, ent: arcs and frontier entries expanded
-};
 
 // Per-workgroup counters of a record-based persistent kernel.
 struct RecCounters {
@@ -1507,7 +1865,7 @@ __global__ __launch_bounds__(B) void k_batched(DevGraph G, const int32_t* order,
     __shared__ uint32_t s_b, s_next, s_end;
     const int tid = threadIdx.x;
     const size_t slot = blockIdx.x;
-    SlotPtrs P;
+    SlotPtrs P{};
     P.ns = base.ns + slot * (size_t)G.n * Lo::SW;
     P.qa = base.qa + slot * (size_t)G.n;
     P.qb = base.qb + slot * (size_t)G.n;
@@ -1707,7 +2065,7 @@ __global__ __launch_bounds__(B) void k_jobs(JobLaunch L, SlotPtrs base, uint32_t
     __shared__ int32_t s_slot;
     const int tid = threadIdx.x;
     const size_t slot = blockIdx.x;
-    SlotPtrs P;
+    SlotPtrs P{};
     P.ns = base.ns + slot * (size_t)L.ncap * Lo::SW;
     P.qa = base.qa + slot * (size_t)L.ncap;
     P.qb = base.qb + slot * (size_t)L.ncap;
@@ -2232,7 +2590,7 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
     __shared__ unsigned long long s_arcs, s_narcs, s_ent, s_ent_lv;
     const int tid = threadIdx.x;
     const size_t slot = blockIdx.x;
-    SlotPtrs P;
+    SlotPtrs P{};
     P.ns = base.ns + slot * (size_t)G.n * Lo::SW;
     P.qa = base.qa + slot * (size_t)G.n;
     P.qb = base.qb + slot * (size_t)G.n;
@@ -2751,22 +3109,43 @@ struct EventPair {
     }
 };
 
-// Level-synchronous slot of the workspace (sized for WW words per node).
+// Bytes per node of a level-synchronous slot: seen and nxt, cur, stamp, lists.
 template <int WW>
-bc_status ensure_plain(Workspace& W_, const DevGraph& G, hipStream_t s) {
-    if (W_.plain_ready && W_.ww == WW) return BC_OK;
-    const size_t N = (size_t)G.n, words = N * Layout<WW>::SW;
-    BC_TRY(W_.seen.alloc_on(sizeof(uint64_t) * words, s));
-    BC_TRY(W_.qa.alloc_on(sizeof(int32_t) * N, s));
-    BC_TRY(W_.qb.alloc_on(sizeof(int32_t) * N, s));
-    BC_TRY(W_.clr.alloc_on(sizeof(int32_t) * N, s));
-    BC_TRY(W_.srcs.alloc_on(sizeof(SrcState) * kBlk, s));
-    BC_TRY(W_.ctl.alloc_on(sizeof(Ctl), s));
-    if (!W_.hctl) BC_HIP(hipHostMalloc((void**)&W_.hctl, 64, hipHostMallocDefault));
-    BC_HIP(hipMemsetAsync(W_.seen.p, 0, sizeof(uint64_t) * words, s));
-    BC_HIP(hipMemsetAsync(W_.ctl.p, 0, sizeof(Ctl), s));
-    if (N > 0) k_slot_init<WW><<<clamp_grid((int64_t)N, 4096), kBlk, 0, s>>>(G.deg, G.n, W_.seen.as<uint64_t>(), 1);
-    W_.plain_ready = true;
+constexpr size_t lv_node_bytes() {
+    return 24 * WW + (WW > 1 ? 4 : 0) + 12;
+}
+
+// `want` level-synchronous slots of WW words per node in the workspace, all
+// zero at rest (every batch resets the nodes it reached).
+template <int WW>
+bc_status ensure_lv(Workspace& Wk, const DevGraph& G, int want, hipStream_t s, LvSlots* out) {
+    Workspace::Lv& V = Wk.lv[WW == 1 ? 0 : (WW == 2 ? 1 : 2)];
+    const size_t N = (size_t)G.n, K = (size_t)std::max(want, V.slots);
+    if (V.slots < want) {
+        V.mem.release();
+        V.slots = 0;
+        Carve c;
+        c.add(V.ctl, sizeof(Ctl) * K);
+        c.add(V.next, sizeof(uint32_t));
+        c.add(V.ns, sizeof(uint64_t) * 2 * WW * N * K);
+        c.add(V.cur, sizeof(uint64_t) * WW * N * K);
+        c.add(V.stamp, WW > 1 ? sizeof(uint32_t) * N * K : 0);
+        const size_t zeroed = c.total;
+        c.add(V.srcs, sizeof(SrcState) * kBlk * K);
+        c.add(V.qa, sizeof(int32_t) * N * K);
+        c.add(V.qb, sizeof(int32_t) * N * K);
+        c.add(V.clr, sizeof(int32_t) * N * K);
+        BC_TRY(c.place_on(V.mem, s));
+        BC_HIP(hipMemsetAsync(V.mem.p, 0, zeroed, s));
+        V.slots = want;
+    }
+    if (!Wk.hctl) BC_HIP(hipHostMalloc((void**)&Wk.hctl, sizeof(LvReport) * kMaxSlots, hipHostMallocMapped));
+    std::memset(out, 0, sizeof(*out));
+    out->base = SlotPtrs{V.ns.as<uint64_t>(), V.qa.as<int32_t>(), V.qb.as<int32_t>(), V.clr.as<int32_t>(),
+                         V.cur.as<uint64_t>(), WW > 1 ? V.stamp.as<uint32_t>() : nullptr};
+    out->n = N;
+    out->C = V.ctl.as<Ctl>();
+    out->S = V.srcs.as<SrcState>();
     return BC_OK;
 }
 
@@ -2796,9 +3175,6 @@ bc_status ensure_batched(Workspace& W_, const DevGraph& G, int want, hipStream_t
     return BC_OK;
 }
 
-// Level-synchronous batches over order[0, count), batches [0, nb), on the
-// plain slot of Wk (sized for WW words per node), adding their kernel time
-// to *ms.
 // Workgroups of a cooperative level launch: as many as the device holds at
 // once, up to kCoopPerCu per compute unit (more make each grid barrier
 // slower than they make a level faster); 0 when the device cannot launch
@@ -2810,7 +3186,7 @@ int coop_grid() {
     int dev = 0, coop = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(k_plain_coop<WW>), kBlk,
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(k_plain_coop<WW>), kLvBlk,
                                                      0) != hipSuccess) {
         (void)hipGetLastError();
         return 0;
@@ -2846,56 +3222,158 @@ bc_status check_level_lists(const SlotPtrs& P, uint32_t flen, uint32_t clen, int
     return BC_OK;
 }
 
-// Workgroups per compute unit of the host loop's grid-stride level kernels
-// other than push and pull (count, build and the clears).  Their lists are
-// often short, and every workgroup of a launch takes a device-wide counter
-// (the last one runs the level's cut step or publishes the list), so fewer
-// workgroups finish a level sooner: 1 per compute unit measured faster than
-// 2, 4 or 8 (BA n = 1M seed batches, R-MAT deferred re-runs).
+// Workgroups (of 1024 threads) per compute unit of the level kernels over all
+// slots of a launch: their lists are often short, and every workgroup ends in
+// device-wide counters (the last one runs the level's cut step or publishes
+// the list), so fewer workgroups finish a level sooner.
 constexpr int kLevelGrid = 1;
+constexpr int kPullGrid = 1;
 
+// Start of a phase: no batch claimed, every slot idle.
+__global__ void k_lv_start(Ctl* C, int slots, uint32_t* next) {
+    if ((int)threadIdx.x < slots) C[threadIdx.x].state = LV_IDLE;
+    if (threadIdx.x == 0) *next = 0;
+}
+
+// The host loop: the narrow kernel runs every slot as far as one workgroup
+// should take it and reports what each waits for; then one wide step of all
+// waiting slots, and so on until no batch is left.  report: where the kernel
+// writes (device address) and where the host reads; a report that is not in
+// mapped host memory is copied.
+struct LvHost {
+    LvReport* dev;
+    LvReport* host;
+    bool mapped;
+};
+
+template <int WW>
+bc_status lv_host_loop(const DevGraph& G, const int32_t* ord, int32_t count, uint32_t nb, LvSlots L, int slots,
+                       uint32_t* next, TopKDev T, QStats* d_st, const LevelParams& lp, const LvHost& H, bool check,
+                       hipStream_t s) {
+    const int W = 64 * WW;
+    const int32_t n = G.n;
+    const int cus = device_cus();
+    const unsigned long long narrow = check ? 0 : kNarrowArcs;
+    std::vector<uint8_t> act((size_t)slots), push, pull, clear;
+    for (int i = 0; i < slots; ++i) act[(size_t)i] = (uint8_t)i;
+    k_lv_start<<<1, 64, 0, s>>>(L.C, slots, next);
+    // workgroups of one slot: `work` threads' worth, and all slots together at
+    // most `per_cu` workgroups per compute unit
+    auto grid = [&](int64_t work, int blk, int per_cu, size_t y) {
+        int64_t b = (work + blk - 1) / blk, cap = std::max<int64_t>((int64_t)per_cu * cus / (int64_t)y, 1);
+        return dim3((unsigned)std::min(std::max<int64_t>(b, 1), cap), (unsigned)y);
+    };
+    auto only = [&](const std::vector<uint8_t>& v) {
+        LvSlots x = L;
+        std::memcpy(x.id, v.data(), v.size());
+        return x;
+    };
+    while (!act.empty()) {
+        k_plain_run<WW><<<(unsigned)act.size(), kBatchBlk, 0, s>>>(G, ord, count, nb, W, only(act), next, T, d_st, lp,
+                                                                   narrow, H.dev);
+        BC_HIP(hipGetLastError());
+        if (!H.mapped)
+            BC_HIP(hipMemcpyAsync(H.host, H.dev, sizeof(LvReport) * act.size(), hipMemcpyDeviceToHost, s));
+        BC_HIP(hipStreamSynchronize(s));
+        push.clear();
+        pull.clear();
+        clear.clear();
+        unsigned long long push_arcs = 0, chunks = 0, flen = 0, clen = 0;
+        std::vector<uint8_t> left;
+        for (size_t i = 0; i < act.size(); ++i) {
+            const LvReport& r = H.host[i];
+            // every list holds distinct nodes, so no length can exceed n: a
+            // longer one means the level step wrote out of order, and no
+            // further kernel may index the lists with it
+            if (r.flen > (uint32_t)n || r.clen > (uint32_t)n) {
+                set_error("internal: level %u list lengths %u/%u exceed n = %d", r.d, r.flen, r.clen, n);
+                return BC_EDEVICE;
+            }
+            if (r.state == LV_DONE) continue;
+            left.push_back(act[i]);
+            if (check) {
+                const SlotPtrs P{nullptr, L.base.qa + act[i] * L.n, nullptr, L.base.clr + act[i] * L.n, nullptr, nullptr};
+                BC_TRY(check_level_lists(P, r.flen, r.clen, n, r.d, s));
+            }
+            if (r.state == LV_CLEAR) {
+                clear.push_back(act[i]);
+                clen = std::max<unsigned long long>(clen, r.clen);
+                continue;
+            }
+            flen = std::max<unsigned long long>(flen, r.flen);
+            if (r.state == LV_PULL) {
+                pull.push_back(act[i]);
+            } else {
+                push.push_back(act[i]);
+                push_arcs = std::max(push_arcs, r.front_arcs);
+                const uint32_t per = expand_chunk(r.flen, r.front_arcs);
+                chunks = std::max<unsigned long long>(chunks, ((unsigned long long)r.flen + per - 1) / per);
+            }
+        }
+        act.swap(left);
+        if (!push.empty()) {
+            // one workgroup per claimed chunk; new nodes <= arcs out of the frontier
+            k_plain_expand<WW><<<grid((int64_t)chunks * kLvBlk, kLvBlk, 2, push.size()), kLvBlk, 0, s>>>(G, only(push),
+                                                                                                         d_st, 0);
+            k_plain_count<WW><<<grid((int64_t)std::min<unsigned long long>(push_arcs, (unsigned long long)n), kLvBlk,
+                                     kLevelGrid, push.size()), kLvBlk, 0, s>>>(G, only(push), T, d_st, W, 0);
+        }
+        if (!pull.empty()) {
+            k_plain_pull<WW><<<grid(n, kLvBlk, kPullGrid, pull.size()), kLvBlk, 0, s>>>(G, only(pull), T, d_st, W, 0);
+            k_plain_clearcur<WW><<<grid((int64_t)flen, kBlk, 4 * kLevelGrid, pull.size()), kBlk, 0, s>>>(only(pull), 0);
+        }
+        if (!push.empty() || !pull.empty()) {
+            // reached nodes <= arcs out of the frontier (push) or n (pull)
+            const int64_t bound =
+                pull.empty() ? (int64_t)std::min<unsigned long long>(push_arcs, (unsigned long long)n) : (int64_t)n;
+            push.insert(push.end(), pull.begin(), pull.end());
+            k_plain_build<WW><<<grid(bound, kLvBlk, kLevelGrid, push.size()), kLvBlk, 0, s>>>(G, only(push), lp, 0);
+        }
+        if (!clear.empty())
+            k_plain_clear<WW><<<grid((int64_t)clen, kBlk, 4 * kLevelGrid, clear.size()), kBlk, 0, s>>>(only(clear));
+        BC_HIP(hipGetLastError());
+    }
+    return BC_OK;
+}
+
+// Level-synchronous batches over order[0, count), batches [0, nb), on up to
+// `slots` slots of Wk, adding their kernel time to *ms.  The captured and the
+// cooperative driver use one slot.
 template <int WW>
 bc_status run_plain_batches(const DevGraph& G, const int32_t* ord, int32_t count, uint32_t nb, Workspace& Wk,
                             TopKDev T, QStats* d_st, const LevelParams& lp, hipStream_t s, double* ms,
-                            int graph_levels) {
+                            int graph_levels, int slots = 1) {
+    if (nb == 0) return BC_OK;
     const bool check_lists = check_lists_enabled();
     const int W = 64 * WW;
     const int32_t n = G.n;
     const int cus = device_cus();
-    if (Wk.ww != WW) {
-        Wk.plain_ready = false;
-        Wk.slots = 0;
-        Wk.ww = WW;
-    }
-    BC_TRY(ensure_plain<WW>(Wk, G, s));
-    SlotPtrs P{Wk.seen.as<uint64_t>(), Wk.qa.as<int32_t>(), Wk.qb.as<int32_t>(), Wk.clr.as<int32_t>()};
-    SrcState* S = Wk.srcs.as<SrcState>();
-    Ctl* C = Wk.ctl.as<Ctl>();
-    uint32_t* hctl = Wk.hctl;
-    const int cgrid = graph_levels == -1 && nb > 0 ? coop_grid<WW>() : 0;
-    if (graph_levels == -1 && nb > 0 && cgrid == 0) {
+    slots = graph_levels == 0 ? (int)std::min<uint32_t>((uint32_t)std::max(slots, 1), nb) : 1;
+    LvSlots L;
+    BC_TRY(ensure_lv<WW>(Wk, G, slots, s, &L));
+    Ctl* C = L.C;
+    const int cgrid = graph_levels == -1 ? coop_grid<WW>() : 0;
+    if (graph_levels == -1 && cgrid == 0) {
         set_error("this device cannot run the level loop as one cooperative launch");
         return BC_EINVAL;
     }
+    EventPair ev;
+    BC_TRY(ev.create());
     if (cgrid > 0) {
         // every level of every batch in one cooperative launch
         BC_HIP(hipMemsetAsync(&C->err, 0, sizeof(uint32_t), s));
-        EventPair ev;
-        BC_TRY(ev.create());
         DevGraph a_g = G;
         const int32_t* a_ord = ord;
         int32_t a_count = count;
         uint32_t a_b0 = 0, a_nb = nb;
         int a_w = W;
-        SlotPtrs a_p = P;
-        SrcState* a_s = S;
-        Ctl* a_c = C;
+        LvSlots a_l = L;
         TopKDev a_t = T;
         QStats* a_st = d_st;
         LevelParams a_lp = lp;
-        void* args[] = {&a_g, &a_ord, &a_count, &a_b0, &a_nb, &a_w, &a_p, &a_s, &a_c, &a_t, &a_st, &a_lp};
+        void* args[] = {&a_g, &a_ord, &a_count, &a_b0, &a_nb, &a_w, &a_l, &a_t, &a_st, &a_lp};
         BC_HIP(hipEventRecord(ev.a, s));
-        BC_HIP(hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_plain_coop<WW>), dim3(cgrid), dim3(kBlk),
+        BC_HIP(hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_plain_coop<WW>), dim3(cgrid), dim3(kLvBlk),
                                           args, 0, s));
         BC_HIP(hipEventRecord(ev.b, s));
         uint32_t err = 0;
@@ -2910,66 +3388,56 @@ bc_status run_plain_batches(const DevGraph& G, const int32_t* ord, int32_t count
         *ms += t;
         return BC_OK;
     }
+    if (graph_levels == 0) {
+        void* dp = nullptr;
+        BC_HIP(hipHostGetDevicePointer(&dp, Wk.hctl, 0));
+        const LvHost H{static_cast<LvReport*>(dp), reinterpret_cast<LvReport*>(Wk.hctl), true};
+        BC_HIP(hipEventRecord(ev.a, s));
+        BC_TRY(lv_host_loop<WW>(G, ord, count, nb, L, slots, Wk.lv[WW == 1 ? 0 : (WW == 2 ? 1 : 2)].next.as<uint32_t>(),
+                                T, d_st, lp, H, check_lists, s));
+        BC_HIP(hipEventRecord(ev.b, s));
+        double t = 0;
+        BC_TRY(ev.ms(&t));
+        *ms += t;
+        return BC_OK;
+    }
     // graph_levels > 0: capture that many gated level steps once and replay
     // them, reading the control block once per replay instead of per level
     GraphHolder gh;
-    if (graph_levels > 0 && nb > 0) {
-        if (!Wk.cap) BC_HIP(hipStreamCreateWithFlags(&Wk.cap, hipStreamNonBlocking));  // default priority
-        BC_HIP(hipStreamBeginCapture(Wk.cap, hipStreamCaptureModeThreadLocal));
-        for (int l = 0; l < graph_levels; ++l) {
-            k_plain_expand<WW><<<8 * cus, kBlk, 0, Wk.cap>>>(G, P, C, d_st, 1);
-            k_plain_count<WW><<<4 * cus, kBlk, 0, Wk.cap>>>(P, S, C, T, d_st, W, 1);
-            k_plain_pull<WW><<<clamp_grid(n, 8 * cus), kBlk, 0, Wk.cap>>>(G, P, S, C, T, d_st, W, 1);
-            k_plain_clearcur<WW><<<4 * cus, kBlk, 0, Wk.cap>>>(P, C, 1);
-            k_plain_build<WW><<<4 * cus, kBlk, 0, Wk.cap>>>(G, P, C, lp, 1);
-        }
-        const hipError_t ce = hipStreamEndCapture(Wk.cap, &gh.graph);
-        BC_HIP(ce);
-        BC_HIP(hipGraphInstantiate(&gh.exec, gh.graph, nullptr, nullptr, 0));
+    if (!Wk.cap) BC_HIP(hipStreamCreateWithFlags(&Wk.cap, hipStreamNonBlocking));  // default priority
+    BC_HIP(hipStreamBeginCapture(Wk.cap, hipStreamCaptureModeThreadLocal));
+    for (int l = 0; l < graph_levels; ++l) {
+        k_plain_expand<WW><<<2 * cus, kLvBlk, 0, Wk.cap>>>(G, L, d_st, 1);
+        k_plain_count<WW><<<kLevelGrid * cus, kLvBlk, 0, Wk.cap>>>(G, L, T, d_st, W, 1);
+        k_plain_pull<WW><<<clamp_grid(n, kPullGrid * cus), kLvBlk, 0, Wk.cap>>>(G, L, T, d_st, W, 1);
+        k_plain_clearcur<WW><<<4 * cus, kBlk, 0, Wk.cap>>>(L, 1);
+        k_plain_build<WW><<<kLevelGrid * cus, kLvBlk, 0, Wk.cap>>>(G, L, lp, 1);
     }
-    EventPair ev;
-    BC_TRY(ev.create());
+    const hipError_t ce = hipStreamEndCapture(Wk.cap, &gh.graph);
+    BC_HIP(ce);
+    BC_HIP(hipGraphInstantiate(&gh.exec, gh.graph, nullptr, nullptr, 0));
+    uint32_t* hctl = Wk.hctl;
     BC_HIP(hipEventRecord(ev.a, s));
     for (uint32_t b = 0; b < nb; ++b) {
-        k_plain_init<WW><<<1, kBlk, 0, s>>>(G, ord, count, b, W, P, S, C, T, d_st);
+        k_plain_init<WW><<<1, kBlk, 0, s>>>(G, ord, count, b, W, L, T, d_st);
         for (;;) {
             BC_HIP(hipMemcpyAsync(hctl, C, 64, hipMemcpyDeviceToHost, s));
             BC_HIP(hipStreamSynchronize(s));
-            // control block words: d, flen, nlen, clen, live, pull, chunk, done, stamp, ran, front_arcs
-            const uint32_t flen = hctl[1], live = hctl[4], pull = hctl[5];
-            // every list holds distinct nodes, so no length can exceed n: a
-            // longer one means the level step wrote out of order, and no
-            // further kernel may index the lists with it
+            // control block words: d, flen, nlen, clen, live, ...
+            const uint32_t flen = hctl[1], live = hctl[4];
             if (flen > (uint32_t)n || hctl[2] > (uint32_t)n || hctl[3] > (uint32_t)n) {
                 set_error("internal: level %u list lengths %u/%u/%u exceed n = %d", hctl[0], flen, hctl[2], hctl[3],
                           n);
                 return BC_EDEVICE;
             }
-            unsigned long long fa;
-            std::memcpy(&fa, hctl + 10, sizeof(fa));
-            if (check_lists) BC_TRY(check_level_lists(P, flen, hctl[3], n, hctl[0], s));
+            if (check_lists) {
+                const SlotPtrs P = L.base;
+                BC_TRY(check_level_lists(P, flen, hctl[3], n, hctl[0], s));
+            }
             if (!live) break;
-            if (gh.exec) {
-                BC_HIP(hipGraphLaunch(gh.exec, s));
-                continue;
-            }
-            if (pull) {
-                k_plain_pull<WW><<<clamp_grid(n, 8 * cus), kBlk, 0, s>>>(G, P, S, C, T, d_st, W, 0);
-            } else {
-                // one workgroup per claimed chunk, up to 8 per compute unit
-                const int64_t chunks = ((int64_t)flen + expand_chunk(flen, fa) - 1) / expand_chunk(flen, fa);
-                k_plain_expand<WW><<<clamp_grid(chunks * kBlk, 8 * cus), kBlk, 0, s>>>(G, P, C, d_st, 0);
-                // new nodes <= arcs out of the frontier
-                k_plain_count<WW><<<clamp_grid((int64_t)std::min<unsigned long long>(fa, (unsigned long long)n),
-                                               kLevelGrid * cus), kBlk, 0, s>>>(P, S, C, T, d_st, W, 0);
-            }
-            k_plain_clearcur<WW><<<clamp_grid(flen, kLevelGrid * cus), kBlk, 0, s>>>(P, C, 0);
-            // reached nodes <= arcs out of the frontier (push) or n (pull)
-            const int64_t bound =
-                pull ? (int64_t)n : (int64_t)std::min<unsigned long long>(fa, (unsigned long long)n);
-            k_plain_build<WW><<<clamp_grid(bound, kLevelGrid * cus), kBlk, 0, s>>>(G, P, C, lp, 0);
+            BC_HIP(hipGraphLaunch(gh.exec, s));
         }
-        k_plain_clear<WW><<<clamp_grid(n, kLevelGrid * cus), kBlk, 0, s>>>(P, C);
+        k_plain_clear<WW><<<clamp_grid(n, 4 * cus), kBlk, 0, s>>>(L);
     }
     BC_HIP(hipEventRecord(ev.b, s));
     BC_HIP(hipGetLastError());
@@ -2998,7 +3466,7 @@ SeedPlan seed_plan(const bc_opts& o, int32_t k, int32_t n, int W) {
 
 template <int WW>
 bc_status run_ww(bc_graph* g, int32_t k, const bc_opts& o, const int32_t* d_order, TopKDev T, QStats* d_st,
-                 Workspace& Wk, int W, Timing& tm, hipStream_t s) {
+                 Workspace& Wk, int W, Timing& tm, hipStream_t s, bool private_ws) {
     using Lo = Layout<WW>;
     const DevGraph& G = g->dg;
     const int32_t n = G.n;
@@ -3015,27 +3483,19 @@ bc_status run_ww(bc_graph* g, int32_t k, const bc_opts& o, const int32_t* d_orde
     const int cus = device_cus();
     if (Wk.ww != WW) {
         // a different width: drop buffers sized for the old one
-        Wk.plain_ready = false;
         Wk.slots = 0;
         Wk.ww = WW;
     }
 
-    auto run_plain = [&](const int32_t* ord, int32_t count, uint32_t nb, double* ms) -> bc_status {
-        return run_plain_batches<WW>(G, ord, count, nb, Wk, T, d_st, lp, s, ms, o.graph_levels);
+    auto run_plain = [&](int width, const int32_t* ord, int32_t count, uint32_t nb, double* ms, int lv) -> bc_status {
+        if (width == 64) return run_plain_batches<1>(G, ord, count, nb, Wk, T, d_st, lp, s, ms, o.graph_levels, lv);
+        if (width == 128) return run_plain_batches<2>(G, ord, count, nb, Wk, T, d_st, lp, s, ms, o.graph_levels, lv);
+        return run_plain_batches<4>(G, ord, count, nb, Wk, T, d_st, lp, s, ms, o.graph_levels, lv);
     };
 
-    if (!batched && seed > 0) BC_TRY(run_plain(d_order, n, seed, &tm.seed_ms));
-    if (batched && sp.batches > 0) {
-        if (sp.sw == W) {
-            BC_TRY(run_plain(d_order, n, sp.batches, &tm.seed_ms));
-        } else {
-            // wider seed batches: the first sp.batches * sp.sw sources of the order
-            Workspace wide(s);
-            if (sp.sw == 128) BC_TRY(run_plain_batches<2>(G, d_order, n, sp.batches, wide, T, d_st, lp, s, &tm.seed_ms, o.graph_levels));
-            else BC_TRY(run_plain_batches<4>(G, d_order, n, sp.batches, wide, T, d_st, lp, s, &tm.seed_ms, o.graph_levels));
-            BC_HIP(hipStreamSynchronize(s));
-        }
-    }
+    if (!batched && seed > 0) BC_TRY(run_plain(W, d_order, n, seed, &tm.seed_ms, 1));
+    // seed batches may be wider: the first sp.batches * sp.sw sources of the order
+    if (batched && sp.batches > 0) BC_TRY(run_plain(sp.sw, d_order, n, sp.batches, &tm.seed_ms, 1));
     if (seed > 0) {
         BC_HIP(hipMemcpyAsync(&tm.seed_stats, d_st, sizeof(QStats), hipMemcpyDeviceToHost, s));
         BC_HIP(hipStreamSynchronize(s));
@@ -3055,7 +3515,8 @@ bc_status run_ww(bc_graph* g, int32_t k, const bc_opts& o, const int32_t* d_orde
         BC_TRY(ensure_batched<WW>(Wk, G, slots, s));
         BC_TRY(Wk.nextb.alloc_on(sizeof(uint32_t), s));
         BC_HIP(hipMemcpyAsync(Wk.nextb.p, &seed, sizeof(uint32_t), hipMemcpyHostToDevice, s));
-        SlotPtrs base{Wk.bseen.as<uint64_t>(), Wk.bqa.as<int32_t>(), Wk.bqb.as<int32_t>(), Wk.bclr.as<int32_t>()};
+        SlotPtrs base{Wk.bseen.as<uint64_t>(), Wk.bqa.as<int32_t>(), Wk.bqb.as<int32_t>(), Wk.bclr.as<int32_t>(),
+                      nullptr, nullptr};
         BC_TRY(Wk.defer.alloc_on(sizeof(int32_t) * N + 64, s));
         uint32_t* dcnt = (uint32_t*)(Wk.defer.as<char>() + sizeof(int32_t) * N);
         BC_HIP(hipMemsetAsync(dcnt, 0, sizeof(uint32_t), s));
@@ -3093,15 +3554,28 @@ bc_status run_ww(bc_graph* g, int32_t k, const bc_opts& o, const int32_t* d_orde
             const int dw = o.defer_width > 0 ? o.defer_width : (ndef <= 64 ? 64 : (ndef <= 128 ? 128 : 256));
             const int32_t* dl = Wk.defer.as<int32_t>();
             const uint32_t dnb = (ndef + (uint32_t)dw - 1) / (uint32_t)dw;
-            if (dw == W) {
-                BC_TRY(run_plain(dl, (int32_t)ndef, dnb, &tm.defer_ms));
-            } else {
-                Workspace wide(s);
-                if (dw == 64) BC_TRY(run_plain_batches<1>(G, dl, (int32_t)ndef, dnb, wide, T, d_st, lp, s, &tm.defer_ms, o.graph_levels));
-                else if (dw == 128) BC_TRY(run_plain_batches<2>(G, dl, (int32_t)ndef, dnb, wide, T, d_st, lp, s, &tm.defer_ms, o.graph_levels));
-                else BC_TRY(run_plain_batches<4>(G, dl, (int32_t)ndef, dnb, wide, T, d_st, lp, s, &tm.defer_ms, o.graph_levels));
-                BC_HIP(hipStreamSynchronize(s));
+            // their batches side by side, a level of each per launch, on as
+            // many slots as memory allows: a query whose workspace ends with it
+            // gives up its persistent slots for them
+            const size_t node = dw == 64 ? lv_node_bytes<1>() : (dw == 128 ? lv_node_bytes<2>() : lv_node_bytes<4>());
+            size_t room = 0;
+            if (private_ws) {
+                room = (size_t)Wk.slots * per_slot;
+                Wk.bseen.release();
+                Wk.bqa.release();
+                Wk.bqb.release();
+                Wk.bclr.release();
+                Wk.slots = 0;
+            } else if (hipMemGetInfo(&freeb, &totalb) == hipSuccess) {
+                room = (size_t)(0.45 * (double)freeb);
             }
+            // a power of two (so that graphs of a size ask the pool for the
+            // same bytes), at most kLvBytes: eight batches fill the GPU on a
+            // graph whose slot takes 100 MB, and new memory costs 0.1 ms a MB
+            room = std::min(room, kLvBytes);
+            int lv = 1;
+            while (lv < kMaxSlots && (uint32_t)lv < dnb && 2 * (size_t)lv * node * N <= room) lv *= 2;
+            BC_TRY(run_plain(dw, dl, (int32_t)ndef, dnb, &tm.defer_ms, lv));
         }
     }
     BC_HIP(hipStreamSynchronize(s));
@@ -3206,9 +3680,9 @@ bc_status run_query(bc_graph* g, int32_t k, bc_opts o, int32_t* ids, uint64_t* f
             }
         } rel{g, own == nullptr};
         bc_status rs;
-        if (W == 64) rs = run_ww<1>(g, kk, o, d_order, T, d_st, *wk, W, tm, s);
-        else if (W == 128) rs = run_ww<2>(g, kk, o, d_order, T, d_st, *wk, W, tm, s);
-        else rs = run_ww<4>(g, kk, o, d_order, T, d_st, *wk, W, tm, s);
+        if (W == 64) rs = run_ww<1>(g, kk, o, d_order, T, d_st, *wk, W, tm, s, own != nullptr);
+        else if (W == 128) rs = run_ww<2>(g, kk, o, d_order, T, d_st, *wk, W, tm, s, own != nullptr);
+        else rs = run_ww<4>(g, kk, o, d_order, T, d_st, *wk, W, tm, s, own != nullptr);
         if (rs != BC_OK) {
             // a failed query may leave marks behind: never reuse its workspace
             std::lock_guard<std::mutex> lk(g->ws_mu);
@@ -3379,6 +3853,13 @@ StaticScratch g_static[64];
 
 size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
+struct StaticCtl {
+    Ctl c;
+    uint32_t next, pad_;
+    LvReport report;
+};
+static_assert((sizeof(StaticCtl) + 255) / 256 == (sizeof(Ctl) + 255) / 256, "the control block's share holds it");
+
 // Bytes of scratch a plain-mode query of W = 64 on n nodes with k results
 // needs: control block, list, statistics, sources, threshold records, order,
 // node records and the three node lists.
@@ -3426,30 +3907,35 @@ bc_status run_topk_static(bc_graph* g, int32_t k, int32_t* ids, uint64_t* farnes
         off += al256(b);
         return p;
     };
-    Ctl* C = reinterpret_cast<Ctl*>(take(sizeof(Ctl)));
+    StaticCtl* SC = reinterpret_cast<StaticCtl*>(take(sizeof(StaticCtl)));
     char* hb = take(kStaticHdr + sizeof(Rec) * (size_t)kk);
     QStats* d_st = reinterpret_cast<QStats*>(take(sizeof(QStats)));
     SrcState* S = reinterpret_cast<SrcState*>(take(sizeof(SrcState) * kBlk));
     ThRec* ring = reinterpret_cast<ThRec*>(take(sizeof(ThRec) * ((size_t)n + 1)));
     int32_t* ord = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)n));
-    SlotPtrs P;
-    P.ns = reinterpret_cast<uint64_t*>(take(sizeof(uint64_t) * Layout<1>::SW * (size_t)n));
-    P.qa = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)n));
-    P.qb = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)n));
-    P.clr = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)n));
+    LvSlots L;
+    std::memset(&L, 0, sizeof(L));
+    const size_t rec_words = 3 * (size_t)n;  // seen, nxt and cur
+    uint64_t* words = reinterpret_cast<uint64_t*>(take(sizeof(uint64_t) * Layout<1>::SW * (size_t)n));
+    L.base.ns = words;
+    L.base.cur = words + 2 * (size_t)n;
+    L.base.qa = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)n));
+    L.base.qb = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)n));
+    L.base.clr = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)n));
+    L.n = (size_t)n;
+    L.C = &SC->c;
+    L.S = S;
     // every call starts from zeroed state (the array keeps the last call's
-    // contents): control block, list header and records, statistics, node
-    // records; then the degrees into the records' meta words
+    // contents): control block, list header and records, statistics, node state
     const int cus = device_cus();
     auto zero = [&](void* p, size_t bytes) {
         const size_t words = al256(bytes) / 8;
         k_zero_words<<<clamp_grid((int64_t)words, 4 * cus), kBlk, 0, s>>>(static_cast<unsigned long long*>(p), words);
     };
-    zero(C, sizeof(Ctl));
+    zero(SC, sizeof(StaticCtl));
     zero(hb, kStaticHdr + sizeof(Rec) * (size_t)kk);
     zero(d_st, sizeof(QStats));
-    zero(P.ns, sizeof(uint64_t) * Layout<1>::SW * (size_t)n);
-    k_slot_init<1><<<clamp_grid((int64_t)n, 4096), kBlk, 0, s>>>(G.deg, n, P.ns, 1);
+    zero(words, sizeof(uint64_t) * rec_words);
     // the graph's degree order when it holds one, else node-id order
     bool have_deg = false;
     {
@@ -3471,36 +3957,9 @@ bc_status run_topk_static(bc_graph* g, int32_t k, int32_t* ids, uint64_t* farnes
     T.all_r = nullptr;
     T.footnote = 0;
     LevelParams lp{3.f, 24.f, 1};
-    constexpr int W = 64;
-    const uint32_t nb = (uint32_t)((n + W - 1) / W);
-    uint32_t hctl[16];  // control block words: d, flen, nlen, clen, live, pull, ..., front_arcs at 10
-    for (uint32_t b = 0; b < nb; ++b) {
-        k_plain_init<1><<<1, kBlk, 0, s>>>(G, ord, n, b, W, P, S, C, T, d_st);
-        for (;;) {
-            BC_HIP(hipMemcpyAsync(hctl, C, sizeof(hctl), hipMemcpyDeviceToHost, s));
-            BC_HIP(hipStreamSynchronize(s));
-            const uint32_t flen = hctl[1], live = hctl[4], pull = hctl[5];
-            if (flen > (uint32_t)n || hctl[2] > (uint32_t)n || hctl[3] > (uint32_t)n) {
-                set_error("internal: level %u list lengths %u/%u/%u exceed n = %d", hctl[0], flen, hctl[2], hctl[3], n);
-                return BC_EDEVICE;
-            }
-            unsigned long long fa;
-            std::memcpy(&fa, hctl + 10, sizeof(fa));
-            if (!live) break;
-            if (pull) {
-                k_plain_pull<1><<<clamp_grid(n, 8 * cus), kBlk, 0, s>>>(G, P, S, C, T, d_st, W, 0);
-            } else {
-                const int64_t chunks = ((int64_t)flen + expand_chunk(flen, fa) - 1) / expand_chunk(flen, fa);
-                k_plain_expand<1><<<clamp_grid(chunks * kBlk, 8 * cus), kBlk, 0, s>>>(G, P, C, d_st, 0);
-                k_plain_count<1><<<clamp_grid((int64_t)std::min<unsigned long long>(fa, (unsigned long long)n), 4 * cus),
-                                   kBlk, 0, s>>>(P, S, C, T, d_st, W, 0);
-            }
-            k_plain_clearcur<1><<<clamp_grid(flen, 4 * cus), kBlk, 0, s>>>(P, C, 0);
-            const int64_t bound = pull ? (int64_t)n : (int64_t)std::min<unsigned long long>(fa, (unsigned long long)n);
-            k_plain_build<1><<<clamp_grid(bound, 4 * cus), kBlk, 0, s>>>(G, P, C, lp, 0);
-        }
-        k_plain_clear<1><<<clamp_grid(n, 4 * cus), kBlk, 0, s>>>(P, C);
-    }
+    const uint32_t nb = (uint32_t)((n + 63) / 64);
+    LvReport rep[1];
+    BC_TRY(lv_host_loop<1>(G, ord, n, nb, L, 1, &SC->next, T, d_st, lp, LvHost{&SC->report, rep, false}, false, s));
     BC_HIP(hipGetLastError());
     int32_t cnt = 0;
     BC_HIP(hipMemcpyAsync(&cnt, T.cnt, sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -3618,7 +4077,7 @@ void launch_jobs(bc_multi* p, hipStream_t st) {
     L.claim = p->ctl.as<unsigned long long>();
     L.W = p->W;
     L.ncap = p->ncap;
-    SlotPtrs base{p->ns.as<uint64_t>(), p->qa.as<int32_t>(), p->qb.as<int32_t>(), p->clr.as<int32_t>()};
+    SlotPtrs base{p->ns.as<uint64_t>(), p->qa.as<int32_t>(), p->qb.as<int32_t>(), p->clr.as<int32_t>(), nullptr, nullptr};
     k_jobs<WW, kBatchBlk><<<p->slots, kBatchBlk, 0, st>>>(L, base, p->stamps.as<uint32_t>());
 }
 
@@ -3924,7 +4383,7 @@ void launch_queue(DevQueue* q) {
     L.last_end = reinterpret_cast<unsigned long long*>(q->claim.as<char>() + 16);
     L.W = q->W;
     L.ncap = q->ncap;
-    SlotPtrs base{q->ns.as<uint64_t>(), q->qa.as<int32_t>(), q->qb.as<int32_t>(), q->clr.as<int32_t>()};
+    SlotPtrs base{q->ns.as<uint64_t>(), q->qa.as<int32_t>(), q->qb.as<int32_t>(), q->clr.as<int32_t>(), nullptr, nullptr};
     k_jobs<WW, kBatchBlk><<<q->slots, kBatchBlk, 0, q->stream>>>(L, base, q->stamps.as<uint32_t>());
 }
 
