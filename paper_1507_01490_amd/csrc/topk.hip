@@ -218,50 +218,6 @@ __device__ inline bool key_gt(uint64_t Ax, uint64_t Fx, int32_t ix, uint64_t Ay,
     return ix < iy;
 }
 
-// Insert one completed source into the top-k list (caller serialises).  When
-// the list is full afterwards, publish its k-th record.
-__device__ void topk_insert(const TopKDev& T, uint64_t A, uint64_t F, uint64_t f, int32_t id, uint32_t r) {
-    const int32_t k = T.k;
-    int32_t c = ld32(T.cnt);
-    if (c == k) {
-        Rec* last = &T.list[k - 1];
-        if (!key_gt(A, F, id, ld64(&last->A), ld64(&last->F), (int32_t)(uint32_t)ld64(&last->idr))) return;
-    }
-    int32_t i;
-    if (c < k) {
-        i = c;
-        c += 1;
-        __hip_atomic_store(T.cnt, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-        i = k - 1;
-    }
-    while (i > 0) {
-        Rec* y = &T.list[i - 1];
-        uint64_t yA = ld64(&y->A), yF = ld64(&y->F), yidr = ld64(&y->idr);
-        if (!key_gt(A, F, id, yA, yF, (int32_t)(uint32_t)yidr)) break;
-        Rec* z = &T.list[i];
-        st64(&z->A, yA);
-        st64(&z->F, yF);
-        st64(&z->f, ld64(&y->f));
-        st64(&z->idr, yidr);
-        --i;
-    }
-    Rec* z = &T.list[i];
-    st64(&z->A, A);
-    st64(&z->F, F);
-    st64(&z->f, f);
-    st64(&z->idr, ((uint64_t)r << 32) | (uint32_t)id);
-    if (c == k) {
-        uint32_t s = __hip_atomic_load(T.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        Rec* kth = &T.list[k - 1];
-        ThRec* o = &T.ring[s];
-        st64(&o->A, ld64(&kth->A));
-        st64(&o->F, ld64(&kth->F));
-        st64((uint64_t*)&o->id, (uint64_t)(int64_t)(int32_t)(uint32_t)ld64(&kth->idr));
-        __hip_atomic_store(T.seq, s + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
-
 // The record at seq-1 was written before seq was published with a release
 // store at agent scope; the acquire load of seq here pairs with it, so the
 // record's three words are visible once seq is (the ring itself is never
@@ -736,26 +692,134 @@ __device__ void build_level(const SlotPtrs& P, const int32_t* N, uint32_t len, u
 // reached (gamma == 0 completes a source).  Then insert completions into the
 // top-k, read the threshold, and cut (or defer).  Writes the active masks
 // and returns the live count (to every thread).
+template <int N>  // sources
 struct CutLds {
-    uint32_t flags[kBlk];
     ThRec th;
     uint32_t have_th, live;
+    // completions that may enter the list, in no order (cA, cF, cid), their
+    // indices by decreasing key (ord), and per rank the list entries above (lb)
+    uint64_t cA[N], cF[N];
+    int32_t cid[N];
+    uint32_t lb[N];
+    uint16_t ord[N];
+    uint32_t nc, nd, nt;
+    int32_t cnt;
+    unsigned long long mv;
+    ThRec kth;
+    uint32_t kset;
 };
+
+// Merge the CL.nc completions into the list, all at once: `mine` threads hold
+// one each (key A, F, id at CL's index `at`, farness f, reach r).  The list
+// entries shift by the number of completions above them, from the tail in
+// chunks of the workgroup, and each completion lands at its rank plus the
+// entries above it.  (Inserted one at a time by one thread, 100 completions
+// into a list of 100 took 2.5 ms of dependent global accesses, and the other
+// workgroups waited on the lock; merged, a few microseconds.)  Whole workgroup.
+template <int N>
+__device__ void topk_merge(const TopKDev& T, CutLds<N>& CL, bool mine, uint32_t at, uint64_t A, uint64_t F, uint64_t f,
+                           int32_t id, uint32_t r, bool locked) {
+    const int tid = threadIdx.x;
+    const int32_t k = T.k;
+    const uint32_t nc = CL.nc;
+    if (tid == 0) {
+        if (locked) lock_acquire(T.lock);
+        CL.cnt = ld32(T.cnt);
+        CL.kset = 0;
+    }
+    uint32_t rank = 0;
+    if (mine) {
+        for (uint32_t j = 0; j < nc; ++j) rank += key_gt(CL.cA[j], CL.cF[j], CL.cid[j], A, F, id) ? 1u : 0u;
+        CL.ord[rank] = (uint16_t)at;
+    }
+    __syncthreads();
+    const int32_t cnt = CL.cnt;
+    if (mine) CL.lb[rank] = (uint32_t)cnt;
+    __syncthreads();
+    // completions above the list entry (a, b, i)
+    auto above = [&](uint64_t a, uint64_t b, int32_t i) {
+        uint32_t lo = 0, hi = nc;
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi) >> 1, c = CL.ord[mid];
+            if (key_gt(CL.cA[c], CL.cF[c], CL.cid[c], a, b, i)) lo = mid + 1; else hi = mid;
+        }
+        return lo;
+    };
+    const int32_t B = (int32_t)blockDim.x;
+    for (int32_t c0 = (cnt - 1) / B * B; c0 >= 0 && cnt > 0; c0 -= B) {
+        const int32_t i = c0 + tid;
+        uint64_t eA = 0, eF = 0, ef = 0, ei = 0;
+        uint32_t g = 0;
+        if (i < cnt) {
+            const Rec* y = &T.list[i];
+            eA = ld64(&y->A);
+            eF = ld64(&y->F);
+            ef = ld64(&y->f);
+            ei = ld64(&y->idr);
+            uint32_t g0 = 0;  // of the entry before
+            if (i > 0) g0 = above(ld64(&y[-1].A), ld64(&y[-1].F), (int32_t)(uint32_t)ld64(&y[-1].idr));
+            g = above(eA, eF, (int32_t)(uint32_t)ei);
+            for (uint32_t q = g0; q < g; ++q) CL.lb[q] = (uint32_t)i;
+        }
+        __syncthreads();
+        const int32_t to = i + (int32_t)g;
+        if (g != 0 && to < k) {
+            Rec* z = &T.list[to];
+            st64(&z->A, eA);
+            st64(&z->F, eF);
+            st64(&z->f, ef);
+            st64(&z->idr, ei);
+            if (to == k - 1) {
+                CL.kth = ThRec{eA, eF, (int64_t)(int32_t)(uint32_t)ei};
+                CL.kset = 1;
+            }
+        }
+        __syncthreads();
+    }
+    if (mine) {
+        const int32_t to = (int32_t)(rank + CL.lb[rank]);
+        if (to < k) {
+            Rec* z = &T.list[to];
+            st64(&z->A, A);
+            st64(&z->F, F);
+            st64(&z->f, f);
+            st64(&z->idr, ((uint64_t)r << 32) | (uint32_t)id);
+            if (to == k - 1) {
+                CL.kth = ThRec{A, F, (int64_t)id};
+                CL.kset = 1;
+            }
+        }
+    }
+    // the list is complete before the lock and the new k-th record are seen
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __syncthreads();
+    if (tid == 0) {
+        __hip_atomic_store(T.cnt, min(k, cnt + (int32_t)nc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (CL.kset) {
+            const uint32_t q = __hip_atomic_load(T.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            ThRec* o = &T.ring[q];
+            st64(&o->A, CL.kth.A);
+            st64(&o->F, CL.kth.F);
+            st64((uint64_t*)&o->id, (uint64_t)CL.kth.id);
+            __hip_atomic_store(T.seq, q + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (locked) lock_release(T.lock);
+    }
+}
 
 template <int WW>
 __device__ uint32_t cut_step(const TopKDev& T, SrcState* S, int W, uint32_t d, bool apply, const uint32_t* cg,
                              const unsigned long long* ct, bool global_counts, bool locked, QStats* st,
-                             uint64_t* active, CutLds& CL, const DeferList* D = nullptr) {
-    uint32_t* s_flags = CL.flags;
+                             uint64_t* active, CutLds<64 * WW>& CL, const DeferList* D = nullptr) {
     uint32_t* s_live = &CL.live;
     const int tid = threadIdx.x;
     // arcs of Gamma_d that the footnote bound leaves out of ~gamma_{d+1}: one
     // edge per node back to Gamma_{d-1} (still scanned, so still in m_vis)
     uint64_t back = 0;
+    bool fl = false;  // the source is complete
     if (tid < W) {
         SrcState& s = S[tid];  // changed field by field: a copied struct ended up in scratch
         const int32_t status = s.status;
-        uint32_t fl = 0;
         if (status == S_LIVE && apply) {
             uint32_t g;
             unsigned long long t;
@@ -768,7 +832,7 @@ __device__ uint32_t cut_step(const TopKDev& T, SrcState* S, int W, uint32_t d, b
             }
             if (g == 0) {
                 s.status = S_DONE;
-                fl = 1;
+                fl = true;
             } else {
                 s.nd += g;
                 s.fd += (uint64_t)d * g;
@@ -776,77 +840,66 @@ __device__ uint32_t cut_step(const TopKDev& T, SrcState* S, int W, uint32_t d, b
                 s.tg = t - back;
             }
         } else if (status == S_TRIVIAL && !apply) {
-            fl = 1;
+            fl = true;
         }
-        s_flags[tid] = fl;
     }
-    if (tid == 0) *s_live = 0;
-    const int any = __syncthreads_or(tid < W ? (int)s_flags[tid] : 0);
     if (tid == 0) {
-        uint32_t nd = 0, nt = 0;
-        unsigned long long mv = 0;
-        if (any && T.all_f) {
-            for (int j = 0; j < W; ++j) {
-                if (!s_flags[j]) continue;
-                const SrcState& s = S[j];
-                const bool triv = s.status == S_TRIVIAL;
-                T.all_f[s.oid] = triv ? 0 : s.fd;
-                T.all_r[s.oid] = triv ? 1u : (uint32_t)s.nd;
-                if (triv) ++nt;
-                else {
-                    ++nd;
-                    mv += s.mvis;
-                }
-            }
-            if (nd) atomicAdd(&st->n_done, (unsigned long long)nd);
-            if (nt) atomicAdd(&st->n_trivial, (unsigned long long)nt);
-            if (mv) atomicAdd(&st->m_vis, mv);
-        } else if (any) {
-            // A completed source whose key is not above a published k-th
-            // record can never enter (the k-th best value only grows): drop
-            // it without the lock, so that the lock is taken only by sources
-            // that may enter (most completions, e.g. trivial sources, never do).
-            ThRec th0;
-            const bool have0 = load_threshold(T, &th0);
-            bool need = false;
-            for (int j = 0; j < W; ++j) {
-                if (!s_flags[j]) continue;
-                const SrcState& s = S[j];
-                const bool triv = s.status == S_TRIVIAL;
-                const uint64_t r = triv ? 1 : s.nd;
-                const uint64_t A = r <= 1 ? 0 : (r - 1) * (r - 1);
-                const uint64_t F = r <= 1 ? 1 : s.fd;
-                if (triv) ++nt;
-                else {
-                    ++nd;
-                    mv += s.mvis;
-                }
-                if (have0 && !key_gt(A, F, s.oid, th0.A, th0.F, (int32_t)th0.id)) s_flags[j] = 0;
-                else need = true;
-            }
-            if (need) {
-                if (locked) lock_acquire(T.lock);
-                for (int j = 0; j < W; ++j) {
-                    if (!s_flags[j]) continue;
-                    const SrcState& s = S[j];
-                    if (s.status == S_TRIVIAL) {
-                        topk_insert(T, 0, 1, 0, s.oid, 1);
-                    } else {
-                        const uint64_t r = s.nd;
-                        const uint64_t A = r <= 1 ? 0 : (r - 1) * (r - 1);
-                        const uint64_t F = r <= 1 ? 1 : s.fd;
-                        topk_insert(T, A, F, s.fd, s.oid, (uint32_t)r);
-                    }
-                }
-                if (locked) lock_release(T.lock);
-            }
-            if (nd) atomicAdd(&st->n_done, (unsigned long long)nd);
-            if (nt) atomicAdd(&st->n_trivial, (unsigned long long)nt);
-            if (mv) atomicAdd(&st->m_vis, mv);
-        }
+        *s_live = 0;
+        CL.nc = CL.nd = CL.nt = 0;
+        CL.mv = 0;
         ThRec th;
         CL.have_th = load_threshold(T, &th) ? 1u : 0u;
         CL.th = th;
+    }
+    if (__syncthreads_or(fl ? 1 : 0)) {
+        bool mine = false;
+        uint32_t at = 0, r = 1;
+        uint64_t A = 0, F = 1, f = 0;
+        int32_t id = 0;
+        if (fl) {
+            const SrcState& s = S[tid];
+            const bool triv = s.status == S_TRIVIAL;
+            id = s.oid;
+            if (!triv) {
+                r = (uint32_t)s.nd;
+                f = s.fd;
+                if (r > 1) {
+                    A = (uint64_t)(r - 1) * (r - 1);
+                    F = f;
+                }
+                atomicAdd(&CL.nd, 1u);
+                if (s.mvis) atomicAdd(&CL.mv, (unsigned long long)s.mvis);
+            } else {
+                atomicAdd(&CL.nt, 1u);
+            }
+            if (T.all_f) {
+                T.all_f[id] = triv ? 0 : f;
+                T.all_r[id] = triv ? 1u : r;
+            } else if (!CL.have_th || key_gt(A, F, id, CL.th.A, CL.th.F, (int32_t)CL.th.id)) {
+                // (a completed source whose key is not above a published k-th
+                // record can never enter, since the k-th best value only
+                // grows: it is dropped without the lock, as most are)
+                mine = true;
+                at = atomicAdd(&CL.nc, 1u);
+                CL.cA[at] = A;
+                CL.cF[at] = F;
+                CL.cid[at] = id;
+            }
+        }
+        __syncthreads();
+        if (tid == 0) {
+            if (CL.nd) atomicAdd(&st->n_done, (unsigned long long)CL.nd);
+            if (CL.nt) atomicAdd(&st->n_trivial, (unsigned long long)CL.nt);
+            if (CL.mv) atomicAdd(&st->m_vis, CL.mv);
+        }
+        if (CL.nc) {
+            topk_merge(T, CL, mine, at, A, F, f, id, r, locked);
+            if (tid == 0) {
+                ThRec th;
+                CL.have_th = load_threshold(T, &th) ? 1u : 0u;
+                CL.th = th;
+            }
+        }
     }
     __syncthreads();
     const bool have_th = CL.have_th != 0;
@@ -895,7 +948,7 @@ __device__ uint32_t cut_step(const TopKDev& T, SrcState* S, int W, uint32_t d, b
 // g = 0 reached nothing new, which the exact count confirms (it completes
 // there).  Writes the active masks and returns the live count.
 __device__ uint32_t trial_cut(const TopKDev& T, SrcState* S, int W, uint32_t d, const uint32_t* cg,
-                              const unsigned long long* ct, QStats* st, uint64_t* active, CutLds& CL) {
+                              const unsigned long long* ct, QStats* st, uint64_t* active, CutLds<64>& CL) {
     const int tid = threadIdx.x;
     if (tid == 0) {
         ThRec th;
@@ -1025,7 +1078,7 @@ __device__ inline uint32_t next_pull(uint32_t pull, unsigned long long fa, uint3
 
 template <int WW>
 __device__ void plain_init_body(const DevGraph& G, const int32_t* order, int32_t count, uint32_t b, int W,
-                                const SlotPtrs& P, SrcState* S, Ctl* C, const TopKDev& T, QStats* st, CutLds& CL,
+                                const SlotPtrs& P, SrcState* S, Ctl* C, const TopKDev& T, QStats* st, CutLds<64 * WW>& CL,
                                 uint32_t& s_flen, unsigned long long& s_arcs, uint64_t* s_act) {
     init_batch<WW, true>(G, order, count, b, W, P, S, &s_flen, &s_arcs);
     const uint32_t live = cut_step<WW>(T, S, W, 0, false, nullptr, nullptr, false, false, st, s_act, CL);
@@ -1049,7 +1102,7 @@ __device__ void plain_init_body(const DevGraph& G, const int32_t* order, int32_t
 template <int WW>
 __global__ __launch_bounds__(kBlk) void k_plain_init(DevGraph G, const int32_t* order, int32_t count, uint32_t b,
                                                     int W, LvSlots L, TopKDev T, QStats* st) {
-    __shared__ CutLds CL;
+    __shared__ CutLds<64 * WW> CL;
     __shared__ uint32_t s_flen;
     __shared__ unsigned long long s_arcs;
     __shared__ uint64_t s_act[4];
@@ -1060,7 +1113,7 @@ __global__ __launch_bounds__(kBlk) void k_plain_init(DevGraph G, const int32_t* 
 // counters; the last workgroup of the slot runs the cut step for the level.
 template <int WW>
 __device__ void plain_level_epilogue(Ctl* C, SrcState* S, const TopKDev& T, QStats* st, int W, const uint32_t* cg,
-                                     const unsigned long long* ct, CutLds& CL, uint64_t* s_act, uint32_t* s_last) {
+                                     const unsigned long long* ct, CutLds<64 * WW>& CL, uint64_t* s_act, uint32_t* s_last) {
     const int tid = threadIdx.x;
     if (tid < W && cg[tid]) {
         atomicAdd(&C->cnt_g[tid], cg[tid]);
@@ -1159,17 +1212,18 @@ __global__ __launch_bounds__(kLvBlk) void k_plain_expand(DevGraph G, LvSlots L, 
 // After a push step: the per-source counters of the level from its list of
 // newly reached nodes (once per node), then the cut step in the last
 // workgroup.  Same gate as the push step.
+template <int WW>
 struct CountLds {
     uint32_t cg[kBlk];
     unsigned long long ct[kBlk];
-    CutLds CL;
+    CutLds<64 * WW> CL;
     uint32_t last;
     uint64_t act[4];
 };
 
 template <int WW>
 __device__ void plain_count_body(const DevGraph& G, const SlotPtrs& P, SrcState* S, Ctl* C, const TopKDev& T,
-                                 QStats* st, int W, CountLds& X) {
+                                 QStats* st, int W, CountLds<WW>& X) {
     const uint32_t tid = threadIdx.x;
     if (tid < kBlk) {
         X.cg[tid] = 0;
@@ -1201,7 +1255,7 @@ __device__ void plain_count_body(const DevGraph& G, const SlotPtrs& P, SrcState*
 template <int WW>
 __global__ __launch_bounds__(kLvBlk) void k_plain_count(DevGraph G, LvSlots L, TopKDev T, QStats* st, int W,
                                                        int gated) {
-    __shared__ CountLds X;
+    __shared__ CountLds<WW> X;
     const size_t i = L.id[blockIdx.y];
     Ctl* C = L.C + i;
     if (gated && (C->live == 0 || C->pull != 0)) return;
@@ -1401,7 +1455,7 @@ struct PullLds {
     int32_t stage[kLvBlk / 64][kStage];
     uint32_t sh[kLvBlk / 64 + 1];
     unsigned long long scanned;
-    CountLds c;
+    CountLds<WW> c;
 };
 
 template <int WW>
@@ -1543,7 +1597,7 @@ struct RecLds {
     SrcState S[kBlk];
     uint32_t cg[kBlk];
     unsigned long long ct[kBlk];
-    CutLds CL;
+    CutLds<64 * WW> CL;
     uint32_t flen, nlen, clen;
     uint64_t act[4];
     unsigned long long arcs, narcs, ent;  // narcs, ent: arcs and frontier entries expanded
@@ -1713,7 +1767,7 @@ __device__ inline void grid_barrier(cooperative_groups::grid_group& g) {
 template <int WW>
 union CoopLds {
     PushLds<WW> push;
-    CountLds count;
+    CountLds<WW> count;
     PullLds<WW> pull;
     BuildLds build;
 };
@@ -1724,7 +1778,7 @@ __global__ __launch_bounds__(kLvBlk) void k_plain_coop(DevGraph G, const int32_t
                                                       LevelParams lp) {
     cooperative_groups::grid_group grid = cooperative_groups::this_grid();
     __shared__ CoopLds<WW> X;
-    __shared__ CutLds CL;
+    __shared__ CutLds<64 * WW> CL;
     __shared__ uint32_t s_flen;
     __shared__ unsigned long long s_arcs;
     __shared__ uint64_t s_act[4];
@@ -2584,7 +2638,7 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
     __shared__ SrcState S[64];
     __shared__ uint32_t cg[kBlk];
     __shared__ unsigned long long ct[kBlk];
-    __shared__ CutLds CL;
+    __shared__ CutLds<64> CL;
     __shared__ uint32_t s_flen, s_nlen, s_clen, s_b, s_mode, s_hasth;
     __shared__ uint64_t s_act[4];
     __shared__ unsigned long long s_arcs, s_narcs, s_ent, s_ent_lv;
