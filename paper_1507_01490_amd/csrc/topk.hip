@@ -1262,188 +1262,135 @@ __global__ __launch_bounds__(kLvBlk) void k_plain_count(DevGraph G, LvSlots L, T
     plain_count_body<WW>(G, slot_ptrs<WW>(L, i), L.S + i * kBlk, C, T, st, W, X);
 }
 
-// OR of x over the 64 lanes of the wave, in every lane.
-__device__ inline uint64_t wave_or(uint64_t x) {
+// Bottom-up step: every node not yet seen by some live source looks for an
+// in-neighbour in the frontier of that source.  One wave owns a node, so all
+// bits it finds are new and counted here.  WW lanes share a node, one word
+// each: a list is walked kPullAhead arcs at a time, whose targets and then
+// whose cur words are all in flight together, and a lane stops when its word's
+// unseen bits are all found.  Nothing goes through LDS and the WW lanes of a
+// node read the WW words of a neighbour side by side, so the step is bound by
+// the gathers of cur (8 WW bytes an arc).  A list of more than kPullWave arcs
+// is walked by a whole wave (64 / WW groups of lanes, each a part of it); the
+// graph keeps a list of these nodes, dealt over the grid, since renumbering
+// puts the hubs side by side.  (Barabasi-Albert graph of 10^6 nodes, W = 256,
+// a level: about 770 us with one thread per node, 200-300 us with the wave's
+// arcs dealt flat over its lanes and collected in LDS, 117-271 us
+// now.)
+constexpr int kPullAhead = 8;
+
+// OR over the lanes that hold the same word (lane % WW), in every lane.
+template <int WW>
+__device__ inline uint64_t group_or(uint64_t x) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x |= __shfl_xor(x, o);
+    for (int o = 32; o >= WW; o >>= 1) x |= __shfl_xor(x, o);
     return x;
 }
 
-// Bottom-up step: every node not yet seen by some live source looks for an
-// in-neighbour in the frontier of that source.  A wave owns 64 nodes, so all
-// bits it finds are new and counted here.  The lists of its nodes with up to
-// kPullWave in-arcs are walked as one flat sequence, 64 arcs at a time (two
-// such rounds in flight), each lane ORing what it finds into its node's word
-// in LDS; a node that has all its unseen bits is passed over.  A longer list
-// is walked by a whole wave, kPullAhead rounds at a time before it looks
-// whether all bits are found; the graph keeps a list of these nodes, dealt one
-// to a wave over the grid, since renumbering puts the hubs side by side and a
-// wave with 64 of them lasted a millisecond.  (One thread per node walked its list with two
-// dependent loads an arc: about 770 us a level on a Barabasi-Albert graph of
-// 10^6 nodes at W = 256, now 200-300.)
-constexpr int kPullAhead = 4;
-constexpr int kPullFlat = 2;
+// The arcs e0, e0 + step, ... below e1 of this lane's part of a list: the
+// bits of `unv` found among the neighbours' word j.  Returns the arcs read.
+template <int WW>
+__device__ __forceinline__ uint32_t pull_walk(const DevGraph& G, const uint64_t* cur_j, int64_t e0, int32_t e1,
+                                              int32_t step, uint64_t unv, uint64_t& acc) {
+    uint32_t read = 0;
+    int64_t e = e0;
+    while (e < e1 && acc != unv) {
+        int32_t u[kPullAhead];
+#pragma unroll
+        for (int q = 0; q < kPullAhead; ++q) {
+            const int64_t x = e + (int64_t)q * step;
+            u[q] = G.icol[x < e1 ? x : e];  // past the end: the first arc again
+        }
+        uint64_t c = 0;
+#pragma unroll
+        for (int q = 0; q < kPullAhead; ++q) c |= cur_j[(size_t)u[q] * WW];
+        acc |= c & unv;
+        read += kPullAhead;
+        e += (int64_t)kPullAhead * step;
+    }
+    return read;
+}
 
 template <int WW>
 struct PullWaveLds {
-    uint64_t acc[64 * WW], unv[64 * WW];
-    uint32_t off[64];
-    int32_t beg[64];
+    uint64_t acc[64 * WW];
 };
 
-// The 64 nodes w .. of one wave (lane's node w < G.n, else none); appends the
-// nodes that found something to N (through stg to a global counter, or without
-// one to a counter in LDS).  Counts the arcs read.  Converged wave.
+// The 64 nodes base .. base + 63 of one wave (actj: the live sources of word
+// lane % WW); appends the nodes that found
+// something to N (through stg to a global counter, or without one to a counter
+// in LDS).  Converged wave.
 template <int WW>
-__device__ __forceinline__ void pull_nodes(const DevGraph& G, const SlotPtrs& P, const uint64_t* act, int64_t w, PullWaveLds<WW>& L,
-                           uint32_t* cg, unsigned long long* ct, WaveStage* stg, uint32_t* nlen,
-                           unsigned long long& scanned) {
+__device__ __forceinline__ void pull_nodes(const DevGraph& G, const SlotPtrs& P, uint64_t actj, int64_t base,
+                                           PullWaveLds<WW>& L, uint32_t* cg, unsigned long long* ct, WaveStage* stg,
+                                           uint32_t* nlen, unsigned long long& scanned) {
     const int lane = (int)lane_id();
-    uint64_t unv[WW];
+    const int j = lane % WW;
+    constexpr int kPer = 64 / WW;  // nodes per round
     uint64_t any = 0;
-    int32_t e0 = 0, e1 = 0;
-    uint64_t* rec = nullptr;
 #pragma unroll
-    for (int j = 0; j < WW; ++j) unv[j] = 0;
-    if (w < G.n) {
-        rec = node_rec<WW, true>(P, (int32_t)w);
-#pragma unroll
-        for (int j = 0; j < WW; ++j) {
-            unv[j] = act[j] & ~rec[j];
-            any |= unv[j];
-        }
-        if (any) {
-            e0 = G.irp[w];
-            e1 = G.irp[w + 1];
-        }
-    }
-    const uint32_t len = e1 - e0 > kPullWave ? 0u : (uint32_t)(e1 - e0);  // longer lists: pull_heavy
-    if (__ballot(len != 0) == 0ull) return;
-    uint32_t x = len;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    const uint32_t total = (uint32_t)__builtin_amdgcn_readfirstlane((int)__shfl(x, 63));
-    L.off[lane] = x - len;
-    L.beg[lane] = e0;
-#pragma unroll
-    for (int j = 0; j < WW; ++j) {
-        L.acc[lane * WW + j] = 0;
-        L.unv[lane * WW + j] = unv[j];
-    }
-    wave_lds_sync();
-    for (uint32_t a0 = 0; a0 < total; a0 += 64 * kPullFlat) {
-        int32_t u[kPullFlat];
-        uint32_t own[kPullFlat];
-#pragma unroll
-        for (int q = 0; q < kPullFlat; ++q) {
-            const uint32_t a = a0 + (uint32_t)(q * 64 + lane);
-            u[q] = -1;
-            own[q] = 0;
-            if (a < total) {
-                // owner: the last lane with off <= a (off[0] = 0), which has arcs
-                uint32_t o = 0;
-#pragma unroll
-                for (uint32_t b = 32; b > 0; b >>= 1)
-                    if (L.off[o + b] <= a) o += b;
-                uint64_t open = 0;
-#pragma unroll
-                for (int j = 0; j < WW; ++j) open |= L.unv[o * WW + j] & ~L.acc[o * WW + j];
-                own[q] = o;
-                if (open) u[q] = G.icol[L.beg[o] + (int32_t)(a - L.off[o])];
+    for (int r = 0; r < WW; ++r) {
+        const int64_t w = base + r * kPer + lane / WW;
+        uint64_t acc = 0;
+        uint32_t read = 0;
+        if (w < G.n) {
+            uint64_t* rec = node_rec<WW, true>(P, (int32_t)w);
+            const uint64_t unv = actj & ~rec[j];
+            const int32_t e0 = G.irp[w], e1 = G.irp[w + 1];
+            if (unv && e1 - e0 <= kPullWave) {  // longer lists: pull_heavy
+                read = min(pull_walk<WW>(G, P.cur + j, e0, e1, 1, unv, acc), (uint32_t)(e1 - e0));
+                if (acc) rec[WW + j] = acc;
             }
         }
-        uint64_t c[kPullFlat * WW];
 #pragma unroll
-        for (int q = 0; q < kPullFlat; ++q) {
-            const uint64_t* cur = node_cur<WW, true>(P, max(u[q], 0));
-            scanned += u[q] >= 0;
-#pragma unroll
-            for (int j = 0; j < WW; ++j) c[q * WW + j] = u[q] >= 0 ? cur[j] : 0ull;
-        }
-#pragma unroll
-        for (int q = 0; q < kPullFlat; ++q) {
-#pragma unroll
-            for (int j = 0; j < WW; ++j) {
-                const uint64_t bits = c[q * WW + j] & L.unv[own[q] * WW + j];
-                if (bits) atomicOr((unsigned long long*)&L.acc[own[q] * WW + j], (unsigned long long)bits);
-            }
-        }
-        wave_lds_sync();
+        for (int o = 1; o < WW; o <<= 1) read = max(read, __shfl_xor(read, o));
+        if (j == 0) scanned += read;
+        L.acc[(r * kPer) * WW + lane] = acc;
+        any |= acc;
     }
-    uint64_t got = 0, acc[WW];
-    uint32_t deg = 0;
+    if (__ballot(any != 0) == 0ull) return;
+    wave_lds_sync();
+    uint64_t nb[WW], got = 0;
 #pragma unroll
-    for (int j = 0; j < WW; ++j) {
-        acc[j] = L.acc[lane * WW + j];
-        got |= acc[j];
-    }
-    if (got) {
-        deg = G.deg[w];
-#pragma unroll
-        for (int j = 0; j < WW; ++j) rec[WW + j] = acc[j];
+    for (int q = 0; q < WW; ++q) {
+        nb[q] = L.acc[lane * WW + q];
+        got |= nb[q];
     }
     wave_lds_sync();
-    wave_count_nodes<WW>(acc, deg, cg, ct);
-    if (stg) stg->push(got != 0, (int32_t)w, P.qb, nlen);
-    else append_if(got != 0, (int32_t)w, P.qb, nlen);
+    const int32_t w = (int32_t)(base + lane);
+    wave_count_nodes<WW>(nb, got ? G.deg[w] : 0u, cg, ct);
+    if (stg) stg->push(got != 0, w, P.qb, nlen);
+    else append_if(got != 0, w, P.qb, nlen);
 }
 
 // One node with more than kPullWave in-arcs, its list read by the whole wave;
 // returns in lane 0 whether it found something.  Converged wave.
 template <int WW>
-__device__ __forceinline__ bool pull_heavy(const DevGraph& G, const SlotPtrs& P, const uint64_t* act, int32_t w,
+__device__ __forceinline__ bool pull_heavy(const DevGraph& G, const SlotPtrs& P, uint64_t actj, int32_t w,
                                            uint32_t* cg, unsigned long long* ct, unsigned long long& scanned) {
     const int lane = (int)lane_id();
+    const int j = lane % WW;
+    constexpr int kGroups = 64 / WW;
     uint64_t* rec = node_rec<WW, true>(P, w);
-    uint64_t unv[WW], acc[WW], any = 0;
-#pragma unroll
-    for (int j = 0; j < WW; ++j) {
-        unv[j] = act[j] & ~rec[j];
-        any |= unv[j];
-        acc[j] = 0;
-    }
-    if (any == 0) return false;  // the same record in every lane
+    const uint64_t unv = actj & ~rec[j];
     const int32_t h0 = G.irp[w], h1 = G.irp[w + 1];
-    for (int64_t eb = h0; eb < h1; eb += 64 * kPullAhead) {
-        int32_t u[kPullAhead];
-#pragma unroll
-        for (int q = 0; q < kPullAhead; ++q) {
-            const int64_t e = eb + q * 64 + lane;
-            u[q] = e < h1 ? G.icol[e] : -1;
-        }
-        uint64_t part[WW];
-#pragma unroll
-        for (int j = 0; j < WW; ++j) part[j] = 0;
-#pragma unroll
-        for (int q = 0; q < kPullAhead; ++q) {
-            const uint64_t* cur = node_cur<WW, true>(P, max(u[q], 0));
-            scanned += u[q] >= 0;
-#pragma unroll
-            for (int j = 0; j < WW; ++j) part[j] |= u[q] >= 0 ? cur[j] : 0ull;
-        }
-        bool full = true;
-#pragma unroll
-        for (int j = 0; j < WW; ++j) {
-            acc[j] |= wave_or(part[j] & unv[j]);
-            full = full && (acc[j] == unv[j]);
-        }
-        if (full) break;
+    uint64_t acc = 0;
+    for (int64_t eb = h0; eb < h1; eb += kGroups * kPullAhead) {
+        if (__ballot(acc != unv) == 0ull) break;
+        const int32_t end = (int32_t)min((int64_t)h1, eb + kGroups * kPullAhead);
+        uint64_t part = acc;
+        (void)pull_walk<WW>(G, P.cur + j, eb + lane / WW, end, kGroups, unv, part);
+        acc = group_or<WW>(part);
+        if (lane == 0) scanned += (unsigned long long)(end - eb);
     }
-    uint64_t got = 0;
-#pragma unroll
-    for (int j = 0; j < WW; ++j) got |= acc[j];
-    if (got == 0) return false;
+    if (__ballot(acc != 0) == 0ull) return false;
     const uint32_t deg = G.deg[w];
-    // lane b counts for source j * 64 + b
+    if (lane < WW && acc) rec[WW + j] = acc;
 #pragma unroll
-    for (int j = 0; j < WW; ++j) {
-        if (lane == 0) rec[WW + j] = acc[j];
-        if ((acc[j] >> lane) & 1ull) {
-            atomicAdd(&cg[j * 64 + lane], 1u);
-            atomicAdd(&ct[j * 64 + lane], (unsigned long long)deg);
+    for (int q = 0; q < WW; ++q) {  // lane b counts for source q * 64 + b
+        const uint64_t x = __shfl(acc, q);
+        if ((x >> lane) & 1ull) {
+            atomicAdd(&cg[q * 64 + lane], 1u);
+            atomicAdd(&ct[q * 64 + lane], (unsigned long long)deg);
         }
     }
     return lane == 0;
@@ -1462,9 +1409,7 @@ template <int WW>
 __device__ void plain_pull_body(const DevGraph& G, const SlotPtrs& P, SrcState* S, Ctl* C, const TopKDev& T,
                                 QStats* st, int W, PullLds<WW>& X) {
     const int tid = threadIdx.x;
-    uint64_t act[WW];
-#pragma unroll
-    for (int j = 0; j < WW; ++j) act[j] = C->active[j];
+    const uint64_t actj = C->active[tid % WW];
     if (tid < kBlk) {
         X.c.cg[tid] = 0;
         X.c.ct[tid] = 0;
@@ -1476,12 +1421,12 @@ __device__ void plain_pull_body(const DevGraph& G, const SlotPtrs& P, SrcState* 
     const uint32_t nheavy = *G.nheavy, waves = gridDim.x * (kLvBlk / 64);
     for (uint32_t h = (uint32_t)(tid >> 6) * gridDim.x + blockIdx.x; h < nheavy; h += waves) {
         const int32_t w = G.heavy[h];
-        stg.push(pull_heavy<WW>(G, P, act, w, X.c.cg, X.c.ct, scanned), w, P.qb, &C->nlen);
+        stg.push(pull_heavy<WW>(G, P, actj, w, X.c.cg, X.c.ct, scanned), w, P.qb, &C->nlen);
     }
     // waves take 64 nodes at a time, neighbouring waves neighbouring nodes
     const int64_t stride = (int64_t)gridDim.x * kLvBlk;
     for (int64_t base = (int64_t)blockIdx.x * kLvBlk + (tid & ~63); base < G.n; base += stride)
-        pull_nodes<WW>(G, P, act, base + (tid & 63), Lw, X.c.cg, X.c.ct, &stg, &C->nlen, scanned);
+        pull_nodes<WW>(G, P, actj, base, Lw, X.c.cg, X.c.ct, &stg, &C->nlen, scanned);
     if (tid == 0) X.scanned = 0;
     block_flush<kLvBlk>(stg, P.qb, &C->nlen, X.sh);
     for (int o = 32; o > 0; o >>= 1) scanned += __shfl_xor(scanned, o);
@@ -1687,16 +1632,14 @@ __global__ __launch_bounds__(kBatchBlk) void k_plain_run(DevGraph G, const int32
         }
         __syncthreads();
         if (pull) {
-            uint64_t act[WW];
-#pragma unroll
-            for (int j = 0; j < WW; ++j) act[j] = uni64(R.act[j]);
+            const uint64_t actj = R.act[tid % WW];
             const uint32_t nheavy = *G.nheavy;
             for (uint32_t h = (uint32_t)tid >> 6; h < nheavy; h += B / 64) {
                 const int32_t w = G.heavy[h];
-                append_if(pull_heavy<WW>(G, P, act, w, R.cg, R.ct, scanned), w, P.qb, &R.nlen);
+                append_if(pull_heavy<WW>(G, P, actj, w, R.cg, R.ct, scanned), w, P.qb, &R.nlen);
             }
             for (int64_t base = tid & ~63; base < G.n; base += B)
-                pull_nodes<WW>(G, P, act, base + (tid & 63), X[tid >> 6], R.cg, R.ct, nullptr, &R.nlen, scanned);
+                pull_nodes<WW>(G, P, actj, base, X[tid >> 6], R.cg, R.ct, nullptr, &R.nlen, scanned);
             __threadfence();  // nxt and the list are read by other waves next
             __syncthreads();
             clear_cur<WW, true>(P, P.qa, flen, 0, B);
