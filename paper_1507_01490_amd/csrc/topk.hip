@@ -265,6 +265,17 @@ __device__ inline bool cut_rule(const SrcState& s, uint32_t d, const ThRec& th) 
 
 __device__ inline uint32_t lane_id() { return __lane_id(); }
 
+// Every store and atomic this wave has issued is done (acknowledged by the
+// cache it goes to).  With a workgroup barrier after it, one thread may then
+// tell other workgroups through an atomic that the workgroup's atomics are
+// done.  A release fence would order the same but writes the XCD's dirty L2
+// lines back to memory, once per wave that executes it: in the level kernels,
+// whose plain stores only later kernels read, 4,096 of them cost 60-100 us.
+__device__ inline void wait_stores() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // nothing moves below
+    __builtin_amdgcn_s_waitcnt(0x0F70);                     // vmcnt(0)
+}
+
 // Seen filter of a batch on the node records: one bit per hashed node id
 // (2^17 bits in LDS), set for every node that has a seen bit in the records.
 // A clear bit proves the node unseen, so its record need not be read.
@@ -790,8 +801,9 @@ __device__ void topk_merge(const TopKDev& T, CutLds<N>& CL, bool mine, uint32_t 
             }
         }
     }
-    // the list is complete before the lock and the new k-th record are seen
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    // the list (written with agent-scope stores) is complete before the lock
+    // and the new k-th record are seen
+    wait_stores();
     __syncthreads();
     if (tid == 0) {
         __hip_atomic_store(T.cnt, min(k, cnt + (int32_t)nc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1119,12 +1131,12 @@ __device__ void plain_level_epilogue(Ctl* C, SrcState* S, const TopKDev& T, QSta
         atomicAdd(&C->cnt_g[tid], cg[tid]);
         atomicAdd(&C->cnt_t[tid], ct[tid]);
     }
-    __threadfence();
+    wait_stores();
     __syncthreads();
     if (tid == 0) *s_last = (atomicAdd(&C->done_blocks, 1u) == gridDim.x - 1) ? 1u : 0u;
     __syncthreads();
     if (!*s_last) return;
-    __threadfence();
+    // the counters other workgroups added to are read with atomic loads
     const uint32_t d = C->d;
     const uint32_t live = cut_step<WW>(T, S, W, d + 1, true, C->cnt_g, C->cnt_t, true, true, st, s_act, CL);
     if (tid < W) {
@@ -1139,8 +1151,7 @@ __device__ void plain_level_epilogue(Ctl* C, SrcState* S, const TopKDev& T, QSta
         C->chunk = 0;
         for (int j = 0; j < 4; ++j) C->active[j] = j < WW ? s_act[j] : 0;
         atomicAdd(&st->levels, 1ull);
-        atomicAdd(&st->discovered, (unsigned long long)C->nlen);
-        __threadfence();
+        atomicAdd(&st->discovered, (unsigned long long)ldu32(&C->nlen));
         C->done_blocks = 0;
     }
 }
@@ -1481,12 +1492,11 @@ __device__ void plain_build_body(const DevGraph& G, const SlotPtrs& P, Ctl* C, c
     block_flush<kLvBlk>(sf, P.qa, &C->done_blocks, X.sh);
     block_flush<kLvBlk>(sc, P.clr, &C->clen, X.sh);
     if (tid == 0 && X.arcs) atomicAdd(&C->acc_arcs, X.arcs);
-    __threadfence();
+    wait_stores();
     __syncthreads();
     if (tid == 0) X.last = (atomicAdd(&C->chunk, 1u) == gridDim.x - 1) ? 1u : 0u;
     __syncthreads();
     if (!X.last || tid != 0) return;
-    __threadfence();
     const uint32_t flen =
         any_live ? __hip_atomic_load(&C->done_blocks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
     const unsigned long long fa = __hip_atomic_load(&C->acc_arcs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1498,7 +1508,6 @@ __device__ void plain_build_body(const DevGraph& G, const SlotPtrs& P, Ctl* C, c
     C->stamp = C->stamp + 1;
     C->chunk = 0;
     C->ran = 0;
-    __threadfence();
     C->done_blocks = 0;
 }
 
@@ -1640,7 +1649,7 @@ __global__ __launch_bounds__(kBatchBlk) void k_plain_run(DevGraph G, const int32
             }
             for (int64_t base = tid & ~63; base < G.n; base += B)
                 pull_nodes<WW>(G, P, actj, base, X[tid >> 6], R.cg, R.ct, nullptr, &R.nlen, scanned);
-            __threadfence();  // nxt and the list are read by other waves next
+            wait_stores();  // nxt is taken with exchanges by other waves next
             __syncthreads();
             clear_cur<WW, true>(P, P.qa, flen, 0, B);
             ++pulls;
