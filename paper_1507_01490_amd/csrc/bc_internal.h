@@ -176,11 +176,14 @@ namespace bc {
 struct Workspace {
     int ww = 0;        // mask words per node the persistent slots were sized for
     int slots = 0;     // persistent slots allocated
-    struct Lv {        // level-synchronous slots of one width (split layout), in one allocation
+    struct Slots {     // node state and lists of consecutive slots, in one allocation
+        DevBuf mem, ns, cur, stamp, qa, qb, clr;
+    };
+    struct Lv : Slots {  // level-synchronous slots of one width
         int slots = 0;
-        DevBuf mem, ctl, next, ns, cur, stamp, srcs, qa, qb, clr;
+        DevBuf cmem, ctl, next, srcs;
     } lv[3];           // W = 64, 128, 256
-    DevBuf bseen, bqa, bqb, bclr;  // persistent slots
+    Slots pers;        // persistent slots
     DevBuf nextb, slot_stamp, defer;
     hipStream_t stream = nullptr;  // stream its buffers are ordered on
     uint32_t* hctl = nullptr;      // pinned: the level-synchronous slots' reports

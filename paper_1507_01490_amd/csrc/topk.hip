@@ -1,13 +1,12 @@
 // Top-k closeness on gfx950: Algorithm 1 with the BFSCut function
 // (Section 2.5), run as bit-parallel multi-source BFS.
 //
-// A batch holds W = 64 * WW sources, one bit each.  Every node has one
-// record per batch slot (SW uint64 words, node-major, one 32/64/128-byte
-// block so that every per-node access touches one cache line):
-//   seen[WW]   sources that have reached the node      (the "visited" marks)
-//   nxt[WW]    sources reaching it in the level being built
-//   cur[WW]    sources for which it is in the current frontier Gamma_d
-//   meta       low 32 bits: first-touch stamp (WW > 1); high 32 bits: out-degree
+// A batch holds W = 64 * WW sources, one bit each.  Every node has, per batch
+// slot, WW words each of
+//   seen   sources that have reached the node      (the "visited" marks)
+//   nxt    sources reaching it in the level being built
+//   cur    sources for which it is in the current frontier Gamma_d
+// (for WW > 1 also the stamp of the level that first touched it last),
 // plus three node lists of capacity n: the current frontier F (compacted to
 // nodes with a live source bit), the nodes reached by the level being built
 // N (each once per level), and the reset list (each node once, when its seen
@@ -18,9 +17,10 @@
 //   tg = ~gamma_{d+1} (sum of out-degrees over Gamma_d), mvis (arcs a
 //   sequential search of this source scans).
 // One level: expand F (every arc u->w with a live bit of cur[u] not yet in
-// seen[w] ORs it into nxt[w]); the thread whose atomic OR newly sets bit b of
-// nxt[w] adds 1 to gamma_{d+1}(b) and deg(w) to ~gamma_{d+2}(b), so each
-// (node, source) pair is counted once.  A source with gamma = 0 is complete
+// seen[w] ORs it into nxt[w]), or, for a wide frontier, a bottom-up step in
+// which every node gathers the cur words of its in-neighbours; each node
+// reached, taken once, adds for every bit b of its nxt 1 to gamma_{d+1}(b)
+// and deg(w) to ~gamma_{d+2}(b).  A source with gamma = 0 is complete
 // (r = nd, f = fd); every other live source is tested against the current
 // k-th best record with the bound of Lemma 1 (undirected, x = r(v)) or
 // Lemma 2 (directed, x in {alpha(v), omega(v)}), and its bit is retired when
@@ -49,19 +49,12 @@ namespace {
 constexpr int kBlk = 256;  // threads per workgroup in every level kernel (and the most sources per batch)
 constexpr int kBatchBlk = 1024;  // threads per workgroup of the persistent batched and the narrow level kernels
 
-// Node state of a slot, in one of two layouts:
-//   record (D = false, the persistent kernels): seen, nxt, cur (WW words each)
-//     and meta (out-degree << 32 | first-touch stamp) in one record padded to
-//     32/64/128 B, so that a node costs one line however much of it is touched
-//   split (D = true, the level-synchronous kernels): seen and nxt side by side
-//     (2 WW words), cur in a dense array of its own and the stamps in another
-//     (WW > 1); out-degrees come from the graph.  A bottom-up step gathers cur
-//     words alone: at W = 256 four nodes share a line instead of one
-template <int WW>
-struct Layout {
-    static constexpr int SW = WW == 1 ? 4 : (WW == 2 ? 8 : 16);
-    static constexpr int NXT = WW, CUR = 2 * WW, META = 3 * WW;
-};
+// Node state of a slot: seen and nxt side by side (2 WW words), the cur words
+// in a dense array of their own, first-touch stamps in another (WW > 1);
+// out-degrees come from the graph.  A push step touches 16 WW bytes of a
+// target in one piece, and a bottom-up step gathers cur words alone: at W = 256
+// four nodes share a line.  (One padded record per node with all of it, 128 B
+// at W = 256, cost a line for each.)
 
 enum : int32_t { S_EMPTY = 0, S_LIVE = 1, S_CUT = 2, S_DONE = 3, S_TRIVIAL = 4, S_DEFER = 5 };
 
@@ -129,26 +122,28 @@ struct Ctl {
 };
 
 struct SlotPtrs {
-    uint64_t* ns;     // n node records (SW words), or n pairs seen, nxt (2 WW words, split layout)
+    uint64_t* ns;     // n pairs seen, nxt (2 WW words)
     int32_t* qa;      // n, frontier list F
     int32_t* qb;      // n, reached list N
     int32_t* clr;     // n, reset list
-    uint64_t* cur;    // split layout: n * WW cur words
-    uint32_t* stamp;  // split layout, WW > 1: n first-touch stamps
+    uint64_t* cur;    // n * WW cur words
+    uint32_t* stamp;  // WW > 1: n first-touch stamps
 };
-template <int WW, bool D>
-__device__ inline uint64_t* node_rec(const SlotPtrs& P, int32_t w) {
-    return &P.ns[(size_t)w * (D ? 2 * WW : Layout<WW>::SW)];
-}
-template <int WW, bool D>
-__device__ inline uint64_t* node_cur(const SlotPtrs& P, int32_t w) {
-    if constexpr (D) return &P.cur[(size_t)w * WW];
-    else return node_rec<WW, false>(P, w) + Layout<WW>::CUR;
-}
-template <int WW, bool D>
-__device__ inline uint32_t* node_stamp(const SlotPtrs& P, int32_t w) {
-    if constexpr (D) return &P.stamp[w];
-    else return reinterpret_cast<uint32_t*>(node_rec<WW, false>(P, w) + Layout<WW>::META);
+template <int WW>
+__device__ inline uint64_t* node_rec(const SlotPtrs& P, int32_t w) { return &P.ns[(size_t)w * (2 * WW)]; }
+template <int WW>
+__device__ inline uint64_t* node_cur(const SlotPtrs& P, int32_t w) { return &P.cur[(size_t)w * WW]; }
+// Slot i of consecutive slots of n nodes.
+template <int WW>
+__device__ inline SlotPtrs slot_at(const SlotPtrs& base, size_t n, size_t i) {
+    SlotPtrs P;
+    P.ns = base.ns + i * n * (2 * WW);
+    P.qa = base.qa + i * n;
+    P.qb = base.qb + i * n;
+    P.clr = base.clr + i * n;
+    P.cur = base.cur + i * n * WW;
+    P.stamp = WW > 1 ? base.stamp + i * n : nullptr;
+    return P;
 }
 
 struct LevelParams {
@@ -178,14 +173,7 @@ struct LvSlots {
 };
 template <int WW>
 __device__ inline SlotPtrs slot_ptrs(const LvSlots& L, size_t i) {
-    SlotPtrs P;
-    P.ns = L.base.ns + i * L.n * (2 * WW);
-    P.qa = L.base.qa + i * L.n;
-    P.qb = L.base.qb + i * L.n;
-    P.clr = L.base.clr + i * L.n;
-    P.cur = L.base.cur + i * L.n * WW;
-    P.stamp = L.base.stamp ? L.base.stamp + i * L.n : nullptr;
-    return P;
+    return slot_at<WW>(L.base, L.n, i);
 }
 
 // ------------------------------------------------------------ helpers
@@ -264,6 +252,15 @@ __device__ inline bool cut_rule(const SrcState& s, uint32_t d, const ThRec& th) 
 }
 
 __device__ inline uint32_t lane_id() { return __lane_id(); }
+
+// The thread's index, opaque: what a phase derives from it (LDS and slot
+// addresses) is not kept in registers across the levels of a persistent
+// kernel, where it spilled.
+__device__ __forceinline__ int phase_tid() {
+    int t = (int)threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
 
 // Every store and atomic this wave has issued is done (acknowledged by the
 // cache it goes to).  With a workgroup barrier after it, one thread may then
@@ -428,66 +425,138 @@ __device__ inline void wave_count_nodes(const uint64_t* nb, uint32_t deg, uint32
     }
 }
 
+// The WW lanes of a group work on each other's nodes in turn, lane j on word
+// j: in round r on the node of lane r.  A node's words are one line, so a
+// load, store or atomic on all of them is one request to L2 in place of WW.
+// Push levels are bound by these requests (seen and nxt of every arc's
+// target, then the atomics): a geometric graph of 65,537 nodes, batched at
+// W = 256, took 163 ms with a lane per node and takes 101 ms so; a
+// collaboration graph of 500,000 nodes 218 and 187 ms.
+
+// This lane's word.  Opaque, so that the pointers made from it are not all
+// kept in registers across the levels (they spilled).
+template <int WW>
+__device__ __forceinline__ uint32_t group_lane() {
+    uint32_t j = lane_id() % WW;
+    if constexpr (WW > 1) asm volatile("" : "+v"(j));
+    return j;
+}
+template <int WW, int R>
+__device__ __forceinline__ int32_t group_bcast(int32_t x) {
+    if constexpr (WW == 1) return x;
+    else if constexpr (WW == 2) return __builtin_amdgcn_mov_dpp(x, R | R << 2 | (2 + R) << 4 | (2 + R) << 6, 15, 15, true);
+    else return __builtin_amdgcn_mov_dpp(x, R * 0x55, 15, 15, true);
+}
+template <int WW>
+__device__ __forceinline__ void group_bcast_all(int32_t x, int32_t* y) {
+    y[0] = group_bcast<WW, 0>(x);
+    if constexpr (WW >= 2) y[1] = group_bcast<WW, 1>(x);
+    if constexpr (WW == 4) {
+        y[2] = group_bcast<WW, 2>(x);
+        y[3] = group_bcast<WW, 3>(x);
+    }
+}
+// p[r]: in round r; true in the lanes whose own round had it in some lane of the group
+template <int WW>
+__device__ __forceinline__ bool group_any(const bool* p) {
+    if constexpr (WW == 1) return p[0];
+    const uint32_t lane = lane_id();
+    unsigned long long b = __ballot(p[0]);
+#pragma unroll
+    for (int r = 1; r < WW; ++r) {
+        const unsigned long long x = __ballot(p[r]);
+        if (lane % WW == (uint32_t)r) b = x;
+    }
+    return ((uint32_t)(b >> (lane & (64u - WW))) & ((1u << WW) - 1u)) != 0u;
+}
+// x[r] of lane j becomes x[j] of lane r
+template <int WW>
+__device__ __forceinline__ void group_transpose(uint64_t* x) {
+#pragma unroll
+    for (int s = 1; s < WW; s <<= 1) {
+        const bool up = (lane_id() & (uint32_t)s) != 0u;
+#pragma unroll
+        for (int r = 0; r < WW; ++r) {
+            if (r & s) continue;
+            const uint64_t give = up ? x[r] : x[r | s];
+            int32_t lo, hi;
+            if (s == 1) {
+                lo = __builtin_amdgcn_mov_dpp((int32_t)(uint32_t)give, 0xB1, 15, 15, true);
+                hi = __builtin_amdgcn_mov_dpp((int32_t)(uint32_t)(give >> 32), 0xB1, 15, 15, true);
+            } else {
+                lo = __builtin_amdgcn_mov_dpp((int32_t)(uint32_t)give, 0x4E, 15, 15, true);
+                hi = __builtin_amdgcn_mov_dpp((int32_t)(uint32_t)(give >> 32), 0x4E, 15, 15, true);
+            }
+            const uint64_t got = (uint64_t)(uint32_t)hi << 32 | (uint32_t)lo;
+            if (up) x[r] = got; else x[r | s] = got;
+        }
+    }
+}
+
 // Counters of the level just reached, from its list N[0, len) of newly
 // reached nodes (each once) after the expansion: the nxt masks are read from
-// L2 (they were written by atomics this level).  The out-degree comes from
-// the record's meta word, or from degs[] when the records are shared by the
-// batches of several graphs (their meta words then hold no degree).
-template <int WW, int B, bool D = false>
+// L2 (they were written by atomics of this workgroup).  degs: out-degrees.
+template <int WW, int B>
 __device__ void count_level(const SlotPtrs& P, const int32_t* N, uint32_t len, uint32_t* cg, unsigned long long* ct,
-                            const uint32_t* degs = nullptr) {
-    using Lo = Layout<WW>;
-    const uint32_t tid = threadIdx.x;
+                            const uint32_t* degs) {
+    const uint32_t tid = phase_tid();
     for (uint32_t rb = 0; rb < len; rb += B) {
         if (rb + (tid & ~63u) >= len) break;  // wave-uniform: nothing left for this wave
         const uint32_t i = rb + tid;
+        const int32_t w = i < len ? N[i] : -1;
+        int32_t wr[WW];
+        group_bcast_all<WW>(w, wr);
         uint64_t nb[WW];
-        uint32_t deg = 0;
+        const uint32_t j = group_lane<WW>();
 #pragma unroll
-        for (int j = 0; j < WW; ++j) nb[j] = 0;
-        if (i < len) {
-            uint64_t* rec = node_rec<WW, D>(P, N[i]);
-#pragma unroll
-            for (int j = 0; j < WW; ++j)
-                nb[j] = __hip_atomic_load(&rec[Lo::NXT + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if constexpr (D) deg = degs[N[i]];
-            else deg = degs ? degs[N[i]] : (uint32_t)(rec[Lo::META] >> 32);
-        }
+        for (int r = 0; r < WW; ++r)
+            nb[r] = wr[r] < 0 ? 0ull
+                              : __hip_atomic_load(&node_rec<WW>(P, wr[r])[WW + j], __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_WORKGROUP);
+        const uint32_t deg = w < 0 ? 0u : degs[w];
+        group_transpose<WW>(nb);
         wave_count_nodes<WW>(nb, deg, cg, ct);
     }
 }
 
-// Arc u->w for the live source bits m of u: OR the unseen ones into nxt[w]
-// (the per-source counters are taken later, once per reached node).  Returns
-// whether w is new this level.
-template <int WW, bool D>
-__device__ inline bool visit(const SlotPtrs& P, int32_t w, const uint64_t* m, uint32_t stamp) {
-    using Lo = Layout<WW>;
-    uint64_t* rec = node_rec<WW, D>(P, w);
-    uint64_t nb[WW];
-    uint64_t any = 0;
+// One arc u->w per lane (on; w = 0 where not), for the live source bits
+// M[own WW ..] of u: OR the unseen ones into nxt[w] (the per-source counters are
+// taken later, once per reached node).  Returns whether w is new this level.
+// A stale nxt only costs an extra atomic.  Converged wave.
+template <int WW>
+__device__ __forceinline__ bool visit(const SlotPtrs& P, bool on, int32_t w, uint32_t own, const uint64_t* M,
+                                      uint32_t stamp) {
     if constexpr (WW == 1) {
-        // seen and nxt share one 16-byte load; a stale nxt only costs an extra atomic
-        const ulonglong2 sn = *reinterpret_cast<const ulonglong2*>(rec);
-        nb[0] = m[0] & ~(sn.x | sn.y);
-        any = nb[0];
-    } else {
-#pragma unroll
-        for (int j = 0; j < WW; ++j) {
-            nb[j] = m[j] & ~(rec[j] | rec[Lo::NXT + j]);
-            any |= nb[j];
-        }
-    }
-    if (!any) return false;
-    if constexpr (WW == 1) {
-        // one word: the first toucher is the one that finds nxt empty (stamp unused)
+        // seen and nxt share one 16-byte load; the first toucher is the one that finds nxt empty
         (void)stamp;
-        return atomicOr((unsigned long long*)&rec[Lo::NXT], (unsigned long long)nb[0]) == 0ull;
+        if (!on) return false;
+        uint64_t* rec = node_rec<WW>(P, w);
+        const ulonglong2 sn = *reinterpret_cast<const ulonglong2*>(rec);
+        const uint64_t nb = M[own] & ~(sn.x | sn.y);
+        return nb && atomicOr((unsigned long long*)&rec[WW], (unsigned long long)nb) == 0ull;
     } else {
+        if (__ballot(on) == 0ull) return false;
+        const uint32_t j = group_lane<WW>();
+        int32_t wr[WW], mr[WW];
+        group_bcast_all<WW>(w, wr);
+        group_bcast_all<WW>(on ? (int32_t)own : -1, mr);
+        uint64_t nb[WW], s[WW], x[WW];
 #pragma unroll
-        for (int j = 0; j < WW; ++j)
-            if (nb[j]) atomicOr((unsigned long long*)&rec[Lo::NXT + j], (unsigned long long)nb[j]);
-        return atomicMax(node_stamp<WW, D>(P, w), stamp) < stamp;
+        for (int r = 0; r < WW; ++r) {
+            const uint64_t* rec = node_rec<WW>(P, wr[r]) + j;
+            s[r] = rec[0];
+            x[r] = rec[WW];
+        }
+#pragma unroll
+        for (int r = 0; r < WW; ++r) nb[r] = mr[r] < 0 ? 0ull : M[mr[r] * WW + j];
+        bool p[WW];
+#pragma unroll
+        for (int r = 0; r < WW; ++r) {
+            nb[r] &= ~(s[r] | x[r]);
+            p[r] = nb[r] != 0ull;
+            if (p[r]) atomicOr((unsigned long long*)(node_rec<WW>(P, wr[r]) + WW + j), (unsigned long long)nb[r]);
+        }
+        return group_any<WW>(p) && atomicMax(&P.stamp[w], stamp) < stamp;
     }
 }
 
@@ -535,32 +604,35 @@ struct LdsExpand {
 // thread takes kArcs arcs per round (a, a + B, ...) and issues all their
 // target loads before it visits any target's record: two in the
 // level-synchronous kernel, one in the persistent kernels, where the second
-// arc's registers cost more than its overlap gains.  In the split layout an
-// entry's cur words are zeroed once read (nothing else reads them in a push
-// step).  With stg, the nodes go through the waves' stages to a global list;
-// without, nctr is a counter in LDS.
-template <int WW, int B = kBlk, int kArcs = 2, bool D = false>
+// arc's registers cost more than its overlap gains.  An entry's cur words are
+// zeroed once read (a bottom-up step may come next, which reads every node's).
+// With stg, the nodes go through the waves' stages to a global list; without,
+// nctr is a counter in LDS.
+template <int WW, int B = kBlk, int kArcs = 2>
 __device__ void expand_entries(const DevGraph& G, const SlotPtrs& P, const int32_t* F, uint32_t e0, uint32_t e1,
                                const uint64_t* act, int32_t* N, uint32_t* nctr, uint32_t stamp, LdsExpand<WW, B>& L,
                                unsigned long long* arcs, unsigned long long* entries, WaveStage* stg = nullptr) {
-    const int tid = threadIdx.x;
+    const int tid = phase_tid();
     const uint32_t e = e0 + tid;
     uint32_t deg = 0;
     int32_t beg = 0;
-    uint64_t m[WW];
+    if (e0 + (tid & ~63) < e1) {  // wave-uniform
+        const int j = (int)group_lane<WW>();
+        const int32_t u = e < e1 ? F[e] : -1;
+        const uint64_t actj = act[j];
+        int32_t ur[WW];
+        group_bcast_all<WW>(u, ur);
+        uint64_t m[WW];
 #pragma unroll
-    for (int j = 0; j < WW; ++j) m[j] = 0;
-    if (e < e1) {
-        const int32_t u = F[e];
-        uint64_t* cur = node_cur<WW, D>(P, u);
-        uint64_t any = 0;
+        for (int r = 0; r < WW; ++r) m[r] = ur[r] < 0 ? 0ull : node_cur<WW>(P, ur[r])[j] & actj;
+        bool p[WW];
 #pragma unroll
-        for (int j = 0; j < WW; ++j) {
-            m[j] = cur[j] & act[j];
-            if constexpr (D) cur[j] = 0;
-            any |= m[j];
+        for (int r = 0; r < WW; ++r) {
+            if (ur[r] >= 0) node_cur<WW>(P, ur[r])[j] = 0;
+            L.m[(tid - j + r) * WW + j] = m[r];
+            p[r] = m[r] != 0ull;
         }
-        if (any) {
+        if (group_any<WW>(p)) {
             beg = G.rp[u];
             deg = (uint32_t)(G.rp[u + 1] - beg);
         }
@@ -568,8 +640,6 @@ __device__ void expand_entries(const DevGraph& G, const SlotPtrs& P, const int32
     const unsigned long long nlive = __ballot(deg != 0);
     if ((tid & 63) == 0 && nlive) atomicAdd(entries, (unsigned long long)__popcll(nlive));
     L.beg[tid] = beg;
-#pragma unroll
-    for (int j = 0; j < WW; ++j) L.m[tid * WW + j] = m[j];
     uint32_t total;
     const uint32_t off = block_exscan<B>(deg, L.scan, &total);
     L.off[tid] = off;
@@ -598,7 +668,7 @@ __device__ void expand_entries(const DevGraph& G, const SlotPtrs& P, const int32
         }
 #pragma unroll
         for (int u = 0; u < kArcs; ++u)
-            if (app[u]) app[u] = visit<WW, D>(P, w[u], &L.m[own[u] * WW], stamp);
+            app[u] = visit<WW>(P, app[u], w[u], own[u], L.m, stamp);
 #pragma unroll
         for (int u = 0; u < kArcs; ++u) {
             if (stg) stg->push(app[u], w[u], N, nctr);
@@ -610,13 +680,10 @@ __device__ void expand_entries(const DevGraph& G, const SlotPtrs& P, const int32
 }
 
 // Zero the cur masks of the list entries [first, len) (stride).
-template <int WW, bool D = false>
+template <int WW>
 __device__ inline void clear_cur(const SlotPtrs& P, const int32_t* F, uint32_t len, uint32_t first, uint32_t stride) {
-    for (uint32_t i = first + threadIdx.x; i < len; i += stride) {
-        uint64_t* cur = node_cur<WW, D>(P, F[i]);
-#pragma unroll
-        for (int j = 0; j < WW; ++j) cur[j] = 0;
-    }
+    const uint64_t end = (uint64_t)len * WW;  // a word per thread
+    for (uint64_t i = (uint64_t)first + phase_tid(); i < end; i += stride) node_cur<WW>(P, F[i / WW])[i % WW] = 0;
 }
 
 // Build the new frontier from the reached list N[0, len) once the cut step
@@ -627,62 +694,61 @@ __device__ inline void clear_cur(const SlotPtrs& P, const int32_t* F, uint32_t l
 // predates the level's atomic updates (a kernel of its own, or after a grid
 // barrier's acquire), so nxt is read with a plain load; otherwise (the
 // persistent and narrow kernels, whose own plain loads may have cached a
-// record before the atomics changed it) it is taken with an exchange.
+// record before the atomics changed it) from L2, where this workgroup's
+// atomics were done.
 // sf, sc: the waves' stages when F and the reset list have global counters
 // (the caller flushes them).
-template <int WW, bool D = false, bool kFresh = false>
+template <int WW, bool kFresh = false>
 __device__ void build_level(const SlotPtrs& P, const int32_t* N, uint32_t len, uint32_t first, uint32_t stride,
                             const uint64_t* act, bool any_live, int32_t* F, uint32_t* fctr, uint32_t* clen,
-                            unsigned long long* arcs, uint32_t* seen_filter = nullptr, const uint32_t* degs = nullptr,
+                            unsigned long long* arcs, const uint32_t* degs, uint32_t* seen_filter = nullptr,
                             WaveStage* sf = nullptr, WaveStage* sc = nullptr) {
-    using Lo = Layout<WW>;
-    const int tid = threadIdx.x;
+    const int tid = phase_tid();
+    const uint64_t actj = act[tid % WW];
     unsigned long long my_arcs = 0;
     for (uint32_t rb = first; rb < len; rb += stride) {
+        if (rb + (tid & ~63) >= len) break;  // wave-uniform
         const uint32_t i = rb + tid;
+        const int32_t w = i < len ? N[i] : -1;
+        int32_t wr[WW];
+        group_bcast_all<WW>(w, wr);
+        const uint32_t jw = group_lane<WW>();
         bool keep = false, fresh = false;
-        int32_t w = 0;
-        if (i < len) {
-            w = N[i];
-            uint64_t* rec = node_rec<WW, D>(P, w);
-            if (!any_live) {
+        if (!any_live) {
 #pragma unroll
-                for (int j = 0; j < WW; ++j) rec[Lo::NXT + j] = 0;
-            } else {
-                uint64_t nb[WW];
-                uint64_t any = 0;
-                if constexpr (kFresh) {
+            for (int r = 0; r < WW; ++r)
+                if (wr[r] >= 0) node_rec<WW>(P, wr[r])[WW + jw] = 0;
+        } else {
+            uint64_t nb[WW], old[WW];
 #pragma unroll
-                    for (int j = 0; j < WW; ++j) nb[j] = rec[Lo::NXT + j];
-#pragma unroll
-                    for (int j = 0; j < WW; ++j) {
-                        rec[Lo::NXT + j] = 0;
-                        nb[j] &= act[j];
-                        any |= nb[j];
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < WW; ++j) {
-                        nb[j] = atomicExch((unsigned long long*)&rec[Lo::NXT + j], 0ull) & act[j];
-                        any |= nb[j];
-                    }
+            for (int r = 0; r < WW; ++r) {
+                nb[r] = old[r] = 0;
+                if (wr[r] >= 0) {
+                    uint64_t* rec = node_rec<WW>(P, wr[r]) + jw;
+                    old[r] = rec[0];
+                    if constexpr (kFresh) nb[r] = rec[WW];
+                    else nb[r] = __hip_atomic_load(&rec[WW], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
-                if (any) {
-                    uint64_t* cur = node_cur<WW, D>(P, w);
-                    uint64_t old_any = 0;
+            }
+            bool pn[WW], po[WW];
 #pragma unroll
-                    for (int j = 0; j < WW; ++j) {
-                        const uint64_t old = rec[j];
-                        old_any |= old;
-                        rec[j] = old | nb[j];
-                        cur[j] = nb[j];
-                    }
-                    keep = true;
-                    fresh = old_any == 0ull;
-                    if constexpr (D) my_arcs += degs[w];
-                    else my_arcs += (uint32_t)(rec[Lo::META] >> 32);
-                    if (seen_filter) filter_set(seen_filter, w);
+            for (int r = 0; r < WW; ++r) {
+                nb[r] &= actj;
+                pn[r] = nb[r] != 0ull;
+                po[r] = old[r] != 0ull;
+                if (wr[r] >= 0) {
+                    uint64_t* rec = node_rec<WW>(P, wr[r]) + jw;
+                    rec[WW] = 0;
+                    if (pn[r]) rec[0] = old[r] | nb[r];
+                    node_cur<WW>(P, wr[r])[jw] = nb[r];
                 }
+            }
+            keep = group_any<WW>(pn);
+            const bool before = group_any<WW>(po);  // every lane takes part
+            fresh = keep && !before;
+            if (keep) {
+                my_arcs += degs[w];
+                if (seen_filter) filter_set(seen_filter, w);
             }
         }
         if (any_live) {
@@ -715,6 +781,7 @@ struct CutLds {
     uint16_t ord[N];
     uint32_t nc, nd, nt;
     int32_t cnt;
+    uint32_t fin[N / 64];  // whether a source of the word is complete
     unsigned long long mv;
     ThRec kth;
     uint32_t kset;
@@ -824,7 +891,7 @@ __device__ uint32_t cut_step(const TopKDev& T, SrcState* S, int W, uint32_t d, b
                              const unsigned long long* ct, bool global_counts, bool locked, QStats* st,
                              uint64_t* active, CutLds<64 * WW>& CL, const DeferList* D = nullptr) {
     uint32_t* s_live = &CL.live;
-    const int tid = threadIdx.x;
+    const int tid = phase_tid();
     // arcs of Gamma_d that the footnote bound leaves out of ~gamma_{d+1}: one
     // edge per node back to Gamma_{d-1} (still scanned, so still in m_vis)
     uint64_t back = 0;
@@ -863,7 +930,12 @@ __device__ uint32_t cut_step(const TopKDev& T, SrcState* S, int W, uint32_t d, b
         CL.have_th = load_threshold(T, &th) ? 1u : 0u;
         CL.th = th;
     }
-    if (__syncthreads_or(fl ? 1 : 0)) {
+    const unsigned long long fin = __ballot(fl);
+    if (tid < W && lane_id() == 0) CL.fin[tid / 64] = fin != 0ull;
+    __syncthreads();
+    uint32_t any_fin = 0;
+    for (int i = 0; i * 64 < W; ++i) any_fin |= CL.fin[i];
+    if (uni32(any_fin)) {
         bool mine = false;
         uint32_t at = 0, r = 1;
         uint64_t A = 0, F = 1, f = 0;
@@ -1004,10 +1076,10 @@ __device__ uint32_t trial_cut(const TopKDev& T, SrcState* S, int W, uint32_t d, 
 
 // Initialise the W sources of batch b: the frontier list F and the reset
 // list hold the sources themselves, each with its one-hot mask.
-template <int WW, bool D = false>
+template <int WW>
 __device__ void init_batch(const DevGraph& G, const int32_t* order, int32_t n, uint32_t b, int W, const SlotPtrs& P,
                            SrcState* S, uint32_t* flen_lds, unsigned long long* arcs_lds) {
-    const int tid = threadIdx.x;
+    const int tid = phase_tid();
     if (tid == 0) {
         *flen_lds = 0;
         *arcs_lds = 0;
@@ -1029,7 +1101,7 @@ __device__ void init_batch(const DevGraph& G, const int32_t* order, int32_t n, u
             s.status = s.x0 <= 1 ? S_TRIVIAL : S_LIVE;
             if (s.status == S_LIVE) {
                 const uint64_t bit = 1ull << (tid & 63);
-                uint64_t *rec = node_rec<WW, D>(P, v), *cur = node_cur<WW, D>(P, v);
+                uint64_t *rec = node_rec<WW>(P, v), *cur = node_cur<WW>(P, v);
 #pragma unroll
                 for (int j = 0; j < WW; ++j) {
                     const uint64_t x = (j == (tid >> 6)) ? bit : 0ull;
@@ -1053,16 +1125,6 @@ __device__ void init_batch(const DevGraph& G, const int32_t* order, int32_t n, u
     __syncthreads();
 }
 
-// Write the out-degree into the meta word of every node record of `slots`
-// consecutive slots (the rest of a record is zero at rest).
-template <int WW>
-__global__ void k_slot_init(const uint32_t* __restrict__ deg, int32_t n, uint64_t* ns, int slots) {
-    using Lo = Layout<WW>;
-    const size_t total = (size_t)n * slots;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x)
-        ns[i * Lo::SW + Lo::META] = (uint64_t)deg[i % (size_t)n] << 32;
-}
-
 // ----------------------------------------------- level-synchronous kernels
 //
 // A batch on a slot of its own (split layout).  The narrow kernel runs every
@@ -1082,8 +1144,10 @@ constexpr int kLvBlk = 1024;  // threads per workgroup: few, large workgroups, s
 __device__ inline uint32_t next_pull(uint32_t pull, unsigned long long fa, uint32_t flen, const DevGraph& G,
                                      const LevelParams& lp) {
     if (lp.can_pull) {
-        if (!pull && lp.pull_alpha > 0.f && (double)fa > (double)G.m / lp.pull_alpha) return 1;
-        if (pull && (double)flen < (double)G.n / lp.pull_beta) return 0;
+        uint64_t n = (uint64_t)G.n, m = (uint64_t)G.m;
+        asm volatile("" : "+s"(n), "+s"(m));  // the quotients are not kept across the levels
+        if (!pull && lp.pull_alpha > 0.f && (double)fa > (double)(int64_t)m / lp.pull_alpha) return 1;
+        if (pull && (double)flen < (double)(int64_t)n / lp.pull_beta) return 0;
     }
     return pull;
 }
@@ -1092,7 +1156,7 @@ template <int WW>
 __device__ void plain_init_body(const DevGraph& G, const int32_t* order, int32_t count, uint32_t b, int W,
                                 const SlotPtrs& P, SrcState* S, Ctl* C, const TopKDev& T, QStats* st, CutLds<64 * WW>& CL,
                                 uint32_t& s_flen, unsigned long long& s_arcs, uint64_t* s_act) {
-    init_batch<WW, true>(G, order, count, b, W, P, S, &s_flen, &s_arcs);
+    init_batch<WW>(G, order, count, b, W, P, S, &s_flen, &s_arcs);
     const uint32_t live = cut_step<WW>(T, S, W, 0, false, nullptr, nullptr, false, false, st, s_act, CL);
     if (threadIdx.x == 0) {
         C->stamp = C->stamp + 1;
@@ -1203,7 +1267,7 @@ __device__ void plain_expand_body(const DevGraph& G, const SlotPtrs& P, Ctl* C, 
         const unsigned long long e0 = (unsigned long long)X.L.chunk * per;
         __syncthreads();
         if (e0 >= flen) break;
-        expand_entries<WW, kLvBlk, 2, true>(G, P, P.qa, (uint32_t)e0, min(flen, (uint32_t)e0 + per), X.act, P.qb,
+        expand_entries<WW, kLvBlk, 2>(G, P, P.qa, (uint32_t)e0, min(flen, (uint32_t)e0 + per), X.act, P.qb,
                                               &C->nlen, stamp, X.L, &X.arcs, &X.ent, &stg);
     }
     block_flush<kLvBlk>(stg, P.qb, &C->nlen, X.sh);
@@ -1252,7 +1316,7 @@ __device__ void plain_count_body(const DevGraph& G, const SlotPtrs& P, SrcState*
         for (int j = 0; j < WW; ++j) nb[j] = 0;
         if (i < len) {
             const int32_t w = P.qb[i];
-            const uint64_t* rec = node_rec<WW, true>(P, w);
+            const uint64_t* rec = node_rec<WW>(P, w);
 #pragma unroll
             for (int j = 0; j < WW; ++j) nb[j] = rec[WW + j];
             deg = G.deg[w];
@@ -1288,6 +1352,7 @@ __global__ __launch_bounds__(kLvBlk) void k_plain_count(DevGraph G, LvSlots L, T
 // arcs dealt flat over its lanes and collected in LDS, 117-271 us
 // now.)
 constexpr int kPullAhead = 8;
+constexpr int kBlockAhead = 4;  // in the persistent kernels, whose other state leaves fewer registers
 
 // OR over the lanes that hold the same word (lane % WW), in every lane.
 template <int WW>
@@ -1299,24 +1364,24 @@ __device__ inline uint64_t group_or(uint64_t x) {
 
 // The arcs e0, e0 + step, ... below e1 of this lane's part of a list: the
 // bits of `unv` found among the neighbours' word j.  Returns the arcs read.
-template <int WW>
+template <int WW, int kAhead>
 __device__ __forceinline__ uint32_t pull_walk(const DevGraph& G, const uint64_t* cur_j, int64_t e0, int32_t e1,
                                               int32_t step, uint64_t unv, uint64_t& acc) {
     uint32_t read = 0;
     int64_t e = e0;
     while (e < e1 && acc != unv) {
-        int32_t u[kPullAhead];
+        int32_t u[kAhead];
 #pragma unroll
-        for (int q = 0; q < kPullAhead; ++q) {
+        for (int q = 0; q < kAhead; ++q) {
             const int64_t x = e + (int64_t)q * step;
             u[q] = G.icol[x < e1 ? x : e];  // past the end: the first arc again
         }
         uint64_t c = 0;
 #pragma unroll
-        for (int q = 0; q < kPullAhead; ++q) c |= cur_j[(size_t)u[q] * WW];
+        for (int q = 0; q < kAhead; ++q) c |= cur_j[(size_t)u[q] * WW];
         acc |= c & unv;
-        read += kPullAhead;
-        e += (int64_t)kPullAhead * step;
+        read += kAhead;
+        e += (int64_t)kAhead * step;
     }
     return read;
 }
@@ -1330,7 +1395,7 @@ struct PullWaveLds {
 // lane % WW); appends the nodes that found
 // something to N (through stg to a global counter, or without one to a counter
 // in LDS).  Converged wave.
-template <int WW>
+template <int WW, int kAhead>
 __device__ __forceinline__ void pull_nodes(const DevGraph& G, const SlotPtrs& P, uint64_t actj, int64_t base,
                                            PullWaveLds<WW>& L, uint32_t* cg, unsigned long long* ct, WaveStage* stg,
                                            uint32_t* nlen, unsigned long long& scanned) {
@@ -1338,17 +1403,17 @@ __device__ __forceinline__ void pull_nodes(const DevGraph& G, const SlotPtrs& P,
     const int j = lane % WW;
     constexpr int kPer = 64 / WW;  // nodes per round
     uint64_t any = 0;
-#pragma unroll
+#pragma unroll 1
     for (int r = 0; r < WW; ++r) {
         const int64_t w = base + r * kPer + lane / WW;
         uint64_t acc = 0;
         uint32_t read = 0;
         if (w < G.n) {
-            uint64_t* rec = node_rec<WW, true>(P, (int32_t)w);
+            uint64_t* rec = node_rec<WW>(P, (int32_t)w);
             const uint64_t unv = actj & ~rec[j];
             const int32_t e0 = G.irp[w], e1 = G.irp[w + 1];
             if (unv && e1 - e0 <= kPullWave) {  // longer lists: pull_heavy
-                read = min(pull_walk<WW>(G, P.cur + j, e0, e1, 1, unv, acc), (uint32_t)(e1 - e0));
+                read = min(pull_walk<WW, kAhead>(G, P.cur + j, e0, e1, 1, unv, acc), (uint32_t)(e1 - e0));
                 if (acc) rec[WW + j] = acc;
             }
         }
@@ -1375,21 +1440,21 @@ __device__ __forceinline__ void pull_nodes(const DevGraph& G, const SlotPtrs& P,
 
 // One node with more than kPullWave in-arcs, its list read by the whole wave;
 // returns in lane 0 whether it found something.  Converged wave.
-template <int WW>
+template <int WW, int kAhead>
 __device__ __forceinline__ bool pull_heavy(const DevGraph& G, const SlotPtrs& P, uint64_t actj, int32_t w,
                                            uint32_t* cg, unsigned long long* ct, unsigned long long& scanned) {
     const int lane = (int)lane_id();
     const int j = lane % WW;
     constexpr int kGroups = 64 / WW;
-    uint64_t* rec = node_rec<WW, true>(P, w);
+    uint64_t* rec = node_rec<WW>(P, w);
     const uint64_t unv = actj & ~rec[j];
     const int32_t h0 = G.irp[w], h1 = G.irp[w + 1];
     uint64_t acc = 0;
-    for (int64_t eb = h0; eb < h1; eb += kGroups * kPullAhead) {
+    for (int64_t eb = h0; eb < h1; eb += kGroups * kAhead) {
         if (__ballot(acc != unv) == 0ull) break;
-        const int32_t end = (int32_t)min((int64_t)h1, eb + kGroups * kPullAhead);
+        const int32_t end = (int32_t)min((int64_t)h1, eb + kGroups * kAhead);
         uint64_t part = acc;
-        (void)pull_walk<WW>(G, P.cur + j, eb + lane / WW, end, kGroups, unv, part);
+        (void)pull_walk<WW, kAhead>(G, P.cur + j, eb + lane / WW, end, kGroups, unv, part);
         acc = group_or<WW>(part);
         if (lane == 0) scanned += (unsigned long long)(end - eb);
     }
@@ -1432,12 +1497,12 @@ __device__ void plain_pull_body(const DevGraph& G, const SlotPtrs& P, SrcState* 
     const uint32_t nheavy = *G.nheavy, waves = gridDim.x * (kLvBlk / 64);
     for (uint32_t h = (uint32_t)(tid >> 6) * gridDim.x + blockIdx.x; h < nheavy; h += waves) {
         const int32_t w = G.heavy[h];
-        stg.push(pull_heavy<WW>(G, P, actj, w, X.c.cg, X.c.ct, scanned), w, P.qb, &C->nlen);
+        stg.push(pull_heavy<WW, kPullAhead>(G, P, actj, w, X.c.cg, X.c.ct, scanned), w, P.qb, &C->nlen);
     }
     // waves take 64 nodes at a time, neighbouring waves neighbouring nodes
     const int64_t stride = (int64_t)gridDim.x * kLvBlk;
     for (int64_t base = (int64_t)blockIdx.x * kLvBlk + (tid & ~63); base < G.n; base += stride)
-        pull_nodes<WW>(G, P, actj, base, Lw, X.c.cg, X.c.ct, &stg, &C->nlen, scanned);
+        pull_nodes<WW, kPullAhead>(G, P, actj, base, Lw, X.c.cg, X.c.ct, &stg, &C->nlen, scanned);
     if (tid == 0) X.scanned = 0;
     block_flush<kLvBlk>(stg, P.qb, &C->nlen, X.sh);
     for (int o = 32; o > 0; o >>= 1) scanned += __shfl_xor(scanned, o);
@@ -1463,7 +1528,7 @@ __global__ __launch_bounds__(kBlk) void k_plain_clearcur(LvSlots L, int gated) {
     const size_t i = L.id[blockIdx.y];
     const Ctl* C = L.C + i;
     if (gated && C->ran == 0) return;
-    clear_cur<WW, true>(slot_ptrs<WW>(L, i), slot_ptrs<WW>(L, i).qa, C->flen, blockIdx.x * kBlk, gridDim.x * kBlk);
+    clear_cur<WW>(slot_ptrs<WW>(L, i), slot_ptrs<WW>(L, i).qa, C->flen, blockIdx.x * kBlk, gridDim.x * kBlk);
 }
 
 // Materialise the level (or only reset nxt when nothing is live); the last
@@ -1487,8 +1552,8 @@ __device__ void plain_build_body(const DevGraph& G, const SlotPtrs& P, Ctl* C, c
     if (tid == 0) X.arcs = 0;
     __syncthreads();
     WaveStage sf{X.stage[tid >> 6][0], 0}, sc{X.stage[tid >> 6][1], 0};
-    build_level<WW, true, true>(P, P.qb, nlen, blockIdx.x * kLvBlk, gridDim.x * kLvBlk, act, any_live, P.qa,
-                                &C->done_blocks, &C->clen, &X.arcs, nullptr, G.deg, &sf, &sc);
+    build_level<WW, true>(P, P.qb, nlen, blockIdx.x * kLvBlk, gridDim.x * kLvBlk, act, any_live, P.qa, &C->done_blocks,
+                          &C->clen, &X.arcs, G.deg, nullptr, &sf, &sc);
     block_flush<kLvBlk>(sf, P.qa, &C->done_blocks, X.sh);
     block_flush<kLvBlk>(sc, P.clr, &C->clen, X.sh);
     if (tid == 0 && X.arcs) atomicAdd(&C->acc_arcs, X.arcs);
@@ -1525,14 +1590,11 @@ __global__ __launch_bounds__(kLvBlk) void k_plain_build(DevGraph G, LvSlots L, L
 // at level 0).
 template <int WW>
 __device__ void plain_clear_body(const SlotPtrs& P, uint32_t nc, uint32_t first, uint32_t stride) {
-    for (uint32_t i = first + threadIdx.x; i < nc; i += stride) {
-        const int32_t w = P.clr[i];
-        uint64_t *rec = node_rec<WW, true>(P, w), *cur = node_cur<WW, true>(P, w);
-#pragma unroll
-        for (int j = 0; j < WW; ++j) {
-            rec[j] = 0;
-            cur[j] = 0;
-        }
+    const uint64_t end = (uint64_t)nc * WW;  // a word per thread
+    for (uint64_t i = (uint64_t)first + phase_tid(); i < end; i += stride) {
+        const int32_t w = P.clr[i / WW];
+        node_rec<WW>(P, w)[i % WW] = 0;
+        node_cur<WW>(P, w)[i % WW] = 0;
     }
 }
 
@@ -1548,6 +1610,7 @@ __global__ __launch_bounds__(kBlk) void k_plain_clear(LvSlots L) {
 template <int WW, int B>
 struct RecLds {
     LdsExpand<WW, B> LE;
+    PullWaveLds<WW> X[B / 64];
     SrcState S[kBlk];
     uint32_t cg[kBlk];
     unsigned long long ct[kBlk];
@@ -1556,6 +1619,27 @@ struct RecLds {
     uint64_t act[4];
     unsigned long long arcs, narcs, ent;  // narcs, ent: arcs and frontier entries expanded
 };
+
+// A bottom-up step of one workgroup: the reached nodes to P.qb (counter
+// R.nlen), the level's counters to R.cg and R.ct, the arcs read to R.narcs.
+// Ends with a barrier after which nxt may be taken.  Whole workgroup.
+template <int WW, int B, int kAhead>
+__device__ __forceinline__ void block_pull(const DevGraph& G, const SlotPtrs& P, RecLds<WW, B>& R) {
+    const uint32_t wave = uni32(threadIdx.x >> 6);
+    const uint64_t actj = R.act[threadIdx.x % WW];
+    const uint32_t nheavy = *G.nheavy;
+    unsigned long long scanned = 0;
+    for (uint32_t h = wave; h < nheavy; h += B / 64) {
+        const int32_t w = G.heavy[h];
+        append_if(pull_heavy<WW, kAhead>(G, P, actj, w, R.cg, R.ct, scanned), w, P.qb, &R.nlen);
+    }
+    for (int64_t base = (int64_t)wave * 64; base < G.n; base += B)
+        pull_nodes<WW, kAhead>(G, P, actj, base, R.X[wave], R.cg, R.ct, nullptr, &R.nlen, scanned);
+    for (int o = 32; o > 0; o >>= 1) scanned += __shfl_xor(scanned, o);
+    if ((threadIdx.x & 63) == 0 && scanned) atomicAdd(&R.narcs, scanned);
+    wait_stores();  // other waves read nxt next
+    __syncthreads();
+}
 
 // Levels that one workgroup runs: up to `narrow` frontier arcs (push), or, on
 // a graph of at most that many nodes and arcs, any level.  A push level of
@@ -1575,7 +1659,6 @@ __global__ __launch_bounds__(kBatchBlk) void k_plain_run(DevGraph G, const int32
                                                         LevelParams lp, unsigned long long narrow, LvReport* report) {
     constexpr int B = kBatchBlk;
     __shared__ RecLds<WW, B> R;
-    __shared__ PullWaveLds<WW> X[B / 64];
     __shared__ uint32_t s_b;
     const int tid = threadIdx.x;
     const size_t slot = L.id[blockIdx.x];
@@ -1593,7 +1676,7 @@ __global__ __launch_bounds__(kBatchBlk) void k_plain_run(DevGraph G, const int32
         R.narcs = 0;
         R.ent = 0;
     }
-    unsigned long long levels = 0, pulls = 0, disc = 0, batches = 0, scanned = 0;
+    unsigned long long levels = 0, pulls = 0, disc = 0, batches = 0;
     __syncthreads();
     for (;;) {
         if (!in_batch) {
@@ -1606,7 +1689,7 @@ __global__ __launch_bounds__(kBatchBlk) void k_plain_run(DevGraph G, const int32
                 break;
             }
             ++batches;
-            init_batch<WW, true>(G, order, count, b, W, P, R.S, &R.flen, &R.arcs);
+            init_batch<WW>(G, order, count, b, W, P, R.S, &R.flen, &R.arcs);
             live = uni32(cut_step<WW>(T, R.S, W, 0, false, nullptr, nullptr, false, true, st, R.act, R.CL));
             flen = clen = uni32(R.flen);
             fa = uni64(R.arcs);
@@ -1641,24 +1724,15 @@ __global__ __launch_bounds__(kBatchBlk) void k_plain_run(DevGraph G, const int32
         }
         __syncthreads();
         if (pull) {
-            const uint64_t actj = R.act[tid % WW];
-            const uint32_t nheavy = *G.nheavy;
-            for (uint32_t h = (uint32_t)tid >> 6; h < nheavy; h += B / 64) {
-                const int32_t w = G.heavy[h];
-                append_if(pull_heavy<WW>(G, P, actj, w, R.cg, R.ct, scanned), w, P.qb, &R.nlen);
-            }
-            for (int64_t base = tid & ~63; base < G.n; base += B)
-                pull_nodes<WW>(G, P, actj, base, X[tid >> 6], R.cg, R.ct, nullptr, &R.nlen, scanned);
-            wait_stores();  // nxt is taken with exchanges by other waves next
-            __syncthreads();
-            clear_cur<WW, true>(P, P.qa, flen, 0, B);
+            block_pull<WW, B, kPullAhead>(G, P, R);
+            clear_cur<WW>(P, P.qa, flen, 0, B);
             ++pulls;
         } else {
             for (uint32_t e0 = 0; e0 < flen; e0 += B)
-                expand_entries<WW, B, 1, true>(G, P, P.qa, e0, min(flen, e0 + B), R.act, P.qb, &R.nlen, stamp, R.LE,
+                expand_entries<WW, B, 1>(G, P, P.qa, e0, min(flen, e0 + B), R.act, P.qb, &R.nlen, stamp, R.LE,
                                                &R.narcs, &R.ent);
             __syncthreads();
-            count_level<WW, B, true>(P, P.qb, uni32(R.nlen), R.cg, R.ct, G.deg);
+            count_level<WW, B>(P, P.qb, uni32(R.nlen), R.cg, R.ct, G.deg);
         }
         __syncthreads();
         const uint32_t nlen = uni32(R.nlen);
@@ -1666,7 +1740,7 @@ __global__ __launch_bounds__(kBatchBlk) void k_plain_run(DevGraph G, const int32
         ++levels;
         ++d;
         live = uni32(cut_step<WW>(T, R.S, W, d, true, R.cg, R.ct, false, true, st, R.act, R.CL));
-        build_level<WW, true>(P, P.qb, nlen, 0, B, R.act, live != 0, P.qa, &R.flen, &R.clen, &R.arcs, nullptr, G.deg);
+        build_level<WW>(P, P.qb, nlen, 0, B, R.act, live != 0, P.qa, &R.flen, &R.clen, &R.arcs, G.deg);
         __syncthreads();
         flen = live ? uni32(R.flen) : 0;
         clen = uni32(R.clen);
@@ -1677,8 +1751,6 @@ __global__ __launch_bounds__(kBatchBlk) void k_plain_run(DevGraph G, const int32
     }
     __syncthreads();
     if ((state == LV_PUSH || state == LV_PULL) && tid < W) Sg[tid] = R.S[tid];
-    for (int o = 32; o > 0; o >>= 1) scanned += __shfl_xor(scanned, o);
-    if ((tid & 63) == 0 && scanned) atomicAdd(&st->node_arcs, scanned);
     if (tid == 0) {
         C->state = state;
         C->d = d;
@@ -1766,7 +1838,7 @@ __global__ __launch_bounds__(kLvBlk) void k_plain_coop(DevGraph G, const int32_t
                 bad = true;
                 break;
             }
-            clear_cur<WW, true>(P, P.qa, ldu32(&C->flen), blockIdx.x * kLvBlk, gridDim.x * kLvBlk);
+            clear_cur<WW>(P, P.qa, ldu32(&C->flen), blockIdx.x * kLvBlk, gridDim.x * kLvBlk);
             grid_barrier(grid);
             plain_build_body<WW>(G, P, C, lp, X.build);
             grid_barrier(grid);
@@ -1784,29 +1856,29 @@ __global__ __launch_bounds__(kLvBlk) void k_plain_coop(DevGraph G, const int32_t
 
 // Per-workgroup counters of a record-based persistent kernel.
 struct RecCounters {
-    unsigned long long levels = 0, batches = 0, disc = 0;
+    unsigned long long levels = 0, pulls = 0, batches = 0, disc = 0;
     unsigned long long ticks[5] = {0, 0, 0, 0, 0};  // set-up, expand, cut, build, reset (100 MHz)
 };
 
-// One whole batch b (sources order[b W .. b W + W)) of graph G on the node
-// records of slot P: level 0, then per level the expansion over the frontier,
-// the counters of the level reached, the cut step and the build of the live
-// bits, until no source is live; then the marks of every node the batch
-// reached are reset, so the slot is all zero again.  degs: out-degrees from
-// the graph (records shared by several graphs) or null (from the records'
-// meta words).  Block-uniform call.
+// One whole batch b (sources order[b W .. b W + W)) of graph G on slot P:
+// level 0, then per level the expansion over the frontier (or, once it holds
+// more than m / pull_alpha arcs, a bottom-up step over all nodes), the counters
+// of the level reached, the cut step and the build of the live bits, until no
+// source is live; then the marks of every node the batch reached are reset, so
+// the slot is all zero again.  (Wide levels bottom up took a collaboration
+// graph of 500,000 nodes at W = 256 from 339 to 218 ms, and 24 uneven graphs
+// of up to 30,000 nodes at W = 64 from 57 to 18 ms.)  Block-uniform call.
 template <int WW, int B>
 __device__ void record_batch(const DevGraph& G, const int32_t* order, int W, uint32_t b, const SlotPtrs& P,
-                             const TopKDev& T, QStats* st, const DeferList* D, const uint32_t* degs,
+                             const TopKDev& T, QStats* st, const DeferList* D, const LevelParams& lp,
                              RecLds<WW, B>& R, uint32_t& stamp, RecCounters& K) {
-    using Lo = Layout<WW>;
     const int tid = threadIdx.x;
     ++K.batches;
     const uint64_t tb = __builtin_amdgcn_s_memrealtime();
     init_batch<WW>(G, order, G.n, b, W, P, R.S, &R.flen, &R.arcs);
     if (tid == 0) R.clen = R.flen;
-    uint32_t live = cut_step<WW>(T, R.S, W, 0, false, nullptr, nullptr, false, true, st, R.act, R.CL, D);
-    uint32_t flen = R.flen, d = 0;
+    uint32_t live = uni32(cut_step<WW>(T, R.S, W, 0, false, nullptr, nullptr, false, true, st, R.act, R.CL, D));
+    uint32_t flen = uni32(R.flen), d = 0, pull = 0;
     uint64_t tp = __builtin_amdgcn_s_memrealtime();
     K.ticks[0] += tp - tb;
     while (live) {
@@ -1817,43 +1889,43 @@ __device__ void record_batch(const DevGraph& G, const int32_t* order, int W, uin
         }
         if (tid == 0) R.nlen = 0;
         __syncthreads();
-        for (uint32_t e0 = 0; e0 < flen; e0 += B)
-            expand_entries<WW, B, 1>(G, P, P.qa, e0, min(flen, e0 + B), R.act, P.qb, &R.nlen, stamp, R.LE, &R.narcs,
-                                     &R.ent);
+        if (pull) {
+            ++K.pulls;
+            block_pull<WW, B, kBlockAhead>(G, P, R);
+            clear_cur<WW>(P, P.qa, flen, 0, B);
+        } else {
+            for (uint32_t e0 = 0; e0 < flen; e0 += B)
+                expand_entries<WW, B, 1>(G, P, P.qa, e0, min(flen, e0 + B), R.act, P.qb, &R.nlen, stamp, R.LE,
+                                         &R.narcs, &R.ent);
+            __syncthreads();
+            count_level<WW, B>(P, P.qb, uni32(R.nlen), R.cg, R.ct, G.deg);
+        }
         __syncthreads();
-        const uint32_t nlen = R.nlen;
-        count_level<WW, B>(P, P.qb, nlen, R.cg, R.ct, degs);
-        __syncthreads();
+        const uint32_t nlen = uni32(R.nlen);
         K.disc += nlen;
         uint64_t tq = __builtin_amdgcn_s_memrealtime();
         K.ticks[1] += tq - tp;
         tp = tq;
         ++d;
         ++K.levels;
-        live = cut_step<WW>(T, R.S, W, d, true, R.cg, R.ct, false, true, st, R.act, R.CL, D);
+        if (tid == 0) {
+            R.flen = 0;
+            R.arcs = 0;
+        }
+        live = uni32(cut_step<WW>(T, R.S, W, d, true, R.cg, R.ct, false, true, st, R.act, R.CL, D));
         tq = __builtin_amdgcn_s_memrealtime();
         K.ticks[2] += tq - tp;
         tp = tq;
-        clear_cur<WW>(P, P.qa, flen, 0, B);
-        if (tid == 0) R.flen = 0;
+        build_level<WW>(P, P.qb, nlen, 0, B, R.act, live != 0, P.qa, &R.flen, &R.clen, &R.arcs, G.deg);
         __syncthreads();
-        build_level<WW>(P, P.qb, nlen, 0, B, R.act, live != 0, P.qa, &R.flen, &R.clen, &R.arcs);
-        __syncthreads();
-        flen = R.flen;
+        flen = uni32(R.flen);
+        pull = next_pull(pull, uni64(R.arcs), flen, G, lp);
         tq = __builtin_amdgcn_s_memrealtime();
         K.ticks[3] += tq - tp;
         tp = tq;
     }
     // reset seen and cur of every node this batch reached
-    const uint32_t nc = R.clen;
-    for (uint32_t i = tid; i < nc; i += B) {
-        uint64_t* rec = &P.ns[(size_t)P.clr[i] * Lo::SW];
-#pragma unroll
-        for (int j = 0; j < WW; ++j) {
-            rec[j] = 0;
-            rec[Lo::CUR + j] = 0;
-        }
-    }
+    plain_clear_body<WW>(P, uni32(R.clen), 0, B);
     __syncthreads();
     K.ticks[4] += __builtin_amdgcn_s_memrealtime() - tp;
 }
@@ -1865,19 +1937,15 @@ __device__ void record_batch(const DevGraph& G, const int32_t* order, int W, uin
 template <int WW, int B>
 __global__ __launch_bounds__(B) void k_batched(DevGraph G, const int32_t* order, int W, uint32_t nbatches,
                                                  uint32_t* next_batch, uint32_t chunk, SlotPtrs base,
-                                                 uint32_t* slot_stamp, TopKDev T, QStats* st, DeferList D) {
-    using Lo = Layout<WW>;
+                                                 uint32_t* slot_stamp, TopKDev T, QStats* st, DeferList D,
+                                                 LevelParams lp) {
     __shared__ RecLds<WW, B> R;
     __shared__ uint32_t s_b, s_next, s_end;
     const int tid = threadIdx.x;
     const size_t slot = blockIdx.x;
-    SlotPtrs P{};
-    P.ns = base.ns + slot * (size_t)G.n * Lo::SW;
-    P.qa = base.qa + slot * (size_t)G.n;
-    P.qb = base.qb + slot * (size_t)G.n;
-    P.clr = base.clr + slot * (size_t)G.n;
+    const SlotPtrs P = slot_at<WW>(base, (size_t)G.n, slot);
     // first-touch stamps keep growing across queries (stamps are never cleared)
-    uint32_t stamp = slot_stamp[slot];
+    uint32_t stamp = uni32(slot_stamp[slot]);
     RecCounters K;
     if (tid == 0) {
         R.narcs = 0;
@@ -1898,10 +1966,11 @@ __global__ __launch_bounds__(B) void k_batched(DevGraph G, const int32_t* order,
         const uint32_t b = s_b;
         __syncthreads();
         if (b >= nbatches) break;
-        record_batch<WW, B>(G, order, W, b, P, T, st, &D, nullptr, R, stamp, K);
+        record_batch<WW, B>(G, order, W, b, P, T, st, &D, lp, R, stamp, K);
     }
     if (tid == 0) {
         atomicAdd(&st->levels, K.levels);
+        if (K.pulls) atomicAdd(&st->pull_levels, K.pulls);
         atomicAdd(&st->batches, K.batches);
         atomicAdd(&st->discovered, K.disc);
         if (R.narcs) atomicAdd(&st->node_arcs, R.narcs);
@@ -2037,6 +2106,8 @@ __device__ inline DevGraph uni_graph(const DevGraph& g) {
     o.x0 = uni_ptr(g.x0);
     o.x1 = uni_ptr(g.x1);
     o.orig = uni_ptr(g.orig);
+    o.heavy = uni_ptr(g.heavy);
+    o.nheavy = uni_ptr(g.nheavy);
     return o;
 }
 __device__ inline TopKDev uni_topk(const TopKDev& t) {
@@ -2064,19 +2135,14 @@ __device__ inline void batch_ended(const JobLaunch& L) {
 
 template <int WW, int B>
 __global__ __launch_bounds__(B) void k_jobs(JobLaunch L, SlotPtrs base, uint32_t* slot_stamp) {
-    using Lo = Layout<WW>;
     __shared__ RecLds<WW, B> R;
     __shared__ JobDesc J;
     __shared__ unsigned long long s_c;
     __shared__ int32_t s_slot;
     const int tid = threadIdx.x;
     const size_t slot = blockIdx.x;
-    SlotPtrs P{};
-    P.ns = base.ns + slot * (size_t)L.ncap * Lo::SW;
-    P.qa = base.qa + slot * (size_t)L.ncap;
-    P.qb = base.qb + slot * (size_t)L.ncap;
-    P.clr = base.clr + slot * (size_t)L.ncap;
-    uint32_t stamp = slot_stamp[slot];
+    const SlotPtrs P = slot_at<WW>(base, (size_t)L.ncap, slot);
+    uint32_t stamp = uni32(slot_stamp[slot]);
     unsigned long long jstart = ~0ull, jend = 0;  // range of the descriptor held in J
     for (;;) {
         if (tid == 0) {
@@ -2183,9 +2249,10 @@ __global__ __launch_bounds__(B) void k_jobs(JobLaunch L, SlotPtrs base, uint32_t
         }
         __syncthreads();
         RecCounters K;
-        record_batch<WW, B>(G, order, L.W, b, P, T, st, nullptr, G.deg, R, stamp, K);
+        record_batch<WW, B>(G, order, L.W, b, P, T, st, nullptr, LevelParams{3.f, 24.f, 1}, R, stamp, K);
         if (tid == 0) {
             atomicAdd(&st->levels, K.levels);
+            if (K.pulls) atomicAdd(&st->pull_levels, K.pulls);
             atomicAdd(&st->batches, K.batches);
             atomicAdd(&st->discovered, K.disc);
             if (R.narcs) atomicAdd(&st->node_arcs, R.narcs);
@@ -2394,7 +2461,6 @@ __device__ uint32_t tab_prologue(const DevGraph& G, const LdsTab& L, const int32
 __device__ uint32_t rec_prologue(const DevGraph& G, const SlotPtrs& P, const int32_t* F, uint32_t e0, uint32_t e1,
                                  uint64_t act, PassScratch& X, unsigned long long* arcs,
                                  unsigned long long* entries) {
-    using Lo = Layout<1>;
     constexpr int B = kLdsBlk;
     const int tid = threadIdx.x;
     const uint32_t e = e0 + (uint32_t)tid;
@@ -2403,7 +2469,7 @@ __device__ uint32_t rec_prologue(const DevGraph& G, const SlotPtrs& P, const int
     uint64_t m = 0;
     if (e < e1) {
         const int32_t u = F[e];
-        m = P.ns[(size_t)u * Lo::SW + Lo::CUR] & act;
+        m = *node_cur<1>(P, u) & act;
         if (m) {
             beg = G.rp[u];
             deg = (uint32_t)(G.rp[u + 1] - beg);
@@ -2470,7 +2536,7 @@ __device__ void tab_arcs(const DevGraph& G, LdsTab& L, const uint64_t* ns, uint3
         for (int u = 0; u < kInflight; ++u) {
             if (P > 1 && m[u] && hpart(w[u], P) != p) m[u] = 0;
             sv[u] = 0;
-            if (kRec && m[u] && filter_maybe(seen_filter, w[u])) sv[u] = ns[(size_t)w[u] * Layout<1>::SW];
+            if (kRec && m[u] && filter_maybe(seen_filter, w[u])) sv[u] = ns[(size_t)w[u] * 2];
         }
 #pragma unroll
         for (int u = 0; u < kInflight; ++u) {
@@ -2532,7 +2598,7 @@ __device__ void tab_cheap_arcs(const DevGraph& G, const LdsTab& L, const uint64_
             uint64_t nb = 0;
             if (m[u]) {
                 uint64_t sv;
-                if (kRec) sv = filter_maybe(seen_filter, w[u]) ? ns[(size_t)w[u] * Layout<1>::SW] : 0ull;
+                if (kRec) sv = filter_maybe(seen_filter, w[u]) ? ns[(size_t)w[u] * 2] : 0ull;
                 else sv = tab_seen(L, w[u]);
                 nb = m[u] & ~sv;
             }
@@ -2578,7 +2644,6 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                                                         TopKDev T, QStats* st, DeferList D, int force_spill,
                                                         int no_trial) {
     static_assert(WW == 1, "LDS-resident batches hold 64 sources");
-    using Lo = Layout<1>;
     constexpr int B = kLdsBlk;
     __shared__ LdsTab L;
     __shared__ union {
@@ -2596,11 +2661,7 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
     __shared__ unsigned long long s_arcs, s_narcs, s_ent, s_ent_lv;
     const int tid = threadIdx.x;
     const size_t slot = blockIdx.x;
-    SlotPtrs P{};
-    P.ns = base.ns + slot * (size_t)G.n * Lo::SW;
-    P.qa = base.qa + slot * (size_t)G.n;
-    P.qb = base.qb + slot * (size_t)G.n;
-    P.clr = base.clr + slot * (size_t)G.n;
+    const SlotPtrs P = slot_at<WW>(base, (size_t)G.n, slot);
     unsigned long long levels = 0, batches = 0, disc = 0, lds_lv = 0, rec_lv = 0, spills = 0;
     // whether a k-th best record has been published (the trial cut needs one)
     auto has_threshold = [&]() -> bool {
@@ -2633,9 +2694,8 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
         for (int i = tid; i < kCapS; i += B) {
             const int32_t w = L.skey[i];
             if (w >= 0) {
-                uint64_t* rec = &P.ns[(size_t)w * Lo::SW];
-                rec[0] = L.sseen[i];
-                rec[Lo::CUR] = L.scur[i];
+                *node_rec<1>(P, w) = L.sseen[i];
+                *node_cur<1>(P, w) = L.scur[i];
             }
             append_if(w >= 0, w, P.clr, &s_clen);
         }
@@ -2829,10 +2889,10 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                                              &s_arcs, &s_arcs);
                     __syncthreads();
                     const uint32_t nlen = uni32(s_nlen);
-                    clear_cur<1>(P, P.qa, flen, 0, B);
                     if (tid == 0) s_flen = 0;
                     __syncthreads();
-                    build_level<1>(P, P.qb, nlen, 0, B, s_act, true, P.qa, &s_flen, &s_clen, &s_arcs, L.filter());
+                    build_level<1>(P, P.qb, nlen, 0, B, s_act, true, P.qa, &s_flen, &s_clen, &s_arcs, G.deg,
+                                   L.filter());
                     __syncthreads();
                     flen = uni32(s_flen);
                     tq = __builtin_amdgcn_s_memrealtime();
@@ -2914,7 +2974,7 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                     unsigned long long tl = 0;
                     for (uint32_t e = tid; e < flen; e += B) {
                         const int32_t u = P.qa[e];
-                        if (P.ns[(size_t)u * Lo::SW + Lo::CUR] & act) tl += G.deg[u];
+                        if (*node_cur<1>(P, u) & act) tl += G.deg[u];
                     }
                     if (tl) atomicAdd(&L.tsum, tl);
                 }
@@ -2973,11 +3033,10 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                                                  LE, &s_arcs, &s_arcs);
                         __syncthreads();
                         const uint32_t nlen = uni32(s_nlen);
-                        clear_cur<1>(P, P.qa, flen, 0, B);
                         if (tid == 0) s_flen = 0;
                         __syncthreads();
-                        build_level<1>(P, P.qb, nlen, 0, B, s_act, true, P.qa, &s_flen, &s_clen, &s_arcs,
-                                       L.filter());
+                        build_level<1>(P, P.qb, nlen, 0, B, s_act, true, P.qa, &s_flen, &s_clen, &s_arcs, G.deg,
+                                   L.filter());
                         __syncthreads();
                         flen = uni32(s_flen);
                     }
@@ -3000,7 +3059,7 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                                          &s_narcs, &s_ent);
                 __syncthreads();
                 const uint32_t nlen = uni32(s_nlen);
-                count_level<1, B>(P, P.qb, nlen, cg, ct);
+                count_level<1, B>(P, P.qb, nlen, cg, ct, G.deg);
                 __syncthreads();
                 disc += nlen;
                 ++rec_lv;
@@ -3013,11 +3072,10 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                 tq = __builtin_amdgcn_s_memrealtime();
                 ticks[2] += tq - tp;
                 tp = tq;
-                clear_cur<1>(P, P.qa, flen, 0, B);
                 if (tid == 0) s_flen = 0;
                 __syncthreads();
-                build_level<1>(P, P.qb, nlen, 0, B, s_act, live != 0, P.qa, &s_flen, &s_clen, &s_arcs,
-                               L.filter());
+                build_level<1>(P, P.qb, nlen, 0, B, s_act, live != 0, P.qa, &s_flen, &s_clen, &s_arcs, G.deg,
+                                   L.filter());
                 __syncthreads();
                 flen = uni32(s_flen);
                 tq = __builtin_amdgcn_s_memrealtime();
@@ -3030,11 +3088,7 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
         // reset the batch state: global records (when used) and the LDS tables
         if (uni32(s_mode) == 1) {
             const uint32_t nc = uni32(s_clen);
-            for (uint32_t i = tid; i < nc; i += B) {
-                uint64_t* rec = &P.ns[(size_t)P.clr[i] * Lo::SW];
-                rec[0] = 0;
-                rec[Lo::CUR] = 0;
-            }
+            plain_clear_body<1>(P, nc, 0, B);
         }
         for (int i = tid; i < kCapS; i += B) {
             L.skey[i] = -1;
@@ -3115,7 +3169,40 @@ struct EventPair {
     }
 };
 
-// Bytes per node of a level-synchronous slot: seen and nxt, cur, stamp, lists.
+// Node state and lists of S consecutive slots of N nodes, in one allocation
+// (`mem`), node state zeroed.
+struct SlotBufs {
+    DevBuf &mem, &ns, &cur, &stamp, &qa, &qb, &clr;
+};
+template <int WW>
+bc_status alloc_slots(SlotBufs b, size_t N, size_t S, bool ordered, hipStream_t s) {
+    Carve c;
+    c.add(b.ns, sizeof(uint64_t) * 2 * WW * N * S);
+    c.add(b.cur, sizeof(uint64_t) * WW * N * S);
+    c.add(b.stamp, WW > 1 ? sizeof(uint32_t) * N * S : 0);
+    const size_t zeroed = c.total;
+    c.add(b.qa, sizeof(int32_t) * N * S);
+    c.add(b.qb, sizeof(int32_t) * N * S);
+    c.add(b.clr, sizeof(int32_t) * N * S);
+    BC_TRY(ordered ? b.mem.alloc_on(c.total, s) : b.mem.alloc(c.total));
+    c.place(b.mem);
+    BC_HIP(hipMemsetAsync(b.mem.p, 0, zeroed, s));
+    return BC_OK;
+}
+inline bc_status alloc_slots_w(int W, SlotBufs b, size_t N, size_t S, bool ordered, hipStream_t s) {
+    if (W == 64) return alloc_slots<1>(b, N, S, ordered, s);
+    return W == 128 ? alloc_slots<2>(b, N, S, ordered, s) : alloc_slots<4>(b, N, S, ordered, s);
+}
+inline SlotPtrs slots_of(const SlotBufs& b, int W) {
+    return SlotPtrs{b.ns.as<uint64_t>(), b.qa.as<int32_t>(), b.qb.as<int32_t>(), b.clr.as<int32_t>(),
+                    b.cur.as<uint64_t>(), W > 64 ? b.stamp.as<uint32_t>() : nullptr};
+}
+template <class T>
+SlotBufs slot_bufs(T& x) {
+    return SlotBufs{x.mem, x.ns, x.cur, x.stamp, x.qa, x.qb, x.clr};
+}
+
+// Bytes per node of a slot: seen and nxt, cur, stamp, lists.
 template <int WW>
 constexpr size_t lv_node_bytes() {
     return 24 * WW + (WW > 1 ? 4 : 0) + 12;
@@ -3129,26 +3216,21 @@ bc_status ensure_lv(Workspace& Wk, const DevGraph& G, int want, hipStream_t s, L
     const size_t N = (size_t)G.n, K = (size_t)std::max(want, V.slots);
     if (V.slots < want) {
         V.mem.release();
+        V.cmem.release();
         V.slots = 0;
         Carve c;
         c.add(V.ctl, sizeof(Ctl) * K);
         c.add(V.next, sizeof(uint32_t));
-        c.add(V.ns, sizeof(uint64_t) * 2 * WW * N * K);
-        c.add(V.cur, sizeof(uint64_t) * WW * N * K);
-        c.add(V.stamp, WW > 1 ? sizeof(uint32_t) * N * K : 0);
         const size_t zeroed = c.total;
         c.add(V.srcs, sizeof(SrcState) * kBlk * K);
-        c.add(V.qa, sizeof(int32_t) * N * K);
-        c.add(V.qb, sizeof(int32_t) * N * K);
-        c.add(V.clr, sizeof(int32_t) * N * K);
-        BC_TRY(c.place_on(V.mem, s));
-        BC_HIP(hipMemsetAsync(V.mem.p, 0, zeroed, s));
+        BC_TRY(c.place_on(V.cmem, s));
+        BC_HIP(hipMemsetAsync(V.cmem.p, 0, zeroed, s));
+        BC_TRY(alloc_slots<WW>(slot_bufs(V), N, K, true, s));
         V.slots = want;
     }
     if (!Wk.hctl) BC_HIP(hipHostMalloc((void**)&Wk.hctl, sizeof(LvReport) * kMaxSlots, hipHostMallocMapped));
     std::memset(out, 0, sizeof(*out));
-    out->base = SlotPtrs{V.ns.as<uint64_t>(), V.qa.as<int32_t>(), V.qb.as<int32_t>(), V.clr.as<int32_t>(),
-                         V.cur.as<uint64_t>(), WW > 1 ? V.stamp.as<uint32_t>() : nullptr};
+    out->base = slots_of(slot_bufs(V), 64 * WW);
     out->n = N;
     out->C = V.ctl.as<Ctl>();
     out->S = V.srcs.as<SrcState>();
@@ -3159,24 +3241,12 @@ bc_status ensure_lv(Workspace& Wk, const DevGraph& G, int want, hipStream_t s, L
 template <int WW>
 bc_status ensure_batched(Workspace& W_, const DevGraph& G, int want, hipStream_t s) {
     if (W_.slots >= want && W_.ww == WW) return BC_OK;
-    const size_t N = (size_t)G.n, words = N * Layout<WW>::SW;
-    const size_t S_ = (size_t)want;
-    W_.bseen.release();
-    W_.bqa.release();
-    W_.bqb.release();
-    W_.bclr.release();
+    W_.pers.mem.release();
     W_.slot_stamp.release();
     W_.slots = 0;
-    BC_TRY(W_.bseen.alloc_on(sizeof(uint64_t) * words * S_, s));
-    BC_TRY(W_.bqa.alloc_on(sizeof(int32_t) * N * S_, s));
-    BC_TRY(W_.bqb.alloc_on(sizeof(int32_t) * N * S_, s));
-    BC_TRY(W_.bclr.alloc_on(sizeof(int32_t) * N * S_, s));
-    BC_TRY(W_.slot_stamp.alloc_on(sizeof(uint32_t) * S_, s));
-    BC_HIP(hipMemsetAsync(W_.bseen.p, 0, sizeof(uint64_t) * words * S_, s));
-    BC_HIP(hipMemsetAsync(W_.slot_stamp.p, 0, sizeof(uint32_t) * S_, s));
-    if (N > 0)
-        k_slot_init<WW><<<clamp_grid((int64_t)(N * S_), 16384), kBlk, 0, s>>>(G.deg, G.n, W_.bseen.as<uint64_t>(),
-                                                                               want);
+    BC_TRY(alloc_slots<WW>(slot_bufs(W_.pers), (size_t)G.n, (size_t)want, true, s));
+    BC_TRY(W_.slot_stamp.alloc_on(sizeof(uint32_t) * (size_t)want, s));
+    BC_HIP(hipMemsetAsync(W_.slot_stamp.p, 0, sizeof(uint32_t) * (size_t)want, s));
     W_.slots = want;
     return BC_OK;
 }
@@ -3473,7 +3543,6 @@ SeedPlan seed_plan(const bc_opts& o, int32_t k, int32_t n, int W) {
 template <int WW>
 bc_status run_ww(bc_graph* g, int32_t k, const bc_opts& o, const int32_t* d_order, TopKDev T, QStats* d_st,
                  Workspace& Wk, int W, Timing& tm, hipStream_t s, bool private_ws) {
-    using Lo = Layout<WW>;
     const DevGraph& G = g->dg;
     const int32_t n = G.n;
     const size_t N = (size_t)n;
@@ -3509,8 +3578,7 @@ bc_status run_ww(bc_graph* g, int32_t k, const bc_opts& o, const int32_t* d_orde
 
     if (batched && seed < nbatches) {
         int slots = o.slots > 0 ? o.slots : cus;
-        // per-slot bytes: node records (SW words) and three int32 lists per node
-        const size_t per_slot = N * (8 * Lo::SW + 12);
+        const size_t per_slot = N * lv_node_bytes<WW>();
         size_t freeb = 0, totalb = 0;
         if (Wk.slots < slots && hipMemGetInfo(&freeb, &totalb) == hipSuccess && per_slot > 0) {
             const size_t have = (size_t)Wk.slots * per_slot;
@@ -3521,8 +3589,7 @@ bc_status run_ww(bc_graph* g, int32_t k, const bc_opts& o, const int32_t* d_orde
         BC_TRY(ensure_batched<WW>(Wk, G, slots, s));
         BC_TRY(Wk.nextb.alloc_on(sizeof(uint32_t), s));
         BC_HIP(hipMemcpyAsync(Wk.nextb.p, &seed, sizeof(uint32_t), hipMemcpyHostToDevice, s));
-        SlotPtrs base{Wk.bseen.as<uint64_t>(), Wk.bqa.as<int32_t>(), Wk.bqb.as<int32_t>(), Wk.bclr.as<int32_t>(),
-                      nullptr, nullptr};
+        const SlotPtrs base = slots_of(slot_bufs(Wk.pers), W);
         BC_TRY(Wk.defer.alloc_on(sizeof(int32_t) * N + 64, s));
         uint32_t* dcnt = (uint32_t*)(Wk.defer.as<char>() + sizeof(int32_t) * N);
         BC_HIP(hipMemsetAsync(dcnt, 0, sizeof(uint32_t), s));
@@ -3539,10 +3606,10 @@ bc_status run_ww(bc_graph* g, int32_t k, const bc_opts& o, const int32_t* d_orde
                                                            (o.bounds & BC_BOUND_NO_TRIAL) ? 1 : 0);
             else
                 k_batched<WW, kBatchBlk><<<slots, kBatchBlk, 0, s>>>(G, d_order, W, nbatches, Wk.nextb.as<uint32_t>(),
-                                                                     chunk, base, Wk.slot_stamp.as<uint32_t>(), T, d_st, D);
+                                                                     chunk, base, Wk.slot_stamp.as<uint32_t>(), T, d_st, D, lp);
         } else {
             k_batched<WW, kBatchBlk><<<slots, kBatchBlk, 0, s>>>(G, d_order, W, nbatches, Wk.nextb.as<uint32_t>(),
-                                                                 chunk, base, Wk.slot_stamp.as<uint32_t>(), T, d_st, D);
+                                                                 chunk, base, Wk.slot_stamp.as<uint32_t>(), T, d_st, D, lp);
         }
         BC_HIP(hipEventRecord(ev.b, s));
         BC_HIP(hipGetLastError());
@@ -3567,10 +3634,7 @@ bc_status run_ww(bc_graph* g, int32_t k, const bc_opts& o, const int32_t* d_orde
             size_t room = 0;
             if (private_ws) {
                 room = (size_t)Wk.slots * per_slot;
-                Wk.bseen.release();
-                Wk.bqa.release();
-                Wk.bqb.release();
-                Wk.bclr.release();
+                Wk.pers.mem.release();
                 Wk.slots = 0;
             } else if (hipMemGetInfo(&freeb, &totalb) == hipSuccess) {
                 room = (size_t)(0.45 * (double)freeb);
@@ -3842,6 +3906,7 @@ bc_status run_farness_all(bc_graph* g, const bc_opts& o, uint64_t* farness, uint
 // copies.
 
 constexpr size_t kStaticBytes = (size_t)64 << 20;  // 64 MiB per device, held until the process ends
+constexpr size_t kStaticWords = 4;                  // words per node set aside for its state (three are used)
 constexpr size_t kStaticHdr = 64;                   // list header: count, lock, sequence
 
 }  // namespace bc
@@ -3873,7 +3938,7 @@ size_t static_need(int32_t n, int32_t kk) {
     const size_t N = (size_t)n;
     return al256(sizeof(Ctl)) + al256(kStaticHdr + sizeof(Rec) * (size_t)kk) + al256(sizeof(QStats)) +
            al256(sizeof(SrcState) * kBlk) + al256(sizeof(ThRec) * (N + 1)) + al256(sizeof(int32_t) * N) +
-           al256(sizeof(uint64_t) * Layout<1>::SW * N) + 3 * al256(sizeof(int32_t) * N);
+           al256(sizeof(uint64_t) * kStaticWords * N) + 3 * al256(sizeof(int32_t) * N);
 }
 
 }  // namespace
@@ -3922,7 +3987,7 @@ bc_status run_topk_static(bc_graph* g, int32_t k, int32_t* ids, uint64_t* farnes
     LvSlots L;
     std::memset(&L, 0, sizeof(L));
     const size_t rec_words = 3 * (size_t)n;  // seen, nxt and cur
-    uint64_t* words = reinterpret_cast<uint64_t*>(take(sizeof(uint64_t) * Layout<1>::SW * (size_t)n));
+    uint64_t* words = reinterpret_cast<uint64_t*>(take(sizeof(uint64_t) * kStaticWords * (size_t)n));
     L.base.ns = words;
     L.base.cur = words + 2 * (size_t)n;
     L.base.qa = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)n));
@@ -4045,7 +4110,7 @@ struct bc_multi {
     hipStream_t s = nullptr;            // stream of the runs
     hipStream_t cap = nullptr;          // private capture stream
     bc::DevBuf orders, rings, state, jobs, ctl;
-    bc::DevBuf ns, qa, qb, clr, stamps;
+    bc::DevBuf mem, ns, cur, stamp, qa, qb, clr, stamps;
     int slots = 0;
     int32_t ncap = 0;
     size_t state_bytes = 0;
@@ -4083,7 +4148,7 @@ void launch_jobs(bc_multi* p, hipStream_t st) {
     L.claim = p->ctl.as<unsigned long long>();
     L.W = p->W;
     L.ncap = p->ncap;
-    SlotPtrs base{p->ns.as<uint64_t>(), p->qa.as<int32_t>(), p->qb.as<int32_t>(), p->clr.as<int32_t>(), nullptr, nullptr};
+    const SlotPtrs base = slots_of(slot_bufs(*p), p->W);
     k_jobs<WW, kBatchBlk><<<p->slots, kBatchBlk, 0, st>>>(L, base, p->stamps.as<uint32_t>());
 }
 
@@ -4113,7 +4178,6 @@ bc_status multi_create(bc_graph* const* graphs, int32_t count, const int32_t* ks
     p->kk.resize((size_t)count);
     p->kreq.assign(ks, ks + count);
     p->state_off.resize((size_t)count);
-    const int SW = W == 64 ? Layout<1>::SW : (W == 128 ? Layout<2>::SW : Layout<4>::SW);
     size_t ord_total = 0, ring_total = 0;
     std::vector<size_t> ord_off((size_t)count), ring_off((size_t)count);
     for (int32_t i = 0; i < count; ++i) {
@@ -4208,19 +4272,15 @@ bc_status multi_create(bc_graph* const* graphs, int32_t count, const int32_t* ks
     int slots = o.slots > 0 ? o.slots : device_cus();
     if ((unsigned long long)slots > p->nbatch) slots = (int)std::max<unsigned long long>(p->nbatch, 1);
     const size_t N = (size_t)std::max(p->ncap, 1);
-    const size_t per_slot = N * (8 * (size_t)SW + 12);
+    const size_t per_slot = N * (W == 64 ? lv_node_bytes<1>() : (W == 128 ? lv_node_bytes<2>() : lv_node_bytes<4>()));
     size_t freeb = 0, totalb = 0;
     if (hipMemGetInfo(&freeb, &totalb) == hipSuccess) {
         const size_t capn = (size_t)(0.45 * (double)freeb) / per_slot;
         if ((size_t)slots > capn) slots = (int)std::max<size_t>(capn, 1);
     }
     p->slots = slots;
-    BC_TRY(p->ns.alloc_on(sizeof(uint64_t) * N * SW * (size_t)slots, s));
-    BC_TRY(p->qa.alloc_on(sizeof(int32_t) * N * (size_t)slots, s));
-    BC_TRY(p->qb.alloc_on(sizeof(int32_t) * N * (size_t)slots, s));
-    BC_TRY(p->clr.alloc_on(sizeof(int32_t) * N * (size_t)slots, s));
+    BC_TRY(alloc_slots_w(W, slot_bufs(*p), N, (size_t)slots, true, s));
     BC_TRY(p->stamps.alloc_on(sizeof(uint32_t) * (size_t)slots, s));
-    BC_HIP(hipMemsetAsync(p->ns.p, 0, sizeof(uint64_t) * N * SW * (size_t)slots, s));
     BC_HIP(hipMemsetAsync(p->stamps.p, 0, sizeof(uint32_t) * (size_t)slots, s));
     BC_HIP(hipStreamSynchronize(s));
     if (capture && p->nbatch > 0) {
@@ -4333,7 +4393,7 @@ struct DevQueue {
     long long wait_since = 0;        // steady-clock ns when the count last left zero (atomic builtins)
     bool yielding = false;           // stop raised to let a launch end for a waiting lane
     std::chrono::steady_clock::time_point t_launch{};
-    DevBuf ctr, claim, ns, qa, qb, clr, stamps;
+    DevBuf ctr, claim, mem, ns, cur, stamp, qa, qb, clr, stamps;
     std::mutex mu;
     std::condition_variable cv;
     std::vector<char> busy;
@@ -4342,10 +4402,7 @@ struct DevQueue {
         if (stream) (void)hipStreamSynchronize(stream);
         if (ev) (void)hipEventDestroy(ev);
         if (host) (void)hipHostFree(host);
-        ns.release();
-        qa.release();
-        qb.release();
-        clr.release();
+        mem.release();
         stamps.release();
         ctr.release();
         claim.release();
@@ -4389,7 +4446,7 @@ void launch_queue(DevQueue* q) {
     L.last_end = reinterpret_cast<unsigned long long*>(q->claim.as<char>() + 16);
     L.W = q->W;
     L.ncap = q->ncap;
-    SlotPtrs base{q->ns.as<uint64_t>(), q->qa.as<int32_t>(), q->qb.as<int32_t>(), q->clr.as<int32_t>(), nullptr, nullptr};
+    const SlotPtrs base = slots_of(slot_bufs(*q), q->W);
     k_jobs<WW, kBatchBlk><<<q->slots, kBatchBlk, 0, q->stream>>>(L, base, q->stamps.as<uint32_t>());
 }
 
@@ -4528,22 +4585,17 @@ bc_status devq_create(int W, int32_t ncap, int slots, DevQueue** out, uint64_t* 
     void* dp = nullptr;
     BC_HIP(hipHostGetDevicePointer(&dp, q->host, 0));
     q->dhost = reinterpret_cast<char*>(dp);
-    const int SW = W == 64 ? Layout<1>::SW : (W == 128 ? Layout<2>::SW : Layout<4>::SW);
     const size_t N = (size_t)q->ncap, S_ = (size_t)q->slots;
     BC_TRY(q->ctr.alloc(sizeof(uint32_t) * 2 * kQueueCap));
     BC_TRY(q->claim.alloc(64));
-    BC_TRY(q->ns.alloc(sizeof(uint64_t) * N * SW * S_));
-    BC_TRY(q->qa.alloc(sizeof(int32_t) * N * S_));
-    BC_TRY(q->qb.alloc(sizeof(int32_t) * N * S_));
-    BC_TRY(q->clr.alloc(sizeof(int32_t) * N * S_));
+    BC_TRY(alloc_slots_w(W, slot_bufs(*q), N, S_, false, q->stream));
     BC_TRY(q->stamps.alloc(sizeof(uint32_t) * S_));
     BC_HIP(hipMemsetAsync(q->ctr.p, 0, q->ctr.bytes, q->stream));
     BC_HIP(hipMemsetAsync(q->claim.p, 0, q->claim.bytes, q->stream));
-    BC_HIP(hipMemsetAsync(q->ns.p, 0, q->ns.bytes, q->stream));
     BC_HIP(hipMemsetAsync(q->stamps.p, 0, q->stamps.bytes, q->stream));
     BC_HIP(hipStreamSynchronize(q->stream));
     if (device_bytes)
-        *device_bytes = q->ns.bytes + q->qa.bytes + q->qb.bytes + q->clr.bytes + q->stamps.bytes + q->ctr.bytes + 64;
+        *device_bytes = q->mem.bytes + q->stamps.bytes + q->ctr.bytes + 64;
     *out = q.release();
     return BC_OK;
 }
