@@ -493,7 +493,23 @@ __device__ __forceinline__ void group_transpose(uint64_t* x) {
     }
 }
 
-// Counters of the level just reached, from its list N[0, len) of newly
+// Whether the reached nodes of a level are better found by a sweep over all n
+// nodes than through their list: the list is in the order of the arcs, so each
+// node is a line of its own (128 B) for the count, for the build and for the
+// next expansion; a sweep reads 16 WW bytes of every node in order, and leaves
+// the frontier in order.  One workgroup sweeps at its latency, not at the
+// memory's rate: on a random graph of 10^5 nodes, W = 64, sweeping from n / 8
+// on gives 23.7 ms, from n / 3 24.9, never 28.3, but a Barabasi-Albert graph
+// of 10^6 nodes, whose last batches are what the launch waits for, takes 7.7,
+// 7.2 and 7.2 ms; at W = 256 a geometric graph of 65,537 nodes 140 ms from
+// n / 8 on, 108 from n / 2 and 109 never.
+template <int WW>
+__device__ __forceinline__ bool sweep_level(uint32_t nlen, int64_t n) {
+    return (uint64_t)nlen * (WW == 1 ? 3 : 2) > (uint64_t)n;
+}
+
+// Counters of the level just reached, from its list N[0, len) (or, with N
+// null, from the nodes 0 .. len - 1) of newly
 // reached nodes (each once) after the expansion: the nxt masks are read from
 // L2 (they were written by atomics of this workgroup).  degs: out-degrees.
 template <int WW, int B>
@@ -503,7 +519,7 @@ __device__ void count_level(const SlotPtrs& P, const int32_t* N, uint32_t len, u
     for (uint32_t rb = 0; rb < len; rb += B) {
         if (rb + (tid & ~63u) >= len) break;  // wave-uniform: nothing left for this wave
         const uint32_t i = rb + tid;
-        const int32_t w = i < len ? N[i] : -1;
+        const int32_t w = i < len ? (N ? N[i] : (int32_t)i) : -1;
         int32_t wr[WW];
         group_bcast_all<WW>(w, wr);
         uint64_t nb[WW];
@@ -709,7 +725,7 @@ __device__ void build_level(const SlotPtrs& P, const int32_t* N, uint32_t len, u
     for (uint32_t rb = first; rb < len; rb += stride) {
         if (rb + (tid & ~63) >= len) break;  // wave-uniform
         const uint32_t i = rb + tid;
-        const int32_t w = i < len ? N[i] : -1;
+        const int32_t w = i < len ? (N ? N[i] : (int32_t)i) : -1;
         int32_t wr[WW];
         group_bcast_all<WW>(w, wr);
         const uint32_t jw = group_lane<WW>();
@@ -733,10 +749,11 @@ __device__ void build_level(const SlotPtrs& P, const int32_t* N, uint32_t len, u
             bool pn[WW], po[WW];
 #pragma unroll
             for (int r = 0; r < WW; ++r) {
+                const bool put = N ? wr[r] >= 0 : nb[r] != 0ull;
                 nb[r] &= actj;
                 pn[r] = nb[r] != 0ull;
                 po[r] = old[r] != 0ull;
-                if (wr[r] >= 0) {
+                if (put) {
                     uint64_t* rec = node_rec<WW>(P, wr[r]) + jw;
                     rec[WW] = 0;
                     if (pn[r]) rec[0] = old[r] | nb[r];
@@ -1889,6 +1906,7 @@ __device__ void record_batch(const DevGraph& G, const int32_t* order, int W, uin
         }
         if (tid == 0) R.nlen = 0;
         __syncthreads();
+        bool sweep = false;
         if (pull) {
             ++K.pulls;
             block_pull<WW, B, kBlockAhead>(G, P, R);
@@ -1898,7 +1916,8 @@ __device__ void record_batch(const DevGraph& G, const int32_t* order, int W, uin
                 expand_entries<WW, B, 1>(G, P, P.qa, e0, min(flen, e0 + B), R.act, P.qb, &R.nlen, stamp, R.LE,
                                          &R.narcs, &R.ent);
             __syncthreads();
-            count_level<WW, B>(P, P.qb, uni32(R.nlen), R.cg, R.ct, G.deg);
+            sweep = sweep_level<WW>(uni32(R.nlen), G.n);
+            count_level<WW, B>(P, sweep ? nullptr : P.qb, sweep ? (uint32_t)G.n : uni32(R.nlen), R.cg, R.ct, G.deg);
         }
         __syncthreads();
         const uint32_t nlen = uni32(R.nlen);
@@ -1916,7 +1935,8 @@ __device__ void record_batch(const DevGraph& G, const int32_t* order, int W, uin
         tq = __builtin_amdgcn_s_memrealtime();
         K.ticks[2] += tq - tp;
         tp = tq;
-        build_level<WW>(P, P.qb, nlen, 0, B, R.act, live != 0, P.qa, &R.flen, &R.clen, &R.arcs, G.deg);
+        build_level<WW>(P, sweep ? nullptr : P.qb, sweep ? (uint32_t)G.n : nlen, 0, B, R.act, live != 0, P.qa, &R.flen,
+                        &R.clen, &R.arcs, G.deg);
         __syncthreads();
         flen = uni32(R.flen);
         pull = next_pull(pull, uni64(R.arcs), flen, G, lp);
@@ -2333,7 +2353,7 @@ constexpr int kCapS = 1024;       // H_seen entries
 constexpr int kCapSLog = 10;
 constexpr uint32_t kPassCap = 4900;   // arcs per counting pass (H_next load <= 0.6)
 constexpr uint32_t kSeenCap = 760;    // H_seen entries allowed after a build (load <= 0.74)
-constexpr uint32_t kPassMax = 8;
+constexpr uint32_t kPassMax = 8;     // passes of a level whose state is in LDS
 
 struct LdsTab {
     int32_t nkey[kCapN];
@@ -2965,25 +2985,26 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                     }
                 }
                 const uint64_t act = uni64(s_act[0]);
-                // When the level's arcs fit the LDS counting passes, count it in
+                // When the level's arcs fit one LDS counting pass, count it in
                 // H_next with the seen bits read from the node records (no global
                 // atomics); the records take the level only if a source survives.
-                if (tid == 0) L.tsum = 0;
-                __syncthreads();
-                {
+                // (A level of more passes walks its arcs once per pass, and mostly
+                // survives: with up to eight of them a random graph of 10^5 nodes
+                // took 30.0 ms, with one 28.3.)
+                bool hybrid = flen <= kPassCap;
+                if (hybrid) {
+                    if (tid == 0) L.tsum = 0;
+                    __syncthreads();
                     unsigned long long tl = 0;
                     for (uint32_t e = tid; e < flen; e += B) {
                         const int32_t u = P.qa[e];
                         if (*node_cur<1>(P, u) & act) tl += G.deg[u];
                     }
                     if (tl) atomicAdd(&L.tsum, tl);
+                    __syncthreads();
+                    hybrid = uni64(L.tsum) <= kPassCap;
                 }
-                __syncthreads();
-                const unsigned long long Tarcs = uni64(L.tsum);
-                const uint32_t npass = (uint32_t)((Tarcs + kPassCap - 1) / kPassCap);
-                bool hybrid = false;
-                if (npass <= kPassMax) {
-                    const uint32_t np = npass > 0 ? npass : 1;
+                if (hybrid) {
                     if (tid < kBlk) {
                         cg[tid] = 0;
                         ct[tid] = 0;
@@ -2993,17 +3014,14 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                         L.over = 0;
                     }
                     __syncthreads();
-                    for (uint32_t p = 0; p < np; ++p) {
-                        for (uint32_t e0 = 0; e0 < flen; e0 += B) {
-                            const uint32_t tot = rec_prologue(G, P, P.qa, e0, min(flen, e0 + B), act, PX,
-                                                              (p == 0 && !counted) ? &s_narcs : nullptr,
-                                                              (p == 0 && !counted) ? &s_ent : nullptr);
-                            tab_arcs<true, true>(G, L, P.ns, tot, np, p, PX, cg, ct, L.filter());
-                            __syncthreads();
-                        }
-                        tab_next_reset<B>(L);
+                    for (uint32_t e0 = 0; e0 < flen; e0 += B) {
+                        const uint32_t tot = rec_prologue(G, P, P.qa, e0, min(flen, e0 + B), act, PX,
+                                                          counted ? nullptr : &s_narcs, counted ? nullptr : &s_ent);
+                        tab_arcs<true, true>(G, L, P.ns, tot, 1, 0, PX, cg, ct, L.filter());
                         __syncthreads();
                     }
+                    tab_next_reset<B>(L);
+                    __syncthreads();
                     hybrid = uni32(L.over) == 0u;
                     if (!hybrid && tid == 0) {
                         s_narcs = ra0;  // recounted below
@@ -3059,7 +3077,8 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                                          &s_narcs, &s_ent);
                 __syncthreads();
                 const uint32_t nlen = uni32(s_nlen);
-                count_level<1, B>(P, P.qb, nlen, cg, ct, G.deg);
+                const bool sweep = sweep_level<1>(nlen, G.n);
+                count_level<1, B>(P, sweep ? nullptr : P.qb, sweep ? (uint32_t)G.n : nlen, cg, ct, G.deg);
                 __syncthreads();
                 disc += nlen;
                 ++rec_lv;
@@ -3074,8 +3093,8 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                 tp = tq;
                 if (tid == 0) s_flen = 0;
                 __syncthreads();
-                build_level<1>(P, P.qb, nlen, 0, B, s_act, live != 0, P.qa, &s_flen, &s_clen, &s_arcs, G.deg,
-                                   L.filter());
+                build_level<1>(P, sweep ? nullptr : P.qb, sweep ? (uint32_t)G.n : nlen, 0, B, s_act, live != 0, P.qa,
+                               &s_flen, &s_clen, &s_arcs, G.deg, L.filter());
                 __syncthreads();
                 flen = uni32(s_flen);
                 tq = __builtin_amdgcn_s_memrealtime();

@@ -47,3 +47,21 @@ def test_bottom_up_levels(gi, width):
     for r in got:
         assert r.ids.tolist() == ref["ids"].tolist()
         assert r.farness.tolist() == ref["f"].tolist() and r.reach.tolist() == ref["r"].tolist()
+
+
+@pytest.mark.parametrize("shape", [(1023, 20), (1600, 7), (3001, 5), (4099, 40)])
+@pytest.mark.parametrize("width", [64, 128, 256])
+def test_levels_found_by_sweep(shape, width):
+    """Top-down levels that reach less and more than a third and a half of the
+    nodes, on the node records and, at width 64, after a batch has left LDS."""
+    g = synth.erdos_renyi(shape[0], shape[1], 5)
+    ref = oracle.topk(g, 33)
+    print(f"[sweep] n={g.n} m={g.m} width={width}", flush=True)
+    with bc.Graph(g.row_ptr, g.col, directed=g.directed) as G:
+        got = [G.topk(33, mode="batched", width=width, lds_tables=lds, seed_batches=sb, **NEVER)
+               for lds in ((True, False) if width == 64 else (False,)) for sb in (0, 2)]
+        f, r, _ = G.farness_all(width=width)
+    for x in got:
+        assert x.ids.tolist() == ref["ids"].tolist()
+        assert x.farness.tolist() == ref["f"].tolist() and x.reach.tolist() == ref["r"].tolist()
+    assert f[ref["ids"]].tolist() == ref["f"].tolist() and r[ref["ids"]].tolist() == ref["r"].tolist()
