@@ -1161,7 +1161,7 @@ constexpr int kLvBlk = 1024;  // threads per workgroup: few, large workgroups, s
 __device__ inline uint32_t next_pull(uint32_t pull, unsigned long long fa, uint32_t flen, const DevGraph& G,
                                      const LevelParams& lp) {
     if (lp.can_pull) {
-        uint64_t n = (uint64_t)G.n, m = (uint64_t)G.m;
+        uint64_t n = uni64((uint64_t)G.n), m = uni64((uint64_t)G.m);
         asm volatile("" : "+s"(n), "+s"(m));  // the quotients are not kept across the levels
         if (!pull && lp.pull_alpha > 0.f && (double)fa > (double)(int64_t)m / lp.pull_alpha) return 1;
         if (pull && (double)flen < (double)(int64_t)n / lp.pull_beta) return 0;
@@ -1637,23 +1637,26 @@ struct RecLds {
     unsigned long long arcs, narcs, ent;  // narcs, ent: arcs and frontier entries expanded
 };
 
-// A bottom-up step of one workgroup: the reached nodes to P.qb (counter
-// R.nlen), the level's counters to R.cg and R.ct, the arcs read to R.narcs.
-// Ends with a barrier after which nxt may be taken.  Whole workgroup.
+// A bottom-up step of one workgroup for the live sources act: the reached
+// nodes to P.qb (counter nlen), the level's counters to cg and ct, the arcs
+// read to narcs (all in LDS).  Ends with a barrier after which nxt may be
+// read.  Whole workgroup.
 template <int WW, int B, int kAhead>
-__device__ __forceinline__ void block_pull(const DevGraph& G, const SlotPtrs& P, RecLds<WW, B>& R) {
+__device__ __forceinline__ void block_pull(const DevGraph& G, const SlotPtrs& P, const uint64_t* act, PullWaveLds<WW>* X,
+                                           uint32_t* cg, unsigned long long* ct, uint32_t* nlen,
+                                           unsigned long long* narcs) {
     const uint32_t wave = uni32(threadIdx.x >> 6);
-    const uint64_t actj = R.act[threadIdx.x % WW];
+    const uint64_t actj = act[threadIdx.x % WW];
     const uint32_t nheavy = *G.nheavy;
     unsigned long long scanned = 0;
     for (uint32_t h = wave; h < nheavy; h += B / 64) {
         const int32_t w = G.heavy[h];
-        append_if(pull_heavy<WW, kAhead>(G, P, actj, w, R.cg, R.ct, scanned), w, P.qb, &R.nlen);
+        append_if(pull_heavy<WW, kAhead>(G, P, actj, w, cg, ct, scanned), w, P.qb, nlen);
     }
     for (int64_t base = (int64_t)wave * 64; base < G.n; base += B)
-        pull_nodes<WW, kAhead>(G, P, actj, base, R.X[wave], R.cg, R.ct, nullptr, &R.nlen, scanned);
+        pull_nodes<WW, kAhead>(G, P, actj, base, X[wave], cg, ct, nullptr, nlen, scanned);
     for (int o = 32; o > 0; o >>= 1) scanned += __shfl_xor(scanned, o);
-    if ((threadIdx.x & 63) == 0 && scanned) atomicAdd(&R.narcs, scanned);
+    if ((threadIdx.x & 63) == 0 && scanned) atomicAdd(narcs, scanned);
     wait_stores();  // other waves read nxt next
     __syncthreads();
 }
@@ -1741,7 +1744,7 @@ __global__ __launch_bounds__(kBatchBlk) void k_plain_run(DevGraph G, const int32
         }
         __syncthreads();
         if (pull) {
-            block_pull<WW, B, kPullAhead>(G, P, R);
+            block_pull<WW, B, kPullAhead>(G, P, R.act, R.X, R.cg, R.ct, &R.nlen, &R.narcs);
             clear_cur<WW>(P, P.qa, flen, 0, B);
             ++pulls;
         } else {
@@ -1909,7 +1912,7 @@ __device__ void record_batch(const DevGraph& G, const int32_t* order, int W, uin
         bool sweep = false;
         if (pull) {
             ++K.pulls;
-            block_pull<WW, B, kBlockAhead>(G, P, R);
+            block_pull<WW, B, kBlockAhead>(G, P, R.act, R.X, R.cg, R.ct, &R.nlen, &R.narcs);
             clear_cur<WW>(P, P.qa, flen, 0, B);
         } else {
             for (uint32_t e0 = 0; e0 < flen; e0 += B)
@@ -2448,7 +2451,7 @@ __device__ uint32_t tab_prologue(const DevGraph& G, const LdsTab& L, const int32
                                  PassScratch& X, unsigned long long* arcs, unsigned long long* entries) {
     constexpr int B = kLdsBlk;
     static_assert(kCapS <= B, "one thread per frontier entry");
-    const int tid = threadIdx.x;
+    const int tid = phase_tid();
     uint32_t deg = 0;
     int32_t beg = 0;
     uint64_t m = 0;
@@ -2482,7 +2485,7 @@ __device__ uint32_t rec_prologue(const DevGraph& G, const SlotPtrs& P, const int
                                  uint64_t act, PassScratch& X, unsigned long long* arcs,
                                  unsigned long long* entries) {
     constexpr int B = kLdsBlk;
-    const int tid = threadIdx.x;
+    const int tid = phase_tid();
     const uint32_t e = e0 + (uint32_t)tid;
     uint32_t deg = 0;
     int32_t beg = 0;
@@ -2524,7 +2527,7 @@ __device__ void tab_arcs(const DevGraph& G, LdsTab& L, const uint64_t* ns, uint3
                          const uint32_t* seen_filter = nullptr) {
     constexpr int B = kLdsBlk;
     constexpr int kInflight = 2;
-    const uint32_t tid = threadIdx.x;
+    const uint32_t tid = phase_tid();
     for (uint32_t a0 = tid; a0 < total; a0 += kInflight * B) {
         int32_t w[kInflight], dg[kInflight];
         uint64_t m[kInflight], sv[kInflight];
@@ -2586,7 +2589,7 @@ __device__ void tab_cheap_arcs(const DevGraph& G, const LdsTab& L, const uint64_
                                const uint32_t* seen_filter = nullptr) {
     constexpr int B = kLdsBlk;
     constexpr int kInflight = 1;
-    const uint32_t tid = threadIdx.x;
+    const uint32_t tid = phase_tid();
     const uint32_t wbase = tid & ~63u;
     // wave-uniform loop: a wave runs while any of its lanes has an arc
     for (uint32_t r = 0; r + wbase < total; r += kInflight * B) {
@@ -2662,13 +2665,14 @@ template <int WW>
 __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32_t* order, int W,
                                                         uint32_t nbatches, uint32_t* next_batch, SlotPtrs base,
                                                         TopKDev T, QStats* st, DeferList D, int force_spill,
-                                                        int no_trial) {
+                                                        int no_trial, LevelParams lp) {
     static_assert(WW == 1, "LDS-resident batches hold 64 sources");
     constexpr int B = kLdsBlk;
     __shared__ LdsTab L;
     __shared__ union {
         LdsExpand<1, B> e;   // global-record levels
         PassScratch x;       // LDS levels
+        PullWaveLds<1> p[B / 64];  // bottom-up levels
     } U;
     LdsExpand<1, B>& LE = U.e;
     PassScratch& PX = U.x;
@@ -2678,11 +2682,11 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
     __shared__ CutLds<64> CL;
     __shared__ uint32_t s_flen, s_nlen, s_clen, s_b, s_mode, s_hasth;
     __shared__ uint64_t s_act[4];
-    __shared__ unsigned long long s_arcs, s_narcs, s_ent, s_ent_lv;
+    __shared__ unsigned long long s_arcs, s_narcs, s_ent, s_ent_lv, s_front;
     const int tid = threadIdx.x;
     const size_t slot = blockIdx.x;
     const SlotPtrs P = slot_at<WW>(base, (size_t)G.n, slot);
-    unsigned long long levels = 0, batches = 0, disc = 0, lds_lv = 0, rec_lv = 0, spills = 0;
+    unsigned long long levels = 0, batches = 0, disc = 0, lds_lv = 0, rec_lv = 0, spills = 0, pulls = 0;
     // whether a k-th best record has been published (the trial cut needs one)
     auto has_threshold = [&]() -> bool {
         if (tid == 0) s_hasth = __hip_atomic_load(T.seq, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) != 0u ? 1u : 0u;
@@ -2782,7 +2786,7 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
         }
         __syncthreads();
         uint32_t live = uni32(cut_step<1>(T, S, W, 0, false, nullptr, nullptr, false, true, st, s_act, CL, &D));
-        uint32_t flen = uni32(s_flen), d = 0, cur = 0, stamp = 0;
+        uint32_t flen = uni32(s_flen), d = 0, cur = 0, stamp = 0, pull = 0;
         uint32_t trial_d = 0;  // level whose over-counted bound test has run (0: none; level 0 needs none)
         uint64_t tp = __builtin_amdgcn_s_memrealtime();
         ticks[0] += tp - tb;
@@ -2957,7 +2961,7 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                 const uint64_t tr0 = tp;
                 const unsigned long long ra0 = uni64(s_narcs), en0 = uni64(s_ent);
                 bool counted = false;
-                if (!no_trial && d >= 1 && trial_d != d + 1 && has_threshold()) {
+                if (!pull && !no_trial && d >= 1 && trial_d != d + 1 && has_threshold()) {
                     trial_d = d + 1;
                     if (tid < kBlk) {
                         cg[tid] = 0;
@@ -2991,7 +2995,7 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                 // (A level of more passes walks its arcs once per pass, and mostly
                 // survives: with up to eight of them a random graph of 10^5 nodes
                 // took 30.0 ms, with one 28.3.)
-                bool hybrid = flen <= kPassCap;
+                bool hybrid = !pull && flen <= kPassCap;
                 if (hybrid) {
                     if (tid == 0) L.tsum = 0;
                     __syncthreads();
@@ -3051,12 +3055,16 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                                                  LE, &s_arcs, &s_arcs);
                         __syncthreads();
                         const uint32_t nlen = uni32(s_nlen);
-                        if (tid == 0) s_flen = 0;
+                        if (tid == 0) {
+                            s_flen = 0;
+                            s_front = 0;
+                        }
                         __syncthreads();
-                        build_level<1>(P, P.qb, nlen, 0, B, s_act, true, P.qa, &s_flen, &s_clen, &s_arcs, G.deg,
+                        build_level<1>(P, P.qb, nlen, 0, B, s_act, true, P.qa, &s_flen, &s_clen, &s_front, G.deg,
                                    L.filter());
                         __syncthreads();
                         flen = uni32(s_flen);
+                        pull = next_pull(0, uni64(s_front), flen, G, lp);
                     }
                     tq = __builtin_amdgcn_s_memrealtime();
                     ticks[3] += tq - tp;
@@ -3072,13 +3080,22 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                 }
                 if (tid == 0) s_nlen = 0;
                 __syncthreads();
-                for (uint32_t e0 = 0; e0 < flen; e0 += B)
-                    expand_entries<1, B, 1>(G, P, P.qa, e0, min(flen, e0 + B), s_act, P.qb, &s_nlen, stamp, LE,
-                                         &s_narcs, &s_ent);
-                __syncthreads();
-                const uint32_t nlen = uni32(s_nlen);
-                const bool sweep = sweep_level<1>(nlen, G.n);
-                count_level<1, B>(P, sweep ? nullptr : P.qb, sweep ? (uint32_t)G.n : nlen, cg, ct, G.deg);
+                uint32_t nlen;
+                bool sweep = false;
+                if (pull) {
+                    ++pulls;
+                    block_pull<1, B, kBlockAhead>(G, P, s_act, U.p, cg, ct, &s_nlen, &s_narcs);
+                    clear_cur<1>(P, P.qa, flen, 0, B);
+                    nlen = uni32(s_nlen);
+                } else {
+                    for (uint32_t e0 = 0; e0 < flen; e0 += B)
+                        expand_entries<1, B, 1>(G, P, P.qa, e0, min(flen, e0 + B), s_act, P.qb, &s_nlen, stamp, LE,
+                                                &s_narcs, &s_ent);
+                    __syncthreads();
+                    nlen = uni32(s_nlen);
+                    sweep = sweep_level<1>(nlen, G.n);
+                    count_level<1, B>(P, sweep ? nullptr : P.qb, sweep ? (uint32_t)G.n : nlen, cg, ct, G.deg);
+                }
                 __syncthreads();
                 disc += nlen;
                 ++rec_lv;
@@ -3091,12 +3108,16 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                 tq = __builtin_amdgcn_s_memrealtime();
                 ticks[2] += tq - tp;
                 tp = tq;
-                if (tid == 0) s_flen = 0;
+                if (tid == 0) {
+                    s_flen = 0;
+                    s_front = 0;
+                }
                 __syncthreads();
                 build_level<1>(P, sweep ? nullptr : P.qb, sweep ? (uint32_t)G.n : nlen, 0, B, s_act, live != 0, P.qa,
-                               &s_flen, &s_clen, &s_arcs, G.deg, L.filter());
+                               &s_flen, &s_clen, &s_front, G.deg, L.filter());
                 __syncthreads();
                 flen = uni32(s_flen);
+                pull = next_pull(pull, uni64(s_front), flen, G, lp);
                 tq = __builtin_amdgcn_s_memrealtime();
                 ticks[3] += tq - tp;
                 tp = tq;
@@ -3119,6 +3140,7 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
     }
     if (tid == 0) {
         atomicAdd(&st->levels, levels);
+        if (pulls) atomicAdd(&st->pull_levels, pulls);
         atomicAdd(&st->batches, batches);
         atomicAdd(&st->discovered, disc);
         if (s_narcs) atomicAdd(&st->node_arcs, s_narcs);
@@ -3620,9 +3642,17 @@ bc_status run_ww(bc_graph* g, int32_t k, const bc_opts& o, const int32_t* d_orde
         const uint32_t chunk = (uint32_t)(o.chunk > 0 ? o.chunk : 1);
         if constexpr (WW == 1) {
             if (o.lds_tables >= 0)
+                // bottom up from m / 2 frontier arcs on where the others take m / 3: a
+                // narrower level is often ended by the trial walk of a top-down one.
+                // (From m / 3 / from m / 2 / never: random graph of 10^5 nodes 25.4 /
+                // 22.5 / 24.6 ms; collaboration graph of 500,000 nodes 293 / 297 /
+                // 672 ms; every farness of 20,011 nodes of a random graph, where no
+                // threshold ends a level, 5.3 / 5.4 / 8.3 ms.)
                 k_batched_lds<1><<<slots, kLdsBlk, 0, s>>>(G, d_order, W, nbatches, Wk.nextb.as<uint32_t>(), base,
                                                            T, d_st, D, o.lds_tables == 1 ? 1 : 0,
-                                                           (o.bounds & BC_BOUND_NO_TRIAL) ? 1 : 0);
+                                                           (o.bounds & BC_BOUND_NO_TRIAL) ? 1 : 0,
+                                                           LevelParams{lp.pull_alpha * (2.f / 3.f), lp.pull_beta,
+                                                                       lp.can_pull});
             else
                 k_batched<WW, kBatchBlk><<<slots, kBatchBlk, 0, s>>>(G, d_order, W, nbatches, Wk.nextb.as<uint32_t>(),
                                                                      chunk, base, Wk.slot_stamp.as<uint32_t>(), T, d_st, D, lp);

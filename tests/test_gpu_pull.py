@@ -42,6 +42,10 @@ def test_bottom_up_levels(gi, width):
         got = [G.topk(20, mode="batched", width=width, lds_tables=False, seed_batches=0, **kw)
                for kw in (ALWAYS, dict(ALWAYS, order="degree"), dict(), NEVER)]
         pulls = [int(r.stats["pull_levels"]) for r in got]
+        if width == 64:  # batches that leave LDS
+            lds = G.topk(20, mode="batched", width=64, seed_batches=0, trial=False, **ALWAYS)
+            assert int(lds.stats["spills"]) == 0 or int(lds.stats["pull_levels"]) > 0
+            got += [lds, G.topk(20, mode="batched", width=64, seed_batches=0, trial=False)]
         got += bc.topk_multi([G, G], [20, 20], width=width)
     assert pulls[0] > 0 and pulls[1] > 0 and pulls[3] == 0, pulls
     for r in got:
