@@ -141,8 +141,9 @@ typedef struct bc_opts {
                                sources, 64, 128 or 256 (0: the narrowest of them that
                                holds every deferred source in one batch, else 256)       */
     const float* mlp;       /* BC_ORDER_LEARNED: host, BC_MLP_PARAMS floats              */
-    int32_t graph_levels;   /* level-synchronous batches: 0 (the default) makes one host
-                               round trip per level; 1..64 captures that many level steps
+    int32_t graph_levels;   /* level-synchronous batches: 0 (the default) runs narrow levels
+                               in one kernel and makes one host round trip per wide level,
+                               several batches side by side; 1..64 captures that many level steps
                                in a HIP graph and replays it, checking for live sources
                                once per replay; -1 runs every level of every batch of a
                                phase in one cooperative launch, grid barriers between the
