@@ -17,11 +17,11 @@
 #include <utility>
 
 #include "bc_internal.h"
+#include "rules.h"
 
 namespace bc {
 
 constexpr int kArcBlk = 256;       // threads per workgroup of the arc kernels
-constexpr int kArcTile = 2048;     // consecutive arcs per workgroup: 8 per thread
 
 // The row of arc e: the last r in [0, n) with rp[r] <= e, which is not empty
 // (0 <= e < rp[n]).  One wave, 64 probes a step: four steps for 10^6 rows in
@@ -30,7 +30,7 @@ __device__ inline int32_t wave_row_of(const int32_t* __restrict__ rp, int32_t n,
     const int32_t lane = (int32_t)__lane_id();
     int32_t lo = 0, hi = n;  // rp[lo] <= e, the answer lies in [lo, hi)
     while (hi - lo > 1) {
-        const int32_t step = (hi - lo + 63) / 64;
+        const int32_t step = probe_step(lo, hi);
         const int64_t p = (int64_t)lo + (int64_t)(lane + 1) * step;
         const bool le = p < hi && rp[p] <= e;
         const int32_t c = __popcll(__ballot(le));  // rp is non-decreasing: a prefix of the lanes
@@ -46,10 +46,10 @@ struct ArcRowLds {
     int32_t r0, r1;
 };
 
-// row[i] = row of arc e0 + i, e0 <= e0 + i < e1 (at most kArcTile arcs, at
-// least one).  Every non-empty row that starts in the tile marks its first
+// row[i] = row of arc e0 + i, i < len (at most kArcTile arcs, at least one).
+// Every non-empty row that starts in the tile marks its first
 // arc; a running maximum spreads the marks.  Whole workgroup of kArcBlk.
-__device__ inline void block_arc_rows(const int32_t* __restrict__ rp, int32_t n, int32_t e0, int32_t e1,
+__device__ inline void block_arc_rows(const int32_t* __restrict__ rp, int32_t n, int32_t e0, int32_t len,
                                       ArcRowLds& L) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int kPer = kArcTile / kArcBlk;
@@ -57,15 +57,15 @@ __device__ inline void block_arc_rows(const int32_t* __restrict__ rp, int32_t n,
         const int32_t r = wave_row_of(rp, n, e0);
         if (lane == 0) L.r0 = r;
     } else if (wave == 1) {
-        const int32_t r = wave_row_of(rp, n, e1 - 1);
+        const int32_t r = wave_row_of(rp, n, e0 + (len - 1));
         if (lane == 0) L.r1 = r;
     }
     for (int i = tid; i < kArcTile; i += kArcBlk) L.row[i] = -1;
     __syncthreads();
-    const int32_t r1 = L.r1;
-    for (int32_t r = L.r0 + tid; r <= r1; r += kArcBlk) {
+    const int64_t r1 = L.r1;
+    for (int64_t r = (int64_t)L.r0 + tid; r <= r1; r += kArcBlk) {
         const int32_t b = rp[r];
-        if (b < rp[r + 1]) L.row[max(b, e0) - e0] = r;
+        if (b < rp[r + 1]) L.row[max(b, e0) - e0] = (int32_t)r;
     }
     __syncthreads();
     int32_t v[kPer], mx = -1;
@@ -90,7 +90,7 @@ __device__ inline void block_arc_rows(const int32_t* __restrict__ rp, int32_t n,
     __syncthreads();
 }
 
-inline unsigned arc_tiles(int64_t m) { return (unsigned)((m + kArcTile - 1) / kArcTile); }
+inline unsigned arc_tiles(int64_t m) { return (unsigned)tile_count(m); }
 
 // ctr[key] += 1 for every lane with `on`, one atomic per distinct key of the
 // wave (nodes of one component come in long runs).  Converged wave.

@@ -80,7 +80,8 @@ __global__ void k_feat_heavy(const int32_t* __restrict__ list, const uint32_t* _
     for (uint32_t q = blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64; q < nh; q += waves) {
         const int32_t v = list[q];
         uint64_t s = 0;
-        for (int32_t e = rp[v] + lane; e < rp[v + 1]; e += 64) s += deg[col[e]];
+        const int64_t end = rp[v + 1];
+        for (int64_t e = (int64_t)rp[v] + lane; e < end; e += 64) s += deg[col[e]];
         for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
         if (lane == 0) s2[v] = s;
     }
@@ -132,7 +133,7 @@ __global__ void k_heavy_list(int32_t n, const uint32_t* __restrict__ deg, int32_
 __device__ inline uint32_t wave_count_at_least(const int32_t* __restrict__ col, int32_t b, int32_t e,
                                                const uint32_t* h, uint32_t c, int lane) {
     uint32_t cnt = 0;
-    for (int32_t i = b + lane; i < e; i += 64) cnt += ld_relaxed(&h[col[i]]) >= c;
+    for (int64_t i = (int64_t)b + lane; i < e; i += 64) cnt += ld_relaxed(&h[col[i]]) >= c;
     for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off, 64);
     return cnt;  // every lane holds the total
 }

@@ -60,14 +60,14 @@ __global__ __launch_bounds__(kArcBlk) void k_validate_arcs(int32_t n, int64_t m,
     if (threadIdx.x == 0) s_bad = __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u;
     __syncthreads();
     if (s_bad) return;
-    const int32_t e0 = (int32_t)(blockIdx.x * (int64_t)kArcTile), e1 = (int32_t)min((int64_t)e0 + kArcTile, m);
-    block_arc_rows(rp, n, e0, e1, L);
+    const int32_t e0 = tile_first(blockIdx.x), len = tile_arcs(e0, m);
+    block_arc_rows(rp, n, e0, len, L);
     uint32_t bits = 0;
-    for (int32_t e = e0 + threadIdx.x; e < e1; e += kArcBlk) {
-        const int32_t u = L.row[e - e0], w = col[e];
+    tile_each<kArcBlk>(threadIdx.x, len, [&](int32_t i) {
+        const int32_t e = e0 + i, u = L.row[i], w = col[e];
         if (w < 0 || w >= n) bits |= 2u;
         if (w == u || (e > rp[u] && w <= col[e - 1])) bits |= 4u;
-    }
+    });
     if (bits) atomicOr(err, bits);
 }
 
@@ -75,13 +75,13 @@ __global__ __launch_bounds__(kArcBlk) void k_validate_arcs(int32_t n, int64_t m,
 __global__ __launch_bounds__(kArcBlk) void k_any_drop(int32_t n, int64_t m, const int32_t* __restrict__ rp,
                                                       const int32_t* __restrict__ col, uint32_t* any) {
     __shared__ ArcRowLds L;
-    const int32_t e0 = (int32_t)(blockIdx.x * (int64_t)kArcTile), e1 = (int32_t)min((int64_t)e0 + kArcTile, m);
-    block_arc_rows(rp, n, e0, e1, L);
+    const int32_t e0 = tile_first(blockIdx.x), len = tile_arcs(e0, m);
+    block_arc_rows(rp, n, e0, len, L);
     bool drop = false;
-    for (int32_t e = e0 + threadIdx.x; e < e1; e += kArcBlk) {
-        const int32_t u = L.row[e - e0], w = col[e];
+    tile_each<kArcBlk>(threadIdx.x, len, [&](int32_t i) {
+        const int32_t e = e0 + i, u = L.row[i], w = col[e];
         drop = drop || w == u || (e > rp[u] && w == col[e - 1]);
-    }
+    });
     if (drop) *any = 1u;
 }
 
@@ -198,7 +198,7 @@ constexpr int kUfRounds = 3;
 __global__ void k_uf_hook(int32_t n, const int32_t* __restrict__ rp, const int32_t* __restrict__ col, int32_t* P) {
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += stride) {
-        const int32_t b = rp[u], e = min(rp[u + 1], b + kUfHook);
+        const int32_t b = rp[u], e = first_arcs(b, rp[u + 1], kUfHook);
         if (b >= e) continue;
         const int32_t r = ld_relaxed(&P[u]);
         for (int32_t i = b; i < e; ++i) {
@@ -615,7 +615,8 @@ __global__ void k_front_scatter(int32_t n, int32_t nf, const int32_t* __restrict
 
 // inv[orig[u]] = u
 __global__ void k_inverse(int32_t n, const int32_t* __restrict__ orig, int32_t* __restrict__ inv) {
-    for (int32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < n; u += gridDim.x * blockDim.x) inv[orig[u]] = u;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += stride) inv[orig[u]] = (int32_t)u;
 }
 
 // rows of the renumbered graph: row u is row orig[u] with every target
@@ -624,11 +625,11 @@ __global__ void k_relabel_rows(int32_t n, const int32_t* __restrict__ orig, cons
                                const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
                                const int32_t* __restrict__ nrp, int32_t* __restrict__ ncol) {
     const int lane = threadIdx.x & 63;
-    const int32_t waves = (int32_t)(gridDim.x * (blockDim.x / 64));
-    for (int32_t u = (int32_t)(blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64); u < n; u += waves) {
+    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / 64);
+    for (int64_t u = (int64_t)blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64; u < n; u += waves) {
         const int32_t o = orig[u];
         const int32_t b = rp[o], len = rp[o + 1] - b, dst = nrp[u];
-        for (int32_t j = lane; j < len; j += 64) ncol[dst + j] = inv[col[b + j]];
+        for (int64_t j = lane; j < len; j += 64) ncol[dst + j] = inv[col[b + j]];
     }
 }
 
@@ -651,7 +652,8 @@ __global__ void k_gather_rows(int32_t n, int width, const int32_t* __restrict__ 
 __global__ void k_relabel_nodes(int32_t n, const int32_t* __restrict__ orig, const uint32_t* __restrict__ deg,
                                 const uint32_t* __restrict__ x, uint32_t* __restrict__ ndeg, uint32_t* __restrict__ x0,
                                 uint32_t* __restrict__ x1) {
-    for (int32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < n; u += gridDim.x * blockDim.x) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += stride) {
         const int32_t v = orig[u];
         ndeg[u] = deg[v];
         x0[u] = x1[u] = x[v];
@@ -661,7 +663,8 @@ __global__ void k_relabel_nodes(int32_t n, const int32_t* __restrict__ orig, con
 // dst[u] = src[orig[u]] (caller's per-node floats into our numbering)
 __global__ void k_gather_f32(int32_t n, const int32_t* __restrict__ orig, const float* __restrict__ src,
                              float* __restrict__ dst) {
-    for (int32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < n; u += gridDim.x * blockDim.x) dst[u] = src[orig[u]];
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += stride) dst[u] = src[orig[u]];
 }
 
 // nodes of more than kPullWave in-arcs

@@ -1,0 +1,42 @@
+// Index arithmetic and rules of the kernels and their launches that need no
+// device builtin: plain C++, so that the tests run the same code on the CPU
+// (under the undefined-behaviour sanitizer) at sizes no test graph reaches.
+#pragma once
+
+#include <stdint.h>
+
+#if defined(__HIPCC__)
+#define BC_HD __host__ __device__ __forceinline__
+#else
+#define BC_HD inline
+#endif
+
+namespace bc {
+
+// ---- arcs dealt out in tiles
+//
+// Offsets and ids are int32 and go up to 2^31 - 2, so an index that steps by
+// more than one passes 2^31 - 1 behind the last arc of the largest graphs.
+// Loops over a tile therefore run over the arcs' positions in the tile, and
+// loops over a whole list in 64 bits.
+
+constexpr int kArcTile = 2048;  // consecutive arcs per workgroup of the arc kernels: 8 per thread
+
+BC_HD int64_t tile_count(int64_t m) { return (m + kArcTile - 1) / kArcTile; }
+BC_HD int32_t tile_first(int64_t tile) { return (int32_t)(tile * kArcTile); }
+// arcs in the tile whose first arc is e0 < m
+BC_HD int32_t tile_arcs(int32_t e0, int64_t m) { return (int32_t)(m - e0 < kArcTile ? m - e0 : kArcTile); }
+
+// The positions of a tile of `len` arcs that thread tid of kBlk takes.
+template <int kBlk, class F>
+BC_HD void tile_each(int32_t tid, int32_t len, F f) {
+    for (int32_t i = tid; i < len; i += kBlk) f(i);
+}
+
+// Distance of the 64 probes of a search over [lo, hi), lo < hi.
+BC_HD int32_t probe_step(int32_t lo, int32_t hi) { return (hi - lo - 1) / 64 + 1; }
+
+// The end of the first `most` arcs of the row [b, e).
+BC_HD int32_t first_arcs(int32_t b, int32_t e, int32_t most) { return e - b > most ? b + most : e; }
+
+}  // namespace bc

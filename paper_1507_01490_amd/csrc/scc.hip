@@ -68,12 +68,12 @@ __global__ __launch_bounds__(kArcBlk) void k_fill_in(int32_t n, int64_t m, const
                                                      const int32_t* __restrict__ col, const int32_t* __restrict__ irp,
                                                      int32_t* __restrict__ fill, int32_t* __restrict__ icol) {
     __shared__ ArcRowLds L;
-    const int32_t e0 = (int32_t)(blockIdx.x * (int64_t)kArcTile), e1 = (int32_t)min((int64_t)e0 + kArcTile, m);
-    block_arc_rows(rp, n, e0, e1, L);
-    for (int32_t e = e0 + threadIdx.x; e < e1; e += kArcBlk) {
-        const int32_t w = col[e];
-        icol[irp[w] + atomicAdd(&fill[w], 1)] = L.row[e - e0];
-    }
+    const int32_t e0 = tile_first(blockIdx.x), len = tile_arcs(e0, m);
+    block_arc_rows(rp, n, e0, len, L);
+    tile_each<kArcBlk>(threadIdx.x, len, [&](int32_t i) {
+        const int32_t w = col[e0 + i];
+        icol[irp[w] + atomicAdd(&fill[w], 1)] = L.row[i];
+    });
 }
 
 __global__ void k_fill_i32(int64_t n, int32_t* p, int32_t v) {
@@ -229,8 +229,8 @@ __global__ __launch_bounds__(kArcBlk) void k_dag_arcs(int32_t n, int64_t m, cons
                                                       uint64_t* __restrict__ keys, int32_t* cnt) {
     __shared__ ArcRowLds L;
     __shared__ uint32_t s_n, s_base;
-    const int32_t e0 = (int32_t)(blockIdx.x * (int64_t)kArcTile), e1 = (int32_t)min((int64_t)e0 + kArcTile, m);
-    block_arc_rows(rp, n, e0, e1, L);
+    const int32_t e0 = tile_first(blockIdx.x), len = tile_arcs(e0, m);
+    block_arc_rows(rp, n, e0, len, L);
     if (threadIdx.x == 0) s_n = 0;
     __syncthreads();
     constexpr int kPer = kArcTile / kArcBlk;
@@ -238,11 +238,11 @@ __global__ __launch_bounds__(kArcBlk) void k_dag_arcs(int32_t n, int64_t m, cons
     uint32_t pos[kPer];
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
-        const int32_t e = e0 + j * kArcBlk + (int32_t)threadIdx.x;
+        const int32_t i = j * kArcBlk + (int32_t)threadIdx.x;
         bool on = false;
         key[j] = 0;
-        if (e < e1) {
-            const int32_t cu = cid[L.row[e - e0]], cw = cid[col[e]];
+        if (i < len) {
+            const int32_t cu = cid[L.row[i]], cw = cid[col[e0 + i]];
             on = cu != cw;
             key[j] = ((uint64_t)(uint32_t)cu << 32) | (uint32_t)cw;
         }
@@ -391,8 +391,8 @@ __global__ __launch_bounds__(kBlk) void k_dag_mid(const int32_t* __restrict__ mi
         const int32_t end = drp[c + 1];
         DagSum A{0, 0, 0, 0};
         bool ready = true;
-        for (int32_t e0 = drp[c]; e0 < end && ready; e0 += 64) {
-            const int32_t e = e0 + lane;
+        for (int64_t e0 = drp[c]; e0 < end && ready; e0 += 64) {
+            const int64_t e = e0 + lane;
             bool ok = true;
             if (e < end) {
                 const int32_t d = dcol[e];

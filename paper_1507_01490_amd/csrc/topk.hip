@@ -2323,7 +2323,8 @@ __global__ __launch_bounds__(B) void k_jobs(JobLaunch L, SlotPtrs base, uint32_t
 
 // Node-id order 0 .. n-1 (any order gives the same answer, Section 2.1).
 __global__ void k_iota(int32_t* a, int32_t n) {
-    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) a[i] = i;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) a[i] = (int32_t)i;
 }
 
 // Zero `words` 8-byte words (the per-query state of a captured job launch:
