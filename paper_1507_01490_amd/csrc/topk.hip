@@ -4128,6 +4128,7 @@ void multi_stats(const QStats& h, double preprocess_ms, double query_ms, double 
     o2.m_vis = h.m_vis;
     o2.node_arcs = h.node_arcs;
     o2.levels = h.levels;
+    o2.pull_levels = h.pull_levels;
     o2.n_cut = h.n_cut;
     o2.n_done = h.n_done;
     o2.n_trivial = h.n_trivial;
