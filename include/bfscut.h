@@ -288,8 +288,8 @@ bc_status bc_topk(bc_graph* g, int32_t k, const bc_opts* opts, int32_t* ids, uin
  *   opts     NULL for the defaults; width (64, 128 or 256, shared by all
  *            queries), order (a rule applied to each graph: BC_ORDER_DEGREE,
  *            BC_ORDER_GROUPED (the default), BC_ORDER_LOCALITY or a learned
- *            order with opts.mlp), slots (workgroups, 0 = one per compute unit)
- *            and bounds (BC_BOUND_FOOTNOTE) apply; mode, seed_*, defer_*,
+ *            order with opts.mlp), slots (workgroups, 0 = one per compute unit),
+ *            pull_alpha, pull_beta and bounds (BC_BOUND_FOOTNOTE) apply; mode, seed_*, defer_*,
  *            lds_tables and graph_levels are ignored (every batch runs in the
  *            launch); BC_ORDER_GIVEN / BC_ORDER_SCORES and opts.first are
  *            rejected (BC_EINVAL)

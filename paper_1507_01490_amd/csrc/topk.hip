@@ -2035,7 +2035,7 @@ struct JobDesc {
     uint32_t bofs;             // local index of its first batch
     uint32_t total;            // batches of the whole query
     uint32_t seed;             // the query's first `seed` batches: the others wait (bounded) for them
-    uint32_t pad_;
+    LevelParams lp;            // its levels' direction
     uint32_t* ctr;             // device, 2 words: finished batches, finished seed batches
     Rec* out;                  // host-visible copy of the finished list (k records), or null
     unsigned long long* out_st;  // host-visible copy of the QStats words, or null
@@ -2132,6 +2132,10 @@ __device__ inline DevGraph uni_graph(const DevGraph& g) {
     o.heavy = uni_ptr(g.heavy);
     o.nheavy = uni_ptr(g.nheavy);
     return o;
+}
+__device__ inline LevelParams uni_params(const LevelParams& p) {
+    return LevelParams{__uint_as_float(uni32(__float_as_uint(p.pull_alpha))),
+                       __uint_as_float(uni32(__float_as_uint(p.pull_beta))), (int32_t)uni32((uint32_t)p.can_pull)};
 }
 __device__ inline TopKDev uni_topk(const TopKDev& t) {
     TopKDev o;
@@ -2272,7 +2276,7 @@ __global__ __launch_bounds__(B) void k_jobs(JobLaunch L, SlotPtrs base, uint32_t
         }
         __syncthreads();
         RecCounters K;
-        record_batch<WW, B>(G, order, L.W, b, P, T, st, nullptr, LevelParams{3.f, 24.f, 1}, R, stamp, K);
+        record_batch<WW, B>(G, order, L.W, b, P, T, st, nullptr, uni_params(J.lp), R, stamp, K);
         if (tid == 0) {
             atomicAdd(&st->levels, K.levels);
             if (K.pulls) atomicAdd(&st->pull_levels, K.pulls);
@@ -3570,6 +3574,11 @@ bc_status run_plain_batches(const DevGraph& G, const int32_t* ord, int32_t count
 // less than several narrow ones and holds more of the deepest sources) and
 // count (default ceil(k / sw), so that k sources complete before the
 // persistent phase and the k-th best value exists).
+// Direction of the levels as the options ask for it.
+LevelParams level_params(const bc_opts& o) {
+    return LevelParams{o.pull_alpha, o.pull_beta > 0.f ? o.pull_beta : 24.f, o.pull_alpha > 0.f ? 1 : 0};
+}
+
 struct SeedPlan {
     int sw;
     uint32_t batches;  // of width sw
@@ -3596,7 +3605,7 @@ bc_status run_ww(bc_graph* g, int32_t k, const bc_opts& o, const int32_t* d_orde
         sp = seed_plan(o, k, n, W);
         seed = (uint32_t)std::min<int64_t>((int64_t)sp.batches * (sp.sw / W), nbatches);
     }
-    LevelParams lp{o.pull_alpha, o.pull_beta > 0.f ? o.pull_beta : 24.f, o.pull_alpha > 0.f ? 1 : 0};
+    const LevelParams lp = level_params(o);
     const int cus = device_cus();
     if (Wk.ww != WW) {
         // a different width: drop buffers sized for the old one
@@ -4291,6 +4300,7 @@ bc_status multi_create(bc_graph* const* graphs, int32_t count, const int32_t* ks
         d.bofs = bofs;
         d.total = nb;
         d.seed = std::min<uint32_t>(nb, (uint32_t)((kq + W - 1) / W));
+        d.lp = level_params(o);
         d.out = nullptr;
         d.out_st = nullptr;
         d.done = nullptr;
@@ -4418,6 +4428,7 @@ struct QueueJob {
     uint32_t nb = 0, seed = 0;
     int32_t kk = 0;
     int32_t footnote = 0;
+    LevelParams lp{};
     bc_graph* g = nullptr;
     DevBuf order, ring, state;
 };
@@ -4592,6 +4603,7 @@ JobDesc job_desc(const DevQueue* q, const QueueJob* j, uint32_t bofs) {
     d.bofs = bofs;
     d.total = j->nb;
     d.seed = j->seed;
+    d.lp = j->lp;
     d.out = dev_view(q, q->out + (size_t)j->slot * kQueueMaxK);
     d.out_st = dev_view(q, q->out_st + (size_t)j->slot * (sizeof(QStats) / 8));
     d.done = dev_view(q, q->done + j->slot);
@@ -4680,6 +4692,7 @@ bc_status devq_submit(DevQueue* q, bc_graph* g, int32_t k, const bc_opts& o_in, 
     j->g = g;
     j->kk = std::min(k, n);
     j->footnote = (!g->dg.directed && (o_in.bounds & BC_BOUND_FOOTNOTE)) ? 1 : 0;
+    j->lp = level_params(o_in);
     bc_opts o = o_in;
     o.mode = BC_MODE_BATCHED;
     o.width = W;
