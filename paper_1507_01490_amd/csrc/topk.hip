@@ -3367,6 +3367,16 @@ struct LvHost {
     LvReport* host;
     bool mapped;
 };
+// Slots of one kind: a fixed array, since bc_topk_static runs this loop and
+// allocates nothing, on the host either.
+struct SlotList {
+    uint8_t id[kMaxSlots];
+    int len = 0;
+    void add(uint8_t i) { id[len++] = i; }
+    void add(const SlotList& o) {
+        for (int i = 0; i < o.len; ++i) add(o.id[i]);
+    }
+};
 
 template <int WW>
 bc_status lv_host_loop(const DevGraph& G, const int32_t* ord, int32_t count, uint32_t nb, LvSlots L, int slots,
@@ -3376,33 +3386,30 @@ bc_status lv_host_loop(const DevGraph& G, const int32_t* ord, int32_t count, uin
     const int32_t n = G.n;
     const int cus = device_cus();
     const unsigned long long narrow = check ? 0 : kNarrowArcs;
-    std::vector<uint8_t> act((size_t)slots), push, pull, clear;
-    for (int i = 0; i < slots; ++i) act[(size_t)i] = (uint8_t)i;
+    SlotList act;
+    for (int i = 0; i < slots; ++i) act.add((uint8_t)i);
     k_lv_start<<<1, 64, 0, s>>>(L.C, slots, next);
     // workgroups of one slot: `work` threads' worth, and all slots together at
     // most `per_cu` workgroups per compute unit
-    auto grid = [&](int64_t work, int blk, int per_cu, size_t y) {
-        int64_t b = (work + blk - 1) / blk, cap = std::max<int64_t>((int64_t)per_cu * cus / (int64_t)y, 1);
+    auto grid = [&](int64_t work, int blk, int per_cu, int y) {
+        int64_t b = (work + blk - 1) / blk, cap = std::max<int64_t>((int64_t)per_cu * cus / y, 1);
         return dim3((unsigned)std::min(std::max<int64_t>(b, 1), cap), (unsigned)y);
     };
-    auto only = [&](const std::vector<uint8_t>& v) {
+    auto only = [&](const SlotList& v) {
         LvSlots x = L;
-        std::memcpy(x.id, v.data(), v.size());
+        std::memcpy(x.id, v.id, (size_t)v.len);
         return x;
     };
-    while (!act.empty()) {
-        k_plain_run<WW><<<(unsigned)act.size(), kBatchBlk, 0, s>>>(G, ord, count, nb, W, only(act), next, T, d_st, lp,
+    while (act.len > 0) {
+        k_plain_run<WW><<<(unsigned)act.len, kBatchBlk, 0, s>>>(G, ord, count, nb, W, only(act), next, T, d_st, lp,
                                                                    narrow, H.dev);
         BC_HIP(hipGetLastError());
         if (!H.mapped)
-            BC_HIP(hipMemcpyAsync(H.host, H.dev, sizeof(LvReport) * act.size(), hipMemcpyDeviceToHost, s));
+            BC_HIP(hipMemcpyAsync(H.host, H.dev, sizeof(LvReport) * (size_t)act.len, hipMemcpyDeviceToHost, s));
         BC_HIP(hipStreamSynchronize(s));
-        push.clear();
-        pull.clear();
-        clear.clear();
+        SlotList push, pull, clear, left;
         unsigned long long push_arcs = 0, chunks = 0, flen = 0, clen = 0;
-        std::vector<uint8_t> left;
-        for (size_t i = 0; i < act.size(); ++i) {
+        for (int i = 0; i < act.len; ++i) {
             const LvReport& r = H.host[i];
             // every list holds distinct nodes, so no length can exceed n: a
             // longer one means the level step wrote out of order, and no
@@ -3412,47 +3419,47 @@ bc_status lv_host_loop(const DevGraph& G, const int32_t* ord, int32_t count, uin
                 return BC_EDEVICE;
             }
             if (r.state == LV_DONE) continue;
-            left.push_back(act[i]);
+            left.add(act.id[i]);
             if (check) {
-                const SlotPtrs P{nullptr, L.base.qa + act[i] * L.n, nullptr, L.base.clr + act[i] * L.n, nullptr, nullptr};
+                const SlotPtrs P{nullptr, L.base.qa + act.id[i] * L.n, nullptr, L.base.clr + act.id[i] * L.n, nullptr, nullptr};
                 BC_TRY(check_level_lists(P, r.flen, r.clen, n, r.d, s));
             }
             if (r.state == LV_CLEAR) {
-                clear.push_back(act[i]);
+                clear.add(act.id[i]);
                 clen = std::max<unsigned long long>(clen, r.clen);
                 continue;
             }
             flen = std::max<unsigned long long>(flen, r.flen);
             if (r.state == LV_PULL) {
-                pull.push_back(act[i]);
+                pull.add(act.id[i]);
             } else {
-                push.push_back(act[i]);
+                push.add(act.id[i]);
                 push_arcs = std::max(push_arcs, r.front_arcs);
                 const uint32_t per = expand_chunk(r.flen, r.front_arcs);
                 chunks = std::max<unsigned long long>(chunks, ((unsigned long long)r.flen + per - 1) / per);
             }
         }
-        act.swap(left);
-        if (!push.empty()) {
+        act = left;
+        if (push.len > 0) {
             // one workgroup per claimed chunk; new nodes <= arcs out of the frontier
-            k_plain_expand<WW><<<grid((int64_t)chunks * kLvBlk, kLvBlk, 2, push.size()), kLvBlk, 0, s>>>(G, only(push),
+            k_plain_expand<WW><<<grid((int64_t)chunks * kLvBlk, kLvBlk, 2, push.len), kLvBlk, 0, s>>>(G, only(push),
                                                                                                          d_st, 0);
             k_plain_count<WW><<<grid((int64_t)std::min<unsigned long long>(push_arcs, (unsigned long long)n), kLvBlk,
-                                     kLevelGrid, push.size()), kLvBlk, 0, s>>>(G, only(push), T, d_st, W, 0);
+                                     kLevelGrid, push.len), kLvBlk, 0, s>>>(G, only(push), T, d_st, W, 0);
         }
-        if (!pull.empty()) {
-            k_plain_pull<WW><<<grid(n, kLvBlk, kPullGrid, pull.size()), kLvBlk, 0, s>>>(G, only(pull), T, d_st, W, 0);
-            k_plain_clearcur<WW><<<grid((int64_t)flen, kBlk, 4 * kLevelGrid, pull.size()), kBlk, 0, s>>>(only(pull), 0);
+        if (pull.len > 0) {
+            k_plain_pull<WW><<<grid(n, kLvBlk, kPullGrid, pull.len), kLvBlk, 0, s>>>(G, only(pull), T, d_st, W, 0);
+            k_plain_clearcur<WW><<<grid((int64_t)flen, kBlk, 4 * kLevelGrid, pull.len), kBlk, 0, s>>>(only(pull), 0);
         }
-        if (!push.empty() || !pull.empty()) {
+        if (push.len + pull.len > 0) {
             // reached nodes <= arcs out of the frontier (push) or n (pull)
             const int64_t bound =
-                pull.empty() ? (int64_t)std::min<unsigned long long>(push_arcs, (unsigned long long)n) : (int64_t)n;
-            push.insert(push.end(), pull.begin(), pull.end());
-            k_plain_build<WW><<<grid(bound, kLvBlk, kLevelGrid, push.size()), kLvBlk, 0, s>>>(G, only(push), lp, 0);
+                pull.len == 0 ? (int64_t)std::min<unsigned long long>(push_arcs, (unsigned long long)n) : (int64_t)n;
+            push.add(pull);
+            k_plain_build<WW><<<grid(bound, kLvBlk, kLevelGrid, push.len), kLvBlk, 0, s>>>(G, only(push), lp, 0);
         }
-        if (!clear.empty())
-            k_plain_clear<WW><<<grid((int64_t)clen, kBlk, 4 * kLevelGrid, clear.size()), kBlk, 0, s>>>(only(clear));
+        if (clear.len > 0)
+            k_plain_clear<WW><<<grid((int64_t)clen, kBlk, 4 * kLevelGrid, clear.len), kBlk, 0, s>>>(only(clear));
         BC_HIP(hipGetLastError());
     }
     return BC_OK;
