@@ -17,7 +17,6 @@
 #include <utility>
 
 #include "bc_internal.h"
-#include "rules.h"
 
 namespace bc {
 

@@ -29,6 +29,7 @@
 #include <vector>
 
 #include "bfscut.h"
+#include "rules.h"
 
 namespace bc {
 

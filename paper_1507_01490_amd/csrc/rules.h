@@ -39,4 +39,15 @@ BC_HD int32_t probe_step(int32_t lo, int32_t hi) { return (hi - lo - 1) / 64 + 1
 // The end of the first `most` arcs of the row [b, e).
 BC_HD int32_t first_arcs(int32_t b, int32_t e, int32_t most) { return e - b > most ? b + most : e; }
 
+
+// ---- level-synchronous slots
+
+// The first of want, want / 2, ... 1 that `fits` takes, or 0 if it takes none.
+template <class Fits>
+inline int halve_until(int want, Fits fits) {
+    for (int k = want; k > 0; k /= 2)
+        if (fits(k)) return k;
+    return 0;
+}
+
 }  // namespace bc

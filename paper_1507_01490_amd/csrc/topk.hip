@@ -3254,12 +3254,14 @@ constexpr size_t lv_node_bytes() {
     return 24 * WW + (WW > 1 ? 4 : 0) + 12;
 }
 
-// `want` level-synchronous slots of WW words per node in the workspace, all
-// zero at rest (every batch resets the nodes it reached).
+// Up to *slots level-synchronous slots of WW words per node in the workspace,
+// all zero at rest (every batch resets the nodes it reached): as many as there
+// is memory for, which *slots then says.
 template <int WW>
-bc_status ensure_lv(Workspace& Wk, const DevGraph& G, int want, hipStream_t s, LvSlots* out) {
+bc_status ensure_lv(Workspace& Wk, const DevGraph& G, int* slots, hipStream_t s, LvSlots* out) {
     Workspace::Lv& V = Wk.lv[WW == 1 ? 0 : (WW == 2 ? 1 : 2)];
-    const size_t N = (size_t)G.n, K = (size_t)std::max(want, V.slots);
+    const int want = *slots;
+    const size_t N = (size_t)G.n, K = (size_t)want;
     if (V.slots < want) {
         V.mem.release();
         V.cmem.release();
@@ -3271,9 +3273,18 @@ bc_status ensure_lv(Workspace& Wk, const DevGraph& G, int want, hipStream_t s, L
         c.add(V.srcs, sizeof(SrcState) * kBlk * K);
         BC_TRY(c.place_on(V.cmem, s));
         BC_HIP(hipMemsetAsync(V.cmem.p, 0, zeroed, s));
-        BC_TRY(alloc_slots<WW>(slot_bufs(V), N, K, true, s));
-        V.slots = want;
+        bc_status rs = BC_OK;
+        V.slots = halve_until(want, [&](int k) {
+            rs = alloc_slots<WW>(slot_bufs(V), N, (size_t)k, true, s);
+            return rs != BC_ENOMEM;
+        });
+        if (rs != BC_OK) {
+            V.mem.release();
+            V.slots = 0;
+            return rs;
+        }
     }
+    *slots = std::min(want, V.slots);
     if (!Wk.hctl) BC_HIP(hipHostMalloc((void**)&Wk.hctl, sizeof(LvReport) * kMaxSlots, hipHostMallocMapped));
     std::memset(out, 0, sizeof(*out));
     out->base = slots_of(slot_bufs(V), 64 * WW);
@@ -3479,7 +3490,7 @@ bc_status run_plain_batches(const DevGraph& G, const int32_t* ord, int32_t count
     const int cus = device_cus();
     slots = graph_levels == 0 ? (int)std::min<uint32_t>((uint32_t)std::max(slots, 1), nb) : 1;
     LvSlots L;
-    BC_TRY(ensure_lv<WW>(Wk, G, slots, s, &L));
+    BC_TRY(ensure_lv<WW>(Wk, G, &slots, s, &L));
     Ctl* C = L.C;
     const int cgrid = graph_levels == -1 ? coop_grid<WW>() : 0;
     if (graph_levels == -1 && cgrid == 0) {

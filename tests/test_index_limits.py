@@ -16,6 +16,7 @@ PROGRAM = r"""
 #include "rules.h"
 #include <cassert>
 #include <cstdio>
+#include <initializer_list>
 #include <vector>
 using namespace bc;
 
