@@ -3266,6 +3266,15 @@ bc_status ensure_lv(Workspace& Wk, const DevGraph& G, int* slots, hipStream_t s,
         V.mem.release();
         V.cmem.release();
         V.slots = 0;
+        // the slots of the three widths together stay within kLvBytes (or the
+        // one slot that is larger): a workspace is kept with its graph
+        size_t held = N * K * lv_node_bytes<WW>();
+        for (Workspace::Lv& o : Wk.lv) held += o.mem.bytes;
+        if (held > kLvBytes)
+            for (Workspace::Lv& o : Wk.lv) {
+                o.mem.release();
+                o.slots = 0;
+            }
         Carve c;
         c.add(V.ctl, sizeof(Ctl) * K);
         c.add(V.next, sizeof(uint32_t));
