@@ -55,7 +55,8 @@ bc_status graph_create(int32_t n, int64_t m, const int32_t* row_ptr, const int32
     // small graphs keep their numbering: their node records stay in the
     // caches anyway, and the second build would dominate their upload
     const bool relabel = !(flags & (BC_DIRECTED | BC_KEEP_IDS)) && n >= kRelabelMinNodes;
-    g->ordered = ordered || relabel;  // the first build of a renumbered graph lasts as long as this call
+    // the first build of a renumbered graph lasts as long as this call
+    g->ordered = ordered || (relabel && pooled_first_build(n, m));
     (void)hipGetDevice(&g->device);
     bc_status s = graph_build(g.get(), n, m, row_ptr, col, flags & ~(uint32_t)BC_KEEP_IDS);
     if (s != BC_OK) {

@@ -40,6 +40,15 @@ BC_HD int32_t probe_step(int32_t lo, int32_t hi) { return (hi - lo - 1) / 64 + 1
 BC_HD int32_t first_arcs(int32_t b, int32_t e, int32_t most) { return e - b > most ? b + most : e; }
 
 
+// ---- uploads
+
+// Whether the first build of a renumbered graph (n nodes, at most m arcs),
+// which ends with the upload, comes from the stream-ordered pool.  The pool
+// never gives memory back, and later calls size their slots by what is free,
+// so only up to 1 GiB of it does: there new memory (0.1 ms a MB) and the free
+// of a plain allocation (250 us) would take longer than the build's kernels.
+BC_HD bool pooled_first_build(int64_t n, int64_t m) { return 12 * m + 16 * n <= (int64_t)1 << 30; }
+
 // ---- level-synchronous slots
 
 // The first of want, want / 2, ... 1 that `fits` takes, or 0 if it takes none.

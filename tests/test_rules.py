@@ -31,3 +31,15 @@ def test_slots_shrink_to_what_fits(tmp_path):
             assert(got == 0 || got == want || 2 * got + 1 >= room);
         }
     """)
+
+
+def test_only_small_first_builds_stay_in_the_pool(tmp_path):
+    """12 bytes an arc and 16 a node of the first build: the pool keeps at most 1 GiB of them."""
+    run(tmp_path, r"""
+    const int64_t gib = (int64_t)1 << 30;
+    assert(pooled_first_build(100000, 0) && pooled_first_build(300000, 5700000));
+    for (int64_t n : {(int64_t)100000, (int64_t)4000000, (int64_t)2147483646})
+        for (int64_t m : {(int64_t)0, (int64_t)89000000, (int64_t)90000000, (int64_t)2147483646})
+            assert(pooled_first_build(n, m) == (12 * m + 16 * n <= gib));
+    assert(!pooled_first_build(2147483646, 2147483646) && !pooled_first_build(500000, 180000000));
+    """)
