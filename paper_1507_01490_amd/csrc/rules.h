@@ -51,6 +51,40 @@ BC_HD bool pooled_first_build(int64_t n, int64_t m) { return 12 * m + 16 * n <= 
 
 // ---- level-synchronous slots
 
+// Bytes per node of a slot of W = 64 WW sources: seen and nxt, cur, stamp (WW >
+// 1), three lists.
+constexpr uint64_t slot_node_bytes(int W) { return 24 * (uint64_t)(W / 64) + (W > 64 ? 4 : 0) + 12; }
+
+constexpr uint64_t kLvBytes = (uint64_t)1 << 30;  // of their slots, unless one alone needs more
+constexpr int kMaxSlots = 32;                     // batches the level-synchronous kernels run side by side
+constexpr uint64_t kLvCtlBytes = 18 << 10;        // of a slot's control block and sources
+
+// Slots for `batches` batches within `room` bytes: a power of two (so that
+// graphs of a size ask the pool for the same bytes), at most kLvBytes: eight
+// batches fill the GPU on a graph whose slot takes 100 MB, and new memory
+// costs 0.1 ms a MB.
+inline int lv_slots(uint64_t batches, uint64_t slot_bytes, uint64_t room) {
+    if (room > kLvBytes) room = kLvBytes;
+    int lv = 1;
+    while (lv < kMaxSlots && (uint64_t)lv < batches && 2 * (uint64_t)lv * slot_bytes <= room) lv *= 2;
+    return lv;
+}
+
+// Width and number of the seed batches of a query (k results, n nodes, W
+// sources per batch) for the options seed_width (0: automatic) and
+// seed_batches (negative: enough for k sources).
+struct SeedPlan {
+    int sw;
+    uint32_t batches;  // of width sw
+};
+inline SeedPlan seed_plan(int32_t seed_width, int32_t seed_batches, int32_t k, int32_t n, int W) {
+    int sw = seed_width > 0 ? seed_width : (k > W ? 256 : W);
+    if (sw < W || sw % W != 0) sw = W;
+    const int64_t nb = ((int64_t)n + sw - 1) / sw;
+    const int64_t sb = seed_batches >= 0 ? seed_batches : ((int64_t)k + sw - 1) / sw;
+    return SeedPlan{sw, (uint32_t)(sb < nb ? sb : nb)};
+}
+
 // The first of want, want / 2, ... 1 that `fits` takes, or 0 if it takes none.
 template <class Fits>
 inline int halve_until(int want, Fits fits) {

@@ -39,9 +39,32 @@
 
 namespace bc {
 
+// The most a query's slots take at one time: the seed batches' slot stays while
+// the persistent slots run; those then make room for the slots of the deferred
+// sources (whose number, and so the width of their batches, is not known
+// before).
+static uint64_t slots_peak(uint64_t N, int W, uint64_t sl, int32_t k, const bc_opts& o) {
+    if (o.mode != BC_MODE_BATCHED) return N * slot_node_bytes(W) + kLvCtlBytes;
+    const int32_t kk = (int32_t)std::min<uint64_t>((uint64_t)std::max(k, 1), N);
+    const SeedPlan sp = seed_plan(o.seed_width, o.seed_batches, kk, (int32_t)N, W);
+    const uint64_t seed = sp.batches > 0 ? N * slot_node_bytes(sp.sw) + kLvCtlBytes : 0;
+    const uint64_t pers = sl * N * slot_node_bytes(W);
+    uint64_t most = pers;
+    for (int dw : {64, 128, 256}) {
+        if (o.defer_arcs < 0 || (o.defer_width > 0 && dw != o.defer_width)) continue;
+        if (o.defer_width <= 0 && dw == 256 && N <= 128) continue;  // fewer sources than a narrower batch holds
+        if (o.defer_width <= 0 && dw == 128 && N <= 64) continue;
+        const uint64_t slot = N * slot_node_bytes(dw), lv = (uint64_t)lv_slots((N + dw - 1) / dw, slot, pers);
+        most = std::max(most, lv * (slot + kLvCtlBytes));
+    }
+    return seed + most;
+}
+
 // Bytes a graph holds while resident, the transient bytes of its upload,
 // and the working memory of one query (an upper estimate: every buffer the
-// query path allocates, at its largest).
+// query path allocates, at its largest).  The list of nodes of many in-arcs,
+// 4 bytes for each 65 arcs at most and kept with the graph, is counted with
+// the queries on it.
 void footprint(int32_t n, int64_t m, bool directed, int32_t k, const bc_opts& o, int32_t slots,
                uint64_t* graph_bytes, uint64_t* upload_bytes, uint64_t* query_bytes) {
     const uint64_t N = (uint64_t)(n > 0 ? n : 0), M = (uint64_t)(m > 0 ? m : 0);
@@ -57,6 +80,8 @@ void footprint(int32_t n, int64_t m, bool directed, int32_t k, const bc_opts& o,
     uint64_t ub = 12 * M + 40 * N + (1u << 20);
     if (!directed && N >= 100000) ub += gb + 16 * N + 4 * M;
     const int W = o.width == 128 || o.width == 256 ? o.width : 64;
+    // a slot is charged as a padded record (32, 64 or 128 B) and three lists per
+    // node; slots_peak says what all of them take
     const uint64_t SW = W == 64 ? 4 : (W == 128 ? 8 : 16);
     const uint64_t per_slot = N * (8 * SW + 12);
     const uint64_t nb = (N + (uint64_t)W - 1) / (uint64_t)W;
@@ -67,11 +92,16 @@ void footprint(int32_t n, int64_t m, bool directed, int32_t k, const bc_opts& o,
     uint64_t qb = 4 * N                     // order
                   + 24 * (N + 1)            // threshold records
                   + 64 + 32 * kk            // top-k list
-                  + 4096                    // statistics, control blocks
-                  + per_slot + 32 * 256     // level-synchronous slot
+                  + 4096                    // statistics
+                  + per_slot                // level-synchronous slot
+                  + 3 * kLvCtlBytes         // control blocks and sources
+                  + 4 * heavy_nodes((int64_t)M)
                   + 4 * N + 64              // deferred sources
                   + 24 * N;                 // order sort temporaries
     if (o.mode == BC_MODE_BATCHED) qb += sl * per_slot + 4 * sl;
+    const uint64_t peak = slots_peak(N, W, sl, k, o);
+    const uint64_t charged = per_slot + 3 * kLvCtlBytes + (o.mode == BC_MODE_BATCHED ? sl * per_slot : 0);
+    if (peak > charged) qb += peak - charged;
     if (o.order == BC_ORDER_LEARNED || o.order == BC_ORDER_LEARNED_GROUPED) qb += 8 * N + 4 * BC_MLP_PARAMS + 16 * N;
     *graph_bytes = gb;
     *upload_bytes = ub;
@@ -373,8 +403,7 @@ bc_status ensure_queue(bc_server* S) {
         for (auto& G : S->graphs) ncap = std::max(ncap, G->n);
     }
     // at most half the budget for the queue's node records
-    const uint64_t SW = S->queue_width == 64 ? 4 : (S->queue_width == 128 ? 8 : 16);
-    const uint64_t per_slot = (uint64_t)std::max(ncap, 1) * (8 * SW + 12) + 4;
+    const uint64_t per_slot = (uint64_t)std::max(ncap, 1) * slot_node_bytes(S->queue_width) + 4;
     int slots = S->queue_slots;
     if (slots <= 0) {
         int dev = 0, cus = 0;

@@ -159,9 +159,8 @@ struct LvReport {  // one per slot, in pinned host memory
     unsigned long long front_arcs, pad_;
 };
 static_assert(sizeof(LvReport) == 32, "one report per 32 bytes");
+static_assert(sizeof(Ctl) + sizeof(SrcState) * kBlk <= kLvCtlBytes, "the serving estimate counts them so");
 
-constexpr size_t kLvBytes = (size_t)1 << 30;  // of their slots, unless one alone needs more
-constexpr int kMaxSlots = 32;  // batches the level-synchronous kernels run side by side
 // The slots a level-synchronous launch works on: gridDim.y of them, blockIdx.y
 // picks one.
 struct LvSlots {
@@ -3248,12 +3247,6 @@ SlotBufs slot_bufs(T& x) {
     return SlotBufs{x.mem, x.ns, x.cur, x.stamp, x.qa, x.qb, x.clr};
 }
 
-// Bytes per node of a slot: seen and nxt, cur, stamp, lists.
-template <int WW>
-constexpr size_t lv_node_bytes() {
-    return 24 * WW + (WW > 1 ? 4 : 0) + 12;
-}
-
 // Up to *slots level-synchronous slots of WW words per node in the workspace,
 // all zero at rest (every batch resets the nodes it reached): as many as there
 // is memory for, which *slots then says.
@@ -3268,7 +3261,7 @@ bc_status ensure_lv(Workspace& Wk, const DevGraph& G, int* slots, hipStream_t s,
         V.slots = 0;
         // the slots of the three widths together stay within kLvBytes (or the
         // one slot that is larger): a workspace is kept with its graph
-        size_t held = N * K * lv_node_bytes<WW>();
+        size_t held = N * K * slot_node_bytes(64 * WW);
         for (Workspace::Lv& o : Wk.lv) held += o.mem.bytes;
         if (held > kLvBytes)
             for (Workspace::Lv& o : Wk.lv) {
@@ -3606,18 +3599,6 @@ LevelParams level_params(const bc_opts& o) {
     return LevelParams{o.pull_alpha, o.pull_beta > 0.f ? o.pull_beta : 24.f, o.pull_alpha > 0.f ? 1 : 0};
 }
 
-struct SeedPlan {
-    int sw;
-    uint32_t batches;  // of width sw
-};
-SeedPlan seed_plan(const bc_opts& o, int32_t k, int32_t n, int W) {
-    int sw = o.seed_width > 0 ? o.seed_width : (k > W ? 256 : W);
-    if (sw < W || sw % W != 0) sw = W;
-    const int64_t nb = ((int64_t)n + sw - 1) / sw;
-    const int64_t sb = o.seed_batches >= 0 ? o.seed_batches : ((int64_t)k + sw - 1) / sw;
-    return SeedPlan{sw, (uint32_t)std::min<int64_t>(std::max<int64_t>(sb, 0), nb)};
-}
-
 template <int WW>
 bc_status run_ww(bc_graph* g, int32_t k, const bc_opts& o, const int32_t* d_order, TopKDev T, QStats* d_st,
                  Workspace& Wk, int W, Timing& tm, hipStream_t s, bool private_ws) {
@@ -3629,7 +3610,7 @@ bc_status run_ww(bc_graph* g, int32_t k, const bc_opts& o, const int32_t* d_orde
     uint32_t seed = nbatches;  // first batch (of width W) of the persistent phase
     SeedPlan sp{W, 0};
     if (batched) {
-        sp = seed_plan(o, k, n, W);
+        sp = seed_plan(o.seed_width, o.seed_batches, k, n, W);
         seed = (uint32_t)std::min<int64_t>((int64_t)sp.batches * (sp.sw / W), nbatches);
     }
     const LevelParams lp = level_params(o);
@@ -3656,7 +3637,7 @@ bc_status run_ww(bc_graph* g, int32_t k, const bc_opts& o, const int32_t* d_orde
 
     if (batched && seed < nbatches) {
         int slots = o.slots > 0 ? o.slots : cus;
-        const size_t per_slot = N * lv_node_bytes<WW>();
+        const size_t per_slot = N * slot_node_bytes(64 * WW);
         size_t freeb = 0, totalb = 0;
         if (Wk.slots < slots && hipMemGetInfo(&freeb, &totalb) == hipSuccess && per_slot > 0) {
             const size_t have = (size_t)Wk.slots * per_slot;
@@ -3716,7 +3697,7 @@ bc_status run_ww(bc_graph* g, int32_t k, const bc_opts& o, const int32_t* d_orde
             // their batches side by side, a level of each per launch, on as
             // many slots as memory allows: a query whose workspace ends with it
             // gives up its persistent slots for them
-            const size_t node = dw == 64 ? lv_node_bytes<1>() : (dw == 128 ? lv_node_bytes<2>() : lv_node_bytes<4>());
+            const size_t node = slot_node_bytes(dw);
             size_t room = 0;
             if (private_ws) {
                 room = (size_t)Wk.slots * per_slot;
@@ -3725,12 +3706,7 @@ bc_status run_ww(bc_graph* g, int32_t k, const bc_opts& o, const int32_t* d_orde
             } else if (hipMemGetInfo(&freeb, &totalb) == hipSuccess) {
                 room = (size_t)(0.45 * (double)freeb);
             }
-            // a power of two (so that graphs of a size ask the pool for the
-            // same bytes), at most kLvBytes: eight batches fill the GPU on a
-            // graph whose slot takes 100 MB, and new memory costs 0.1 ms a MB
-            room = std::min(room, kLvBytes);
-            int lv = 1;
-            while (lv < kMaxSlots && (uint32_t)lv < dnb && 2 * (size_t)lv * node * N <= room) lv *= 2;
+            const int lv = lv_slots(dnb, node * N, room);
             BC_TRY(run_plain(dw, dl, (int32_t)ndef, dnb, &tm.defer_ms, lv));
         }
     }
@@ -3943,7 +3919,7 @@ bc_status build_order(bc_graph* g, const bc_opts& o, int32_t kk, int32_t* d_orde
             BC_TRY(order_learned(g, o.mlp, d_order, s));
         } else if (ord == BC_ORDER_LEARNED_LOCALITY) {
             // the k best-scored sources, then the locality order without them
-            const SeedPlan sp = seed_plan(o, kk, n, W);
+            const SeedPlan sp = seed_plan(o.seed_width, o.seed_batches, kk, n, W);
             const int64_t head =
                 std::min<int64_t>((int64_t)n, std::min<int64_t>((int64_t)sp.batches * sp.sw, (int64_t)kk));
             DevBuf bys;
@@ -3957,7 +3933,7 @@ bc_status build_order(bc_graph* g, const bc_opts& o, int32_t kk, int32_t* d_orde
             BC_TRY(order_locality(g, W, d_order, s));
             if (head > 0) BC_TRY(order_front(g, h.data(), (int32_t)head, d_order, s, false));
         } else {
-            const SeedPlan sp = seed_plan(o, kk, n, W);
+            const SeedPlan sp = seed_plan(o.seed_width, o.seed_batches, kk, n, W);
             // the k best-scored sources first (the predicted top-k), then the
             // grouped order, which fills the rest of the seed batches with the
             // highest-degree nodes
@@ -4360,7 +4336,7 @@ bc_status multi_create(bc_graph* const* graphs, int32_t count, const int32_t* ks
     int slots = o.slots > 0 ? o.slots : device_cus();
     if ((unsigned long long)slots > p->nbatch) slots = (int)std::max<unsigned long long>(p->nbatch, 1);
     const size_t N = (size_t)std::max(p->ncap, 1);
-    const size_t per_slot = N * (W == 64 ? lv_node_bytes<1>() : (W == 128 ? lv_node_bytes<2>() : lv_node_bytes<4>()));
+    const size_t per_slot = N * slot_node_bytes(W);
     size_t freeb = 0, totalb = 0;
     if (hipMemGetInfo(&freeb, &totalb) == hipSuccess) {
         const size_t capn = (size_t)(0.45 * (double)freeb) / per_slot;
