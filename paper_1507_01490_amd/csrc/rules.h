@@ -40,6 +40,18 @@ BC_HD int32_t probe_step(int32_t lo, int32_t hi) { return (hi - lo - 1) / 64 + 1
 BC_HD int32_t first_arcs(int32_t b, int32_t e, int32_t most) { return e - b > most ? b + most : e; }
 
 
+// ---- direction of the levels
+
+// Whether the next level runs bottom up: from m / alpha frontier arcs on (alpha
+// = 0: never), and until the frontier holds less than n / beta nodes.  Written
+// as products: two quotients cost 0.3 us a level in the persistent kernels.
+BC_HD uint32_t next_direction(uint32_t pull, uint64_t arcs, uint32_t nodes, int64_t n, int64_t m, float alpha,
+                              float beta) {
+    if (!pull && alpha > 0.f && (double)arcs * alpha > (double)m) return 1;
+    if (pull && (double)nodes * beta < (double)n) return 0;
+    return pull;
+}
+
 // ---- uploads
 
 // Whether the first build of a renumbered graph (n nodes, at most m arcs),

@@ -252,6 +252,29 @@ __device__ inline bool cut_rule(const SrcState& s, uint32_t d, const ThRec& th) 
 
 __device__ inline uint32_t lane_id() { return __lane_id(); }
 
+// Sum over the wave, in every lane.  Converged wave.  (The compiler turns an
+// atomic on LDS by every lane into a loop over the 64 lanes, 1.7 us; as the end
+// of build_level it made a level of a job launch on a cycle of 6,000 nodes 9.2 us
+// at W = 64, with this sum 6.9.)
+template <int kCtrl>
+__device__ __forceinline__ uint64_t dpp_add64(uint64_t x) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, kCtrl, 15, 15, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), kCtrl, 15, 15, true);
+    return x + ((uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ uint64_t wave_sum64(uint64_t x) {
+    x = dpp_add64<0x111>(x);  // row_shr 1, 2, 4, 8: lane 15 of each row of 16 holds the row's sum
+    x = dpp_add64<0x112>(x);
+    x = dpp_add64<0x114>(x);
+    x = dpp_add64<0x118>(x);
+    uint64_t sum = 0;
+#pragma unroll
+    for (int l = 15; l < 64; l += 16)
+        sum += (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), l) << 32 |
+               (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, l);
+    return sum;
+}
+
 // The thread's index, opaque: what a phase derives from it (LDS and slot
 // addresses) is not kept in registers across the levels of a persistent
 // kernel, where it spilled.
@@ -745,6 +768,7 @@ __device__ void build_level(const SlotPtrs& P, const int32_t* N, uint32_t len, u
                     else nb[r] = __hip_atomic_load(&rec[WW], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
             }
+            const uint32_t deg = w < 0 ? 0u : degs[w];  // before the stores: a load behind them waits for them
             bool pn[WW], po[WW];
 #pragma unroll
             for (int r = 0; r < WW; ++r) {
@@ -763,7 +787,7 @@ __device__ void build_level(const SlotPtrs& P, const int32_t* N, uint32_t len, u
             const bool before = group_any<WW>(po);  // every lane takes part
             fresh = keep && !before;
             if (keep) {
-                my_arcs += degs[w];
+                my_arcs += deg;
                 if (seen_filter) filter_set(seen_filter, w);
             }
         }
@@ -777,7 +801,8 @@ __device__ void build_level(const SlotPtrs& P, const int32_t* N, uint32_t len, u
             }
         }
     }
-    if (my_arcs) atomicAdd(arcs, my_arcs);
+    my_arcs = wave_sum64(my_arcs);
+    if (lane_id() == 0 && my_arcs) atomicAdd(arcs, my_arcs);
 }
 
 // The per-level decision for the W sources of a batch (first W threads of one
@@ -1159,13 +1184,10 @@ constexpr int kLvBlk = 1024;  // threads per workgroup: few, large workgroups, s
 // Direction of the next level from the frontier's arcs and nodes.
 __device__ inline uint32_t next_pull(uint32_t pull, unsigned long long fa, uint32_t flen, const DevGraph& G,
                                      const LevelParams& lp) {
-    if (lp.can_pull) {
-        uint64_t n = uni64((uint64_t)G.n), m = uni64((uint64_t)G.m);
-        asm volatile("" : "+s"(n), "+s"(m));  // the quotients are not kept across the levels
-        if (!pull && lp.pull_alpha > 0.f && (double)fa > (double)(int64_t)m / lp.pull_alpha) return 1;
-        if (pull && (double)flen < (double)(int64_t)n / lp.pull_beta) return 0;
-    }
-    return pull;
+    if (!lp.can_pull) return pull;
+    uint64_t n = uni64((uint64_t)G.n), m = uni64((uint64_t)G.m);
+    asm volatile("" : "+s"(n), "+s"(m));  // their conversions are not kept across the levels
+    return next_direction(pull, fa, flen, (int64_t)n, (int64_t)m, lp.pull_alpha, lp.pull_beta);
 }
 
 template <int WW>

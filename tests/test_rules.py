@@ -43,3 +43,25 @@ def test_only_small_first_builds_stay_in_the_pool(tmp_path):
             assert(pooled_first_build(n, m) == (12 * m + 16 * n <= gib));
     assert(!pooled_first_build(2147483646, 2147483646) && !pooled_first_build(500000, 180000000));
     """)
+
+
+def test_direction_of_the_levels(tmp_path):
+    """Bottom up from m / alpha frontier arcs on, top down below n / beta nodes."""
+    run(tmp_path, r"""
+    const int64_t n = 1000, m = 6000;
+    for (uint64_t arcs = 0; arcs <= 6000; arcs += 1) {
+        assert(next_direction(0, arcs, 10, n, m, 3.f, 24.f) == (arcs > 2000));
+        assert(next_direction(0, arcs, 10, n, m, 2.f, 24.f) == (arcs > 3000));
+        assert(next_direction(0, arcs, 10, n, m, 0.f, 24.f) == 0);
+        assert(next_direction(0, arcs, 10, n, m, -1.f, 24.f) == 0);
+        assert(next_direction(0, arcs, 10, n, m, 1e9f, 1e9f) == (arcs > 0));
+    }
+    for (uint32_t nodes = 0; nodes <= 1000; ++nodes) {
+        assert(next_direction(1, 0, nodes, n, m, 3.f, 20.f) == (nodes >= 50));
+        assert(next_direction(1, 0, nodes, n, m, 3.f, 1e-9f) == 0);
+        assert(next_direction(1, 0, nodes, n, m, 3.f, 1e9f) == (nodes > 0));
+    }
+    const int64_t top = 2147483646;
+    assert(next_direction(0, (uint64_t)top, 1, top, top, 1.5f, 24.f) == 1);
+    assert(next_direction(0, (uint64_t)top, 1, top, top, 1.f, 24.f) == 0);
+    """)
