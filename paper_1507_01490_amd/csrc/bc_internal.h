@@ -55,6 +55,7 @@ struct DevGraph {
     int32_t n;
     int64_t m;
     int32_t directed;
+    int32_t heavy_count;      // *nheavy, for the launches
     const int32_t* rp;
     const int32_t* col;
     const int32_t* irp;

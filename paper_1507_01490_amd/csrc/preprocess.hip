@@ -679,6 +679,7 @@ __global__ void k_heavy_nodes(int32_t n, const int32_t* __restrict__ irp, int32_
     }
 }
 
+// (dg.heavy_count is set once the stream has been waited for)
 bc_status heavy_list(bc_graph* g, hipStream_t s) {
     BC_HIP(hipMemsetAsync(g->nheavy.p, 0, sizeof(uint32_t), s));
     if (g->dg.n > 0)
@@ -686,6 +687,7 @@ bc_status heavy_list(bc_graph* g, hipStream_t s) {
                                                         g->nheavy.as<uint32_t>());
     g->dg.heavy = g->heavy.as<int32_t>();
     g->dg.nheavy = g->nheavy.as<uint32_t>();
+    BC_HIP(hipMemcpyAsync(&g->dg.heavy_count, g->nheavy.p, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     return BC_OK;
 }
 

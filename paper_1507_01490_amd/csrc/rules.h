@@ -52,6 +52,12 @@ BC_HD uint32_t next_direction(uint32_t pull, uint64_t arcs, uint32_t nodes, int6
     return pull;
 }
 
+// Threads a bottom-up step has work for: one per node, and a wave for each of
+// the `heavy` nodes of many in-arcs, which outnumber the others' waves on a
+// dense graph (3,000 nodes of 600 arcs: 3 workgroups by the nodes alone, the
+// seed batch of a query 0.34 ms; 188 by the heavy ones, 0.14 ms).
+BC_HD int64_t pull_threads(int64_t n, int64_t heavy) { return heavy * 64 > n ? heavy * 64 : n; }
+
 // ---- uploads
 
 // Whether the first build of a renumbered graph (n nodes, at most m arcs),

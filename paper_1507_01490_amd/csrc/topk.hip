@@ -2141,6 +2141,7 @@ __device__ inline DevGraph uni_graph(const DevGraph& g) {
     o.n = (int32_t)uni32((uint32_t)g.n);
     o.m = (int64_t)uni64((uint64_t)g.m);
     o.directed = (int32_t)uni32((uint32_t)g.directed);
+    o.heavy_count = (int32_t)uni32((uint32_t)g.heavy_count);
     o.rp = uni_ptr(g.rp);
     o.col = uni_ptr(g.col);
     o.irp = uni_ptr(g.irp);
@@ -3483,7 +3484,8 @@ bc_status lv_host_loop(const DevGraph& G, const int32_t* ord, int32_t count, uin
                                      kLevelGrid, push.len), kLvBlk, 0, s>>>(G, only(push), T, d_st, W, 0);
         }
         if (pull.len > 0) {
-            k_plain_pull<WW><<<grid(n, kLvBlk, kPullGrid, pull.len), kLvBlk, 0, s>>>(G, only(pull), T, d_st, W, 0);
+            k_plain_pull<WW><<<grid(pull_threads(n, G.heavy_count), kLvBlk, kPullGrid, pull.len), kLvBlk, 0, s>>>(
+                G, only(pull), T, d_st, W, 0);
             k_plain_clearcur<WW><<<grid((int64_t)flen, kBlk, 4 * kLevelGrid, pull.len), kBlk, 0, s>>>(only(pull), 0);
         }
         if (push.len + pull.len > 0) {
@@ -3573,7 +3575,8 @@ bc_status run_plain_batches(const DevGraph& G, const int32_t* ord, int32_t count
     for (int l = 0; l < graph_levels; ++l) {
         k_plain_expand<WW><<<2 * cus, kLvBlk, 0, Wk.cap>>>(G, L, d_st, 1);
         k_plain_count<WW><<<kLevelGrid * cus, kLvBlk, 0, Wk.cap>>>(G, L, T, d_st, W, 1);
-        k_plain_pull<WW><<<clamp_grid(n, kPullGrid * cus), kLvBlk, 0, Wk.cap>>>(G, L, T, d_st, W, 1);
+        k_plain_pull<WW><<<clamp_grid(std::max<int64_t>(n, pull_threads(n, G.heavy_count) / 4), kPullGrid * cus), kLvBlk,
+                           0, Wk.cap>>>(G, L, T, d_st, W, 1);
         k_plain_clearcur<WW><<<4 * cus, kBlk, 0, Wk.cap>>>(L, 1);
         k_plain_build<WW><<<kLevelGrid * cus, kLvBlk, 0, Wk.cap>>>(G, L, lp, 1);
     }

@@ -65,3 +65,11 @@ def test_direction_of_the_levels(tmp_path):
     assert(next_direction(0, (uint64_t)top, 1, top, top, 1.5f, 24.f) == 1);
     assert(next_direction(0, (uint64_t)top, 1, top, top, 1.f, 24.f) == 0);
     """)
+
+
+def test_a_bottom_up_step_has_a_wave_per_heavy_node(tmp_path):
+    run(tmp_path, r"""
+    assert(pull_threads(3000, 0) == 3000 && pull_threads(3000, 3000) == 192000);
+    assert(pull_threads(6400, 100) == 6400 && pull_threads(6400, 101) == 6464);
+    assert(pull_threads(2147483646, 33038209) == 2147483646 && pull_threads(40000000, 33038209) == 2114445376);
+    """)
