@@ -1181,13 +1181,16 @@ __device__ void init_batch(const DevGraph& G, const int32_t* order, int32_t n, u
 constexpr int kLvBlk = 1024;  // threads per workgroup: few, large workgroups, since each ends in up to
                               // 512 device-wide atomics (the level's counters; see WaveStage for their cost)
 
-// Direction of the next level from the frontier's arcs and nodes.
+// Direction of the next level from the frontier's arcs and nodes.  kBlock: the
+// level is one workgroup's.
+template <bool kBlock = false>
 __device__ inline uint32_t next_pull(uint32_t pull, unsigned long long fa, uint32_t flen, const DevGraph& G,
                                      const LevelParams& lp) {
     if (!lp.can_pull) return pull;
     uint64_t n = uni64((uint64_t)G.n), m = uni64((uint64_t)G.m);
     asm volatile("" : "+s"(n), "+s"(m));  // their conversions are not kept across the levels
-    return next_direction(pull, fa, flen, (int64_t)n, (int64_t)m, lp.pull_alpha, lp.pull_beta);
+    const int64_t arcs = kBlock ? block_pull_arcs((int64_t)n, (int64_t)m) : (int64_t)m;
+    return next_direction(pull, fa, flen, (int64_t)n, arcs, lp.pull_alpha, lp.pull_beta);
 }
 
 template <int WW>
@@ -1963,7 +1966,7 @@ __device__ void record_batch(const DevGraph& G, const int32_t* order, int W, uin
                         &R.clen, &R.arcs, G.deg);
         __syncthreads();
         flen = uni32(R.flen);
-        pull = next_pull(pull, uni64(R.arcs), flen, G, lp);
+        pull = next_pull<true>(pull, uni64(R.arcs), flen, G, lp);
         tq = __builtin_amdgcn_s_memrealtime();
         K.ticks[3] += tq - tp;
         tp = tq;
@@ -3091,7 +3094,7 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                                    L.filter());
                         __syncthreads();
                         flen = uni32(s_flen);
-                        pull = next_pull(0, uni64(s_front), flen, G, lp);
+                        pull = next_pull<true>(0, uni64(s_front), flen, G, lp);
                     }
                     tq = __builtin_amdgcn_s_memrealtime();
                     ticks[3] += tq - tp;
@@ -3144,7 +3147,7 @@ __global__ __launch_bounds__(kLdsBlk) void k_batched_lds(DevGraph G, const int32
                                &s_flen, &s_clen, &s_front, G.deg, L.filter());
                 __syncthreads();
                 flen = uni32(s_flen);
-                pull = next_pull(pull, uni64(s_front), flen, G, lp);
+                pull = next_pull<true>(pull, uni64(s_front), flen, G, lp);
                 tq = __builtin_amdgcn_s_memrealtime();
                 ticks[3] += tq - tp;
                 tp = tq;

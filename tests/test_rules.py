@@ -73,3 +73,16 @@ def test_a_bottom_up_step_has_a_wave_per_heavy_node(tmp_path):
     assert(pull_threads(6400, 100) == 6400 && pull_threads(6400, 101) == 6464);
     assert(pull_threads(2147483646, 33038209) == 2147483646 && pull_threads(40000000, 33038209) == 2114445376);
     """)
+
+
+def test_one_workgroup_goes_bottom_up_on_graphs_with_arcs_only(tmp_path):
+    run(tmp_path, r"""
+    // connected graphs (m >= 2 n - 2): the rule on the arcs alone
+    assert(block_pull_arcs(1000, 6000) == 6000 && block_pull_arcs(1000, 2000) == 2000);
+    // few arcs per node: never, at the default
+    const int64_t n = 2000000, m = 9000;
+    assert(next_direction(0, m, 1500, n, block_pull_arcs(n, m), 3.f, 24.f) == 0);
+    assert(next_direction(0, m, 1500, n, m, 3.f, 24.f) == 1);
+    assert(next_direction(0, 1, 1, n, block_pull_arcs(n, m), 1e9f, 24.f) == 1);
+    assert(block_pull_arcs(2147483646, 5) == 4294967292);
+    """)
