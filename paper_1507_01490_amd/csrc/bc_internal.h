@@ -53,6 +53,7 @@ void set_error(const char* fmt, ...);
 
 struct DevGraph {
     int32_t n;
+    float block_alpha;        // factor of pull_alpha for levels of one workgroup at W = 256
     int64_t m;
     int32_t directed;
     int32_t heavy_count;      // *nheavy, for the launches

@@ -667,27 +667,37 @@ __global__ void k_gather_f32(int32_t n, const int32_t* __restrict__ orig, const 
     for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += stride) dst[u] = src[orig[u]];
 }
 
-// nodes of more than kPullWave in-arcs
+// nodes of more than kPullWave in-arcs; nheavy: their number, their in-arcs
 __global__ void k_heavy_nodes(int32_t n, const int32_t* __restrict__ irp, int32_t* __restrict__ heavy,
                               uint32_t* nheavy) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < n; base += stride) {
         const int64_t v = base + threadIdx.x;
-        const bool on = v < n && irp[v + 1] - irp[v] > kPullWave;
+        uint32_t arcs = v < n ? (uint32_t)(irp[v + 1] - irp[v]) : 0u;
+        const bool on = arcs > (uint32_t)kPullWave;
         const uint32_t p = wave_claim(on, nheavy);
         if (on) heavy[p] = (int32_t)v;
+        if (!on) arcs = 0;
+        for (int o = 32; o > 0; o >>= 1) arcs += __shfl_xor(arcs, o);
+        if (arcs && (threadIdx.x & 63) == 0) atomicAdd(&nheavy[1], arcs);
     }
 }
 
-// (dg.heavy_count is set once the stream has been waited for)
+// The list of these nodes and what the launches' rules take from it; waits for
+// the stream.
 bc_status heavy_list(bc_graph* g, hipStream_t s) {
-    BC_HIP(hipMemsetAsync(g->nheavy.p, 0, sizeof(uint32_t), s));
+    uint32_t h[2] = {0, 0};
+    BC_HIP(hipMemsetAsync(g->nheavy.p, 0, sizeof(h), s));
     if (g->dg.n > 0)
         k_heavy_nodes<<<grid_for(g->dg.n), kBlk, 0, s>>>(g->dg.n, g->dg.irp, g->heavy.as<int32_t>(),
                                                         g->nheavy.as<uint32_t>());
+    BC_HIP(hipGetLastError());
+    BC_HIP(hipMemcpyAsync(h, g->nheavy.p, sizeof(h), hipMemcpyDeviceToHost, s));
+    BC_HIP(hipStreamSynchronize(s));
     g->dg.heavy = g->heavy.as<int32_t>();
     g->dg.nheavy = g->nheavy.as<uint32_t>();
-    BC_HIP(hipMemcpyAsync(&g->dg.heavy_count, g->nheavy.p, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    g->dg.heavy_count = (int32_t)h[0];
+    g->dg.block_alpha = block_alpha(g->dg.directed != 0, g->dg.n, g->dg.m, h[0], h[1]);
     return BC_OK;
 }
 
@@ -744,7 +754,7 @@ bc_status graph_build(bc_graph* g, int32_t n, int64_t m, const int32_t* rp_in, c
         c.add(g->x0, sizeof(uint32_t) * (size_t)n);
         c.add(g->x1, sizeof(uint32_t) * (size_t)n);
         c.add(g->heavy, sizeof(int32_t) * heavy_nodes(mc));
-        c.add(g->nheavy, sizeof(uint32_t));
+        c.add(g->nheavy, 2 * sizeof(uint32_t));
         return gplace(g, c, g->base, s);
     };
     if (err & 4u) {
@@ -844,8 +854,6 @@ bc_status graph_build(bc_graph* g, int32_t n, int64_t m, const int32_t* rp_in, c
         BC_TRY(directed_reach(g));
     }
     BC_TRY(heavy_list(g, s));
-    BC_HIP(hipGetLastError());
-    BC_HIP(hipStreamSynchronize(s));
     auto t1 = std::chrono::steady_clock::now();
     g->preprocess_ms = std::chrono::duration<double, std::milli>(t1 - t0).count();
     return BC_OK;
@@ -1355,7 +1363,7 @@ bc_status graph_relabel(bc_graph* g, bool ordered, bc_graph** out) {
     c.add(h->orig, sizeof(int32_t) * (size_t)n);
     c.add(h->inv, sizeof(int32_t) * (size_t)n);
     c.add(h->heavy, sizeof(int32_t) * heavy_nodes(m));
-    c.add(h->nheavy, sizeof(uint32_t));
+    c.add(h->nheavy, 2 * sizeof(uint32_t));
     BC_TRY(gplace(h.get(), c, h->base, s));
     int32_t *rp = h->rp.as<int32_t>(), *col = h->col.as<int32_t>();
     uint32_t* deg = h->deg.as<uint32_t>();
@@ -1392,7 +1400,6 @@ bc_status graph_relabel(bc_graph* g, bool ordered, bc_graph** out) {
     d.x1 = h->x1.as<uint32_t>();
     d.orig = h->orig.as<int32_t>();
     BC_TRY(heavy_list(h.get(), s));
-    BC_HIP(hipStreamSynchronize(s));
     h->relabeled = true;
     h->preprocess_ms =
         g->preprocess_ms + std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();

@@ -59,6 +59,23 @@ BC_HD uint32_t next_direction(uint32_t pull, uint64_t arcs, uint32_t nodes, int6
 // undirected graph has 2 n - 2 arcs or more.
 BC_HD int64_t block_pull_arcs(int64_t n, int64_t m) { return m > 2 * n ? m : 2 * n; }
 
+// The factor of pull_alpha for levels of one workgroup at W = 256, where a
+// bottom-up step reads four words of every node that is not complete.  (Job
+// launches of one query, k = 10; ms at factor 1 and at the one taken, and top
+// down only before there was a bottom-up step.)
+//   directed: a node that no source reaches is scanned in full, level after
+//     level (R-MAT scale 17, batched query: 6.4 -> 3.5, before 6.1)
+//   most arcs at a few nodes of many: these take a wave each and are walked one
+//     after the other (collaboration graph of 20,000 nodes 7.2 -> 6.1, before
+//     7.1; 60,000 29.4 -> 25.3, before 25.4; 200,000 71 -> 64; 500,000 269 ->
+//     241).  Where fewer of the arcs are theirs (Barabasi-Albert graph, 60 arcs
+//     a node) it would lose, 21.4 -> 23.8, or where most nodes are such (a
+//     random graph of 120 arcs a node), 31 -> 41.
+BC_HD float block_alpha(bool directed, int64_t n, int64_t m, int64_t heavy, int64_t heavy_arcs) {
+    if (directed) return 2.f / 3.f;
+    return 2 * heavy_arcs > m && 2 * heavy < n ? 0.4f : 1.f;
+}
+
 // Threads a bottom-up step has work for: one per node, and a wave for each of
 // the `heavy` nodes of many in-arcs, which outnumber the others' waves on a
 // dense graph (3,000 nodes of 600 arcs: 3 workgroups by the nodes alone, the

@@ -1923,6 +1923,7 @@ __device__ void record_batch(const DevGraph& G, const int32_t* order, int W, uin
     if (tid == 0) R.clen = R.flen;
     uint32_t live = uni32(cut_step<WW>(T, R.S, W, 0, false, nullptr, nullptr, false, true, st, R.act, R.CL, D));
     uint32_t flen = uni32(R.flen), d = 0, pull = 0;
+    const LevelParams lpw{lp.pull_alpha * G.block_alpha, lp.pull_beta, lp.can_pull};
     uint64_t tp = __builtin_amdgcn_s_memrealtime();
     K.ticks[0] += tp - tb;
     while (live) {
@@ -1966,7 +1967,7 @@ __device__ void record_batch(const DevGraph& G, const int32_t* order, int W, uin
                         &R.clen, &R.arcs, G.deg);
         __syncthreads();
         flen = uni32(R.flen);
-        pull = next_pull<true>(pull, uni64(R.arcs), flen, G, lp);
+        pull = next_pull<true>(pull, uni64(R.arcs), flen, G, WW < 4 ? lp : lpw);
         tq = __builtin_amdgcn_s_memrealtime();
         K.ticks[3] += tq - tp;
         tp = tq;
@@ -2145,6 +2146,7 @@ __device__ inline DevGraph uni_graph(const DevGraph& g) {
     o.m = (int64_t)uni64((uint64_t)g.m);
     o.directed = (int32_t)uni32((uint32_t)g.directed);
     o.heavy_count = (int32_t)uni32((uint32_t)g.heavy_count);
+    o.block_alpha = __uint_as_float(uni32(__float_as_uint(g.block_alpha)));
     o.rp = uni_ptr(g.rp);
     o.col = uni_ptr(g.col);
     o.irp = uni_ptr(g.irp);

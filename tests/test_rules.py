@@ -86,3 +86,13 @@ def test_one_workgroup_goes_bottom_up_on_graphs_with_arcs_only(tmp_path):
     assert(next_direction(0, 1, 1, n, block_pull_arcs(n, m), 1e9f, 24.f) == 1);
     assert(block_pull_arcs(2147483646, 5) == 4294967292);
     """)
+
+
+def test_factor_of_the_wide_batches_in_one_workgroup(tmp_path):
+    run(tmp_path, r"""
+    assert(block_alpha(true, 1000, 9000, 900, 9000) == 2.f / 3.f && block_alpha(true, 1000, 0, 0, 0) == 2.f / 3.f);
+    assert(block_alpha(false, 60000, 1105268, 6300, 784000) == 0.4f);   // most arcs at a tenth of the nodes
+    assert(block_alpha(false, 50000, 2999070, 10950, 1412000) == 1.f);  // less than half of the arcs
+    assert(block_alpha(false, 30000, 3600000, 29990, 3599000) == 1.f);  // nearly all nodes
+    assert(block_alpha(false, 1000, 6000, 0, 0) == 1.f && block_alpha(false, 5, 0, 0, 0) == 1.f);
+    """)
