@@ -264,7 +264,9 @@ bc_status bc_graph_csr(const bc_graph* g, int32_t* row_ptr, int32_t* col);
  * BC_ENOMEM, BC_EDEVICE.  With the environment variable BC_CHECK_LISTS=1
  * (a debugging aid), the host-driven level loop also copies the frontier
  * and reset lists after every level and fails with BC_EDEVICE if an entry
- * is not a node id.
+ * is not a node id; with BC_CHECK_LISTS=2 it does so for the levels that
+ * one workgroup hands back to it, without changing which they are.  (Their
+ * lengths are checked on every run.)
  */
 bc_status bc_topk(bc_graph* g, int32_t k, const bc_opts* opts, int32_t* ids, uint64_t* farness,
                   uint32_t* reach, int32_t* count, bc_stats* stats);

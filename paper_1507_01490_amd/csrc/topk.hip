@@ -118,7 +118,7 @@ struct Ctl {
     unsigned long long active[4];
     uint32_t cnt_g[256];
     unsigned long long cnt_t[256];
-    uint32_t err;                  // cooperative level loop: a list outgrew n (the loop stopped)
+    uint32_t err;                  // a list outgrew n: the level kernels stop
 };
 
 struct SlotPtrs {
@@ -153,7 +153,9 @@ struct LevelParams {
 
 // What the batch of a level-synchronous slot waits for when the narrow kernel
 // hands it back to the host.
-enum : uint32_t { LV_IDLE = 0, LV_PUSH = 1, LV_PULL = 2, LV_CLEAR = 3, LV_DONE = 4 };
+// LV_BAD: a list outgrew the n nodes it can hold (each node is in it once), so
+// a level wrote out of order and nothing may index by it.
+enum : uint32_t { LV_IDLE = 0, LV_PUSH = 1, LV_PULL = 2, LV_CLEAR = 3, LV_DONE = 4, LV_BAD = 5 };
 struct LvReport {  // one per slot, in pinned host memory
     uint32_t state, flen, clen, d;
     unsigned long long front_arcs, pad_;
@@ -1368,6 +1370,14 @@ __device__ void plain_count_body(const DevGraph& G, const SlotPtrs& P, SrcState*
     plain_level_epilogue<WW>(C, S, T, st, W, X.cg, X.ct, X.CL, X.act, &X.last);
 }
 
+// Whether the list of the level just expanded holds more than n nodes (the same
+// for every workgroup of the slot: the length is final).  k_plain_run reports it.
+__device__ inline bool list_outgrown(const DevGraph& G, Ctl* C) {
+    if (C->nlen <= (uint32_t)G.n) return false;
+    if (threadIdx.x == 0) __hip_atomic_store(&C->err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+}
+
 template <int WW>
 __global__ __launch_bounds__(kLvBlk) void k_plain_count(DevGraph G, LvSlots L, TopKDev T, QStats* st, int W,
                                                        int gated) {
@@ -1375,6 +1385,7 @@ __global__ __launch_bounds__(kLvBlk) void k_plain_count(DevGraph G, LvSlots L, T
     const size_t i = L.id[blockIdx.y];
     Ctl* C = L.C + i;
     if (gated && (C->live == 0 || C->pull != 0)) return;
+    if (list_outgrown(G, C)) return;
     plain_count_body<WW>(G, slot_ptrs<WW>(L, i), L.S + i * kBlk, C, T, st, W, X);
 }
 
@@ -1623,6 +1634,7 @@ __global__ __launch_bounds__(kLvBlk) void k_plain_build(DevGraph G, LvSlots L, L
     const size_t i = L.id[blockIdx.y];
     Ctl* C = L.C + i;
     if (gated && C->ran == 0) return;
+    if (list_outgrown(G, C)) return;
     plain_build_body<WW>(G, slot_ptrs<WW>(L, i), C, lp, X);
 }
 
@@ -1721,8 +1733,14 @@ __global__ __launch_bounds__(kBatchBlk) void k_plain_run(DevGraph G, const int32
         R.ent = 0;
     }
     unsigned long long levels = 0, pulls = 0, disc = 0, batches = 0;
+    const uint32_t n = (uint32_t)G.n;
+    bool bad = C->err != 0;
     __syncthreads();
     for (;;) {
+        if (bad || flen > n || clen > n) {
+            state = LV_BAD;
+            break;
+        }
         if (!in_batch) {
             if (tid == 0) s_b = atomicAdd(next_batch, 1u);
             __syncthreads();
@@ -1780,6 +1798,8 @@ __global__ __launch_bounds__(kBatchBlk) void k_plain_run(DevGraph G, const int32
         }
         __syncthreads();
         const uint32_t nlen = uni32(R.nlen);
+        bad = nlen > n;
+        if (bad) continue;
         disc += nlen;
         ++levels;
         ++d;
@@ -3368,9 +3388,11 @@ int coop_grid() {
 // the host and check that every listed id is a node (the lengths are checked
 // on every run).  A violation fails the query before any kernel indexes
 // the records with a bad id.
-bool check_lists_enabled() {
+// 1: every level through the wide kernels, so that all lists come by; 2: the
+// lists that the narrow kernel hands back.
+int check_lists_enabled() {
     const char* e = std::getenv("BC_CHECK_LISTS");
-    return e && e[0] == '1';
+    return e && (e[0] == '1' || e[0] == '2') ? e[0] - '0' : 0;
 }
 
 bc_status check_level_lists(const SlotPtrs& P, uint32_t flen, uint32_t clen, int32_t n, uint32_t level,
@@ -3427,12 +3449,12 @@ struct SlotList {
 
 template <int WW>
 bc_status lv_host_loop(const DevGraph& G, const int32_t* ord, int32_t count, uint32_t nb, LvSlots L, int slots,
-                       uint32_t* next, TopKDev T, QStats* d_st, const LevelParams& lp, const LvHost& H, bool check,
+                       uint32_t* next, TopKDev T, QStats* d_st, const LevelParams& lp, const LvHost& H, int check,
                        hipStream_t s) {
     const int W = 64 * WW;
     const int32_t n = G.n;
     const int cus = device_cus();
-    const unsigned long long narrow = check ? 0 : kNarrowArcs;
+    const unsigned long long narrow = check == 1 ? 0 : kNarrowArcs;
     SlotList act;
     for (int i = 0; i < slots; ++i) act.add((uint8_t)i);
     k_lv_start<<<1, 64, 0, s>>>(L.C, slots, next);
@@ -3461,8 +3483,8 @@ bc_status lv_host_loop(const DevGraph& G, const int32_t* ord, int32_t count, uin
             // every list holds distinct nodes, so no length can exceed n: a
             // longer one means the level step wrote out of order, and no
             // further kernel may index the lists with it
-            if (r.flen > (uint32_t)n || r.clen > (uint32_t)n) {
-                set_error("internal: level %u list lengths %u/%u exceed n = %d", r.d, r.flen, r.clen, n);
+            if (r.state == LV_BAD || r.flen > (uint32_t)n || r.clen > (uint32_t)n) {
+                set_error("internal: level %u list lengths (frontier %u, reset %u) exceed n = %d", r.d, r.flen, r.clen, n);
                 return BC_EDEVICE;
             }
             if (r.state == LV_DONE) continue;
@@ -3521,7 +3543,7 @@ bc_status run_plain_batches(const DevGraph& G, const int32_t* ord, int32_t count
                             TopKDev T, QStats* d_st, const LevelParams& lp, hipStream_t s, double* ms,
                             int graph_levels, int slots = 1) {
     if (nb == 0) return BC_OK;
-    const bool check_lists = check_lists_enabled();
+    const int check_lists = check_lists_enabled();
     const int W = 64 * WW;
     const int32_t n = G.n;
     const int cus = device_cus();
@@ -4128,7 +4150,7 @@ bc_status run_topk_static(bc_graph* g, int32_t k, int32_t* ids, uint64_t* farnes
     LevelParams lp{3.f, 24.f, 1};
     const uint32_t nb = (uint32_t)((n + 63) / 64);
     LvReport rep[1];
-    BC_TRY(lv_host_loop<1>(G, ord, n, nb, L, 1, &SC->next, T, d_st, lp, LvHost{&SC->report, rep, false}, false, s));
+    BC_TRY(lv_host_loop<1>(G, ord, n, nb, L, 1, &SC->next, T, d_st, lp, LvHost{&SC->report, rep, false}, 0, s));
     BC_HIP(hipGetLastError());
     int32_t cnt = 0;
     BC_HIP(hipMemcpyAsync(&cnt, T.cnt, sizeof(int32_t), hipMemcpyDeviceToHost, s));
