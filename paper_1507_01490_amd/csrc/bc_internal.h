@@ -70,7 +70,6 @@ struct DevGraph {
     const uint32_t* nheavy;
 };
 
-constexpr int32_t kPullWave = 64;  // in-arcs above which a bottom-up step gives a node a wave of its own
 inline size_t heavy_nodes(int64_t m) { return (size_t)(m / (kPullWave + 1)) + 1; }
 
 // Raise the release threshold of the device's default memory pool once per

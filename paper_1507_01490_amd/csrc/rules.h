@@ -3,6 +3,7 @@
 // (under the undefined-behaviour sanitizer) at sizes no test graph reaches.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
 #if defined(__HIPCC__)
@@ -74,6 +75,66 @@ BC_HD int64_t block_pull_arcs(int64_t n, int64_t m) { return m > 2 * n ? m : 2 *
 BC_HD float block_alpha(bool directed, int64_t n, int64_t m, int64_t heavy, int64_t heavy_arcs) {
     if (directed) return 2.f / 3.f;
     return 2 * heavy_arcs > m && 2 * heavy < n ? 0.4f : 1.f;
+}
+
+// ---- bottom-up step
+//
+// WW lanes share a node, lane j on word j, and a wave takes 64 nodes in WW
+// rounds; a node of more than kPullWave in-arcs takes the whole wave.
+
+constexpr int32_t kPullWave = 64;
+
+// Node of a lane in round r of the 64 nodes from `base` on, and the word of a
+// wave's buffer for what it found: node i of the 64 has words i WW .. i WW + WW - 1.
+template <int WW>
+BC_HD int64_t pull_node(int64_t base, int r, int lane) {
+    return base + r * (64 / WW) + lane / WW;
+}
+BC_HD int pull_word(int r, int lane) { return r * 64 + lane; }
+
+// The arcs e0, e0 + step, ... below e1 of a lane's part of a list: the bits of
+// `unv` found among the neighbours' words cur_j.  kAhead arcs at a time, their
+// targets and then their words all in flight together, until every bit is
+// found.  Returns the arcs read.
+template <int WW, int kAhead, class Col, class Cur>
+BC_HD uint32_t pull_walk(const Col& icol, const Cur& cur_j, int64_t e0, int32_t e1, int32_t step, uint64_t unv,
+                         uint64_t& acc) {
+    uint32_t read = 0;
+    int64_t e = e0;
+    while (e < e1 && acc != unv) {
+        int32_t u[kAhead];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            const int64_t x = e + (int64_t)q * step;
+            u[q] = icol[x < e1 ? x : e];  // past the end: the first arc again
+        }
+        uint64_t c = 0;
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) c |= cur_j[(size_t)u[q] * WW];
+        acc |= c & unv;
+        read += kAhead;
+        e += (int64_t)kAhead * step;
+    }
+    return read;
+}
+
+// A short list [e0, e1), walked by the lane of each word; the arcs read.
+template <int WW, int kAhead, class Col, class Cur>
+BC_HD uint32_t pull_short(const Col& icol, const Cur& cur_j, int32_t e0, int32_t e1, uint64_t unv, uint64_t& acc) {
+    const uint32_t read = pull_walk<WW, kAhead>(icol, cur_j, e0, e1, 1, unv, acc), len = (uint32_t)(e1 - e0);
+    return read < len ? read : len;
+}
+
+// A lane's arcs among the next (64 / WW) kAhead of a long list from eb on; the
+// end of those.
+template <int WW, int kAhead, class Col, class Cur>
+BC_HD int32_t pull_long(const Col& icol, const Cur& cur_j, int64_t eb, int32_t h1, int lane, uint64_t unv,
+                        uint64_t& acc) {
+    constexpr int kGroups = 64 / WW;
+    const int64_t to = eb + kGroups * kAhead;
+    const int32_t end = (int32_t)(to < h1 ? to : h1);
+    (void)pull_walk<WW, kAhead>(icol, cur_j, eb + lane / WW, end, kGroups, unv, acc);
+    return end;
 }
 
 // Threads a bottom-up step has work for: one per node, and a wave for each of

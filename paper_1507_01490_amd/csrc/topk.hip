@@ -1414,30 +1414,6 @@ __device__ inline uint64_t group_or(uint64_t x) {
     return x;
 }
 
-// The arcs e0, e0 + step, ... below e1 of this lane's part of a list: the
-// bits of `unv` found among the neighbours' word j.  Returns the arcs read.
-template <int WW, int kAhead>
-__device__ __forceinline__ uint32_t pull_walk(const DevGraph& G, const uint64_t* cur_j, int64_t e0, int32_t e1,
-                                              int32_t step, uint64_t unv, uint64_t& acc) {
-    uint32_t read = 0;
-    int64_t e = e0;
-    while (e < e1 && acc != unv) {
-        int32_t u[kAhead];
-#pragma unroll
-        for (int q = 0; q < kAhead; ++q) {
-            const int64_t x = e + (int64_t)q * step;
-            u[q] = G.icol[x < e1 ? x : e];  // past the end: the first arc again
-        }
-        uint64_t c = 0;
-#pragma unroll
-        for (int q = 0; q < kAhead; ++q) c |= cur_j[(size_t)u[q] * WW];
-        acc |= c & unv;
-        read += kAhead;
-        e += (int64_t)kAhead * step;
-    }
-    return read;
-}
-
 template <int WW>
 struct PullWaveLds {
     uint64_t acc[64 * WW];
@@ -1453,11 +1429,10 @@ __device__ __forceinline__ void pull_nodes(const DevGraph& G, const SlotPtrs& P,
                                            uint32_t* nlen, unsigned long long& scanned) {
     const int lane = (int)lane_id();
     const int j = lane % WW;
-    constexpr int kPer = 64 / WW;  // nodes per round
     uint64_t any = 0;
 #pragma unroll 1
     for (int r = 0; r < WW; ++r) {
-        const int64_t w = base + r * kPer + lane / WW;
+        const int64_t w = pull_node<WW>(base, r, lane);
         uint64_t acc = 0;
         uint32_t read = 0;
         if (w < G.n) {
@@ -1465,14 +1440,14 @@ __device__ __forceinline__ void pull_nodes(const DevGraph& G, const SlotPtrs& P,
             const uint64_t unv = actj & ~rec[j];
             const int32_t e0 = G.irp[w], e1 = G.irp[w + 1];
             if (unv && e1 - e0 <= kPullWave) {  // longer lists: pull_heavy
-                read = min(pull_walk<WW, kAhead>(G, P.cur + j, e0, e1, 1, unv, acc), (uint32_t)(e1 - e0));
+                read = pull_short<WW, kAhead>(G.icol, P.cur + j, e0, e1, unv, acc);
                 if (acc) rec[WW + j] = acc;
             }
         }
 #pragma unroll
         for (int o = 1; o < WW; o <<= 1) read = max(read, __shfl_xor(read, o));
         if (j == 0) scanned += read;
-        L.acc[(r * kPer) * WW + lane] = acc;
+        L.acc[pull_word(r, lane)] = acc;
         any |= acc;
     }
     if (__ballot(any != 0) == 0ull) return;
@@ -1504,9 +1479,8 @@ __device__ __forceinline__ bool pull_heavy(const DevGraph& G, const SlotPtrs& P,
     uint64_t acc = 0;
     for (int64_t eb = h0; eb < h1; eb += kGroups * kAhead) {
         if (__ballot(acc != unv) == 0ull) break;
-        const int32_t end = (int32_t)min((int64_t)h1, eb + kGroups * kAhead);
         uint64_t part = acc;
-        (void)pull_walk<WW, kAhead>(G, P.cur + j, eb + lane / WW, end, kGroups, unv, part);
+        const int32_t end = pull_long<WW, kAhead>(G.icol, P.cur + j, eb, h1, lane, unv, part);
         acc = group_or<WW>(part);
         if (lane == 0) scanned += (unsigned long long)(end - eb);
     }

@@ -81,7 +81,7 @@ def test_tiles_and_searches_at_the_limit(tmp_path):
     src = tmp_path / "limits.cpp"
     src.write_text(PROGRAM)
     exe = tmp_path / "limits"
-    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fsanitize=undefined", "-fno-sanitize-recover=all",
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wno-unknown-pragmas", "-Werror", "-fsanitize=undefined", "-fno-sanitize-recover=all",
                     "-I", CSRC, str(src), "-o", str(exe)], check=True)
     assert subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout == "ok\n"
 

@@ -13,7 +13,7 @@ def run(tmp_path, body):
     src.write_text('#include "rules.h"\n#include <cassert>\n#include <cstdio>\n#include <initializer_list>\nusing namespace bc;\nint main() {\n'
                    + body + '\nstd::puts("ok");\n}\n')
     exe = tmp_path / "rules"
-    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fsanitize=undefined", "-fno-sanitize-recover=all",
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wno-unknown-pragmas", "-Werror", "-fsanitize=undefined", "-fno-sanitize-recover=all",
                     "-I", CSRC, str(src), "-o", str(exe)], check=True)
     assert subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout == "ok\n"
 
