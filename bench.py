@@ -55,16 +55,22 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def algorithmic_bytes(arcs: int, entries: int, discovered: int, W: int, trial: bool = True) -> int:
-    """Minimal HBM bytes of the level work of the persistent kernel:
-    per scanned arc: col[e] (4 B) + seen[w] gather (W/8 B), plus deg[col[e]]
+def algorithmic_bytes(arcs: int, entries: int, discovered: int, W: int, trial: bool = True, swept: int = 0) -> int:
+    """Bytes that the level work of the persistent kernel asks memory for, each
+    access counted by itself (what the caches serve of it stays in; reads of
+    nodes in order, such as the sweeps that count and build a wide top-down
+    level, are left out):
+    per scanned arc: col[e] (4 B) + a gather of W/8 B (seen of the target top
+    down, cur of the in-neighbour bottom up, where arcs count up to the step
+    of eight or four in which the last source was found), plus deg[col[e]]
     (4 B) in the W = 64 kernel, whose over-counted bound test (trial) sums the
     degree of every arc's target;
+    per node a bottom-up step passes over (swept): seen (W/8 B) + row_ptr (4 B);
     per expanded frontier entry: list entry (4 B) + row_ptr pair (8 B) + cur[u] (W/8 B);
     per discovered entry of an exactly counted level: list entry (4 B) + deg (4 B)
     + nxt read+reset (2 W/8 B) + seen read+write (2 W/8 B) + cur write (W/8 B)."""
     wb = W // 8
-    return arcs * ((8 if trial else 4) + wb) + entries * (12 + wb) + discovered * (8 + 5 * wb)
+    return arcs * ((8 if trial else 4) + wb) + entries * (12 + wb) + discovered * (8 + 5 * wb) + swept * (wb + 4)
 
 
 def measured_traffic(kernel: str, workload: str):
@@ -248,9 +254,12 @@ def main():
         out = step(args.mode)
         for k, r in zip(ks, out):
             s = r.stats
+            # bottom-up levels are counted per query: all but the seed batches' few
+            # belong to the launch unless deferred sources were re-run after it
+            swept = s["pull_levels"] * g.n if s["n_deferred"] == 0 else 0
             agg["alg_bytes"] += algorithmic_bytes(s["persistent_arcs"], s["persistent_entries"],
                                                   s["persistent_discovered"], width_of(k),
-                                                  trial=width_of(k) == 64 and bool(args.trial))
+                                                  trial=width_of(k) == 64 and bool(args.trial), swept=swept)
             agg["persistent_ms"] += s["persistent_ms"]
             agg["seed_ms"] += s["seed_ms"]
             agg["defer_ms"] += s["defer_ms"]
