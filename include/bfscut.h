@@ -124,7 +124,11 @@ typedef struct bc_opts {
     int32_t width;          /* W: sources per bit-parallel batch, 64, 128 or 256         */
     const int32_t* perm;    /* BC_ORDER_GIVEN: host, n entries                           */
     const float* scores;    /* BC_ORDER_SCORES: host, n entries                          */
-    float pull_alpha;       /* push -> pull when frontier arcs > m / pull_alpha (0 = never pull) */
+    float pull_alpha;       /* push -> pull when frontier arcs > m / pull_alpha (0 = never pull).
+                               In the levels of one workgroup (batched mode's launch, job
+                               launches) 2 n counts for m where it is more, and the value is
+                               taken times 2/3 for batches in LDS and, at W = 256, times 2/3
+                               on directed graphs and 0.4 where a few nodes hold most arcs  */
     float pull_beta;        /* pull -> push when frontier nodes < n / pull_beta          */
     int32_t slots;          /* BC_MODE_BATCHED: concurrent workgroup batches (0 = auto)  */
     int32_t seed_batches;   /* BC_MODE_BATCHED: level-synchronous batches first (-1 = auto) */
@@ -142,10 +146,10 @@ typedef struct bc_opts {
                                holds every deferred source in one batch, else 256)       */
     const float* mlp;       /* BC_ORDER_LEARNED: host, BC_MLP_PARAMS floats              */
     int32_t graph_levels;   /* level-synchronous batches: 0 (the default) runs narrow levels
-                               in one kernel and makes one host round trip per wide level,
-                               several batches side by side; 1..64 captures that many level steps
-                               in a HIP graph and replays it, checking for live sources
-                               once per replay; -1 runs every level of every batch of a
+                               in one kernel and makes one host round trip per wide level
+                               (deferred sources: of several batches side by side);
+                               1..64 captures that many level steps in a HIP graph and
+                               replays it, checking for live sources once per replay; -1 runs every level of every batch of a
                                phase in one cooperative launch, grid barriers between the
                                level steps (BC_EINVAL where the device cannot launch it
                                cooperatively). The default measures fastest on gfx950.  */

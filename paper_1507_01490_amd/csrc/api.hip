@@ -58,7 +58,7 @@ bc_status graph_create(int32_t n, int64_t m, const int32_t* row_ptr, const int32
     // the first build of a renumbered graph lasts as long as this call
     g->ordered = ordered || (relabel && pooled_first_build(n, m));
     (void)hipGetDevice(&g->device);
-    bc_status s = graph_build(g.get(), n, m, row_ptr, col, flags & ~(uint32_t)BC_KEEP_IDS);
+    bc_status s = graph_build(g.get(), n, m, row_ptr, col, flags & ~(uint32_t)BC_KEEP_IDS, !relabel);
     if (s != BC_OK) {
         (void)hipStreamSynchronize(g->stream);
         return s;

@@ -254,8 +254,10 @@ namespace bc {
 
 // Pre-processing (preprocess.hip): validation, canonical CSR, degrees,
 // transpose and reach data.  rp/col are host or device pointers per flags.
+// searched: queries will run on it (a graph that is renumbered next needs no
+// lists for the bottom-up step).
 bc_status graph_build(bc_graph* g, int32_t n, int64_t m, const int32_t* rp, const int32_t* col,
-                      uint32_t flags);
+                      uint32_t flags, bool searched);
 // Renumber a built undirected graph in breadth-first order (the locality
 // seed order): *out receives the renumbered graph (built on the same stream,
 // with orig/inv), g is left as it was for the caller to release.

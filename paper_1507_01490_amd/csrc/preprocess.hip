@@ -164,7 +164,10 @@ __device__ inline void uf_unite(int32_t* P, int32_t a, int32_t b) {
 }
 
 // Components in steps, since nearly all arcs of a real graph join nodes that
-// already share one:
+// already share one (a few arcs of every row, then the largest component found
+// by sampling and skipped: the Afforest scheme of Sutton, Ben-Nun and Barak,
+// "Optimizing Parallel Graph Connectivity Computation via Subgraph Sampling",
+// IPDPS 2018):
 //   k_uf_init   every node points to its smallest neighbour if that is
 //               smaller than itself (a forest without any atomic: pointers
 //               only fall), then to its root (k_uf_flatten)
@@ -668,19 +671,27 @@ __global__ void k_gather_f32(int32_t n, const int32_t* __restrict__ orig, const 
 }
 
 // nodes of more than kPullWave in-arcs; nheavy: their number, their in-arcs
-__global__ void k_heavy_nodes(int32_t n, const int32_t* __restrict__ irp, int32_t* __restrict__ heavy,
-                              uint32_t* nheavy) {
+__global__ __launch_bounds__(kBlk) void k_heavy_nodes(int32_t n, const int32_t* __restrict__ irp,
+                                                      int32_t* __restrict__ heavy, uint32_t* nheavy) {
+    __shared__ uint32_t s_arcs;
+    if (threadIdx.x == 0) s_arcs = 0;
+    __syncthreads();
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    uint32_t mine = 0;
     for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < n; base += stride) {
         const int64_t v = base + threadIdx.x;
-        uint32_t arcs = v < n ? (uint32_t)(irp[v + 1] - irp[v]) : 0u;
+        const uint32_t arcs = v < n ? (uint32_t)(irp[v + 1] - irp[v]) : 0u;
         const bool on = arcs > (uint32_t)kPullWave;
         const uint32_t p = wave_claim(on, nheavy);
-        if (on) heavy[p] = (int32_t)v;
-        if (!on) arcs = 0;
-        for (int o = 32; o > 0; o >>= 1) arcs += __shfl_xor(arcs, o);
-        if (arcs && (threadIdx.x & 63) == 0) atomicAdd(&nheavy[1], arcs);
+        if (on) {
+            heavy[p] = (int32_t)v;
+            mine += arcs;
+        }
     }
+    for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
+    if (mine && (threadIdx.x & 63) == 0) atomicAdd(&s_arcs, mine);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_arcs) atomicAdd(&nheavy[1], s_arcs);
 }
 
 // The list of these nodes and what the launches' rules take from it; waits for
@@ -689,7 +700,7 @@ bc_status heavy_list(bc_graph* g, hipStream_t s) {
     uint32_t h[2] = {0, 0};
     BC_HIP(hipMemsetAsync(g->nheavy.p, 0, sizeof(h), s));
     if (g->dg.n > 0)
-        k_heavy_nodes<<<grid_for(g->dg.n), kBlk, 0, s>>>(g->dg.n, g->dg.irp, g->heavy.as<int32_t>(),
+        k_heavy_nodes<<<grid_for(g->dg.n, 4 * kReduceGrid), kBlk, 0, s>>>(g->dg.n, g->dg.irp, g->heavy.as<int32_t>(),
                                                         g->nheavy.as<uint32_t>());
     BC_HIP(hipGetLastError());
     BC_HIP(hipMemcpyAsync(h, g->nheavy.p, sizeof(h), hipMemcpyDeviceToHost, s));
@@ -714,7 +725,7 @@ bc_status cub_call(F&& f, hipStream_t s, DevBuf& tmp) {
 }  // namespace
 
 bc_status graph_build(bc_graph* g, int32_t n, int64_t m, const int32_t* rp_in, const int32_t* col_in,
-                      uint32_t flags) {
+                      uint32_t flags, bool searched) {
     auto t0 = std::chrono::steady_clock::now();
     hipStream_t s = g->stream;
     const bool dev = (flags & BC_DEVICE_PTRS) != 0;
@@ -853,7 +864,9 @@ bc_status graph_build(bc_graph* g, int32_t n, int64_t m, const int32_t* rp_in, c
         g->big_scc = (flags & BC_BIG_SCC) != 0;
         BC_TRY(directed_reach(g));
     }
-    BC_TRY(heavy_list(g, s));
+    BC_HIP(hipGetLastError());
+    if (searched) BC_TRY(heavy_list(g, s));  // waits for the stream
+    else BC_HIP(hipStreamSynchronize(s));
     auto t1 = std::chrono::steady_clock::now();
     g->preprocess_ms = std::chrono::duration<double, std::milli>(t1 - t0).count();
     return BC_OK;

@@ -51,8 +51,8 @@ __device__ inline int32_t ld_rel(const int32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// In-degrees and the in-CSR, one arc per thread (kArcTile arcs per workgroup,
-// see arcs.h).  Bound by the atomics on the targets' counters; with one
+// In-degrees and the in-CSR, one arc per thread (in-degrees over the grid, the
+// rows of the in-CSR's arcs recovered tile by tile, see arcs.h).  Bound by the atomics on the targets' counters; with one
 // thread per row the longest row set the time (R-MAT scale 18, 3.9M arcs:
 // in-degrees 4376 -> 208 us, filling 6295 -> 222 us).
 __global__ __launch_bounds__(kArcBlk) void k_indeg(int64_t m, const int32_t* __restrict__ col,
@@ -223,7 +223,8 @@ __global__ __launch_bounds__(kBlk) void k_cid(int32_t n, const int32_t* __restri
     if (threadIdx.x == 0 && s_common) atomicAdd(&wsize[cc], s_common);
 }
 
-// Arcs between components, one arc per thread, one append per wave.
+// Arcs between components, one arc per thread, one append per tile (positions
+// within it are claimed per wave in LDS).
 __global__ __launch_bounds__(kArcBlk) void k_dag_arcs(int32_t n, int64_t m, const int32_t* __restrict__ rp,
                                                       const int32_t* __restrict__ col, const int32_t* __restrict__ cid,
                                                       uint64_t* __restrict__ keys, int32_t* cnt) {

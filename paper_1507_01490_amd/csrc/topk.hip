@@ -1671,8 +1671,8 @@ __device__ __forceinline__ void block_pull(const DevGraph& G, const SlotPtrs& P,
     __syncthreads();
 }
 
-// Levels that one workgroup runs: up to `narrow` frontier arcs (push), or, on
-// a graph of at most that many nodes and arcs, any level.  A push level of
+// Levels that one workgroup runs: up to `narrow` frontier arcs (push), and
+// bottom-up levels on a graph of at most kNarrowPull nodes and arcs.  A push level of
 // kNarrowArcs arcs takes one workgroup about 40 us, as long as the wide
 // kernels' launches and the round trip to the host; below that it wins (a
 // level of 600 arcs: 12 against 45 us).
@@ -2034,10 +2034,11 @@ __global__ __launch_bounds__(B) void k_batched(DevGraph G, const int32_t* order,
 // descriptor (JobDesc) covers a contiguous range of it: `count` batches of
 // one query, its local batches bofs .. bofs + count.  A query may have two
 // ranges (its seed batches early in the sequence, the rest later), which
-// share its state.  Workgroups claim global batches one at a time with a
-// compare-and-swap that never passes the published total, so every claimed
-// batch exists and is run; the total only grows (a serving queue appends
-// queries while the kernel runs).  Node records are shared by all queries:
+// share its state.  Workgroups claim global batches one at a time, in a serving
+// queue with a compare-and-swap that never passes the published total, so every
+// claimed batch exists and is run; the total only grows (the queue appends
+// queries while the kernel runs).  A launch whose batches were all published
+// before it adds one instead and ends at the total.  Node records are shared by all queries:
 // they are sized for the largest graph and all zero at rest, degrees come
 // from each graph's own array.
 
