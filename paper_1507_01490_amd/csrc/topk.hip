@@ -1905,7 +1905,9 @@ struct RecCounters {
 // source is live; then the marks of every node the batch reached are reset, so
 // the slot is all zero again.  (Wide levels bottom up took a collaboration
 // graph of 500,000 nodes at W = 256 from 339 to 218 ms, and 24 uneven graphs
-// of up to 30,000 nodes at W = 64 from 57 to 18 ms.)  Block-uniform call.
+// of up to 30,000 nodes at W = 64 from 57 to 18 ms, each on one card; the second
+// launch takes up to half as long again on one card as on another, before and
+// after alike.)  Block-uniform call.
 template <int WW, int B>
 __device__ void record_batch(const DevGraph& G, const int32_t* order, int W, uint32_t b, const SlotPtrs& P,
                              const TopKDev& T, QStats* st, const DeferList* D, const LevelParams& lp,
