@@ -30,3 +30,31 @@ def test_few_arcs_run_top_down(width, directed):
     for r in res:
         assert r.ids.tolist() == ref["ids"].tolist() and r.farness.tolist() == ref["f"].tolist()
         assert r.reach.tolist() == ref["r"].tolist() and r.stats["pull_levels"] == 0, r.stats
+
+
+def test_short_batches_are_claimed_without_contention():
+    """6,250 batches, nearly all of which end at once: the launch stays within
+    a few times the batched query (it took 40 times as long while its 256
+    workgroups claimed by compare-and-exchange)."""
+    g = spread(400_000, 1500)
+    with bc.Graph(g.row_ptr, g.col) as G:
+        query = min(G.topk(10, mode="batched").stats["query_ms"] for _ in range(5))
+        M = bc.MultiLaunch([G], [10])
+        launch = min(M.run()[0].stats["persistent_ms"] for _ in range(5))
+    print(f"[sparse] query {query:.2f} ms, launch {launch:.2f} ms", flush=True)
+    assert launch < 8 * query
+
+
+@pytest.mark.parametrize("capture", [False, True])
+@pytest.mark.parametrize("n", [5, 64, 65, 256 * 64 - 1, 256 * 64, 256 * 64 + 1])
+def test_every_batch_is_claimed_in_every_run(n, capture):
+    """As many batches as workgroups, one less and one more, run after run."""
+    g = synth.cycle(n) if n < 1000 else spread(n, 300)
+    ref = oracle.topk(g, 4)
+    with bc.Graph(g.row_ptr, g.col) as G:
+        M = bc.MultiLaunch([G, G], [4, 2], capture=capture)
+        for _ in range(3):
+            a, b = M.run()
+            assert a.ids.tolist() == ref["ids"].tolist() and a.farness.tolist() == ref["f"].tolist()
+            assert b.ids.tolist() == ref["ids"].tolist()[:2]
+            assert int(a.stats["n_cut"] + a.stats["n_done"] + a.stats["n_trivial"]) == g.n
